@@ -240,7 +240,7 @@ struct Workspace {
     DevBuf p32;         // F32 [n_pair_slots]
     DevBuf flags;       // uint8 [n_pair_slots]: bit0 non-robust, bit1 marked for FP64
     DevBuf p64;         // F64 [n_pair_slots]
-    DevBuf half_units;  // uint64 [n_cells], then the score's 64 counter bytes
+    DevBuf half_units;  // uint64 [n_cells], then the score's counter bytes
     DevBuf finfo;       // uint32 [n_frames]: frame info of the stream kernel
     DevBuf flen;        // F32 [rows]: frame (or mean) lengths (Euclidean BF16 form)
     DevBuf recheck_list, recount_list;
@@ -317,7 +317,7 @@ struct TaskImpl {
     int64_t n_units_small = 0;
     int64_t sum_nx = 0;             // sum over cells of |X|
     hvec<int32_t> rb;               // fused kernel row blocks [n][4] (<= 64 frames)
-    std::vector<int64_t> long_slots;  // pair slots with an item of more than 64 frames (FP64 kernel)
+    std::vector<int64_t> long_slots;  // unordered pairs x | y << 32 with an item of more than 64 frames (FP64 kernel)
     std::vector<int32_t> g_rb0, g_nrb;
     std::vector<std::unique_ptr<ColPlan>> col_plans;  // by column block width, made on demand
     int64_t fused_cells = 0;        // frame pairs the fused kernel covers

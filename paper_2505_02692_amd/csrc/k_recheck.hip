@@ -3,21 +3,20 @@
 // robust.  Works from the raw features (F32 or BF16 widened exactly):
 //   unit vector  u times 1 / ||u||, ||u|| = sqrt of the sum of squares
 //   cosine       sum of products of the unit vectors
-//   angle        acos(cos) when |cos| < 1 - 2^-20, else the half-chord form
-//                2 atan2(||u - v||, ||u + v||), which stays accurate near 0 and pi
+//   angle        acos(cos) when |cos| < 1 - 2^-20, else from the half chord
+//                ||u - v|| / 2 or ||u + v|| / 2, which stays accurate near 0 and pi
 //   distance     angle / pi; DTW with the diagonal > left > up predecessor order
 // or, for the Euclidean distance (euclid != 0), the square root of the sum of
 // squared differences of the raw frames (or means).
-// Contraction into FMA is disabled.
+// Contraction into FMA is disabled (the fused multiply-adds are written out).
 //
-// Persistent grid: each 256-thread block takes listed pairs in turn.  The
-// frame norms and most frame products are sums over the lanes of a wave
-// ending in one butterfly; the frame products of k_recheck_dtw for pairs of
-// more than 256 frame pairs are sequential sums per frame pair.  Either
-// differs from the strictly sequential sums of the definition only in
-// rounding (about 1e-16 relative), and every pair of a kernel goes through
-// the same arithmetic (exact copies have equal lengths, so they meet in the
-// same kernel), so equal inputs still give equal distances.
+// The cosines of a pair's frames are an FP64 matrix product and run on the
+// matrix cores: v_mfma_f64_16x16x4, 16 x 16 frame pairs at a time, operands
+// straight from the features into registers (no LDS staging).  Every sum goes
+// through the same steps whatever the frames' places in the tiles and
+// whichever item comes first (a fused multiply-add chain over the features in
+// one fixed order), so equal inputs still give equal distances, and the two
+// orientations of a pair share one evaluation.
 #include "device_common.h"
 #include "kernels.h"
 
@@ -27,7 +26,7 @@ namespace fabx {
 namespace kern {
 namespace {
 
-constexpr int kMaxL = 64;                    // items of at most this many frames: k_recheck_dtw
+constexpr int kMaxL = 64;                    // items of at most this many frames: k_recheck_small, k_recheck_tiled
 constexpr int kLongMax = FABX_MAX_ITEM_FRAMES;  // longer ones (up to this): k_long_dtw
 constexpr double kPi = 3.14159265358979323846;
 
@@ -68,372 +67,643 @@ __device__ __forceinline__ double wave_inv_norm(const T *row, int dim, int lane)
     return 1.0 / sqrt(wave_sum_f64(s));
 }
 
-// Angular distance of frames u and v with inverse norms su and sv (the whole
-// wave, its lanes splitting the dimension; every lane gets it).
-template <typename T>
-__device__ __forceinline__ double wave_frame_distance(const T *u, const T *v, double su, double sv, int dim,
-                                                      int lane) {
-    double c = 0.0;
-#pragma unroll 4
-    for (int k = lane; k < dim; k += dev::kWave) c += (ld(u, k) * su) * (ld(v, k) * sv);
-    c = wave_sum_f64(c);
-    double sm = 0.0, sp = 0.0;
-    if (!(fabs(c) < 1.0 - 0x1p-20)) {   // wave-uniform: c is the same in every lane
-#pragma unroll 4
-        for (int k = lane; k < dim; k += dev::kWave) {
-            const double a = ld(u, k) * su, b = ld(v, k) * sv;
-            sm += (a - b) * (a - b);
-            sp += (a + b) * (a + b);
-        }
-        sm = wave_sum_f64(sm);
-        sp = wave_sum_f64(sp);
-    }
-    return angle_over_pi_units(c, sm, sp);
+// Angle / pi of nearly parallel or opposite unit vectors u, v (|cos| within
+// 2^-20 of 1, so the half chord h is below 1e-3) from sm = ||u - v||^2 and
+// sp = ||u + v||^2: twice the arc sine of the half chord, whose series to h^7
+// is exact to FP64 rounding there.
+__device__ __forceinline__ double near_angle_over_pi(double sm, double sp) {
+    const double h2 = 0.25 * fmin(sm, sp), h = sqrt(h2);
+    const double a = 2.0 * h * (1.0 + h2 * (1.0 / 6.0 + h2 * (3.0 / 40.0 + h2 * (15.0 / 336.0)))) / kPi;
+    return sm <= sp ? a : 1.0 - a;
 }
 
-// Euclidean distance of frames u and v (the whole wave; every lane gets it).
+// The same of frames f and g (the whole wave, its lanes splitting the
+// dimension; every lane gets it).
 template <typename T>
-__device__ __forceinline__ double wave_euclid_distance(const T *u, const T *v, int dim, int lane) {
-    double s = 0.0;
+__device__ __forceinline__ double wave_near_distance(const T *f, const T *g, int dim, int lane) {
+    const double su = wave_inv_norm(f, dim, lane), sv = wave_inv_norm(g, dim, lane);
+    double sm = 0.0, sp = 0.0;
 #pragma unroll 4
     for (int k = lane; k < dim; k += dev::kWave) {
-        const double a = ld(u, k) - ld(v, k);
-        s += a * a;
+        const double a = ld(f, k) * su, b = ld(g, k) * sv;
+        sm += (a - b) * (a - b);
+        sp += (a + b) * (a + b);
     }
-    return sqrt(wave_sum_f64(s));
+    return near_angle_over_pi(wave_sum_f64(sm), wave_sum_f64(sp));
 }
 
-// The DTW update of cell (i, j) from its neighbours' costs and path lengths,
-// with the first row and column accumulating along themselves and the
-// diagonal > left > up order on exact ties.
-__device__ __forceinline__ void dtw_update(int i, int j, double d, double diag, int ldiag, double left,
-                                           int lleft, double up, int lup, double &c, int &len) {
-    if (i == 0 && j == 0) {
-        c = d;
-        len = 1;
-    } else if (i == 0) {
-        c = left + d;
-        len = lleft + 1;
-    } else if (j == 0) {
-        c = up + d;
-        len = lup + 1;
-    } else if (diag <= left && diag <= up) {
-        c = diag + d;
-        len = ldiag + 1;
-    } else if (left <= up) {
-        c = left + d;
-        len = lleft + 1;
-    } else {
-        c = up + d;
-        len = lup + 1;
-    }
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+
+// Value of lane - 1 over the whole wave, or within each row of 16 lanes; the
+// first lane gets `edge`.
+__device__ __forceinline__ int shr1(int edge, int v, std::false_type) {
+    return __builtin_amdgcn_update_dpp(edge, v, 0x138, 0xf, 0xf, false);  // wave_shr:1
+}
+__device__ __forceinline__ int shr1(int edge, int v, std::true_type) {
+    return __builtin_amdgcn_update_dpp(edge, v, 0x111, 0xf, 0xf, false);  // row_shr:1
+}
+// the cost above: +inf above the first row
+template <typename Row16>
+__device__ __forceinline__ double shr1_cost(double v, Row16 r) {
+    const long long b = __builtin_bit_cast(long long, v);
+    const uint32_t lo = uint32_t(shr1(0, int(b), r)), hi = uint32_t(shr1(0x7FF00000, int(b >> 32), r));
+    return __builtin_bit_cast(double, (long long)((uint64_t(hi) << 32) | lo));
 }
 
-// LDS staging of k_recheck_dtw's frame products: room for 132 rows (N + M
-// frames and the tiles' overreach of up to 3 rows) of 32 features (+1 pad);
-// fewer rows take longer feature chunks
-constexpr int kRstage = (2 * kMaxL + 4) * 33;
-constexpr int kRper = 8;  // staging loads a thread has in flight at once
+// One anti-diagonal sweep: lane i holds row i of a DTW and is on column t - i
+// at step t.  The path lengths of both orientations go along, packed (low
+// half: rows as given, diagonal before left before up on exact ties; high
+// half: the transposed problem, whose left is this one's up).  The costs are
+// the same in both.  Steps off a row's columns compute values that nothing
+// reads: the first column of a row takes +inf to its left, and a row's last
+// cell is read at its own step.
+struct Sweep {
+    double c = 0.0, up_prev = 0.0;
+    uint32_t len = 0, lup_prev = 0;
+    // first: column 0; row0: no row above at all; up, lup: the cell above (+inf, 0 for row0)
+    __device__ __forceinline__ void step(bool first, bool row0, double d, double up, uint32_t lup) {
+        constexpr double inf = __builtin_huge_val();
+        const double diag = first ? (row0 ? 0.0 : inf) : up_prev;  // virtual cell (-1, -1): cost 0, length 0
+        const double left = first ? inf : c;
+        const bool from_diag = diag <= left && diag <= up;
+        const bool from_left = row0 || left <= up;  // before up, rows as given
+        const bool from_up = up <= left;            // before left, transposed
+        const double best = from_diag ? diag : from_left ? left : up;
+        const uint32_t lo = from_diag ? lup_prev : from_left ? len : lup;
+        const uint32_t hi = from_diag ? lup_prev : from_up ? lup : len;
+        up_prev = up;
+        lup_prev = lup;
+        c = best + d;
+        len = ((hi & 0xFFFF0000u) | (lo & 0xFFFFu)) + 0x00010001u;
+    }
+};
 
-// One 256-thread block per listed pair of items of at most kMaxL frames (the
-// others are left to k_long_dtw).  The four waves share the N + M frame norms
-// (a wave per frame, its lanes splitting the dimension).  The N x M frame
-// products are then a register-tiled FP64 product: the frames go through LDS
-// in chunks of features (as many as kRstage holds for N + M + 3 rows; each
-// thread issues kRper loads before their stores), as unit-vector
-// components (or raw values for the Euclidean distance), and a thread
-// accumulates T x T frame pairs, each a sequential sum over the features in
-// order, so every pair gets the same arithmetic whatever its tile: T = 2
-// (thread t on (2 (t / 16) + r, 2 (t % 16) + c)) when both items have at most
-// 32 frames, else T = 4.  Pairs of at most kSmallPairs frame pairs go to the
-// kTiled = false instantiation instead, whose small footprint keeps more
-// blocks per CU: there a wave takes a frame pair at a time, its lanes
-// splitting the features (one butterfly sum).  The class depends on N * M
-// only, so both orientations of a pair, and copies, share the arithmetic;
-// each instantiation skips the other's pairs.  A frame pair whose cosine is within 2^-20 of +-1 is
-// finished by a wave (lanes splitting the dimension) with the half-chord
-// sums.  The distances stay in LDS; one wave then runs the DTW over
-// anti-diagonals (lane = row i), with the diagonal > left > up predecessor
-// order on exact ties.
-constexpr int kSmallPairs = 256;  // pairs of at most this many frame pairs: a wave per frame pair
-
-template <typename T, bool kTiled>
-__global__ __launch_bounds__(256) void k_recheck_dtw(const T *__restrict__ feat, int dim,
-                                                     const int64_t *__restrict__ g_item0,
-                                                     const int64_t *__restrict__ g_n,
-                                                     const int64_t *__restrict__ g_pair_base,
-                                                     int64_t n_groups,
-                                                     const int64_t *__restrict__ item_src,
-                                                     const int32_t *__restrict__ item_len,
-                                                     const int64_t *__restrict__ list,
-                                                     const unsigned int *__restrict__ count,
-                                                     int64_t max_count, int norm, int euclid,
-                                                     double *__restrict__ p64) {
-    constexpr int kDm = kTiled ? kMaxL * kMaxL : kSmallPairs;  // room for N * M distances
-    __shared__ double inrm[2 * kMaxL];     // 1 / ||frame|| of the N rows, then the M columns
-    __shared__ double dm[kDm];             // frame distances, row-major [N][M]
-    __shared__ double st[kTiled ? kRstage : 1];  // a feature chunk of the N + M frames
-    __shared__ uint8_t near[kDm];                // cosine within 2^-20 of +-1
-    const int lane = threadIdx.x % dev::kWave, w = threadIdx.x / dev::kWave;
-    const int ti = threadIdx.x / 16, tj = threadIdx.x % 16;  // this thread's tile of frame pairs
-    const int64_t total = min(int64_t(*count), max_count);
-    for (int64_t e = blockIdx.x; e < total; e += gridDim.x) {
-        const int64_t slot = list[e];
-        const int64_t g = dev::find_segment_wave(g_pair_base, n_groups, slot);
-        const int64_t n = g_n[g];
-        const int64_t local = slot - g_pair_base[g];
-        const int64_t x = g_item0[g] + local / n, y = g_item0[g] + local % n;
-        const int N = item_len[x], M = item_len[y];
-        if (N > kMaxL || M > kMaxL || (N * M <= kSmallPairs) == kTiled) continue;  // block-uniform
-        const T *fx = feat + item_src[x] * int64_t(dim);
-        const T *fy = feat + item_src[y] * int64_t(dim);
-        auto frame = [&](int f) { return f < N ? fx + int64_t(f) * dim : fy + int64_t(f - N) * dim; };
-        // norms of the N + M frames, a wave per frame (angular distance)
-        if (!euclid)
-            for (int f = w; f < N + M; f += 4) {
-                const double r = wave_inv_norm(frame(f), dim, lane);
-                if (lane == 0) inrm[f] = r;
+// A whole DTW of rows of at most 64 (Row16: 16) lanes, lane i (first lane of the
+// wave, or of its 16) on row i: row = its distances, steps t = 0 .. steps - 1,
+// fin = the step of the lane's result.  Distances are read four steps ahead;
+// the reads may run 8 past the last column and i before the first (the rows
+// lie one after another, so both stay in the tile or its pad of 8).
+template <typename Row16>
+__device__ __forceinline__ void sweep_rows(const double *row, int i, int steps, int fin, double &cost,
+                                           uint32_t &len) {
+    Sweep w;
+    const double *at = row - i;
+    double da[4], db[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) da[k] = at[k];
+    auto four = [&](const double (&d)[4], int t0) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int t = t0 + k;
+            const double up = shr1_cost(w.c, Row16{});
+            const uint32_t lup = uint32_t(shr1(0, int(w.len), Row16{}));
+            w.step(t == i, i == 0, d[k], up, lup);
+            if (t == fin) {
+                cost = w.c;
+                len = w.len;
             }
-        __syncthreads();
-        // frame products.  Rows of st: 0..N-1 the x frames, N..N+M-1 the y
-        // frames; a tile reaching past them (i >= N or j >= M) reads at most 3
-        // rows further (inside st, whatever they hold) and its sums are dropped.
-        const int kc = min(dim, kRstage / (N + M + 3) - 1);  // features per chunk
-        const int pad = kc + 1;
-        auto products = [&](auto tile_tag) {
-            constexpr int kT = decltype(tile_tag)::value;
-            const int i0 = kT * ti, j0 = kT * tj;
-            const bool active = i0 < N && j0 < M;
-            double acc[kT][kT];
-#pragma unroll
-            for (int r = 0; r < kT; ++r)
-#pragma unroll
-                for (int c = 0; c < kT; ++c) acc[r][c] = 0.0;
-            for (int k0 = 0; k0 < dim; k0 += kc) {
-                const int kn = min(kc, dim - k0);
-                // kRper loads in flight per thread before their stores
-                const int nq = (N + M) * kc;
-                for (int q0 = 0; q0 < nq; q0 += 256 * kRper) {
-                    double v[kRper];
-#pragma unroll
-                    for (int u = 0; u < kRper; ++u) {
-                        const int q = q0 + threadIdx.x + 256 * u, f = q / kc, kk = q - f * kc;
-                        v[u] = q < nq && kk < kn ? ld(frame(f), k0 + kk) : 0.0;
-                    }
-#pragma unroll
-                    for (int u = 0; u < kRper; ++u) {
-                        const int q = q0 + threadIdx.x + 256 * u, f = q / kc, kk = q - f * kc;
-                        if (q < nq) st[f * pad + kk] = euclid ? v[u] : v[u] * inrm[f];
-                    }
-                }
-                __syncthreads();
-                if (active) {
-                    const double *sa = st + i0 * pad;
-                    const double *sb = st + (N + j0) * pad;
-                    for (int kk = 0; kk < kn; ++kk) {
-                        double a[kT], b[kT];
-#pragma unroll
-                        for (int r = 0; r < kT; ++r) a[r] = sa[r * pad + kk];
-#pragma unroll
-                        for (int c = 0; c < kT; ++c) b[c] = sb[c * pad + kk];
-#pragma unroll
-                        for (int r = 0; r < kT; ++r)
-#pragma unroll
-                            for (int c = 0; c < kT; ++c) {
-                                if (euclid) {
-                                    const double d = a[r] - b[c];
-                                    acc[r][c] = acc[r][c] + d * d;
-                                } else {
-                                    acc[r][c] = acc[r][c] + a[r] * b[c];
-                                }
-                            }
-                    }
-                }
-                __syncthreads();
-            }
-            if (active) {
-#pragma unroll
-                for (int r = 0; r < kT; ++r)
-#pragma unroll
-                    for (int c = 0; c < kT; ++c) {
-                        const int i = i0 + r, j = j0 + c;
-                        if (i < N && j < M) {
-                            const double v = acc[r][c];
-                            if (euclid) {
-                                dm[i * M + j] = sqrt(v);
-                                near[i * M + j] = 0;
-                            } else {
-                                const bool nr = !(fabs(v) < 1.0 - 0x1p-20);
-                                dm[i * M + j] = nr ? 0.0 : acos(v) / kPi;
-                                near[i * M + j] = nr ? 1 : 0;
-                            }
-                        }
-                    }
-            }
-        };
-        if constexpr (!kTiled) {
-            // few frame pairs: a wave per pair, its lanes splitting the features
-            // (one butterfly sum), which keeps the lanes busy where tiles would not
-            for (int cidx = w; cidx < N * M; cidx += 4) {
-                const int i = cidx / M, j = cidx % M;
-                const T *u = fx + int64_t(i) * dim, *v = fy + int64_t(j) * dim;
-                const double d = euclid ? wave_euclid_distance(u, v, dim, lane)
-                                        : wave_frame_distance(u, v, inrm[i], inrm[N + j], dim, lane);
-                if (lane == 0) {
-                    dm[cidx] = d;
-                    near[cidx] = 0;
-                }
-            }
-        } else if (N <= 32 && M <= 32) {
-            products(std::integral_constant<int, 2>{});
-        } else {
-            products(std::integral_constant<int, 4>{});
         }
-        __syncthreads();
-        // near-parallel pairs: the half-chord form, a wave per pair
-        if (!euclid)
-            for (int cidx = w; cidx < N * M; cidx += 4) {
-                if (!near[cidx]) continue;  // wave-uniform
-                const int i = cidx / M, j = cidx % M;
-                const double d = wave_frame_distance(fx + int64_t(i) * dim, fy + int64_t(j) * dim, inrm[i],
-                                                     inrm[N + j], dim, lane);
-                if (lane == 0) dm[cidx] = d;
+    };
+    for (int t = 0; t < steps; t += 8) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) db[k] = at[min(t + 4 + k, steps + 3)];
+        four(da, t);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) da[k] = at[min(t + 8 + k, steps + 3)];
+        four(db, t + 4);
+    }
+}
+
+// Four features of a row as they are stored.  load4 takes them with one access
+// of the element type's alignment (rows of any width and base: the hardware
+// takes dword and byte aligned vector loads); load4_tail fills with zeros past
+// dim.  widen: one of them, exactly.
+template <typename T>
+struct Four;
+template <>
+struct Four<float> {
+    typedef float V __attribute__((ext_vector_type(4), aligned(4)));
+};
+template <>
+struct Four<uint16_t> {
+    typedef unsigned short V __attribute__((ext_vector_type(4), aligned(2)));
+};
+template <typename T>
+__device__ __forceinline__ typename Four<T>::V load4(const T *p) {
+    return *reinterpret_cast<const typename Four<T>::V *>(p);
+}
+template <typename T>
+__device__ __forceinline__ typename Four<T>::V load4_tail(const T *row, int k, int dim) {
+    typename Four<T>::V v;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = k + e < dim ? row[k + e] : T(0);
+    return v;
+}
+__device__ __forceinline__ double widen(float f) { return double(f); }
+__device__ __forceinline__ double widen(unsigned short h) { return double(dev::bf16_to_f32(h)); }
+
+// Sum over the four lanes that share lane % 16 (each holds the features
+// 16 c + 4 (lane / 16) + 0..3 of its frame); every lane gets it.
+__device__ __forceinline__ double sum_quarters(double v) {
+    v += __shfl_xor(v, 16, dev::kWave);
+    v += __shfl_xor(v, 32, dev::kWave);
+    return v;
+}
+
+__device__ __forceinline__ double ror1(double v) {
+    const long long b = __builtin_bit_cast(long long, v);
+    const uint32_t lo = uint32_t(__builtin_amdgcn_update_dpp(0, int(b), 0x121, 0xf, 0xf, true));
+    const uint32_t hi = uint32_t(__builtin_amdgcn_update_dpp(0, int(b >> 32), 0x121, 0xf, 0xf, true));
+    return __builtin_bit_cast(double, (long long)((uint64_t(hi) << 32) | lo));
+}
+
+// Distances of kT tiles of 16 x 16 frame pairs by one wave.  Tile u: rows are
+// the frames pa(u)(0..nr-1), columns pb(u)(0..nc-1); lane l loads row and column
+// frame l % 16 (clamped to the last one) and the features 4 (l / 16) + 0..3 of
+// each 16.  at(u, i, j) is where element (i, j) goes in LDS (also those of
+// clamped rows and columns).
+//  angular: cos from the MFMA accumulators (register r of lane l is row
+//    l / 16 + 4 r, column l % 16) times the inverse norms, whose sums of squares
+//    come from the same loads; an element with |cos| within 2^-20 of 1 is
+//    redone afterwards by the whole wave with the half-chord sums.
+//  Euclidean: the differences cannot go through a product without cancelling,
+//    so each lane keeps its row frame against all 16 column frames, which it
+//    gets by rotating them through the 16 lanes (DPP), and sums the squares of
+//    its quarter of the features.
+template <typename T, bool kEuclid, int kT, int kStages = sizeof(T) == 4 ? 3 : 4, typename Ptr, typename At>
+__device__ __forceinline__ void tile_distances(int n_tiles, Ptr &&ptr, int dim, At &&at) {
+    const int lane = threadIdx.x % dev::kWave, i16 = lane % 16, q = lane / 16;
+    const T *pa[kT], *pb[kT];
+    int nr[kT], nc[kT];
+#pragma unroll
+    for (int u = 0; u < kT; ++u) {
+        pa[u] = pb[u] = nullptr;
+        nr[u] = nc[u] = 0;
+        if (u < n_tiles) {
+            const T *a0, *b0;
+            ptr(u, a0, nr[u], b0, nc[u]);
+            pa[u] = a0 + int64_t(min(i16, nr[u] - 1)) * dim;
+            pb[u] = b0 + int64_t(min(i16, nc[u] - 1)) * dim;
+        }
+    }
+    if constexpr (kEuclid) {
+        for (int u = 0; u < n_tiles; ++u) {
+            const T *a_row = pa[0], *b_row = pb[0];
+#pragma unroll
+            for (int k = 1; k < kT; ++k)
+                if (k == u) { a_row = pa[k]; b_row = pb[k]; }
+            double acc[16];
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[r] = 0.0;
+            for (int k0 = 0; k0 < dim; k0 += 16) {
+                const bool whole = k0 + 16 <= dim;
+                const typename Four<T>::V a = whole ? load4(a_row + k0 + 4 * q) : load4_tail(a_row, k0 + 4 * q, dim);
+                const typename Four<T>::V b = whole ? load4(b_row + k0 + 4 * q) : load4_tail(b_row, k0 + 4 * q, dim);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const double x = widen(a[e]);
+                    double y = widen(b[e]);
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        const double d = x - y;
+                        acc[r] = __builtin_fma(d, d, acc[r]);
+                        y = ror1(y);
+                    }
+                }
             }
+            int j = i16;  // the column frame of rotation r, moved along with the values
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const double s = sum_quarters(acc[r]);
+                if (q == r / 4) *at(u, i16, j) = sqrt(s);
+                j = __builtin_amdgcn_update_dpp(0, j, 0x121, 0xf, 0xf, true);
+            }
+        }
+    } else {
+        f64x4 acc[kT];
+        double sa[kT], sb[kT];
+#pragma unroll
+        for (int u = 0; u < kT; ++u) {
+            acc[u] = f64x4{0.0, 0.0, 0.0, 0.0};
+            sa[u] = sb[u] = 0.0;
+        }
+        // kStages register buffers of 16 features each, kStages - 1 of them in
+        // flight while the products take one (a listed pair's frames are usually
+        // not in L2: one buffer ahead left the wave waiting on memory)
+        typename Four<T>::V a[kStages][kT], b[kStages][kT];
+        auto load = [&](int st, int k0) {
+#pragma unroll
+            for (int u = 0; u < kT; ++u)
+                if (u < n_tiles) {
+                    a[st][u] = load4(pa[u] + k0 + 4 * q);
+                    b[st][u] = load4(pb[u] + k0 + 4 * q);
+                }
+        };
+        auto products = [&](int st) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int u = 0; u < kT; ++u)
+                    if (u < n_tiles) {
+                        const double x = widen(a[st][u][e]), y = widen(b[st][u][e]);
+                        acc[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(x, y, acc[u], 0, 0, 0);
+                        sa[u] = __builtin_fma(x, x, sa[u]);
+                        sb[u] = __builtin_fma(y, y, sb[u]);
+                    }
+        };
+        const int full = dim & ~15;
+#pragma unroll
+        for (int st = 0; st < kStages - 1; ++st)
+            if (16 * st < full) load(st, 16 * st);
+        for (int k0 = 0; k0 < full; k0 += 16 * kStages) {
+#pragma unroll
+            for (int st = 0; st < kStages; ++st) {
+                const int k = k0 + 16 * st;
+                if (k >= full) break;
+                const int ahead = k + 16 * (kStages - 1);
+                if (ahead < full) load((st + kStages - 1) % kStages, ahead);
+                products(st);
+            }
+        }
+        if (full < dim) {
+#pragma unroll
+            for (int u = 0; u < kT; ++u)
+                if (u < n_tiles) {
+                    a[0][u] = load4_tail(pa[u], full + 4 * q, dim);
+                    b[0][u] = load4_tail(pb[u], full + 4 * q, dim);
+                }
+            products(0);
+        }
+        bool near = false;
+#pragma unroll
+        for (int u = 0; u < kT; ++u) {
+            if (u >= n_tiles) continue;
+            const double su = 1.0 / sqrt(sum_quarters(sa[u])), sv = 1.0 / sqrt(sum_quarters(sb[u]));
+            // (not unrolled: one copy of acos keeps the registers few)
+#pragma unroll 1
+            for (int r = 0; r < 4; ++r) {
+                const int i = q + 4 * r;
+                const double dot = r == 0 ? acc[u][0] : r == 1 ? acc[u][1] : r == 2 ? acc[u][2] : acc[u][3];
+                const double c = dot * (__shfl(su, i, dev::kWave) * sv);
+                const bool is_near = !(fabs(c) < 1.0 - 0x1p-20);
+                near = near || is_near;
+                *at(u, i, i16) = is_near ? -1.0 : acos(c) / kPi;
+            }
+        }
+        // the elements left at -1 (distances are >= 0), by the whole wave
+        if (__any(near))
+#pragma unroll 1
+            for (int u = 0; u < n_tiles; ++u) {
+                const T *a, *b;
+                int n_r, n_c;
+                ptr(u, a, n_r, b, n_c);
+#pragma unroll 1
+                for (int e = 0; e < n_r * n_c; ++e) {
+                    const int i = e / n_c, j = e % n_c;
+                    double *d = at(u, i, j);
+                    if (!(*d < 0.0)) continue;  // wave-uniform
+                    const double v = wave_near_distance(a + int64_t(i) * dim, b + int64_t(j) * dim, dim, lane);
+                    if (lane == 0) *d = v;
+                }
+            }
+    }
+}
+
+// A listed pair: task items x (low word) and y (high word) of one group.
+struct Pair {
+    int64_t x, y;
+};
+__device__ __forceinline__ Pair pair_of(int64_t entry) {
+    return {int64_t(uint32_t(entry)), int64_t(uint64_t(entry) >> 32)};
+}
+struct PairSlots {
+    int64_t xy, yx;
+};
+__device__ __forceinline__ PairSlots slots_of(const Pair &pr, const int32_t *__restrict__ item_group,
+                                              const int64_t *__restrict__ g_item0,
+                                              const int64_t *__restrict__ g_n,
+                                              const int64_t *__restrict__ g_pair_base) {
+    const int64_t g = item_group[pr.x], n = g_n[g], i0 = g_item0[g], base = g_pair_base[g];
+    return {base + (pr.x - i0) * n + (pr.y - i0), base + (pr.y - i0) * n + (pr.x - i0)};
+}
+
+// The value of both orientations, from the cost and the packed path lengths.
+__device__ __forceinline__ void store_pair(const Pair &pr, double cost, uint32_t len, int norm,
+                                           const int32_t *__restrict__ item_group,
+                                           const int64_t *__restrict__ g_item0, const int64_t *__restrict__ g_n,
+                                           const int64_t *__restrict__ g_pair_base, double *__restrict__ p64) {
+    const PairSlots s = slots_of(pr, item_group, g_item0, g_n, g_pair_base);
+    const bool path = norm == FABX_NORM_PATH;
+    p64[s.xy] = path ? cost / double(len & 0xFFFFu) : cost;
+    p64[s.yx] = path ? cost / double(len >> 16) : cost;
+}
+
+// Tiles t0, t0 + step, ... (row-major) of a pair's frame distances into dm, two
+// at a time.
+template <typename T, bool kEuclid>
+__device__ __forceinline__ void pair_tiles(const T *__restrict__ feat, int dim, const Pair &pr, int N, int M,
+                                           const int64_t *__restrict__ item_src, int t0, int step, double *dm,
+                                           int ld_dm) {
+    const T *fx = feat + item_src[pr.x] * int64_t(dim);
+    const T *fy = feat + item_src[pr.y] * int64_t(dim);
+    const int tm = (M + 15) / 16, n_tiles = (N + 15) / 16 * tm;
+#pragma unroll 1
+    for (int t = t0; t < n_tiles; t += 2 * step) {
+        const int ti[2] = {t / tm, (t + step) / tm}, tj[2] = {t % tm, (t + step) % tm};
+        tile_distances<T, kEuclid, 2>(
+            t + step < n_tiles ? 2 : 1,
+            [&](int u, const T *&a, int &nr, const T *&b, int &nc) {
+                a = fx + int64_t(16 * ti[u]) * dim;
+                b = fy + int64_t(16 * tj[u]) * dim;
+                nr = min(16, N - 16 * ti[u]);
+                nc = min(16, M - 16 * tj[u]);
+            },
+            dim, [&](int u, int r, int c) { return dm + (16 * ti[u] + r) * ld_dm + 16 * tj[u] + c; });
+    }
+}
+
+// Pairs of items of at most 16 frames: one tile each.  A wave takes kP pairs
+// at a time: their products on the matrix cores two by two (independent
+// chains), their distances into LDS, then their DTWs side by side, 16 lanes each.
+// Bound by the FP64 matrix rate (a tile is a 16 x 16 x dim product: lengths of
+// about 10 frames use 40% of it) and the loads from L2.  Lists too short to
+// give every SIMD a wave of four pairs take one pair a wave (kP = 1), which
+// ends sooner.  The XCDs take contiguous parts of the list (its pairs are
+// grouped by row item, so a part's frames stay in that XCD's L2).  365,261
+// marked pairs of the 100,000-item task at dim 768 (lengths 5-25): 22.1 ms with
+// a block per pair and a wave per frame pair, 2.6 ms here.
+constexpr int kTileLd = 17;
+template <typename T, bool kEuclid, int kP>
+__device__ __forceinline__ void small_pairs(const T *__restrict__ feat, int dim, int64_t e0, int64_t total,
+                                            double *dm, const int64_t *__restrict__ g_item0,
+                                            const int64_t *__restrict__ g_n,
+                                            const int64_t *__restrict__ g_pair_base,
+                                            const int64_t *__restrict__ item_src,
+                                            const int32_t *__restrict__ item_len,
+                                            const int32_t *__restrict__ item_group,
+                                            const int64_t *__restrict__ list, int norm,
+                                            double *__restrict__ p64) {
+    const int lane = threadIdx.x % dev::kWave, i = lane % 16, q = lane / 16;
+    const int n_pairs = int(min<int64_t>(kP, total - e0));
+    // (the previous DTW's reads of dm are over: same wave, LDS in order)
+#pragma unroll 1
+    for (int h = 0; h < n_pairs; h += 2)
+        tile_distances<T, kEuclid, kP < 2 ? 1 : 2>(
+            min(2, n_pairs - h),
+            [&](int u, const T *&a, int &nr, const T *&b, int &nc) {
+                const Pair pr = pair_of(list[e0 + h + u]);
+                a = feat + item_src[pr.x] * int64_t(dim);
+                b = feat + item_src[pr.y] * int64_t(dim);
+                nr = item_len[pr.x];
+                nc = item_len[pr.y];
+            },
+            dim, [&](int u, int r, int c) { return dm + ((h + u) * 16 + r) * kTileLd + c; });
+    __builtin_amdgcn_wave_barrier();
+    const int qp = min(q, n_pairs - 1);
+    const Pair pr = pair_of(list[e0 + qp]);
+    const int N = item_len[pr.x], M = item_len[pr.y];
+    int steps = N + M - 1;
+#pragma unroll
+    for (int o = 32; o >= 16; o >>= 1) steps = max(steps, __shfl_xor(steps, o, dev::kWave));
+    double cost = 0.0;
+    uint32_t len = 0;
+    sweep_rows<std::true_type>(dm + (qp * 16 + i) * kTileLd, i,
+                               __builtin_amdgcn_readfirstlane(steps), N + M - 2, cost, len);
+    if (q == qp && i == N - 1) store_pair(pr, cost, len, norm, item_group, g_item0, g_n, g_pair_base, p64);
+    __builtin_amdgcn_wave_barrier();
+}
+
+template <typename T, bool kEuclid>
+__global__ __launch_bounds__(256, 3) void k_recheck_small(const T *__restrict__ feat, int dim,
+                                                          const int64_t *__restrict__ g_item0,
+                                                          const int64_t *__restrict__ g_n,
+                                                          const int64_t *__restrict__ g_pair_base,
+                                                          const int64_t *__restrict__ item_src,
+                                                          const int32_t *__restrict__ item_len,
+                                                          const int32_t *__restrict__ item_group,
+                                                          const int64_t *__restrict__ list,
+                                                          const unsigned int *__restrict__ count,
+                                                          int64_t max_count, int norm, double *__restrict__ p64) {
+    constexpr int kP = 4;
+    __shared__ double dm_s[4 * kP * 16 * kTileLd + 8];
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / dev::kWave);
+    const int64_t total = min(int64_t(*count), max_count);
+    const int64_t waves = int64_t(gridDim.x / 8) * 4;  // per XCD; gridDim.x is a multiple of 8
+    const int64_t first = int64_t(blockIdx.x / 8) * 4 + w;
+    auto go = [&](auto p_tag) {
+        constexpr int p = decltype(p_tag)::value;
+        const int64_t part = ((total + 7) / 8 + p - 1) / p * p;  // pairs per XCD
+        const int64_t lo = int64_t(blockIdx.x % 8) * part, hi = min(total, lo + part);
+        for (int64_t e = lo + first * p; e < hi; e += waves * p)
+            small_pairs<T, kEuclid, p>(feat, dim, e, hi, dm_s + w * (kP * 16 * kTileLd), g_item0, g_n, g_pair_base, item_src,
+                                       item_len, item_group, list, norm, p64);
+    };
+    if (total >= 8 * waves * kP)
+        go(std::integral_constant<int, kP>{});
+    else
+        go(std::integral_constant<int, 1>{});
+}
+
+// Pairs with an item of 17 to 32 frames: a wave per pair, its up to four tiles
+// two at a time, then its DTW; no barriers, so the waves of a SIMD overlap one's
+// products with another's sweep.  A list too short to fill the chip with waves is
+// left to k_recheck_tiled, whose four waves a pair end sooner (2,664 marked pairs
+// of the same task: 68 us with a wave a pair, 32 us with a block).  The 17-25
+// frame pairs of that task's 365,261: 4.6 ms from LDS-staged register tiles,
+// 2.2 ms with a block per pair, 1.35 ms here.
+constexpr int kMidL = 32, kMidMin = 2048;
+template <typename T, bool kEuclid>
+__global__ __launch_bounds__(256, 3) void k_recheck_mid(const T *__restrict__ feat, int dim,
+                                                        const int64_t *__restrict__ g_item0,
+                                                        const int64_t *__restrict__ g_n,
+                                                        const int64_t *__restrict__ g_pair_base,
+                                                        const int64_t *__restrict__ item_src,
+                                                        const int32_t *__restrict__ item_len,
+                                                        const int32_t *__restrict__ item_group,
+                                                        const int64_t *__restrict__ list,
+                                                        const unsigned int *__restrict__ count,
+                                                        int64_t max_count, int norm, double *__restrict__ p64) {
+    constexpr int kLd = kMidL + 1;
+    __shared__ double dm_s[4 * kMidL * kLd + 8 + kMidL];  // pad: idle lanes read up to 32 rows further
+    const int lane = threadIdx.x % dev::kWave;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / dev::kWave);
+    double *dm = dm_s + w * (kMidL * kLd);
+    const int64_t total = min(int64_t(*count), max_count);
+    if (total < kMidMin) return;
+    const int64_t part = (total + 7) / 8, lo = int64_t(blockIdx.x % 8) * part, hi = min(total, lo + part);
+    for (int64_t e = lo + int64_t(blockIdx.x / 8) * 4 + w; e < hi; e += int64_t(gridDim.x / 8) * 4) {
+        const Pair pr = pair_of(list[e]);
+        const int N = item_len[pr.x], M = item_len[pr.y];
+        pair_tiles<T, kEuclid>(feat, dim, pr, N, M, item_src, 0, 1, dm, kLd);
+        __builtin_amdgcn_wave_barrier();
+        double cost = 0.0;
+        uint32_t len = 0;
+        sweep_rows<std::false_type>(dm + min(lane, kMidL - 1) * kLd, lane, N + M - 1, N + M - 2, cost, len);
+        if (lane == N - 1) store_pair(pr, cost, len, norm, item_group, g_item0, g_n, g_pair_base, p64);
+        __builtin_amdgcn_wave_barrier();
+    }
+}
+
+// Pairs with an item of 33 to 64 frames (and a short list of the class before):
+// a 256-thread block per pair, its four waves sharing the tiles; wave 0 then
+// runs the DTW.  10,687 pairs of 1-60 frames at dim 512: 5.7 -> 0.73 ms (from a
+// serial sum per frame pair over LDS-staged features).
+template <typename T, bool kEuclid>
+__global__ __launch_bounds__(256, 3) void k_recheck_tiled(const T *__restrict__ feat, int dim,
+                                                          const int64_t *__restrict__ g_item0,
+                                                          const int64_t *__restrict__ g_n,
+                                                          const int64_t *__restrict__ g_pair_base,
+                                                          const int64_t *__restrict__ item_src,
+                                                          const int32_t *__restrict__ item_len,
+                                                          const int32_t *__restrict__ item_group,
+                                                          PairLists lists, int norm, double *__restrict__ p64) {
+    constexpr int kLd = kMaxL + 1;
+    __shared__ double dm[kMaxL * kLd + 8 + kMaxL];
+    const int lane = threadIdx.x % dev::kWave;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / dev::kWave);
+    const int64_t n_mid = *lists.n_mid < kMidMin ? int64_t(*lists.n_mid) : 0;
+    const int64_t total = min(int64_t(*lists.n_large), lists.cap) + n_mid;
+    const int64_t part = (total + 7) / 8, lo = int64_t(blockIdx.x % 8) * part, hi = min(total, lo + part);
+    for (int64_t e = lo + blockIdx.x / 8; e < hi; e += gridDim.x / 8) {
+        // the large class fills its list from the end
+        const Pair pr = pair_of(e < n_mid ? lists.mid[e] : lists.small_large[lists.cap - 1 - (e - n_mid)]);
+        const int N = item_len[pr.x], M = item_len[pr.y];
+        pair_tiles<T, kEuclid>(feat, dim, pr, N, M, item_src, w, 4, dm, kLd);
         __syncthreads();
         if (w == 0) {
-            // lane i is on column t - i at step t: c[i-1][j] comes from lane i - 1
-            // one step earlier, c[i-1][j-1] two steps earlier
-            const int i = lane;
-            double c = 0.0, up_prev = 0.0;
-            int len = 0, lup_prev = 0;
-            for (int t = 0; t < N + M - 1; ++t) {
-                const int j = t - i;
-                const double up = __shfl_up(c, 1, dev::kWave);   // lane i - 1's cost, step t - 1
-                const int lup = __shfl_up(len, 1, dev::kWave);
-                const double diag = up_prev, left = c;
-                const int ldiag = lup_prev, lleft = len;
-                up_prev = up;
-                lup_prev = lup;
-                if (i < N && j >= 0 && j < M)
-                    dtw_update(i, j, dm[i * M + j], diag, ldiag, left, lleft, up, lup, c, len);
-            }
-            if (i == N - 1) p64[slot] = norm == FABX_NORM_PATH ? c / double(len) : c;
+            double cost = 0.0;
+            uint32_t len = 0;
+            sweep_rows<std::false_type>(dm + lane * kLd, lane, N + M - 1, N + M - 2, cost, len);
+            if (lane == N - 1) store_pair(pr, cost, len, norm, item_group, g_item0, g_n, g_pair_base, p64);
         }
         __syncthreads();
     }
 }
 
-// One 256-thread block per listed pair in which an item has more than kMaxL
-// frames (pairs of shorter items are skipped): the same arithmetic as
-// k_recheck_dtw, tiled.  Rows go in chunks of 64 (lane = row), each chunk
+// Pairs in which an item has more than kMaxL frames, each unordered pair once:
+// the same arithmetic, tiled.  Rows go in chunks of 64 (lane = row), each chunk
 // sweeping all M columns along anti-diagonals; a chunk hands its last row's
-// costs and path lengths to the next one through LDS (`rowc`, `rowl`).  The
-// frame distances of a chunk are made 32 columns at a time by the four waves
-// into a ring of three 32-column tiles: at step s lane i reads column s - i,
-// so the steps of tile k (s in [32k, 32k + 32)) read tiles k - 2 .. k only,
-// and tile k + 1 may overwrite tile k - 2 once those steps are done.
-// The result of pair `slot` goes to p64, and also to p32 and flags (0: robust,
-// unmarked) when they are given (the first computation of such a pair).
-template <typename T>
-__global__ __launch_bounds__(256) void k_long_dtw(const T *__restrict__ feat, int dim,
+// costs and path lengths to the next one through LDS (`rowc`, `rowl`).  Waves
+// 0..3 make the frame distances of a chunk 32 columns at a time (16 x 16 tiles,
+// two per wave) into a ring of four 32-column tiles while wave 4 runs the DTW on
+// the tile before: at step s lane i reads column s - i, so the steps of tile k
+// (s in [32k, 32k + 32)) read tiles k - 2 .. k only, and tile k + 1 goes where
+// tile k - 3 was.  Rows are the item that needs fewer chunk steps.  Bound by the
+// sweep's chain of dependent FP64 steps (two blocks fit a CU by their LDS).
+// 682 items of 10-200 frames in 60 groups, dim 256, 9.3e7 frame pairs: 92 ms
+// (each orientation by itself, a wave per frame pair), 4.1 ms here.
+// The value of pair (x, y) goes to p64, p32 and flags (0: robust, unmarked) of
+// both its slots.
+template <typename T, bool kEuclid>
+__global__ __launch_bounds__(320, 3) void k_long_dtw(const T *__restrict__ feat, int dim,
                                                   const int64_t *__restrict__ g_item0,
                                                   const int64_t *__restrict__ g_n,
                                                   const int64_t *__restrict__ g_pair_base,
-                                                  int64_t n_groups,
                                                   const int64_t *__restrict__ item_src,
                                                   const int32_t *__restrict__ item_len,
-                                                  const int64_t *__restrict__ list,
-                                                  const unsigned int *__restrict__ count,
-                                                  int64_t max_count, int norm, int euclid,
+                                                  const int32_t *__restrict__ item_group,
+                                                  const int64_t *__restrict__ list, int64_t n_list, int norm,
                                                   double *__restrict__ p64, float *__restrict__ p32,
                                                   uint8_t *__restrict__ flags) {
-    constexpr int kTc = 32, kRing = 3, kRingCols = kRing * kTc;
-    __shared__ double dm[dev::kWave * kRingCols];  // [row of chunk][ring column]
-    __shared__ double rinv_r[dev::kWave], rinv_c[kTc];
+    constexpr int kTc = 32, kRing = 4, kLd = kRing * kTc + 1;
+    __shared__ double dm[dev::kWave * kLd];        // [row of chunk][ring column]
     __shared__ double rowc[kLongMax];              // previous chunk's last row: costs
-    __shared__ int rowl[kLongMax];                 // and path lengths
-    const int lane = threadIdx.x % dev::kWave, w = threadIdx.x / dev::kWave;
-    const int64_t total = count ? min(int64_t(*count), max_count) : max_count;
-    for (int64_t e = blockIdx.x; e < total; e += gridDim.x) {
-        const int64_t slot = list[e];
-        const int64_t g = dev::find_segment_wave(g_pair_base, n_groups, slot);
-        const int64_t n = g_n[g];
-        const int64_t local = slot - g_pair_base[g];
-        const int64_t x = g_item0[g] + local / n, y = g_item0[g] + local % n;
-        const int N = item_len[x], M = item_len[y];
-        if (N <= kMaxL && M <= kMaxL) continue;  // block-uniform: k_recheck_dtw's pairs
-        const T *fx = feat + item_src[x] * int64_t(dim);
-        const T *fy = feat + item_src[y] * int64_t(dim);
+    __shared__ uint32_t rowl[kLongMax];            // and path lengths
+    const int lane = threadIdx.x % dev::kWave;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / dev::kWave);
+    for (int64_t e = blockIdx.x; e < n_list; e += gridDim.x) {
+        Pair pr = pair_of(list[e]);
+        int N = item_len[pr.x], M = item_len[pr.y];
+        if ((N + 63) / 64 * (M + 63) > (M + 63) / 64 * (N + 63)) {
+            const Pair sw = {pr.y, pr.x};
+            pr = sw;
+            const int n = N;
+            N = M;
+            M = n;
+        }
+        const T *fx = feat + item_src[pr.x] * int64_t(dim);
+        const T *fy = feat + item_src[pr.y] * int64_t(dim);
         const int n_tiles = (M + kTc - 1) / kTc;
-        double c = 0.0;
-        int len = 0;
+        Sweep s;
         for (int r0 = 0; r0 < N; r0 += dev::kWave) {
             const int nr = min(dev::kWave, N - r0);
-            __syncthreads();  // the previous chunk's steps are done with the norms and the ring
-            if (!euclid)
-                for (int f = w; f < nr; f += 4) {
-                    const double r = wave_inv_norm(fx + int64_t(r0 + f) * dim, dim, lane);
-                    if (lane == 0) rinv_r[f] = r;
-                }
-            // wave 0's sweep state: lane i holds row r0 + i at column s - i
-            const int i = lane;
-            double up_prev = 0.0;
-            int lup_prev = 0;
-            c = 0.0;
-            len = 0;
-            int s = 0;
+            s = Sweep{};
+            int t = 0;
             const int steps = M + nr - 1;
-            for (int k = 0; k < n_tiles; ++k) {
-                const int c0 = k * kTc, nc = min(kTc, M - c0);
-                const int ring0 = (k % kRing) * kTc;
-                __syncthreads();  // tile k - 2's steps are done (and the row norms are in)
-                if (!euclid)
-                    for (int f = w; f < nc; f += 4) {
-                        const double r = wave_inv_norm(fy + int64_t(c0 + f) * dim, dim, lane);
-                        if (lane == 0) rinv_c[f] = r;
+            // tile k is made in phase k and swept in phase k + 1
+            for (int k = 0; k <= n_tiles; ++k) {
+                if (w < 4) {
+                    const int r = 16 * w, c0 = k * kTc;
+                    if (k < n_tiles && r < nr) {
+                        const int nc = min(kTc, M - c0);
+                        double *out = dm + r * kLd + (k % kRing) * kTc;
+                        tile_distances<T, kEuclid, 2, 2>(
+                            nc > 16 ? 2 : 1,
+                            [&](int u, const T *&a, int &na, const T *&b, int &nb) {
+                                a = fx + int64_t(r0 + r) * dim;
+                                b = fy + int64_t(c0 + 16 * u) * dim;
+                                na = min(16, nr - r);
+                                nb = min(16, nc - 16 * u);
+                            },
+                            dim,
+                            [&](int u, int i, int j) { return out + i * kLd + 16 * u + j; });
                     }
-                __syncthreads();
-                for (int cidx = w; cidx < nr * nc; cidx += 4) {
-                    const int ii = cidx / nc, jj = cidx % nc;
-                    const T *u = fx + int64_t(r0 + ii) * dim, *v = fy + int64_t(c0 + jj) * dim;
-                    const double d = euclid ? wave_euclid_distance(u, v, dim, lane)
-                                            : wave_frame_distance(u, v, rinv_r[ii], rinv_c[jj], dim, lane);
-                    if (lane == 0) dm[ii * kRingCols + ring0 + jj] = d;
-                }
-                __syncthreads();
-                if (w == 0) {
-                    const int s_end = k == n_tiles - 1 ? steps : c0 + kTc;
-                    for (; s < s_end; ++s) {
-                        const int j = s - i;
-                        double up = __shfl_up(c, 1, dev::kWave);   // lane i - 1's cost, step s - 1
-                        int lup = __shfl_up(len, 1, dev::kWave);
-                        if (i == 0) {  // the row above the chunk, read before this step's store
-                            const bool in = r0 > 0 && j >= 0 && j < M;
-                            up = in ? rowc[j] : 0.0;
-                            lup = in ? rowl[j] : 0;
-                        }
-                        const double diag = up_prev, left = c;
-                        const int ldiag = lup_prev, lleft = len;
-                        up_prev = up;
-                        lup_prev = lup;
-                        if (i < nr && j >= 0 && j < M) {
-                            const double d = dm[i * kRingCols + ((j / kTc) % kRing) * kTc + j % kTc];
-                            dtw_update(r0 + i, j, d, diag, ldiag, left, lleft, up, lup, c, len);
-                            if (i == nr - 1) {  // this chunk's last row, for the next chunk
-                                rowc[j] = c;
-                                rowl[j] = len;
+                } else if (k > 0) {
+                    const int i = lane, t_end = k == n_tiles ? steps : k * kTc;
+                    // four steps' distances (and the row above the chunk, lane 0's) at a time
+                    auto four = [&](const double (&d)[4], const double (&ru)[4], const uint32_t (&rl)[4], int n) {
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            if (q >= n) break;
+                            const int j = t - i;
+                            double up = shr1_cost(s.c, std::false_type{});  // lane i - 1's cost, step t - 1
+                            uint32_t lup = uint32_t(shr1(0, int(s.len), std::false_type{}));
+                            if (r0 > 0 && i == 0) {
+                                up = ru[q];
+                                lup = rl[q];
                             }
+                            s.step(j == 0, r0 == 0 && i == 0, d[q], up, lup);
+                            if (i == nr - 1 && j >= 0 && j < M) {  // this chunk's last row, for the next chunk
+                                rowc[j] = s.c;
+                                rowl[j] = s.len;
+                            }
+                            ++t;
                         }
+                    };
+                    auto fetch = [&](double (&d)[4], double (&ru)[4], uint32_t (&rl)[4], int t0) {
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            d[q] = dm[i * kLd + ((t0 + q - i) & (kRing * kTc - 1))];
+                            const int j = min(t0 + q, kLongMax - 1);
+                            ru[q] = r0 > 0 ? rowc[j] : 0.0;
+                            rl[q] = r0 > 0 ? rowl[j] : 0;
+                        }
+                    };
+                    double d0[4], d1[4], u0[4], u1[4];
+                    uint32_t l0[4], l1[4];
+                    fetch(d0, u0, l0, t);
+                    while (t < t_end) {
+                        fetch(d1, u1, l1, t + 4);
+                        four(d0, u0, l0, t_end - t);
+                        if (t >= t_end) break;
+                        fetch(d0, u0, l0, t + 4);
+                        four(d1, u1, l1, t_end - t);
                     }
                 }
+                __syncthreads();
             }
         }
-        // lane (N - 1) % 64 of wave 0 ended on cell (N - 1, M - 1)
-        if (w == 0 && lane == (N - 1) % dev::kWave) {
-            const double v = norm == FABX_NORM_PATH ? c / double(len) : c;
-            p64[slot] = v;
-            if (p32) p32[slot] = float(v);
-            if (flags) flags[slot] = 0;
+        // lane (N - 1) % 64 of wave 4 ended on cell (N - 1, M - 1)
+        if (w == 4 && lane == (N - 1) % dev::kWave) {
+            const PairSlots sl = slots_of(pr, item_group, g_item0, g_n, g_pair_base);
+            const bool path = norm == FABX_NORM_PATH;
+            const double vxy = path ? s.c / double(s.len & 0xFFFFu) : s.c;
+            const double vyx = path ? s.c / double(s.len >> 16) : s.c;
+            p64[sl.xy] = vxy;
+            p64[sl.yx] = vyx;
+            p32[sl.xy] = float(vxy);
+            p32[sl.yx] = float(vyx);
+            flags[sl.xy] = flags[sl.yx] = 0;
         }
     }
 }
@@ -507,48 +777,64 @@ __global__ __launch_bounds__(256) void k_recheck_pooled(const T *__restrict__ fe
 
 }  // namespace
 
+// Calls go(typed features, euclid tag) for the dataset's type and distance.
+template <typename Go>
+static void typed(const void *features, int dtype, int euclid, Go &&go) {
+    if (dtype == FABX_DTYPE_F32) {
+        const float *f = static_cast<const float *>(features);
+        euclid ? go(f, std::true_type{}) : go(f, std::false_type{});
+    } else {
+        const uint16_t *f = static_cast<const uint16_t *>(features);
+        euclid ? go(f, std::true_type{}) : go(f, std::false_type{});
+    }
+}
+
 void long_dtw(hipStream_t s, const void *features, int dtype, int dim, const GroupTables &g,
-              const ItemTables &it, const int64_t *list, const unsigned int *count, int64_t max_count, int norm,
+              const ItemTables &it, const int32_t *item_group, const int64_t *list, int64_t n_list, int norm,
               int euclid, double *p64, float *p32, uint8_t *flags) {
-    if (max_count <= 0) return;
-    const unsigned blocks = unsigned(std::min<int64_t>(max_count, 4096));
-    if (dtype == FABX_DTYPE_F32)
-        hipLaunchKernelGGL(k_long_dtw<float>, dim3(blocks), dim3(256), 0, s, static_cast<const float *>(features),
-                           dim, g.item0, g.n_items, g.pair_base, g.n_groups, it.src, it.len, list, count,
-                           max_count, norm, euclid, p64, p32, flags);
-    else
-        hipLaunchKernelGGL(k_long_dtw<uint16_t>, dim3(blocks), dim3(256), 0, s,
-                           static_cast<const uint16_t *>(features), dim, g.item0, g.n_items, g.pair_base,
-                           g.n_groups, it.src, it.len, list, count, max_count, norm, euclid, p64, p32, flags);
+    if (n_list <= 0) return;
+    const unsigned blocks = unsigned(std::min<int64_t>(n_list, 4096));
+    typed(features, dtype, euclid, [&](auto *f, auto eu) {
+        using T = std::remove_const_t<std::remove_pointer_t<decltype(f)>>;
+        hipLaunchKernelGGL((k_long_dtw<T, decltype(eu)::value>), dim3(blocks), dim3(320), 0, s, f, dim,
+                           g.item0, g.n_items, g.pair_base, it.src, it.len,
+                           item_group, list, n_list, norm, p64, p32, flags);
+    });
     FABX_HIP(hipGetLastError());
 }
 
-void recheck_fp64(hipStream_t s, const void *features, int dtype, int dim, const GroupTables &g,
-                  const ItemTables &it, const int64_t *list, const unsigned int *count,
-                  int64_t max_count, int mode, int norm, bool has_long, int euclid, double *p64) {
+void recheck_dtw(hipStream_t s, const void *features, int dtype, int dim, const GroupTables &g,
+                 const ItemTables &it, const int32_t *item_group, const PairLists &lists, int n_cu, int max_len,
+                 int norm, int euclid, double *p64) {
+    const int64_t cap = lists.cap;
+    if (cap <= 0) return;
+    // three blocks of four waves per CU (their registers), or fewer when the list cannot fill them
+    const int64_t per_xcd = std::max(1, 3 * n_cu / 8);
+    const unsigned small = 8u * unsigned(std::max<int64_t>(1, std::min<int64_t>(per_xcd, (cap + 31) / 32)));
+    const unsigned mid = small;
+    const unsigned tiled = 8u * unsigned(std::max<int64_t>(1, std::min<int64_t>(per_xcd, (cap + 7) / 8)));
+    typed(features, dtype, euclid, [&](auto *f, auto eu) {
+        using T = std::remove_const_t<std::remove_pointer_t<decltype(f)>>;
+        hipLaunchKernelGGL((k_recheck_small<T, decltype(eu)::value>), dim3(small), dim3(256), 0, s, f, dim, g.item0,
+                           g.n_items, g.pair_base, it.src, it.len, item_group, lists.small_large, lists.n_small, cap,
+                           norm, p64);
+        if (max_len > 16 && cap >= kMidMin)
+            hipLaunchKernelGGL((k_recheck_mid<T, decltype(eu)::value>), dim3(mid), dim3(256), 0, s, f, dim, g.item0,
+                               g.n_items, g.pair_base, it.src, it.len, item_group, lists.mid, lists.n_mid, cap, norm,
+                               p64);
+        if (max_len > 16)
+            hipLaunchKernelGGL((k_recheck_tiled<T, decltype(eu)::value>), dim3(tiled), dim3(256), 0, s, f, dim,
+                               g.item0, g.n_items, g.pair_base, it.src, it.len, item_group, lists, norm, p64);
+    });
+    FABX_HIP(hipGetLastError());
+}
+
+void recheck_pooled(hipStream_t s, const void *features, int dtype, int dim, const GroupTables &g,
+                    const ItemTables &it, const int64_t *list, const unsigned int *count, int64_t max_count,
+                    int euclid, double *p64) {
     if (max_count <= 0) return;
-    if (mode == FABX_MODE_POOLED && dim > 2048) fail(FABX_EINVAL, "pooled recheck supports dim <= 2048");
+    if (dim > 2048) fail(FABX_EINVAL, "pooled recheck supports dim <= 2048");
     const unsigned blocks = unsigned(std::min<int64_t>(max_count, 4096));
-    if (mode == FABX_MODE_DTW && has_long)
-        long_dtw(s, features, dtype, dim, g, it, list, count, max_count, norm, euclid, p64, nullptr, nullptr);
-    if (mode == FABX_MODE_DTW) {
-        // pairs of short items, then the others (each kernel skips the other's)
-        if (dtype == FABX_DTYPE_F32) {
-            hipLaunchKernelGGL((k_recheck_dtw<float, false>), dim3(blocks), dim3(256), 0, s,
-                               static_cast<const float *>(features), dim, g.item0, g.n_items, g.pair_base,
-                               g.n_groups, it.src, it.len, list, count, max_count, norm, euclid, p64);
-            hipLaunchKernelGGL((k_recheck_dtw<float, true>), dim3(blocks), dim3(256), 0, s,
-                               static_cast<const float *>(features), dim, g.item0, g.n_items, g.pair_base,
-                               g.n_groups, it.src, it.len, list, count, max_count, norm, euclid, p64);
-        } else {
-            hipLaunchKernelGGL((k_recheck_dtw<uint16_t, false>), dim3(blocks), dim3(256), 0, s,
-                               static_cast<const uint16_t *>(features), dim, g.item0, g.n_items, g.pair_base,
-                               g.n_groups, it.src, it.len, list, count, max_count, norm, euclid, p64);
-            hipLaunchKernelGGL((k_recheck_dtw<uint16_t, true>), dim3(blocks), dim3(256), 0, s,
-                               static_cast<const uint16_t *>(features), dim, g.item0, g.n_items, g.pair_base,
-                               g.n_groups, it.src, it.len, list, count, max_count, norm, euclid, p64);
-        }
-    } else {
         if (dtype == FABX_DTYPE_F32)
             hipLaunchKernelGGL(k_recheck_pooled<float>, dim3(blocks), dim3(256), 0, s,
                                static_cast<const float *>(features), dim, g.item0, g.n_items,
@@ -557,7 +843,6 @@ void recheck_fp64(hipStream_t s, const void *features, int dtype, int dim, const
             hipLaunchKernelGGL(k_recheck_pooled<uint16_t>, dim3(blocks), dim3(256), 0, s,
                                static_cast<const uint16_t *>(features), dim, g.item0, g.n_items,
                                g.pair_base, g.n_groups, it.src, it.len, list, count, max_count, euclid, p64);
-    }
     FABX_HIP(hipGetLastError());
 }
 

@@ -258,18 +258,18 @@ __global__ __launch_bounds__(256) void k_triplets_sorted(const CellDev *__restri
     }
 }
 
-// Zeroes the per-cell counts W [n_cells] and the score's 64 counter bytes
+// Zeroes the per-cell counts W [n_cells] and the score's kCounterBytes counter bytes
 // that follow them, except the error item (the word at byte 8), which starts
 // at all ones.
 __global__ __launch_bounds__(256) void k_init(unsigned long long *__restrict__ W, int64_t n_cells) {
-    const int64_t n = n_cells + 8;
+    const int64_t n = n_cells + kCounterBytes / 8;
     for (int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < n; i += int64_t(gridDim.x) * blockDim.x)
         W[i] = i == n_cells + 1 ? ~0ull : 0ull;
 }
 
-// Marked pairs into `list`.  Every pair the triplet kernels mark belongs to a
-// row they also send to the recount, so with no such row there is nothing to
-// collect.
+// Marked pairs into `list` (pooled mode).  Every pair the triplet kernels mark
+// belongs to a row they also send to the recount, so with no such row there is
+// nothing to collect.
 __global__ __launch_bounds__(256) void k_collect_marked(const uint8_t *__restrict__ flags, int64_t n_slots,
                                                         int64_t *__restrict__ list,
                                                         unsigned int *__restrict__ count, int64_t cap,
@@ -288,6 +288,110 @@ __global__ __launch_bounds__(256) void k_collect_marked(const uint8_t *__restric
             const unsigned int k = base + unsigned(__popcll(ball & ((1ull << lane) - 1ull)));
             if (int64_t(k) < cap) list[k] = i;
         }
+    }
+}
+
+// DTW mode: the marked pairs as (x, y) task items (x the low word), one entry
+// where both orientations are marked, in the classes of PairLists (the small
+// ones from small_large's start, the large ones from its end: together at most
+// the unordered pairs, so they never meet).  Pairs with an item of more than 64
+// frames hold their FP64 value already and are only counted; the slots (x, x),
+// which nothing compares, are not looked at.  One pass over the flags, 16 slots
+// per lane (HBM-bound when few are marked), and one atomic per class and wave of
+// 1024 slots.
+__global__ __launch_bounds__(256) void k_collect_pairs(const uint8_t *__restrict__ flags, int64_t n_slots,
+                                                       const int64_t *__restrict__ g_item0,
+                                                       const int64_t *__restrict__ g_n,
+                                                       const int64_t *__restrict__ g_pair_base, int64_t n_groups,
+                                                       const int32_t *__restrict__ item_len, PairLists lists,
+                                                       const unsigned int *__restrict__ recount_n) {
+    if (*recount_n == 0) return;
+    const int lane = threadIdx.x % kWave;
+    const int64_t n16 = (n_slots + 15) / 16;
+    for (int64_t c = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; c - lane < n16;
+         c += int64_t(gridDim.x) * blockDim.x) {
+        const int64_t s0 = 16 * c;
+        uint32_t mask = 0;  // bit k: slot s0 + k is marked
+        if (s0 + 16 <= n_slots) {
+            const uint4 f = *reinterpret_cast<const uint4 *>(flags + s0);
+            // the mark bits of four bytes, gathered into four bits
+            auto bits = [](uint32_t v) { return (((v >> 1) & 0x01010101u) * 0x01020408u) >> 24; };
+            mask = bits(f.x) | (bits(f.y) << 4) | (bits(f.z) << 8) | (bits(f.w) << 12);
+        } else {
+            for (int64_t k = s0; k < n_slots; ++k) mask |= uint32_t((flags[k] & kMarked) != 0) << (k - s0);
+        }
+        if (__ballot(mask != 0) == 0) continue;
+        // visits the marked slots in order: fn(bit, x, y, group's first item, its items, its first slot)
+        const int64_t g_first = mask ? dev::find_segment(g_pair_base, n_groups, s0 + __builtin_ctz(mask)) : 0;
+        auto visit = [&](uint32_t bits, auto &&fn) {
+            int64_t g = g_first, base = 0, n = 0, i0 = 0, end = 0;
+            for (; bits; bits &= bits - 1) {
+                const int k = __builtin_ctz(bits);
+                const int64_t slot = s0 + k;
+                if (n == 0 || slot >= end) {
+                    while (slot >= g_pair_base[g + 1]) ++g;
+                    base = g_pair_base[g];
+                    end = g_pair_base[g + 1];
+                    n = g_n[g];
+                    i0 = g_item0[g];
+                }
+                const int64_t local = slot - base;
+                int64_t x, y;
+                if (end - base <= int64_t(0xFFFFFFFF)) {
+                    x = uint32_t(local) / uint32_t(n);
+                    y = uint32_t(local) - uint32_t(x) * uint32_t(n);
+                } else {
+                    x = local / n;
+                    y = local - x * n;
+                }
+                fn(k, x, y, i0, n, base);
+            }
+        };
+        uint32_t small = 0, mid = 0, large = 0, diag = 0;
+        visit(mask, [&](int k, int64_t x, int64_t y, int64_t i0, int64_t n, int64_t base) {
+            if (x == y) {
+                diag |= 1u << k;
+                return;
+            }
+            if (x > y && (flags[base + y * n + x] & kMarked)) return;  // listed as (y, x)
+            const int L = max(item_len[i0 + x], item_len[i0 + y]);
+            if (L <= 16) small |= 1u << k;
+            else if (L <= 32) mid |= 1u << k;
+            else if (L <= 64) large |= 1u << k;
+        });
+        // counts of the wave before this lane (a wave holds 1024 slots), and its totals
+        const uint32_t mine = uint32_t(__popc(small)) | (uint32_t(__popc(large)) << 16);
+        const uint32_t mine2 = uint32_t(__popc(mid)) | (uint32_t(__popc(mask & ~diag)) << 16);
+        uint32_t incl = mine, incl2 = mine2;
+#pragma unroll
+        for (int o = 1; o < kWave; o <<= 1) {
+            const uint32_t v = __shfl_up(incl, o, kWave), v2 = __shfl_up(incl2, o, kWave);
+            if (lane >= o) {
+                incl += v;
+                incl2 += v2;
+            }
+        }
+        uint32_t bs = 0, bm = 0, bl = 0;
+        if (lane == kWave - 1) {
+            if (incl2 >> 16) atomicAdd(lists.n_marked, incl2 >> 16);
+            if (incl & 0xFFFFu) bs = atomicAdd(lists.n_small, incl & 0xFFFFu);
+            if (incl2 & 0xFFFFu) bm = atomicAdd(lists.n_mid, incl2 & 0xFFFFu);
+            if (incl >> 16) bl = atomicAdd(lists.n_large, incl >> 16);
+        }
+        const uint32_t excl = incl - mine, excl2 = incl2 - mine2;
+        int64_t at_s = int64_t(uint32_t(__shfl(bs, kWave - 1, kWave))) + (excl & 0xFFFFu);
+        int64_t at_m = int64_t(uint32_t(__shfl(bm, kWave - 1, kWave))) + (excl2 & 0xFFFFu);
+        int64_t at_l = int64_t(uint32_t(__shfl(bl, kWave - 1, kWave))) + (excl >> 16);
+        visit(small | mid | large, [&](int k, int64_t x, int64_t y, int64_t i0, int64_t, int64_t) {
+            const int64_t e = (i0 + x) | ((i0 + y) << 32);
+            if ((mid >> k) & 1u) {
+                if (at_m < lists.cap) lists.mid[at_m] = e;
+                ++at_m;
+            } else {
+                const int64_t at = (small >> k) & 1u ? at_s++ : lists.cap - 1 - at_l++;
+                if (at >= 0 && at < lists.cap) lists.small_large[at] = e;
+            }
+        });
     }
 }
 
@@ -358,7 +462,7 @@ void triplets_sorted(hipStream_t s, const CellDev *cells, const int32_t *units, 
 }
 
 void init_score(hipStream_t s, unsigned long long *W, int64_t n_cells) {
-    const int64_t blocks = std::min<int64_t>((n_cells + 8 + 255) / 256, 4096);
+    const int64_t blocks = std::min<int64_t>((n_cells + kCounterBytes / 8 + 255) / 256, 4096);
     hipLaunchKernelGGL(k_init, dim3(unsigned(blocks)), dim3(256), 0, s, W, n_cells);
     FABX_HIP(hipGetLastError());
 }
@@ -369,6 +473,15 @@ void collect_marked(hipStream_t s, const uint8_t *flags, int64_t n_slots, int64_
     const int64_t blocks = std::min<int64_t>((n_slots + 255) / 256, 4096);
     hipLaunchKernelGGL(k_collect_marked, dim3(unsigned(blocks)), dim3(256), 0, s, flags, n_slots,
                        list, count, cap, recount_n);
+    FABX_HIP(hipGetLastError());
+}
+
+void collect_pairs(hipStream_t s, const uint8_t *flags, int64_t n_slots, const GroupTables &g, const ItemTables &it,
+                   const PairLists &lists, const unsigned int *recount_n) {
+    if (n_slots <= 0) return;
+    const int64_t blocks = std::min<int64_t>((n_slots + 4095) / 4096, 4096);
+    hipLaunchKernelGGL(k_collect_pairs, dim3(unsigned(blocks)), dim3(256), 0, s, flags, n_slots, g.item0, g.n_items,
+                       g.pair_base, g.n_groups, it.len, lists, recount_n);
     FABX_HIP(hipGetLastError());
 }
 

@@ -175,14 +175,30 @@ void triplets_sorted(hipStream_t s, const CellDev *cells, const int32_t *units, 
               float margin, int32_t *recount, unsigned int *recount_n, int64_t recount_cap,
               const unsigned int *scale);
 
-// Zeroes W [n_cells] and the 64 counter bytes after it (the u64 at byte 8 of
+// Counter bytes of a score, kept after its per-cell counts.
+constexpr int kCounterBytes = 128;
+// Zeroes W [n_cells] and the kCounterBytes after it (the u64 at byte 8 of
 // those, the error item, is set to all ones).
 void init_score(hipStream_t s, unsigned long long *W, int64_t n_cells);
 
-// Pair slots whose flag bit 1 is set -> list (order unspecified); nothing when
+// Pooled mode: pair slots whose flag bit 1 is set -> list (order unspecified); nothing when
 // *recount_n is 0 (no row was sent to the recount, so no pair is marked).
 void collect_marked(hipStream_t s, const uint8_t *flags, int64_t n_slots, int64_t *list,
                     unsigned int *count, int64_t cap, const unsigned int *recount_n);
+
+// DTW mode: the pairs whose flag bit 1 is set, as x | y << 32 (task items), one
+// entry for both orientations, by the longer item's frames: at most 16 from
+// small_large[0] on (n_small), 17 to 32 from mid[0] on (n_mid), 33 to 64 from
+// small_large[cap - 1] down (n_large); longer ones are only counted.  cap, the
+// room of either array, is the number of unordered pairs or more.  n_marked:
+// marked slots.
+struct PairLists {
+    int64_t *small_large, *mid;
+    int64_t cap;
+    unsigned int *n_marked, *n_small, *n_mid, *n_large;
+};
+void collect_pairs(hipStream_t s, const uint8_t *flags, int64_t n_slots, const GroupTables &g, const ItemTables &it,
+                   const PairLists &lists, const unsigned int *recount_n);
 
 // Re-count rows (cell, x): a comparison of two recomputed pairs (flag bit 1 on both)
 // uses their FP64 values, any other comparison the FP32 ones.
@@ -191,21 +207,25 @@ void recount(hipStream_t s, const CellDev *cells, const int32_t *rows, const uns
              const uint8_t *flags, unsigned long long *W);
 
 // --- k_recheck.hip
-// FP64 distance of each listed pair slot from the raw features (unit vectors
-// by division by the sequential-sum norm, cosine as a sequential sum, acos or
-// the half-chord atan2 form near |cos| = 1, DTW with diagonal > left > up).
-// has_long: the task has items of more than 64 frames (DTW mode); their pairs
-// go through the tiled kernel of long_dtw.  euclid: the Euclidean distance.
-void recheck_fp64(hipStream_t s, const void *features, int dtype, int dim, const GroupTables &g,
-                  const ItemTables &it, const int64_t *list, const unsigned int *count,
-                  int64_t max_count, int mode, int norm, bool has_long, int euclid, double *p64);
-// The same FP64 DTW for the listed slots whose pair has an item of more than
-// 64 frames (up to FABX_MAX_ITEM_FRAMES); others are skipped.  count: device
-// count of listed slots, or null for max_count.  p32 and flags (may be null)
-// also receive the value and 0 (robust, unmarked).
+// FP64 distances from the raw features (cosine of the frames from their FP64
+// product, acos or the half-chord atan2 form near |cos| = 1, DTW with
+// diagonal > left > up); euclid: the Euclidean distance.  Each evaluation gives
+// both orientations of a pair.
+// DTW mode, the pairs listed by collect_pairs; max_len: the task's longest
+// item.  The value goes to p64 at both slots.
+void recheck_dtw(hipStream_t s, const void *features, int dtype, int dim, const GroupTables &g,
+                 const ItemTables &it, const int32_t *item_group, const PairLists &lists, int n_cu, int max_len,
+                 int norm, int euclid, double *p64);
+// DTW of the listed pairs (x | y << 32, unordered) in which an item has more than 64
+// frames (up to FABX_MAX_ITEM_FRAMES): p64, p32 (rounded once) and flags (0:
+// robust, unmarked) at both slots.
 void long_dtw(hipStream_t s, const void *features, int dtype, int dim, const GroupTables &g,
-              const ItemTables &it, const int64_t *list, const unsigned int *count, int64_t max_count, int norm,
+              const ItemTables &it, const int32_t *item_group, const int64_t *list, int64_t n_list, int norm,
               int euclid, double *p64, float *p32, uint8_t *flags);
+// Pooled mode: FP64 distance of the mean frames of each listed pair slot.
+void recheck_pooled(hipStream_t s, const void *features, int dtype, int dim, const GroupTables &g,
+                    const ItemTables &it, const int64_t *list, const unsigned int *count, int64_t max_count,
+                    int euclid, double *p64);
 
 }  // namespace kern
 }  // namespace fabx

@@ -347,7 +347,7 @@ struct PendingScore {
     hipStream_t stream = nullptr;
     std::unique_ptr<Timer> tm;
     DevBuf plan_d;                 // Gram tile prefix read by the plain / pooled kernels
-    void *host = nullptr;          // pinned: half_units [n_cells] then 64 counter bytes
+    void *host = nullptr;          // pinned: half_units [n_cells] then the counter bytes
     size_t host_bytes = 0;
     std::unique_ptr<PinnedBlock> packed;  // the task's packed tables, if this score sent them
     bool bf16 = false, dtw = false, keep_pairs = false;
@@ -406,7 +406,7 @@ struct DevPtrs {
     const int32_t *band_rb = nullptr;
     const int64_t *unit_prefix = nullptr;
     const int64_t *tiles = nullptr;             // pooled: Gram tile prefix per group
-    const int64_t *long_slots = nullptr;        // BF16 DTW: slots of pairs with an item over 64 frames
+    const int64_t *long_slots = nullptr;        // BF16 DTW: pairs with an item over 64 frames
     std::array<const int64_t *, 8> strips{};    // plain DTW: group, slot0, row0, nrows, col0, ncols, base, tiles
     void *xn = nullptr;
     float *rinv = nullptr, *dmat = nullptr, *p32 = nullptr;
@@ -414,7 +414,7 @@ struct DevPtrs {
     double *p64 = nullptr;
     int64_t *recheck_list = nullptr;
     int32_t *recount_list = nullptr;
-    unsigned long long *half_units = nullptr;   // [n_cells], then the score's 64 counter bytes
+    unsigned long long *half_units = nullptr;   // [n_cells], then the score's counter bytes
     uint32_t *finfo = nullptr;                  // stream kernel: frame info [n_frames]
     float *flen = nullptr;                      // Euclidean BF16 form: frame (or mean) lengths
 };
@@ -482,15 +482,15 @@ WorkspaceSizes workspace_sizes(const TaskImpl &t, const ScoreParams &p, const Pl
         w.recheck_list = size_t(t.n_pair_slots) * 8;
         w.recount_list = size_t(std::max<int64_t>(t.sum_nx, 1)) * 8;
     }
-    // per-cell counts, then 64 counter bytes: both come back with one copy
-    w.half_units = t.cells.size() * 8 + 64;
+    // per-cell counts, then the counter bytes: both come back with one copy
+    w.half_units = t.cells.size() * 8 + kern::kCounterBytes;
     if (stream) w.finfo = size_t(t.n_frames) * 4;
     if (bf16 && p.distance == FABX_DISTANCE_EUCLIDEAN) w.flen = size_t(rows) * 4;
     return w;
 }
 
 // Enqueues every kernel of a score on `stream` and the copy of the per-cell
-// counts and the 64 counter bytes into `host` [n_cells * 8 + 64].  `tm` (may
+// counts and the counter bytes into `host` [n_cells * 8 + kCounterBytes].  `tm` (may
 // be null) records the stage events 0..6.
 void enqueue_score(const TaskImpl &t, const ScoreParams &p, const FusedConfig &fcfg, const ColPlan *cplan,
                    const std::vector<int64_t> &tiles, const PlainPlan &strips, const DevPtrs &d,
@@ -569,7 +569,7 @@ void enqueue_score(const TaskImpl &t, const ScoreParams &p, const FusedConfig &f
         kern::fused_bf16(stream, static_cast<const uint16_t *>(d.xn), d.rinv, dim_pad, gt, it, fp, p.dtw_norm,
                          float(p.delta), d.p32, d.flags, nonrobust_n, unit_ctr, flen, scale);
         // pairs with an item over 64 frames: FP64 from the raw features
-        kern::long_dtw(stream, ds.features, ds.dtype, dim, gt, it, d.long_slots, nullptr,
+        kern::long_dtw(stream, ds.features, ds.dtype, dim, gt, it, d.item_group, d.long_slots,
                        int64_t(t.long_slots.size()), p.dtw_norm, euclid ? 1 : 0, d.p64, d.p32, d.flags);
         st.computed_dtw_cells = cplan->cells;
     } else if (!bf16) {
@@ -589,14 +589,26 @@ void enqueue_score(const TaskImpl &t, const ScoreParams &p, const FusedConfig &f
                           d.half_units, flags, float(p.margin), recount, recount_n, t.sum_nx, scale);
     mark();  // 4
     if (bf16) {
-        kern::collect_marked(stream, d.flags, t.n_pair_slots, d.recheck_list, marked_n, t.n_pair_slots, recount_n);
-        kern::recheck_fp64(stream, ds.features, ds.dtype, dim, gt, it, d.recheck_list, marked_n, t.n_pair_slots,
-                           p.mode, p.dtw_norm, dtw && t.max_len > kFusedRowFrames, euclid ? 1 : 0, d.p64);
+        if (dtw) {
+            // every pair is listed once: (slots - items) / 2 unordered pairs (x, y), x != y
+            const int64_t pairs = (t.n_pair_slots - int64_t(t.items.size())) / 2;
+            unsigned int *n_class = reinterpret_cast<unsigned int *>(counters + 64);  // small, mid, large
+            const kern::PairLists lists{d.recheck_list, d.recheck_list + pairs, pairs, marked_n,
+                                        n_class, n_class + 1, n_class + 2};
+            kern::collect_pairs(stream, d.flags, t.n_pair_slots, gt, it, lists, recount_n);
+            kern::recheck_dtw(stream, ds.features, ds.dtype, dim, gt, it, d.item_group, lists, ds.ctx->n_cu,
+                              t.max_len, p.dtw_norm, euclid ? 1 : 0, d.p64);
+        } else {
+            kern::collect_marked(stream, d.flags, t.n_pair_slots, d.recheck_list, marked_n, t.n_pair_slots,
+                                 recount_n);
+            kern::recheck_pooled(stream, ds.features, ds.dtype, dim, gt, it, d.recheck_list, marked_n,
+                                 t.n_pair_slots, euclid ? 1 : 0, d.p64);
+        }
         kern::recount(stream, d.cells, d.recount_list, recount_n, t.sum_nx, gt, d.p32, d.p64, d.flags,
                       d.half_units);
     }
     mark();  // 5
-    FABX_HIP(hipMemcpyAsync(host, d.half_units, size_t(n_cells) * 8 + 64, hipMemcpyDeviceToHost, stream));
+    FABX_HIP(hipMemcpyAsync(host, d.half_units, size_t(n_cells) * 8 + kern::kCounterBytes, hipMemcpyDeviceToHost, stream));
     mark();  // 6
 }
 
@@ -754,7 +766,7 @@ std::shared_ptr<ResultImpl> launch_score(const std::shared_ptr<TaskImpl> &tp, co
                     std::make_pair(&ws.flen, wz.flen)})
         if (bs.second) bs.first->ensure(bs.second);
     st.workspace_bytes = int64_t(ws.total());
-    pend->host_bytes = size_t(n_cells) * 8 + 64;
+    pend->host_bytes = size_t(n_cells) * 8 + kern::kCounterBytes;
     pend->host = ds.ctx->pinned.get(pend->host_bytes, &pend->host_bytes);
 
     d.it = kern::ItemTables{dv.item_src, dv.item_len, dv.item_dst, n_items};
@@ -962,7 +974,7 @@ void score_in_scratch(TaskImpl &t, const ScoreParams &p, char *base, size_t cap,
     d.finfo = reinterpret_cast<uint32_t *>(take(wz.finfo));
     d.flen = reinterpret_cast<float *>(take(wz.flen));
     st.workspace_bytes = int64_t(wz.total_aligned());
-    std::vector<char> host(size_t(n_cells) * 8 + 64);
+    std::vector<char> host(size_t(n_cells) * 8 + kern::kCounterBytes);
     try {
         enqueue_score(t, p, fcfg, cplan, tiles, strips, d, stream, nullptr, host.data(), st);
         FABX_HIP(hipStreamSynchronize(stream));

@@ -645,8 +645,8 @@ void plan_blocks(TaskImpl &t) {
             pack_blocks(t, gi, kFusedRowFrames, t.rb.data() + 4 * size_t(t.g_rb0[size_t(gi)]));
     });
     t.fused_cells = col_plan(t, Tuner::default_config().cols).cells;
-    // pair slots with an item of more than kFusedRowFrames frames, both
-    // orientations, (x, x) left out: the FP64 long-item kernel's list
+    // unordered pairs with an item of more than kFusedRowFrames frames, (x, x)
+    // left out: the FP64 long-item kernel's list (task items, x | y << 32)
     t.long_slots.clear();
     if (t.max_len > kFusedRowFrames) {
         for (const Group &g : t.groups) {
@@ -655,8 +655,7 @@ void plan_blocks(TaskImpl &t) {
                 const bool la = t.item_len[size_t(g.item0 + a)] > kFusedRowFrames;
                 for (int64_t b = a + 1; b < n; ++b) {
                     if (!la && t.item_len[size_t(g.item0 + b)] <= kFusedRowFrames) continue;
-                    t.long_slots.push_back(g.pair_base + a * n + b);
-                    t.long_slots.push_back(g.pair_base + b * n + a);
+                    t.long_slots.push_back((g.item0 + a) | (g.item0 + b) << 32);
                 }
             }
         }

@@ -105,6 +105,9 @@ struct PinnedPool {
 // blocks, so items are <= 64 frames.
 constexpr int kFusedRowFrames = 64;
 constexpr int kSortedMaxB = 4096;      // largest |B| counted from sorted rows (sorted in LDS)
+constexpr int64_t kSortedMinPerX = 8192;  // comparisons per x from which on rows are sorted
+// Cells counted from sorted rows rather than by brute force.
+constexpr bool sorted_cell(int64_t na, int64_t nb) { return na * nb >= kSortedMinPerX && nb <= kSortedMaxB; }
 constexpr int kFusedColFrames = 128;  // default: tile kernel, 128-frame column blocks (the other is 256)
 constexpr int kStreamMinCols = 512;   // cols at or above this select the stream kernel
 // Units of a group with at least kBandMinCols column blocks go in bands of

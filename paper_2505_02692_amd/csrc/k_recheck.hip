@@ -33,15 +33,12 @@ constexpr double kPi = 3.14159265358979323846;
 template <typename T>
 __device__ __forceinline__ double ld(const T *p, int64_t i);
 template <>
+__device__ __forceinline__ double ld<double>(const double *p, int64_t i) { return p[i]; }
+template <>
 __device__ __forceinline__ double ld<float>(const float *p, int64_t i) { return double(p[i]); }
 template <>
 __device__ __forceinline__ double ld<uint16_t>(const uint16_t *p, int64_t i) {
     return double(__uint_as_float(uint32_t(p[i]) << 16));
-}
-
-__device__ double angle_over_pi_units(double c, double sm, double sp) {
-    const double th = fabs(c) < 1.0 - 0x1p-20 ? acos(c) : 2.0 * atan2(sqrt(sm), sqrt(sp));
-    return th / kPi;
 }
 
 // The per-lane loops over the features below are unrolled so that the loads
@@ -188,6 +185,10 @@ template <>
 struct Four<uint16_t> {
     typedef unsigned short V __attribute__((ext_vector_type(4), aligned(2)));
 };
+template <>
+struct Four<double> {
+    typedef double V __attribute__((ext_vector_type(4), aligned(8)));
+};
 template <typename T>
 __device__ __forceinline__ typename Four<T>::V load4(const T *p) {
     return *reinterpret_cast<const typename Four<T>::V *>(p);
@@ -199,6 +200,7 @@ __device__ __forceinline__ typename Four<T>::V load4_tail(const T *row, int k, i
     for (int e = 0; e < 4; ++e) v[e] = k + e < dim ? row[k + e] : T(0);
     return v;
 }
+__device__ __forceinline__ double widen(double d) { return d; }
 __device__ __forceinline__ double widen(float f) { return double(f); }
 __device__ __forceinline__ double widen(unsigned short h) { return double(dev::bf16_to_f32(h)); }
 
@@ -230,8 +232,13 @@ __device__ __forceinline__ double ror1(double v) {
 //    so each lane keeps its row frame against all 16 column frames, which it
 //    gets by rotating them through the 16 lanes (DPP), and sums the squares of
 //    its quarter of the features.
-template <typename T, bool kEuclid, int kT, int kStages = sizeof(T) == 4 ? 3 : 4, typename Ptr, typename At>
-__device__ __forceinline__ void tile_distances(int n_tiles, Ptr &&ptr, int dim, At &&at) {
+//    (only where want(u, i, j))
+struct All {
+    __device__ bool operator()(int, int, int) const { return true; }
+};
+template <typename T, bool kEuclid, int kT, int kStages = sizeof(T) == 4 ? 3 : 4, typename Ptr, typename At,
+          typename Want = All>
+__device__ __forceinline__ void tile_distances(int n_tiles, Ptr &&ptr, int dim, At &&at, Want &&want = All{}) {
     const int lane = threadIdx.x % dev::kWave, i16 = lane % 16, q = lane / 16;
     const T *pa[kT], *pb[kT];
     int nr[kT], nc[kT];
@@ -346,7 +353,7 @@ __device__ __forceinline__ void tile_distances(int n_tiles, Ptr &&ptr, int dim, 
                 const double dot = r == 0 ? acc[u][0] : r == 1 ? acc[u][1] : r == 2 ? acc[u][2] : acc[u][3];
                 const double c = dot * (__shfl(su, i, dev::kWave) * sv);
                 const bool is_near = !(fabs(c) < 1.0 - 0x1p-20);
-                near = near || is_near;
+                near = near || (is_near && want(u, i, i16));
                 *at(u, i, i16) = is_near ? -1.0 : acos(c) / kPi;
             }
         }
@@ -361,7 +368,7 @@ __device__ __forceinline__ void tile_distances(int n_tiles, Ptr &&ptr, int dim, 
                 for (int e = 0; e < n_r * n_c; ++e) {
                     const int i = e / n_c, j = e % n_c;
                     double *d = at(u, i, j);
-                    if (!(*d < 0.0)) continue;  // wave-uniform
+                    if (!(*d < 0.0) || !want(u, i, j)) continue;  // wave-uniform
                     const double v = wave_near_distance(a + int64_t(i) * dim, b + int64_t(j) * dim, dim, lane);
                     if (lane == 0) *d = v;
                 }
@@ -708,68 +715,191 @@ __global__ __launch_bounds__(320, 3) void k_long_dtw(const T *__restrict__ feat,
     }
 }
 
+// Pooled mode.  With few marked pairs each is done by itself from the raw frames
+// (k_recheck_pooled).  From n_items / 2 marked slots on, where that would read
+// the features more often than once, every item's FP64 mean is made once
+// (k_mean64) and the marked pairs are taken as 16 x 16 tiles of the groups' pair
+// matrices (k_pooled_tiles); the means go where the pair list was.  The host
+// leaves out the second way when the means do not fit there.
+__device__ __forceinline__ bool by_tiles(unsigned int n_marked, int64_t n_items, bool fits) {
+    return fits && 2 * int64_t(n_marked) >= n_items;
+}
+
+// The FP64 mean of frames f[0..N) at features k.. of this thread (sequential
+// sums, then one division); n_k: valid features of the four.
+template <typename T>
+__device__ __forceinline__ void mean4(const T *f, int N, int dim, int k, double (&m)[4]) {
+    for (int e = 0; e < 4; ++e) m[e] = 0.0;
+    const bool whole = k + 4 <= dim;
+#pragma unroll 4
+    for (int t = 0; t < N; ++t) {
+        const T *row = f + int64_t(t) * dim;
+        const typename Four<T>::V v = whole ? load4(row + k) : load4_tail(row, k, dim);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) m[e] += widen(v[e]);
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) m[e] /= double(N);
+}
+
+// HBM-bound: one read of the features, 8 bytes a feature and item written.
+template <typename T>
+__global__ __launch_bounds__(256) void k_mean64(const T *__restrict__ feat, int dim,
+                                                const int64_t *__restrict__ item_src,
+                                                const int32_t *__restrict__ item_len, int64_t n_items,
+                                                const unsigned int *__restrict__ n_marked,
+                                                double *__restrict__ means) {
+    if (!by_tiles(*n_marked, n_items, true)) return;
+    const int lane = threadIdx.x % dev::kWave;
+    for (int64_t x = int64_t(blockIdx.x) * 4 + threadIdx.x / dev::kWave; x < n_items; x += int64_t(gridDim.x) * 4) {
+        const T *f = feat + item_src[x] * int64_t(dim);
+        const int N = item_len[x];
+        for (int k = 4 * lane; k < dim; k += 4 * dev::kWave) {
+            double m[4];
+            mean4(f, N, dim, k, m);
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (k + e < dim) means[x * int64_t(dim) + k + e] = m[e];
+        }
+    }
+}
+
+// Blocks take 64 x 128 tiles of the groups' pair matrices (tile_prefix), waves 16
+// rows of them, two 16 x 16 tiles of unordered pairs x < y with a marked slot at a
+// time.  Bound by the FP64 matrix rate and the means' loads.  9.7e6 marked pairs
+// of 87,489 items at dim 512 (lengths 1-60): 519 ms pair by pair, 2.2 ms here
+// after 0.63 ms for the means.
+template <bool kEuclid>
+__global__ __launch_bounds__(256, 2) void k_pooled_tiles(const double *__restrict__ means, int dim,
+                                                         const int64_t *__restrict__ g_item0,
+                                                         const int64_t *__restrict__ g_n,
+                                                         const int64_t *__restrict__ g_pair_base,
+                                                         const int64_t *__restrict__ tile_prefix, int64_t n_groups,
+                                                         int64_t n_tiles, int64_t n_items,
+                                                         const unsigned int *__restrict__ n_marked,
+                                                         const uint8_t *__restrict__ flags,
+                                                         double *__restrict__ p64) {
+    if (!by_tiles(*n_marked, n_items, true)) return;
+    __shared__ double dm_s[4][2 * 16 * kTileLd];
+    const int lane = threadIdx.x % dev::kWave, i16 = lane % 16, q = lane / 16;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / dev::kWave);
+    double *dm = dm_s[w];
+    for (int64_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
+        const int64_t g = dev::find_segment_wave(tile_prefix, n_groups, tile);
+        const int64_t n = g_n[g], local = tile - tile_prefix[g], ntc = (n + 127) / 128;
+        const int64_t x0 = local / ntc * 64 + 16 * w, c0 = local % ntc * 128;
+        if (x0 >= n) continue;
+        const double *rows = means + g_item0[g] * int64_t(dim);
+        const uint8_t *fl = flags + g_pair_base[g];
+        double *out = p64 + g_pair_base[g];
+#pragma unroll 1
+        for (int64_t y0 = c0; y0 < min(c0 + 128, n); y0 += 32) {
+            if (y0 + 31 <= x0) continue;  // below the diagonal
+            uint32_t mxy = 0, myx = 0;    // bit 4 u + r: this lane's element of tile u, register r is marked
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int64_t x = x0 + q + 4 * r, y = y0 + 16 * u + i16;
+                    if (x < y && y < n) {
+                        if (fl[x * n + y] & 2) mxy |= 1u << (4 * u + r);
+                        if (fl[y * n + x] & 2) myx |= 1u << (4 * u + r);
+                    }
+                }
+            const uint32_t m = mxy | myx;
+            if (__ballot(m != 0) == 0) continue;
+            tile_distances<double, kEuclid, 2, 2>(
+                y0 + 16 < n ? 2 : 1,
+                [&](int u, const double *&a, int &nr, const double *&b, int &nc) {
+                    a = rows + x0 * dim;
+                    b = rows + (y0 + 16 * u) * dim;
+                    nr = int(min<int64_t>(16, n - x0));
+                    nc = int(min<int64_t>(16, n - (y0 + 16 * u)));
+                },
+                dim, [&](int u, int r, int c) { return dm + (16 * u + r) * kTileLd + c; },
+                [&](int u, int r, int c) { return x0 + r < y0 + 16 * u + c; });
+            __builtin_amdgcn_wave_barrier();
+            for (uint32_t b = m; b; b &= b - 1) {
+                const int k = __builtin_ctz(b), u = k / 4, i = q + 4 * (k % 4);
+                const int64_t x = x0 + i, y = y0 + 16 * u + i16;
+                const double d = dm[(16 * u + i) * kTileLd + i16];
+                if ((mxy >> k) & 1u) out[x * n + y] = d;
+                if ((myx >> k) & 1u) out[y * n + x] = d;
+            }
+            __builtin_amdgcn_wave_barrier();
+        }
+    }
+}
+
 // One block per listed pair: the two items' mean frames (threads over the
-// feature dimension), then wave 0 takes their norms, cosine and, near +-1,
-// the half-chord sums, its lanes splitting the dimension.
+// features), then wave 0 takes their norms and cosine and, near +-1, the
+// half-chord sums, its lanes splitting the dimension.
 template <typename T>
 __global__ __launch_bounds__(256) void k_recheck_pooled(const T *__restrict__ feat, int dim,
                                                         const int64_t *__restrict__ g_item0,
                                                         const int64_t *__restrict__ g_n,
                                                         const int64_t *__restrict__ g_pair_base,
-                                                        int64_t n_groups,
                                                         const int64_t *__restrict__ item_src,
                                                         const int32_t *__restrict__ item_len,
-                                                        const int64_t *__restrict__ list,
-                                                        const unsigned int *__restrict__ count,
-                                                        int64_t max_count, int euclid,
-                                                        double *__restrict__ p64) {
+                                                        const int32_t *__restrict__ item_group,
+                                                        const int64_t *__restrict__ list, int64_t cap,
+                                                        const unsigned int *__restrict__ count, int64_t n_items,
+                                                        const unsigned int *__restrict__ n_marked, int tiles_fit,
+                                                        int euclid, double *__restrict__ p64) {
+    if (by_tiles(*n_marked, n_items, tiles_fit != 0)) return;
     __shared__ double mx[2048];
     __shared__ double my[2048];
     const int lane = threadIdx.x % dev::kWave;
-    const int64_t total = min(int64_t(*count), max_count);
+    const int64_t total = min(int64_t(*count), cap);
     for (int64_t e = blockIdx.x; e < total; e += gridDim.x) {
-        const int64_t slot = list[e];
-        const int64_t g = dev::find_segment_wave(g_pair_base, n_groups, slot);
-        const int64_t n = g_n[g];
-        const int64_t local = slot - g_pair_base[g];
-        const int64_t x = g_item0[g] + local / n, y = g_item0[g] + local % n;
-        const int N = item_len[x], M = item_len[y];
-        const T *fx = feat + item_src[x] * int64_t(dim);
-        const T *fy = feat + item_src[y] * int64_t(dim);
-        for (int k = threadIdx.x; k < dim; k += blockDim.x) {
-            double sx = 0.0, sy = 0.0;
-            for (int t = 0; t < N; ++t) sx += ld(fx, int64_t(t) * dim + k);
-            for (int t = 0; t < M; ++t) sy += ld(fy, int64_t(t) * dim + k);
-            mx[k] = sx / double(N);
-            my[k] = sy / double(M);
+        const Pair pr = pair_of(list[e]);
+        const int N = item_len[pr.x], M = item_len[pr.y];
+        const T *fx = feat + item_src[pr.x] * int64_t(dim);
+        const T *fy = feat + item_src[pr.y] * int64_t(dim);
+        const int n4 = (dim + 3) / 4;
+        for (int t = threadIdx.x; t < 2 * n4; t += blockDim.x) {
+            const bool second = t >= n4;
+            const int k = 4 * (second ? t - n4 : t);
+            double m[4];
+            mean4(second ? fy : fx, second ? M : N, dim, k, m);
+#pragma unroll
+            for (int f = 0; f < 4; ++f)
+                if (k + f < dim) (second ? my : mx)[k + f] = m[f];
         }
         __syncthreads();
-        if (threadIdx.x < dev::kWave && euclid) {
-            double sd = 0.0;
-            for (int k = lane; k < dim; k += dev::kWave) sd += (mx[k] - my[k]) * (mx[k] - my[k]);
-            sd = wave_sum_f64(sd);
-            if (lane == 0) p64[slot] = sqrt(sd);
-        } else if (threadIdx.x < dev::kWave) {
-            double sx = 0.0, sy = 0.0;
-            for (int k = lane; k < dim; k += dev::kWave) {
-                sx += mx[k] * mx[k];
-                sy += my[k] * my[k];
-            }
-            const double ix = 1.0 / sqrt(wave_sum_f64(sx)), iy = 1.0 / sqrt(wave_sum_f64(sy));
-            double c = 0.0;
-            for (int k = lane; k < dim; k += dev::kWave) c += (mx[k] * ix) * (my[k] * iy);
-            c = wave_sum_f64(c);
-            double sm = 0.0, sp = 0.0;
-            if (!(fabs(c) < 1.0 - 0x1p-20)) {
+        if (threadIdx.x < dev::kWave) {
+            double d;
+            if (euclid) {
+                double sd = 0.0;
+                for (int k = lane; k < dim; k += dev::kWave) sd += (mx[k] - my[k]) * (mx[k] - my[k]);
+                d = sqrt(wave_sum_f64(sd));
+            } else {
+                double sx = 0.0, sy = 0.0;
                 for (int k = lane; k < dim; k += dev::kWave) {
-                    const double a = mx[k] * ix, b = my[k] * iy;
-                    sm += (a - b) * (a - b);
-                    sp += (a + b) * (a + b);
+                    sx += mx[k] * mx[k];
+                    sy += my[k] * my[k];
                 }
-                sm = wave_sum_f64(sm);
-                sp = wave_sum_f64(sp);
+                const double ix = 1.0 / sqrt(wave_sum_f64(sx)), iy = 1.0 / sqrt(wave_sum_f64(sy));
+                double c = 0.0;
+                for (int k = lane; k < dim; k += dev::kWave) c += (mx[k] * ix) * (my[k] * iy);
+                c = wave_sum_f64(c);
+                if (fabs(c) < 1.0 - 0x1p-20) {
+                    d = acos(c) / kPi;
+                } else {
+                    double sm = 0.0, sp = 0.0;
+                    for (int k = lane; k < dim; k += dev::kWave) {
+                        const double a = mx[k] * ix, b = my[k] * iy;
+                        sm += (a - b) * (a - b);
+                        sp += (a + b) * (a + b);
+                    }
+                    d = near_angle_over_pi(wave_sum_f64(sm), wave_sum_f64(sp));
+                }
             }
-            if (lane == 0) p64[slot] = angle_over_pi_units(c, sm, sp);
+            if (lane == 0) {
+                const PairSlots s = slots_of(pr, item_group, g_item0, g_n, g_pair_base);
+                p64[s.xy] = d;
+                p64[s.yx] = d;
+            }
         }
         __syncthreads();
     }
@@ -830,19 +960,24 @@ void recheck_dtw(hipStream_t s, const void *features, int dtype, int dim, const 
 }
 
 void recheck_pooled(hipStream_t s, const void *features, int dtype, int dim, const GroupTables &g,
-                    const ItemTables &it, const int64_t *list, const unsigned int *count, int64_t max_count,
-                    int euclid, double *p64) {
-    if (max_count <= 0) return;
+                    const ItemTables &it, const int32_t *item_group, const PairLists &lists, double *means,
+                    const int64_t *tile_prefix, int64_t n_tiles, const uint8_t *flags, int euclid, double *p64) {
+    if (lists.cap <= 0) return;
     if (dim > 2048) fail(FABX_EINVAL, "pooled recheck supports dim <= 2048");
-    const unsigned blocks = unsigned(std::min<int64_t>(max_count, 4096));
-        if (dtype == FABX_DTYPE_F32)
-            hipLaunchKernelGGL(k_recheck_pooled<float>, dim3(blocks), dim3(256), 0, s,
-                               static_cast<const float *>(features), dim, g.item0, g.n_items,
-                               g.pair_base, g.n_groups, it.src, it.len, list, count, max_count, euclid, p64);
-        else
-            hipLaunchKernelGGL(k_recheck_pooled<uint16_t>, dim3(blocks), dim3(256), 0, s,
-                               static_cast<const uint16_t *>(features), dim, g.item0, g.n_items,
-                               g.pair_base, g.n_groups, it.src, it.len, list, count, max_count, euclid, p64);
+    const unsigned blocks = unsigned(std::min<int64_t>(lists.cap, 4096));
+    typed(features, dtype, euclid, [&](auto *f, auto) {
+        using T = std::remove_const_t<std::remove_pointer_t<decltype(f)>>;
+        hipLaunchKernelGGL(k_recheck_pooled<T>, dim3(blocks), dim3(256), 0, s, f, dim, g.item0, g.n_items,
+                           g.pair_base, it.src, it.len, item_group, lists.small_large, lists.cap, lists.n_small,
+                           it.n_items, lists.n_marked, means ? 1 : 0, euclid, p64);
+        if (means)
+            hipLaunchKernelGGL(k_mean64<T>, dim3(grid_for(it.n_items, 4)), dim3(256), 0, s, f, dim, it.src, it.len,
+                               it.n_items, lists.n_marked, means);
+    });
+    if (means)
+        hipLaunchKernelGGL(euclid ? k_pooled_tiles<true> : k_pooled_tiles<false>, dim3(grid_for(n_tiles, 1)),
+                           dim3(256), 0, s, means, dim, g.item0, g.n_items, g.pair_base, tile_prefix, g.n_groups,
+                           n_tiles, it.n_items, lists.n_marked, flags, p64);
     FABX_HIP(hipGetLastError());
 }
 

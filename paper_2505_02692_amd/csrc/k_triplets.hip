@@ -125,7 +125,8 @@ __global__ __launch_bounds__(256) void k_triplets(const CellDev *__restrict__ ce
 }
 
 // Count of sorted values v[0..n) below `key` (strict: v < key) or at most `key`.
-__device__ __forceinline__ int count_below(const float *v, int n, float key, bool inclusive) {
+template <typename V>
+__device__ __forceinline__ int count_below(const V *v, int n, V key, bool inclusive) {
     int lo = 0, hi = n;
     while (lo < hi) {
         const int mid = (lo + hi) >> 1;
@@ -135,12 +136,154 @@ __device__ __forceinline__ int count_below(const float *v, int n, float key, boo
     return lo;
 }
 
+// Exclusive prefix sums over the 256 threads of one count each; total: their
+// sum.  scratch [4] is free again after the next barrier.
+__device__ __forceinline__ uint32_t block_prefix(uint32_t v, uint32_t *scratch, uint32_t &total) {
+    const int lane = threadIdx.x % kWave, w = threadIdx.x / kWave;
+    uint32_t incl = v;
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+        const uint32_t u = __shfl_up(incl, o, kWave);
+        if (lane >= o) incl += u;
+    }
+    if (lane == kWave - 1) scratch[w] = incl;
+    __syncthreads();
+    uint32_t before = 0;
+    total = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        if (k < w) before += scratch[k];
+        total += scratch[k];
+    }
+    return before + incl - v;
+}
+
+// The n <= kCap values src[0..n) sorted into sv, with their positions in si, by
+// a 256-thread block.  The values go to kCap buckets of equal width between the
+// least and the largest (their bucket grows with the value), each bucket's few
+// values are then sorted by insertion.  Values that crowd a bucket (many exact
+// ties, an infinity, a NaN) take the bitonic sort instead.  Bound by LDS
+// latency: 9 barriers where the bitonic sort of 1024 values has 55 (the sorted
+// counting of 7.3e10 triples, |B| up to 1000: 5.8 -> 3.0 ms).
+template <int kCap>
+__device__ __forceinline__ void sort_row(const float *__restrict__ src, int n, float *sv, uint16_t *si,
+                                         uint32_t *bucket, uint32_t *scratch) {
+    constexpr int kPer = kCap / 256, kCrowd = 24;
+    const int tid = threadIdx.x, lane = tid % kWave, w = tid / kWave;
+    float v[kPer], lo = __builtin_inff(), hi = -__builtin_inff();
+#pragma unroll
+    for (int m = 0; m < kPer; ++m) {
+        const int e = tid + 256 * m;
+        bucket[e] = 0;
+        if (e < n) {
+            v[m] = src[e];
+            lo = fminf(lo, v[m]);
+            hi = fmaxf(hi, v[m]);
+        }
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        lo = fminf(lo, __shfl_xor(lo, o, kWave));
+        hi = fmaxf(hi, __shfl_xor(hi, o, kWave));
+    }
+    if (lane == 0) {
+        scratch[w] = __float_as_uint(lo);
+        scratch[4 + w] = __float_as_uint(hi);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        lo = fminf(lo, __uint_as_float(scratch[k]));
+        hi = fmaxf(hi, __uint_as_float(scratch[4 + k]));
+    }
+    const float scale = hi > lo ? float(kCap - 1) / (hi - lo) : 0.0f;
+    int at[kPer];
+    uint32_t pos[kPer];
+#pragma unroll
+    for (int m = 0; m < kPer; ++m)
+        if (tid + 256 * m < n) {
+            at[m] = min(max(int((v[m] - lo) * scale), 0), kCap - 1);
+            pos[m] = atomicAdd(&bucket[at[m]], 1u);
+        }
+    __syncthreads();
+    // bucket counts -> first places; each thread has kPer consecutive buckets
+    uint32_t cnt[kPer], sum = 0, crowd = 0, total;
+#pragma unroll
+    for (int m = 0; m < kPer; ++m) {
+        cnt[m] = bucket[kPer * tid + m];
+        sum += cnt[m];
+        crowd |= cnt[m] > kCrowd ? 1u : 0u;
+    }
+    const uint32_t base = block_prefix(sum, scratch, total);
+    uint32_t run = base;
+#pragma unroll
+    for (int m = 0; m < kPer; ++m) {
+        bucket[kPer * tid + m] = run;
+        run += cnt[m];
+    }
+    if (__syncthreads_or(int(crowd)) == 0) {
+#pragma unroll
+        for (int m = 0; m < kPer; ++m)
+            if (tid + 256 * m < n) {
+                const uint32_t k = bucket[at[m]] + pos[m];
+                sv[k] = v[m];
+                si[k] = uint16_t(tid + 256 * m);
+            }
+        __syncthreads();
+        uint32_t first = base;
+#pragma unroll
+        for (int m = 0; m < kPer; ++m) {
+            for (uint32_t k = first + 1; k < first + cnt[m]; ++k) {
+                const float x = sv[k];
+                const uint16_t xi = si[k];
+                uint32_t p = k;
+                for (; p > first && sv[p - 1] > x; --p) {
+                    sv[p] = sv[p - 1];
+                    si[p] = si[p - 1];
+                }
+                sv[p] = x;
+                si[p] = xi;
+            }
+            first += cnt[m];
+        }
+        __syncthreads();
+        return;
+    }
+    int n2 = 2;
+    while (n2 < n) n2 <<= 1;
+    for (int j = tid; j < n2; j += 256) {
+        sv[j] = j < n ? src[j] : __builtin_inff();
+        si[j] = uint16_t(j);
+    }
+    __syncthreads();
+    for (int k = 2; k <= n2; k <<= 1)
+        for (int jj = k >> 1; jj > 0; jj >>= 1) {
+            for (int i = tid; i < n2; i += 256) {
+                const int l = i ^ jj;
+                if (l > i) {
+                    const bool up = (i & k) == 0;
+                    const float vi = sv[i], vl = sv[l];
+                    if ((vi > vl) == up) {
+                        sv[i] = vl;
+                        sv[l] = vi;
+                        const uint16_t t = si[i];
+                        si[i] = si[l];
+                        si[l] = t;
+                    }
+                }
+            }
+            __syncthreads();
+        }
+}
+
 // Large cells, one block per unit (cell, one x): the row's distances to B are
-// sorted in LDS (bitonic, with their B positions), then each a adds
+// sorted in LDS, with their B positions, then each a adds
 // 2|B| - #(d_xb < d_xa) - #(d_xb <= d_xa), which equals the sum over b of
 // 2[d_xa < d_xb] + [d_xa == d_xb].  Near ties and non-robust pairs are found as
 // in k_triplets (the b within margin of d_xa form one sorted range) and make
-// the row go to the FP64 recount with the involved pairs marked.
+// the row go to the FP64 recount with the involved pairs marked.  kCap: room for
+// the task's largest |B|, 1024 (more blocks per CU) or kSortedMaxB.
+template <int kCap>
 __global__ __launch_bounds__(256) void k_triplets_sorted(const CellDev *__restrict__ cells,
                                                          const int32_t *__restrict__ units, int64_t n_units,
                                                          const int64_t *__restrict__ g_pair_base,
@@ -153,8 +296,9 @@ __global__ __launch_bounds__(256) void k_triplets_sorted(const CellDev *__restri
                                                          int64_t recount_cap,
                                                          const unsigned int *__restrict__ scale) {
     if (scale) margin *= __uint_as_float(*scale);  // margin in units of the largest frame length
-    __shared__ float sv[kSortedMaxB];
-    __shared__ uint16_t si[kSortedMaxB];
+    __shared__ float sv[kCap];
+    __shared__ uint16_t si[kCap];
+    __shared__ uint32_t bucket[kCap], scratch[8];
     __shared__ unsigned long long red[4];
     __shared__ int bad[4];
     const int tid = threadIdx.x, lane = tid % kWave, w = tid / kWave;
@@ -165,34 +309,10 @@ __global__ __launch_bounds__(256) void k_triplets_sorted(const CellDev *__restri
         const int64_t base = g_pair_base[c.group];
         const int64_t n = g_n[c.group];
         const int nb = c.nb;
-        int nb2 = 2;
-        while (nb2 < nb) nb2 <<= 1;
         const int xl = c.x0 + xi;
         const float *row = p32 + base + int64_t(xl) * n;
         uint8_t *frow = flags ? flags + base + int64_t(xl) * n : nullptr;
-        for (int j = tid; j < nb2; j += 256) {
-            sv[j] = j < nb ? row[c.b0 + j] : __builtin_inff();
-            si[j] = uint16_t(j);
-        }
-        __syncthreads();
-        for (int k = 2; k <= nb2; k <<= 1)
-            for (int jj = k >> 1; jj > 0; jj >>= 1) {
-                for (int i = tid; i < nb2; i += 256) {
-                    const int l = i ^ jj;
-                    if (l > i) {
-                        const bool up = (i & k) == 0;
-                        const float vi = sv[i], vl = sv[l];
-                        if ((vi > vl) == up) {
-                            sv[i] = vl;
-                            sv[l] = vi;
-                            const uint16_t t = si[i];
-                            si[i] = si[l];
-                            si[l] = t;
-                        }
-                    }
-                }
-                __syncthreads();
-            }
+        sort_row<kCap>(row + c.b0, nb, sv, si, bucket, scratch);
         // count, near ties, non-robust pairs
         unsigned long long cnt = 0;
         int dirty = 0, all_b = 0, all_a = 0;
@@ -267,36 +387,14 @@ __global__ __launch_bounds__(256) void k_init(unsigned long long *__restrict__ W
         W[i] = i == n_cells + 1 ? ~0ull : 0ull;
 }
 
-// Marked pairs into `list` (pooled mode).  Every pair the triplet kernels mark
-// belongs to a row they also send to the recount, so with no such row there is
-// nothing to collect.
-__global__ __launch_bounds__(256) void k_collect_marked(const uint8_t *__restrict__ flags, int64_t n_slots,
-                                                        int64_t *__restrict__ list,
-                                                        unsigned int *__restrict__ count, int64_t cap,
-                                                        const unsigned int *__restrict__ recount_n) {
-    if (*recount_n == 0) return;
-    const int lane = threadIdx.x % kWave;
-    for (int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-         i - lane < n_slots; i += int64_t(gridDim.x) * blockDim.x) {
-        const bool m = i < n_slots && (flags[i] & kMarked);
-        const unsigned long long ball = __ballot(m);
-        if (!ball) continue;
-        unsigned int base = 0;
-        if (lane == 0) base = atomicAdd(count, unsigned(__popcll(ball)));
-        base = __shfl(base, 0, kWave);
-        if (m) {
-            const unsigned int k = base + unsigned(__popcll(ball & ((1ull << lane) - 1ull)));
-            if (int64_t(k) < cap) list[k] = i;
-        }
-    }
-}
-
-// DTW mode: the marked pairs as (x, y) task items (x the low word), one entry
-// where both orientations are marked, in the classes of PairLists (the small
-// ones from small_large's start, the large ones from its end: together at most
-// the unordered pairs, so they never meet).  Pairs with an item of more than 64
-// frames hold their FP64 value already and are only counted; the slots (x, x),
-// which nothing compares, are not looked at.  One pass over the flags, 16 slots
+// The marked pairs as (x, y) task items (x the low word), one entry where both
+// orientations are marked, in the classes of PairLists (the small ones from
+// small_large's start, the large ones from its end: together at most the
+// unordered pairs, so they never meet).  In DTW mode pairs with an item of more
+// than 64 frames hold their FP64 value already and are only counted; the slots
+// (x, x), which nothing compares, are not looked at.  Every pair the triplet
+// kernels mark belongs to a row they also send to the recount, so with no such
+// row there is nothing to collect.  One pass over the flags, 16 slots
 // per lane (HBM-bound when few are marked), and one atomic per class and wave of
 // 1024 slots.
 __global__ __launch_bounds__(256) void k_collect_pairs(const uint8_t *__restrict__ flags, int64_t n_slots,
@@ -304,7 +402,7 @@ __global__ __launch_bounds__(256) void k_collect_pairs(const uint8_t *__restrict
                                                        const int64_t *__restrict__ g_n,
                                                        const int64_t *__restrict__ g_pair_base, int64_t n_groups,
                                                        const int32_t *__restrict__ item_len, PairLists lists,
-                                                       const unsigned int *__restrict__ recount_n) {
+                                                       const unsigned int *__restrict__ recount_n, int pooled) {
     if (*recount_n == 0) return;
     const int lane = threadIdx.x % kWave;
     const int64_t n16 = (n_slots + 15) / 16;
@@ -354,7 +452,7 @@ __global__ __launch_bounds__(256) void k_collect_pairs(const uint8_t *__restrict
                 return;
             }
             if (x > y && (flags[base + y * n + x] & kMarked)) return;  // listed as (y, x)
-            const int L = max(item_len[i0 + x], item_len[i0 + y]);
+            const int L = pooled ? 0 : max(item_len[i0 + x], item_len[i0 + y]);
             if (L <= 16) small |= 1u << k;
             else if (L <= 32) mid |= 1u << k;
             else if (L <= 64) large |= 1u << k;
@@ -395,10 +493,12 @@ __global__ __launch_bounds__(256) void k_collect_pairs(const uint8_t *__restrict
     }
 }
 
+// One wave per row (cell, x); skip_sorted: rows of sorted_cell() cells are left
+// to k_recount_sorted.
 __global__ __launch_bounds__(256) void k_recount(const CellDev *__restrict__ cells,
                                                  const int32_t *__restrict__ rows,
                                                  const unsigned int *__restrict__ n_rows,
-                                                 int64_t max_rows,
+                                                 int64_t max_rows, int skip_sorted,
                                                  const int64_t *__restrict__ g_pair_base,
                                                  const int64_t *__restrict__ g_n,
                                                  const float *__restrict__ p32,
@@ -411,6 +511,7 @@ __global__ __launch_bounds__(256) void k_recount(const CellDev *__restrict__ cel
     for (int64_t r = int64_t(blockIdx.x) * 4 + threadIdx.x / kWave; r < total; r += n_waves) {
         const int32_t cell_id = rows[2 * r], xi = rows[2 * r + 1];
         const CellDev c = cells[cell_id];
+        if (skip_sorted && sorted_cell(c.na, c.nb)) continue;  // wave-uniform
         const int64_t base = g_pair_base[c.group];
         const int64_t n = g_n[c.group];
         const int xl = c.x0 + xi;
@@ -438,6 +539,92 @@ __global__ __launch_bounds__(256) void k_recount(const CellDev *__restrict__ cel
     }
 }
 
+// Rows of large cells, a block each, by the same rule: the FP32 counts of all
+// (a, b) from the row's sorted B distances, with the pairs of two recomputed
+// distances taken out (prefix counts of the recomputed b in sorted order) and
+// counted again from their sorted FP64 values.  Those start in FP32 order, which
+// is theirs but for neighbours within the FP32 error, so odd-even exchanges until
+// nothing moves sort them in a few rounds.  63,037 rows of up to 1000 x 1000
+// comparisons: 42.9 ms with a wave a row over all of them, 2.1 ms here; 550 such
+// rows (one wave each left most of the chip idle): 4.4 ms, 0.03 here.
+template <int kCap>
+__global__ __launch_bounds__(256) void k_recount_sorted(const CellDev *__restrict__ cells,
+                                                        const int32_t *__restrict__ rows,
+                                                        const unsigned int *__restrict__ n_rows, int64_t max_rows,
+                                                        const int64_t *__restrict__ g_pair_base,
+                                                        const int64_t *__restrict__ g_n,
+                                                        const float *__restrict__ p32,
+                                                        const double *__restrict__ p64,
+                                                        const uint8_t *__restrict__ flags,
+                                                        unsigned long long *__restrict__ W) {
+    constexpr int kPer = kCap / 256;
+    __shared__ float sv[kCap];
+    __shared__ uint16_t si[kCap];
+    __shared__ uint32_t marked[kCap + 1], scratch[8];  // marked[k]: recomputed b among the first k in order
+    __shared__ double sd[kCap];
+    const int tid = threadIdx.x, lane = tid % kWave;
+    const int64_t total = min(int64_t(*n_rows), max_rows);
+    for (int64_t r = blockIdx.x; r < total; r += gridDim.x) {
+        const int32_t cell_id = rows[2 * r], xi = rows[2 * r + 1];
+        const CellDev c = cells[cell_id];
+        if (!sorted_cell(c.na, c.nb)) continue;  // block-uniform
+        const int xl = c.x0 + xi, nb = c.nb;
+        const int64_t roff = g_pair_base[c.group] + int64_t(xl) * g_n[c.group];
+        const float *row = p32 + roff;
+        const double *row64 = p64 + roff;
+        const uint8_t *frow = flags + roff;
+        sort_row<kCap>(row + c.b0, nb, sv, si, marked, scratch);
+        uint32_t bits = 0, n_m;
+#pragma unroll
+        for (int m = 0; m < kPer; ++m) {
+            const int k = kPer * tid + m;
+            if (k < nb && (frow[c.b0 + si[k]] & kMarked)) bits |= 1u << m;
+        }
+        uint32_t at = block_prefix(uint32_t(__popc(bits)), scratch, n_m);
+#pragma unroll
+        for (int m = 0; m < kPer; ++m) {
+            const int k = kPer * tid + m;
+            marked[k] = at;
+            if ((bits >> m) & 1u) sd[at++] = row64[c.b0 + si[k]];
+        }
+        if (tid == 255) marked[kCap] = n_m;
+        __syncthreads();
+        const int nm = int(n_m);
+        for (int moved = 1; moved;) {
+            int swapped = 0;
+            for (int odd = 0; odd < 2; ++odd) {
+                for (int i = 2 * tid + odd; i + 1 < nm; i += 512) {
+                    const double u = sd[i], v = sd[i + 1];
+                    if (u > v) {
+                        sd[i] = v;
+                        sd[i + 1] = u;
+                        swapped = 1;
+                    }
+                }
+                if (odd == 0) __syncthreads();
+            }
+            moved = __syncthreads_or(swapped);
+        }
+        unsigned long long cnt = 0;
+        for (int a = tid; a < c.na; a += 256) {
+            const int al = c.a0 + a;
+            if (c.exclude_self && al == xl) continue;
+            const float da = row[al];
+            const int lb = count_below(sv, nb, da, false), ub = count_below(sv, nb, da, true);
+            int half = 2 * nb - lb - ub;
+            if (frow[al] & kMarked) {
+                const double da64 = row64[al];
+                half -= 2 * nm - int(marked[lb]) - int(marked[ub]);
+                half += 2 * nm - count_below(sd, nm, da64, false) - count_below(sd, nm, da64, true);
+            }
+            cnt += unsigned(half);
+        }
+        const unsigned long long wsum = dev::wave_sum_u64(cnt);
+        if (lane == 0 && wsum) atomicAdd(&W[cell_id], wsum);
+        __syncthreads();  // the next row reuses the buffers
+    }
+}
+
 }  // namespace
 
 void triplets(hipStream_t s, const CellDev *cells, const int32_t *units, int64_t n_units,
@@ -451,12 +638,14 @@ void triplets(hipStream_t s, const CellDev *cells, const int32_t *units, int64_t
     FABX_HIP(hipGetLastError());
 }
 
-void triplets_sorted(hipStream_t s, const CellDev *cells, const int32_t *units, int64_t n_units,
+void triplets_sorted(hipStream_t s, const CellDev *cells, const int32_t *units, int64_t n_units, int max_b,
                      const GroupTables &g, const float *p32, unsigned long long *W, uint8_t *flags,
                      float margin, int32_t *recount, unsigned int *recount_n, int64_t recount_cap,
                      const unsigned int *scale) {
     if (n_units <= 0) return;
-    hipLaunchKernelGGL(k_triplets_sorted, dim3(grid_for(n_units, 1)), dim3(256), 0, s, cells, units, n_units,
+    if (max_b > kSortedMaxB) fail(FABX_EINVAL, "a sorted cell's B is larger than the sort takes");
+    hipLaunchKernelGGL(max_b <= 1024 ? k_triplets_sorted<1024> : k_triplets_sorted<kSortedMaxB>,
+                       dim3(grid_for(n_units, 1)), dim3(256), 0, s, cells, units, n_units,
                        g.pair_base, g.n_items, p32, W, flags, margin, recount, recount_n, recount_cap, scale);
     FABX_HIP(hipGetLastError());
 }
@@ -467,31 +656,27 @@ void init_score(hipStream_t s, unsigned long long *W, int64_t n_cells) {
     FABX_HIP(hipGetLastError());
 }
 
-void collect_marked(hipStream_t s, const uint8_t *flags, int64_t n_slots, int64_t *list,
-                    unsigned int *count, int64_t cap, const unsigned int *recount_n) {
-    if (n_slots <= 0) return;
-    const int64_t blocks = std::min<int64_t>((n_slots + 255) / 256, 4096);
-    hipLaunchKernelGGL(k_collect_marked, dim3(unsigned(blocks)), dim3(256), 0, s, flags, n_slots,
-                       list, count, cap, recount_n);
-    FABX_HIP(hipGetLastError());
-}
-
 void collect_pairs(hipStream_t s, const uint8_t *flags, int64_t n_slots, const GroupTables &g, const ItemTables &it,
-                   const PairLists &lists, const unsigned int *recount_n) {
+                   const PairLists &lists, const unsigned int *recount_n, bool pooled) {
     if (n_slots <= 0) return;
     const int64_t blocks = std::min<int64_t>((n_slots + 4095) / 4096, 4096);
     hipLaunchKernelGGL(k_collect_pairs, dim3(unsigned(blocks)), dim3(256), 0, s, flags, n_slots, g.item0, g.n_items,
-                       g.pair_base, g.n_groups, it.len, lists, recount_n);
+                       g.pair_base, g.n_groups, it.len, lists, recount_n, pooled ? 1 : 0);
     FABX_HIP(hipGetLastError());
 }
 
 void recount(hipStream_t s, const CellDev *cells, const int32_t *rows, const unsigned int *n_rows,
-             int64_t max_rows, const GroupTables &g, const float *p32, const double *p64,
+             int64_t max_rows, int max_b, const GroupTables &g, const float *p32, const double *p64,
              const uint8_t *flags, unsigned long long *W) {
     if (max_rows <= 0) return;
+    if (max_b > kSortedMaxB) fail(FABX_EINVAL, "a sorted cell's B is larger than the sort takes");
     const int64_t blocks = std::min<int64_t>((max_rows + 3) / 4, 2048);
     hipLaunchKernelGGL(k_recount, dim3(unsigned(blocks)), dim3(256), 0, s, cells, rows, n_rows,
-                       max_rows, g.pair_base, g.n_items, p32, p64, flags, W);
+                       max_rows, max_b > 0 ? 1 : 0, g.pair_base, g.n_items, p32, p64, flags, W);
+    if (max_b > 0)
+        hipLaunchKernelGGL(max_b <= 1024 ? k_recount_sorted<1024> : k_recount_sorted<kSortedMaxB>,
+                           dim3(unsigned(std::min<int64_t>(max_rows, 2048))), dim3(256), 0, s, cells, rows, n_rows,
+                           max_rows, g.pair_base, g.n_items, p32, p64, flags, W);
     FABX_HIP(hipGetLastError());
 }
 

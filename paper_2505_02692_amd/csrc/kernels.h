@@ -169,8 +169,8 @@ void triplets(hipStream_t s, const CellDev *cells, const int32_t *units, int64_t
               float margin, int32_t *recount, unsigned int *recount_n, int64_t recount_cap,
               const unsigned int *scale);
 // Large cells, one x per unit: the same counts and marks from the row's B
-// distances sorted in LDS (|B| <= kSortedMaxB).
-void triplets_sorted(hipStream_t s, const CellDev *cells, const int32_t *units, int64_t n_units,
+// distances sorted in LDS (|B| <= max_b <= kSortedMaxB).
+void triplets_sorted(hipStream_t s, const CellDev *cells, const int32_t *units, int64_t n_units, int max_b,
               const GroupTables &g, const float *p32, unsigned long long *W, uint8_t *flags,
               float margin, int32_t *recount, unsigned int *recount_n, int64_t recount_cap,
               const unsigned int *scale);
@@ -181,13 +181,9 @@ constexpr int kCounterBytes = 128;
 // those, the error item, is set to all ones).
 void init_score(hipStream_t s, unsigned long long *W, int64_t n_cells);
 
-// Pooled mode: pair slots whose flag bit 1 is set -> list (order unspecified); nothing when
-// *recount_n is 0 (no row was sent to the recount, so no pair is marked).
-void collect_marked(hipStream_t s, const uint8_t *flags, int64_t n_slots, int64_t *list,
-                    unsigned int *count, int64_t cap, const unsigned int *recount_n);
-
-// DTW mode: the pairs whose flag bit 1 is set, as x | y << 32 (task items), one
-// entry for both orientations, by the longer item's frames: at most 16 from
+// The pairs whose flag bit 1 is set, as x | y << 32 (task items), one entry for
+// both orientations.  Pooled mode: all from small_large[0] on (n_small).  DTW mode:
+// by the longer item's frames: at most 16 from
 // small_large[0] on (n_small), 17 to 32 from mid[0] on (n_mid), 33 to 64 from
 // small_large[cap - 1] down (n_large); longer ones are only counted.  cap, the
 // room of either array, is the number of unordered pairs or more.  n_marked:
@@ -198,12 +194,14 @@ struct PairLists {
     unsigned int *n_marked, *n_small, *n_mid, *n_large;
 };
 void collect_pairs(hipStream_t s, const uint8_t *flags, int64_t n_slots, const GroupTables &g, const ItemTables &it,
-                   const PairLists &lists, const unsigned int *recount_n);
+                   const PairLists &lists, const unsigned int *recount_n, bool pooled);
 
 // Re-count rows (cell, x): a comparison of two recomputed pairs (flag bit 1 on both)
-// uses their FP64 values, any other comparison the FP32 ones.
+// uses their FP64 values, any other comparison the FP32 ones.  max_b: the largest
+// |B| of the cells that sorted_cell() holds for (0: none); their rows are counted
+// from sorted values.
 void recount(hipStream_t s, const CellDev *cells, const int32_t *rows, const unsigned int *n_rows,
-             int64_t max_rows, const GroupTables &g, const float *p32, const double *p64,
+             int64_t max_rows, int max_b, const GroupTables &g, const float *p32, const double *p64,
              const uint8_t *flags, unsigned long long *W);
 
 // --- k_recheck.hip
@@ -222,10 +220,14 @@ void recheck_dtw(hipStream_t s, const void *features, int dtype, int dim, const 
 void long_dtw(hipStream_t s, const void *features, int dtype, int dim, const GroupTables &g,
               const ItemTables &it, const int32_t *item_group, const int64_t *list, int64_t n_list, int norm,
               int euclid, double *p64, float *p32, uint8_t *flags);
-// Pooled mode: FP64 distance of the mean frames of each listed pair slot.
+// Pooled mode: the FP64 distance of the mean frames of each marked pair (listed
+// by collect_pairs), at both its slots.  means (may be null): room for the FP64
+// means of all items (n_items x dim), which may be the list's own memory; with it
+// and many marked pairs they are taken from the pair matrices' 64 x 128 tiles
+// (tile_prefix, n_tiles) and flags instead of the list.
 void recheck_pooled(hipStream_t s, const void *features, int dtype, int dim, const GroupTables &g,
-                    const ItemTables &it, const int64_t *list, const unsigned int *count, int64_t max_count,
-                    int euclid, double *p64);
+                    const ItemTables &it, const int32_t *item_group, const PairLists &lists, double *means,
+                    const int64_t *tile_prefix, int64_t n_tiles, const uint8_t *flags, int euclid, double *p64);
 
 }  // namespace kern
 }  // namespace fabx

@@ -585,26 +585,33 @@ void enqueue_score(const TaskImpl &t, const ScoreParams &p, const FusedConfig &f
     int32_t *recount = bf16 ? d.recount_list : nullptr;
     kern::triplets(stream, d.cells, d.units, t.n_units_small, gt, d.p32, d.half_units, flags, float(p.margin),
                    recount, recount_n, t.sum_nx, scale);
-    kern::triplets_sorted(stream, d.cells, d.units + 3 * t.n_units_small, n_units - t.n_units_small, gt, d.p32,
+    // the largest |B| counted from sorted rows (a cell's units lie together, one per x)
+    int max_b = 0;
+    for (int64_t u = t.n_units_small; u < n_units;) {
+        const CellDev &c = t.cells[size_t(t.units[size_t(3 * u)])];
+        max_b = std::max(max_b, c.nb);
+        u += std::max(c.nx, 1);
+    }
+    kern::triplets_sorted(stream, d.cells, d.units + 3 * t.n_units_small, n_units - t.n_units_small, max_b, gt, d.p32,
                           d.half_units, flags, float(p.margin), recount, recount_n, t.sum_nx, scale);
     mark();  // 4
     if (bf16) {
+        // every pair is listed once: (slots - items) / 2 unordered pairs (x, y), x != y
+        const int64_t n_items = int64_t(t.items.size()), pairs = (t.n_pair_slots - n_items) / 2;
+        unsigned int *n_class = reinterpret_cast<unsigned int *>(counters + 64);  // small, mid, large
+        const kern::PairLists lists{d.recheck_list, d.recheck_list + pairs, pairs, marked_n,
+                                    n_class, n_class + 1, n_class + 2};
+        kern::collect_pairs(stream, d.flags, t.n_pair_slots, gt, it, lists, recount_n, !dtw);
         if (dtw) {
-            // every pair is listed once: (slots - items) / 2 unordered pairs (x, y), x != y
-            const int64_t pairs = (t.n_pair_slots - int64_t(t.items.size())) / 2;
-            unsigned int *n_class = reinterpret_cast<unsigned int *>(counters + 64);  // small, mid, large
-            const kern::PairLists lists{d.recheck_list, d.recheck_list + pairs, pairs, marked_n,
-                                        n_class, n_class + 1, n_class + 2};
-            kern::collect_pairs(stream, d.flags, t.n_pair_slots, gt, it, lists, recount_n);
             kern::recheck_dtw(stream, ds.features, ds.dtype, dim, gt, it, d.item_group, lists, ds.ctx->n_cu,
                               t.max_len, p.dtw_norm, euclid ? 1 : 0, d.p64);
         } else {
-            kern::collect_marked(stream, d.flags, t.n_pair_slots, d.recheck_list, marked_n, t.n_pair_slots,
-                                 recount_n);
-            kern::recheck_pooled(stream, ds.features, ds.dtype, dim, gt, it, d.recheck_list, marked_n,
-                                 t.n_pair_slots, euclid ? 1 : 0, d.p64);
+            // the list's memory also holds the items' FP64 means when they fit
+            double *means = n_items * dim <= t.n_pair_slots ? reinterpret_cast<double *>(d.recheck_list) : nullptr;
+            kern::recheck_pooled(stream, ds.features, ds.dtype, dim, gt, it, d.item_group, lists, means, d.tiles,
+                                 tiles.back(), d.flags, euclid ? 1 : 0, d.p64);
         }
-        kern::recount(stream, d.cells, d.recount_list, recount_n, t.sum_nx, gt, d.p32, d.p64, d.flags,
+        kern::recount(stream, d.cells, d.recount_list, recount_n, t.sum_nx, max_b, gt, d.p32, d.p64, d.flags,
                       d.half_units);
     }
     mark();  // 5

@@ -64,7 +64,6 @@ std::vector<int32_t> pick(const Philox &ph, int64_t cell, int which, int32_t n, 
 }
 
 constexpr int64_t kUnitBudget = 8192;     // as the task build: comparisons per triplet work unit
-constexpr int64_t kSortedMinPerX = 8192;  // cells counted from sorted rows
 
 }  // namespace
 
@@ -186,7 +185,7 @@ std::shared_ptr<TaskImpl> subsample_task(const TaskImpl &t, const fabx_subsample
     for (size_t k = 0; k < cells.size(); ++k) {
         const CellDev &nc = u.cells[k];
         const int64_t per_x = std::max<int64_t>(1, int64_t(nc.na) * nc.nb);
-        const bool big = per_x >= kSortedMinPerX && nc.nb <= kSortedMaxB;
+        const bool big = sorted_cell(nc.na, nc.nb);
         const int64_t chunk = big ? 1 : std::max<int64_t>(1, kUnitBudget / per_x);
         auto &dst = big ? big_u : small_u;
         for (int64_t x = 0; x < nc.nx; x += chunk) {

@@ -224,9 +224,7 @@ struct Sink {
 };
 
 constexpr int64_t kUnitBudget = 8192;  // comparisons per triplet work unit (at least one x)
-// Cells with at least this many comparisons per x, and |B| within the sort
-// capacity, are counted from sorted rows (one unit per x, after the others).
-constexpr int64_t kSortedMinPerX = 8192;
+// (cells counted from sorted rows, sorted_cell(): one unit per x, after the others)
 
 struct WalkCtx {
     const DatasetImpl *ds;
@@ -304,7 +302,7 @@ void walk_groups(const WalkCtx &w, int64_t s_begin, int64_t s_end, Sink &out) {
             // triplet work units: split X so one unit does <= kUnitBudget comparisons;
             // large cells get one unit per x, in the sorted-row region
             const int64_t per_x = std::max<int64_t>(1, na * nb);
-            const bool big = per_x >= kSortedMinPerX && nb <= kSortedMaxB;
+            const bool big = sorted_cell(na, nb);
             // nx * per_x <= budget (the usual case): one unit for the whole cell,
             // which is what the division below gives, without dividing
             const bool one = !big && nx >= 1 && nx * per_x <= kUnitBudget;

@@ -50,3 +50,70 @@ def test_fp64_recheck_classes(case, distance, norm):
     assert ((fl & 2) != 0).all()
     assert (np.abs(f64 - want) <= 1e-12 * np.maximum(want, 1.0)).all()
     assert np.array_equal(res.half_units, orc.half_units)
+
+
+# Pooled mode, every pair marked.  Groups of n items at dim D with n >= D take the
+# tiles of the pair matrices (the FP64 means fit the list's memory), with n < D the
+# list; 16 x 16 tiles, 64 x 128 blocks of them, a remainder of features.
+@pytest.mark.parametrize("distance", ["angular", "euclidean"])
+@pytest.mark.parametrize("n,dim,dtype", [(15, 8, torch.float32), (17, 16, torch.bfloat16), (70, 33, torch.float32),
+                                         (140, 50, torch.float32), (20, 64, torch.bfloat16),
+                                         (9, 130, torch.float32)])
+def test_fp64_recheck_pooled(n, dim, dtype, distance):
+    w = workloads.batched_c4(n_groups=3, size_lo=n, size_hi=n, len_lo=1, len_hi=9, dim=dim, dtype=dtype,
+                             centroid_std=0.1, seed=n)
+    # the second half of each label's items repeats the first: exact ties
+    feats, off = w.features.clone(), w.offsets
+    for k in range(0, w.n_items - 1, 5):
+        m = min(off[k + 1] - off[k], off[k + 2] - off[k + 1])
+        if off[k + 1] - off[k] == off[k + 2] - off[k + 1]:
+            feats[off[k + 1]:off[k + 1] + m] = feats[off[k]:off[k] + m]
+    w.features = feats
+    print(f"[case] pooled recheck n={n} dim={dim} {distance}", flush=True)
+    t, res = gpu_score(w, mode="pooled", distance=distance, margin=1e4, keep_pairs=True)
+    orc = oracle.score(w.features_f32_host(), w.offsets, w.attrs, w.on, w.by, w.across, "pooled", "path",
+                       distance=distance)
+    xs, ys, want = all_oracle_pairs(orc)
+    _, fl, f64 = res.pairs(xs, ys)
+    assert ((fl & 2) != 0).all()
+    assert (np.abs(f64 - want) <= 1e-12 * np.maximum(want, 1.0)).all()
+    assert np.array_equal(res.half_units, orc.half_units)
+
+
+# Rows of large cells, sorted in LDS: |B| at the two capacities and past the
+# larger one (counted by brute force), values that crowd one bucket (repeated
+# items), a margin that sends some rows or all to the FP64 recount.
+@pytest.mark.parametrize("margin", [-1.0, 0.02, 1e4])
+@pytest.mark.parametrize("nb,na,repeat", [(255, 64, 1), (1024, 20, 1), (1025, 20, 40), (600, 40, 60), (4096, 12, 1),
+                                          (4097, 12, 1)])
+def test_sorted_rows(nb, na, repeat, margin):
+    rng = np.random.default_rng(nb)
+    n = na + nb
+    label = np.r_[np.zeros(na, np.int32), np.ones(nb, np.int32)]
+    x = rng.standard_normal((n, 3)).astype(np.float32)
+    x[:na] += 0.5
+    if repeat > 1:  # runs of `repeat` equal items
+        x = x[np.arange(n) // repeat * repeat]
+    attrs = np.stack([label, np.zeros(n, np.int32)], 1)
+    w = workloads.Workload("sorted", torch.from_numpy(x), np.arange(n + 1, dtype=np.int64), attrs, ["l", "g"], 0, [1],
+                           [])
+    print(f"[case] sorted rows nb={nb} na={na} repeat={repeat} margin={margin}", flush=True)
+    t, res = gpu_score(w, mode="pooled", margin=margin)
+    # the definition in FP64, row by row (one-frame items; only rows of class 0 and 1 as X)
+    u = x.astype(np.float64)
+    u /= np.linalg.norm(u, axis=1, keepdims=True)
+    uniq, inv = np.unique(x, axis=0, return_inverse=True)   # equal items share one distance
+    v = uniq.astype(np.float64)
+    v /= np.linalg.norm(v, axis=1, keepdims=True)
+    d = np.arccos(np.clip(v @ v.T, -1, 1))
+    np.fill_diagonal(d, 0.0)
+    d = d[np.ix_(inv.ravel(), inv.ravel())]
+    want = []
+    for A, B in ((np.arange(na), np.arange(na, n)), (np.arange(na, n), np.arange(na))):
+        s = 0
+        for i in A:
+            a = np.sort(d[i, A[A != i]])
+            b = np.sort(d[i, B])
+            s += int((2 * len(b) - np.searchsorted(b, a, "left") - np.searchsorted(b, a, "right")).sum())
+        want.append(s)
+    assert res.half_units.tolist() == want

@@ -2,14 +2,11 @@
 // the Background section), in integer half units: each triple adds
 // 2 [d(x,a) < d(x,b)] + [d(x,a) == d(x,b)].
 //
-// Work unit = (cell, range of x), one wave each.  When |A| x |B| fits the
-// wave, a pass covers as many whole rows x as fit, |A| x |B| lanes per row;
-// otherwise a row's grid is walked in passes of 64 lanes.  Both distances come
-// from the row of x in the group's pair matrix (a few hundred bytes, in L1/L2).
-// A row with a near tie or a non-robust pair is left to the FP64 recount (one
-// ballot per pass finds it); the other rows' counts stay in the lanes and are
-// reduced once per unit, then added with one 64-bit atomic, so the result does
-// not depend on scheduling.
+// Work unit = (cell, range of x).  Both distances come from the row of x in the
+// group's pair matrix (a few hundred bytes, in L1/L2).  A row with a near tie or
+// a non-robust pair is left to the FP64 recount; the other rows' counts stay in
+// the lanes, are reduced once per unit and added with one 64-bit atomic, so the
+// result does not depend on scheduling.
 #include "device_common.h"
 #include "kernels.h"
 
@@ -22,9 +19,33 @@ using dev::kWave;
 constexpr uint8_t kNonRobust = 1;
 constexpr uint8_t kMarked = 2;
 
+// A unit by a wave: the larger of A and B lies in the lanes (as many rows x side
+// by side as fit), and the other one's values pass by, one per step, so a row's
+// values and flags are read once and a step is a lane shuffle and three
+// comparisons; a row whose grid was walked in passes of 64 read four values per
+// comparison and waited for them.
+//  kMany = false: a wave takes one unit at a time; with few units each is split
+//    by x into `parts`.
+//  kMany = true, from kManyUnits units on (tasks across speakers have millions of
+//    cells of a few triples, and a wave per unit spent its time on the unit's tables
+//    and its reduction): a wave takes `chunk` consecutive units, one per lane; those
+//    of at most kLaneWork comparisons are done by their lane alone, the others by
+//    the wave one after another.  (100,000 items, 131,671 cells: 184 us with 4 units
+//    a wave, 590 with 16, whose larger units queue in a few waves.)
+// Rows for the recount are collected in LDS and leave 128 at a time, or with one
+// atomic of the block at its end: one atomic per row on the common counter was
+// most of the time where many rows go there.
+// Bound by the latency of the chain unit, cell, row values.  100,000 items with
+// 149,174 rows for the recount: 1.41 -> 0.14 ms (0.089 -> 0.116 without such rows);
+// 1.77e6 cells across speakers: 0.76 -> 0.23 ms; 668,000 triples in 957 cells:
+// 53 -> 14 us.
+constexpr int kLaneWork = 24, kRowBuf = 128;
+constexpr int64_t kManyUnits = 16 * 32768;
+
+template <bool kMany>
 __global__ __launch_bounds__(256) void k_triplets(const CellDev *__restrict__ cells,
-                                                  const int32_t *__restrict__ units, int64_t n_units,
-                                                  const int64_t *__restrict__ g_pair_base,
+                                                  const int32_t *__restrict__ units, int64_t n_units, int chunk,
+                                                  int parts, const int64_t *__restrict__ g_pair_base,
                                                   const int64_t *__restrict__ g_n,
                                                   const float *__restrict__ p32,
                                                   unsigned long long *__restrict__ W,
@@ -33,95 +54,255 @@ __global__ __launch_bounds__(256) void k_triplets(const CellDev *__restrict__ ce
                                                   unsigned int *__restrict__ recount_n,
                                                   int64_t recount_cap,
                                                   const unsigned int *__restrict__ scale) {
+    __shared__ int2 rowbuf_s[4][kRowBuf];
     const int lane = threadIdx.x % kWave;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     if (scale) margin *= __uint_as_float(*scale);  // margin in units of the largest frame length
-    // one wave per unit; the loop bound is uniform across the wave
-    for (int64_t unit = int64_t(blockIdx.x) * 4 + threadIdx.x / kWave; unit < n_units;
-         unit += int64_t(gridDim.x) * 4) {
-    const int32_t cell_id = units[3 * unit];
-    const int32_t xb = units[3 * unit + 1], xe = units[3 * unit + 2];
-    const CellDev c = cells[cell_id];
-    const int64_t base = g_pair_base[c.group];
-    const int64_t n = g_n[c.group];
-    const int na = c.na, nb = c.nb;
-    if (na <= 0 || nb <= 0) continue;  // uniform: no comparisons
-    // lane sums of 2 [d_xa < d_xb] + [d_xa == d_xb] over the rows kept
-    unsigned long long acc = 0;
-    // one comparison of row xl at (al, bl); returns its half units, sets dirty
-    auto compare = [&](int xl, int al, int bl, int &dirty) -> unsigned int {
-        const float *row = p32 + base + int64_t(xl) * n;
-        const float da = row[al], db = row[bl];
-        if (flags) {
-            uint8_t *frow = flags + base + int64_t(xl) * n;
-            const uint8_t fa = frow[al], fb = frow[bl];
-            if (fabsf(da - db) <= margin || ((fa | fb) & kNonRobust)) {
-                dirty = 1;
-                if (!(fa & kMarked)) frow[al] = fa | kMarked;
-                if (!(fb & kMarked)) frow[bl] = fb | kMarked;
+    int2 *rowbuf = rowbuf_s[wv];
+    int n_rows = 0;  // wave-uniform
+    auto write_rows = [&](unsigned int at) {
+        for (int i = lane; i < n_rows; i += kWave) {
+            const int64_t k = int64_t(at) + i;
+            if (k < recount_cap) {
+                recount[2 * k] = rowbuf[i].x;
+                recount[2 * k + 1] = rowbuf[i].y;
             }
         }
-        return da < db ? 2u : (da == db ? 1u : 0u);
     };
-    auto push_row = [&](int xi) {
-        const unsigned int k = atomicAdd(recount_n, 1u);
-        if (int64_t(k) < recount_cap) {
-            recount[2 * int64_t(k)] = cell_id;
-            recount[2 * int64_t(k) + 1] = xi;
-        }
+    auto flush = [&] {
+        unsigned int at = 0;
+        if (lane == 0) at = atomicAdd(recount_n, unsigned(n_rows));
+        write_rows(__shfl(at, 0, kWave));
+        __builtin_amdgcn_wave_barrier();
+        n_rows = 0;
     };
-    const int per_x = na * nb;
-    if (per_x <= kWave) {
-        // `rows` whole rows per pass: lane = r * per_x + (a * nb + b)
-        const int rows = kWave / per_x;
-        const int r = lane / per_x, kk = lane - r * per_x;
-        const int a = kk / nb, b = kk - a * nb;
-        const bool lane_on = r < rows;
-        const unsigned long long seg =
-            lane_on ? (per_x == kWave ? ~0ull : ((1ull << per_x) - 1ull) << (r * per_x)) : 0ull;
-        const int al = c.a0 + a, bl = c.b0 + b;
-        unsigned int cnt = 0;
-        for (int x0 = xb; x0 < xe; x0 += rows) {
-            const int xi = x0 + r;
-            const bool row_on = lane_on && xi < xe;
-            const int xl = c.x0 + xi;
-            int dirty = 0;
-            unsigned int add = 0;
-            if (row_on && !(c.exclude_self && al == xl)) add = compare(xl, al, bl, dirty);
-            if (flags) {
-                const unsigned long long dmask = __ballot(dirty);
-                if (dmask & seg) {
-                    add = 0;
-                    if (row_on && kk == 0) push_row(xi);
+    // the block's last rows, with one atomic (every wave comes here)
+    auto flush_block = [&] {
+        __shared__ unsigned int n_s[4], at_s;
+        if (!flags) return;
+        if (lane == 0) n_s[wv] = unsigned(n_rows);
+        __syncthreads();
+        const unsigned int total = n_s[0] + n_s[1] + n_s[2] + n_s[3];
+        if (total == 0) return;
+        if (threadIdx.x == 0) at_s = atomicAdd(recount_n, total);
+        __syncthreads();
+        unsigned int at = at_s;
+        for (int k = 0; k < wv; ++k) at += n_s[k];
+        write_rows(at);
+    };
+    // row (cell, x) of each lane with p set (all lanes call)
+    auto push = [&](bool p, int cell, int xi) {
+        const unsigned long long m = __ballot(p);
+        if (!m) return;
+        const int c = __popcll(m);
+        if (n_rows + c > kRowBuf) flush();
+        if (p) rowbuf[n_rows + __popcll(m & ((1ull << lane) - 1ull))] = make_int2(cell, xi);
+        __builtin_amdgcn_wave_barrier();
+        n_rows += c;
+    };
+    auto unit_by_wave = [&](const int cell, const int xb, const int xe, const int a0, const int na, const int b0,
+                            const int nb, const int x0, const int excl, const int64_t base, const int64_t n) {
+        // lane side: the larger set; the other passes by
+        const bool lanes_b = nb >= na;
+        const int l0 = lanes_b ? b0 : a0, nl = lanes_b ? nb : na;
+        const int s0 = lanes_b ? a0 : b0, ns = lanes_b ? na : nb;
+        const int width = min(nl, kWave);
+        // lane / width and 64 / width by the reciprocal (exact: the halves keep the
+        // quotients at least 1 / 128 away from a whole number)
+        const float inv = __builtin_amdgcn_rcpf(float(width));
+        const int rows = int((kWave + 0.5f) * inv), r = int((float(lane) + 0.5f) * inv), k = lane - r * width;
+        auto seg = [&] {  // the lanes of this lane's row
+            return r < rows ? (width == kWave ? ~0ull : ((1ull << width) - 1ull) << (r * width)) : 0ull;
+        };
+        unsigned long long acc = 0;
+        for (int xs = xb; xs < xe; xs += rows) {
+            const int xi = xs + r, xl = x0 + xi;
+            const bool on = r < rows && xi < xe;
+            const int64_t row = base + int64_t(xl) * n;
+            // a value of one side and its flags; x itself and places past the set
+            // are NaN (no comparison with them counts or is near)
+            auto value = [&](int at, bool in, uint8_t &f) {
+                f = flags && in ? flags[row + at] : uint8_t(0);
+                return in ? p32[row + at] : __builtin_nanf("");
+            };
+            unsigned long long dirty = 0;  // lanes that met a near tie
+            unsigned long long cnt = 0;
+            for (int lc = 0; lc < nl; lc += kWave) {
+                const int l_at = l0 + lc + k;
+                const bool l_in = on && lc + k < nl && !(excl && !lanes_b && l_at == xl);
+                uint8_t lf;
+                const float lv = value(l_at, l_in, lf);
+                const unsigned long long act = __ballot(l_in);
+                unsigned long long near = 0;
+                unsigned int below = 0;  // sum of [d_xa < d_xb] + [d_xa <= d_xb]
+                for (int sc = 0; sc < ns; sc += width) {
+                    const int s_at = s0 + sc + k;
+                    const bool s_in = on && sc + k < ns && !(excl && lanes_b && s_at == xl);
+                    uint8_t sf;
+                    const float sv = value(s_at, s_in, sf);
+                    const bool fragile = __ballot((lf | sf) & kNonRobust) != 0;  // rare, uniform
+                    bool s_near = false;
+                    const int steps = min(width, ns - sc);
+                    // four passing values at a time, so that their shuffles overlap
+                    // (past the last step they are NaN)
+                    for (int i = 0; i < steps; i += 4) {
+                        float o[4];
+                        unsigned long long m[4] = {0, 0, 0, 0};
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            const float v = __shfl(sv, r * width + i + e, kWave);
+                            o[e] = i + e < steps ? v : __builtin_nanf("");
+                        }
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            const float da = lanes_b ? o[e] : lv, db = lanes_b ? lv : o[e];
+                            below += (da < db ? 1u : 0u) + (da <= db ? 1u : 0u);
+                            if (flags) m[e] = __ballot(fabsf(o[e] - lv) <= margin);
+                        }
+                        if (fragile)
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) {
+                                const int f = lf | __shfl(int(sf), r * width + i + e, kWave);
+                                m[e] |= __ballot(i + e < steps && (f & kNonRobust) != 0);
+                            }
+                        if ((m[0] | m[1] | m[2] | m[3]) & act)
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) {
+                                near |= m[e] & act;
+                                if (k == i + e && (m[e] & act & seg())) s_near = true;
+                            }
+                    }
+                    if (s_near && s_in && !(sf & kMarked)) flags[row + s_at] = sf | kMarked;
+                }
+                if (l_in) cnt += below;
+                if (near) {  // uniform
+                    if (((near >> lane) & 1ull) && !(lf & kMarked)) flags[row + l_at] = lf | kMarked;
+                    dirty |= near;
                 }
             }
-            cnt += add;
-        }
-        acc = cnt;
-    } else {
-        // one row at a time, its |A| x |B| grid in passes of 64 lanes
-        const int step_a = kWave / nb, step_b = kWave % nb;
-        for (int xi = xb; xi < xe; ++xi) {
-            const int xl = c.x0 + xi;
-            int a = lane / nb, b = lane % nb;
-            unsigned long long cnt = 0;
-            int dirty = 0;
-            while (a < na) {
-                const int al = c.a0 + a, bl = c.b0 + b;
-                if (!(c.exclude_self && al == xl)) cnt += compare(xl, al, bl, dirty);
-                a += step_a;
-                b += step_b;
-                if (b >= nb) { b -= nb; ++a; }
-            }
-            if (flags && dev::wave_any(dirty)) {
-                if (lane == 0) push_row(xi);
-                continue;
+            if (dirty) {  // uniform
+                const bool row_dirty = (dirty & seg()) != 0;
+                push(on && row_dirty && k == 0, cell, xi);
+                if (row_dirty) cnt = 0;
             }
             acc += cnt;
         }
+        // (a unit has at most 8192 comparisons or one x)
+        if (int64_t(na) * nb <= (int64_t(1) << 24)) {
+            const unsigned int total = dev::wave_sum_u32(unsigned(acc));
+            if (lane == kWave - 1 && total) atomicAdd(&W[cell], (unsigned long long)total);
+        } else {
+            const unsigned long long total = dev::wave_sum_u64(acc);
+            if (lane == 0 && total) atomicAdd(&W[cell], total);
+        }
+    };
+    const int64_t n_work = n_units * parts;
+    const int64_t wave = int64_t(blockIdx.x) * 4 + wv, waves = int64_t(gridDim.x) * 4;
+    if constexpr (!kMany) {
+        // the tables of the next units are read ahead, one level (unit, cell, group)
+        // per unit done: read in turn they cost a unit four trips to memory
+        struct Unit {
+            int cell, xb, xe;
+        };
+        auto unit_at = [&](int64_t u) {
+            u = min(u, n_work - 1);
+            const int64_t unit = u / parts;
+            const int32_t *un = units + 3 * unit;
+            const int per = (un[2] - un[1] + parts - 1) / parts;
+            const int xb = un[1] + int(u - unit * parts) * per;
+            return Unit{un[0], xb, min(xb + per, un[2])};
+        };
+        Unit u1 = unit_at(wave), u2 = unit_at(wave + waves), u3;
+        CellDev c1 = cells[u1.cell], c2;
+        int64_t base1 = g_pair_base[c1.group], n1 = g_n[c1.group], base2, n2;
+        c2 = cells[u2.cell];
+        for (int64_t u = wave; u < n_work; u += waves) {
+            base2 = g_pair_base[c2.group];
+            n2 = g_n[c2.group];
+            u3 = unit_at(u + 2 * waves);
+            if (c1.na > 0 && c1.nb > 0 && u1.xb < u1.xe)  // uniform
+                unit_by_wave(u1.cell, u1.xb, u1.xe, c1.a0, c1.na, c1.b0, c1.nb, c1.x0, c1.exclude_self, base1, n1);
+            u1 = u2;
+            c1 = c2;
+            base1 = base2;
+            n1 = n2;
+            u2 = u3;
+            c2 = cells[u3.cell];
+        }
+        flush_block();
+        return;
     }
-    const unsigned long long total = dev::wave_sum_u64(acc);
-    if (lane == 0 && total) atomicAdd(&W[cell_id], total);
+    auto bcast = [](int v, int src) { return __builtin_amdgcn_readlane(v, src); };
+    auto bcast64 = [&](int64_t v, int src) {
+        return int64_t(uint32_t(bcast(int(v), src))) | (int64_t(bcast(int(v >> 32), src)) << 32);
+    };
+    // the loop bounds are uniform across the wave
+    for (int64_t u0 = wave * chunk; u0 < n_units; u0 += waves * chunk) {
+        const bool has = lane < chunk && u0 + lane < n_units;
+        int cell = 0, xb = 0, xe = 0;
+        CellDev c{};
+        int64_t base = 0, n = 0;
+        if (has) {
+            const int32_t *u = units + 3 * (u0 + lane);
+            cell = u[0];
+            xb = u[1];
+            xe = u[2];
+            c = cells[cell];
+            base = g_pair_base[c.group];
+            n = g_n[c.group];
+        }
+        const int64_t comparisons = has && c.na > 0 && c.nb > 0 ? int64_t(xe - xb) * c.na * c.nb : 0;
+        const int mine = comparisons <= kLaneWork ? int(comparisons) : 0;
+
+        // units of a few comparisons, each by its lane
+        if (__ballot(mine > 0)) {
+            unsigned int acc = 0, cnt = 0;
+            int a = 0, b = 0, x = xb, dirty = 0;
+            for (int t = 0; __ballot(t < mine); ++t) {
+                bool end = false;
+                if (t < mine) {
+                    const int xl = c.x0 + x, al = c.a0 + a, bl = c.b0 + b;
+                    if (!(c.exclude_self && al == xl)) {
+                        const int64_t row = base + int64_t(xl) * n;
+                        const float da = p32[row + al], db = p32[row + bl];
+                        if (flags) {
+                            const uint8_t fa = flags[row + al], fb = flags[row + bl];
+                            if (fabsf(da - db) <= margin || ((fa | fb) & kNonRobust)) {
+                                dirty = 1;
+                                if (!(fa & kMarked)) flags[row + al] = fa | kMarked;
+                                if (!(fb & kMarked)) flags[row + bl] = fb | kMarked;
+                            }
+                        }
+                        cnt += da < db ? 2u : (da == db ? 1u : 0u);
+                    }
+                    if (++b == c.nb) {
+                        b = 0;
+                        if (++a == c.na) {
+                            a = 0;
+                            end = true;
+                        }
+                    }
+                }
+                if (flags) push(end && dirty, cell, x);
+                if (end) {
+                    if (!dirty) acc += cnt;
+                    cnt = 0;
+                    dirty = 0;
+                    ++x;
+                }
+            }
+            if (acc) atomicAdd(&W[cell], (unsigned long long)acc);
+        }
+
+        // the others, by the wave
+        for (unsigned long long todo = __ballot(comparisons > kLaneWork); todo; todo &= todo - 1) {
+            const int src = __builtin_ctzll(todo);
+            unit_by_wave(bcast(cell, src), bcast(xb, src), bcast(xe, src), bcast(c.a0, src), bcast(c.na, src),
+                         bcast(c.b0, src), bcast(c.nb, src), bcast(c.x0, src), bcast(c.exclude_self, src),
+                         bcast64(base, src), bcast64(n, src));
+        }
     }
+    flush_block();
 }
 
 // Count of sorted values v[0..n) below `key` (strict: v < key) or at most `key`.
@@ -632,9 +813,18 @@ void triplets(hipStream_t s, const CellDev *cells, const int32_t *units, int64_t
               float margin, int32_t *recount, unsigned int *recount_n, int64_t recount_cap,
               const unsigned int *scale) {
     if (n_units <= 0) return;
-    hipLaunchKernelGGL(k_triplets, dim3(grid_for(n_units, 4)), dim3(256), 0, s, cells, units, n_units,
-                       g.pair_base, g.n_items, p32, W, flags, margin, recount, recount_n,
-                       recount_cap, scale);
+    if (n_units >= kManyUnits) {
+        const int chunk = int(std::min<int64_t>(kWave, n_units / 32768));
+        hipLaunchKernelGGL(k_triplets<true>, dim3(grid_for(n_units, 4 * chunk)), dim3(256), 0, s, cells, units, n_units,
+                           chunk, 1, g.pair_base, g.n_items, p32, W, flags, margin, recount, recount_n, recount_cap,
+                           scale);
+    } else {
+        // a wave's units lie far apart, so that neighbouring large ones spread out
+        const int parts = n_units >= 8192 ? 1 : n_units >= 2048 ? 4 : 8;
+        hipLaunchKernelGGL(k_triplets<false>, dim3(grid_for(n_units * parts, 4, 8192)), dim3(256), 0, s, cells, units,
+                           n_units, 1, parts, g.pair_base, g.n_items, p32, W, flags, margin, recount, recount_n,
+                           recount_cap, scale);
+    }
     FABX_HIP(hipGetLastError());
 }
 

@@ -127,6 +127,12 @@ void fused_bf16(hipStream_t s, const uint16_t *xn, const float *rinv, int dim_pa
                 float delta, float *p32, uint8_t *flags, unsigned int *nonrobust_n,
                 unsigned int *unit_ctr, const float *flen, const unsigned int *scale);
 
+// --- k_plain_fused.hip (plain FP32 form and discrete units, DTW mode, items of at
+// most 64 frames): p32 of every pair slot, bit for bit as gram_angular_f32 /
+// unit_mismatch and dtw_plain give it.  packed: the packed rows (or codes).
+void plain_fused(hipStream_t s, const void *packed, int dim_pad, const GroupTables &g, const ItemTables &it,
+                 const FusedPlan &plan, int distance, int norm, float *p32);
+
 // --- k_stream.hip (BF16 form, DTW mode: the column-stream kernel)
 // Per task frame: bit 31 first frame of its item, bit 30 last frame, bits
 // 6..29 the item's place in its BY group, bits 0..5 the frame's index in

@@ -178,6 +178,12 @@ struct PlainPlan {
     int64_t max_cells = 0;                                                     // largest batch
 };
 
+// The plain DTW form goes through distance matrices in HBM only when an item is
+// longer than a row block of the fused kernels.
+bool needs_strips(const TaskImpl &t, const ScoreParams &p) {
+    return p.mode == FABX_MODE_DTW && p.precision == FABX_PREC_FP32 && t.max_len > kFusedRowFrames;
+}
+
 PlainPlan plain_plan(const TaskImpl &t, int64_t cap) {
     PlainPlan pl;
     pl.tiles.push_back(0);
@@ -474,7 +480,7 @@ WorkspaceSizes workspace_sizes(const TaskImpl &t, const ScoreParams &p, const Pl
     w.xn = p.distance == FABX_DISTANCE_UNITS ? size_t(rows) * 4  // packed codes
                                              : size_t(rows) * size_t(dim_pad) * (bf16 ? 2 : 4);
     if (bf16) w.rinv = size_t(rows) * 4;
-    if (dtw && !bf16) w.dmat = size_t(std::max<int64_t>(strips.max_cells, 1)) * 4;
+    if (strips.max_cells > 0) w.dmat = size_t(strips.max_cells) * 4;
     w.p32 = size_t(t.n_pair_slots) * 4;
     if (bf16) {
         w.flags = size_t(t.n_pair_slots);
@@ -498,7 +504,7 @@ void enqueue_score(const TaskImpl &t, const ScoreParams &p, const FusedConfig &f
     const DatasetImpl &ds = *t.ds;
     const bool bf16 = p.precision == FABX_PREC_BF16_RECHECK;
     const bool dtw = p.mode == FABX_MODE_DTW;
-    const bool plain_dtw = dtw && !bf16;
+    const bool plain_strips = needs_strips(t, p);
     const int dim = ds.dim;
     const int dim_pad = int(round_up(dim, 64));
     const int64_t n_cells = int64_t(t.cells.size());
@@ -536,7 +542,15 @@ void enqueue_score(const TaskImpl &t, const ScoreParams &p, const FusedConfig &f
                              err_item, flen, scale);
     mark();  // 2
     const auto &sp = d.strips;
-    if (plain_dtw) {
+    auto fused_plan = [&] {
+        return kern::FusedPlan{d.rb, d.cb, d.unit_prefix, d.band_rb, d.g_cb0, d.rb_cstart,
+                               int64_t(cplan->band_rb.size()) - 1, cplan->unit_prefix.back(), fcfg.cols,
+                               fcfg.blocks_per_cu, ds.ctx->n_cu};
+    };
+    if (dtw && !bf16 && !plain_strips) {
+        kern::plain_fused(stream, d.xn, dim_pad, gt, it, fused_plan(), p.distance, p.dtw_norm, d.p32);
+        st.computed_dtw_cells = cplan->cells;
+    } else if (plain_strips) {
         // one batch of strips at a time through the distance buffer (stream order
         // keeps a batch's Gram from overwriting the previous batch's DTW input)
         for (const auto &b : strips.batches) {
@@ -563,11 +577,8 @@ void enqueue_score(const TaskImpl &t, const ScoreParams &p, const FusedConfig &f
                           p.dtw_norm, delta_q, d.p32, d.flags, nonrobust_n, unit_ctr);
         st.computed_dtw_cells = cplan->cells;
     } else if (dtw) {
-        kern::FusedPlan fp{d.rb, d.cb, d.unit_prefix, d.band_rb, d.g_cb0, d.rb_cstart,
-                           int64_t(cplan->band_rb.size()) - 1, cplan->unit_prefix.back(), fcfg.cols,
-                           fcfg.blocks_per_cu, ds.ctx->n_cu};
-        kern::fused_bf16(stream, static_cast<const uint16_t *>(d.xn), d.rinv, dim_pad, gt, it, fp, p.dtw_norm,
-                         float(p.delta), d.p32, d.flags, nonrobust_n, unit_ctr, flen, scale);
+        kern::fused_bf16(stream, static_cast<const uint16_t *>(d.xn), d.rinv, dim_pad, gt, it, fused_plan(),
+                         p.dtw_norm, float(p.delta), d.p32, d.flags, nonrobust_n, unit_ctr, flen, scale);
         // pairs with an item over 64 frames: FP64 from the raw features
         kern::long_dtw(stream, ds.features, ds.dtype, dim, gt, it, d.item_group, d.long_slots,
                        int64_t(t.long_slots.size()), p.dtw_norm, euclid ? 1 : 0, d.p64, d.p32, d.flags);
@@ -693,9 +704,9 @@ std::shared_ptr<ResultImpl> launch_score(const std::shared_ptr<TaskImpl> &tp, co
     Trace tr("score");
     const int64_t n_units = int64_t(t.units.size() / 3);
     const bool pooled = !dtw;
-    const bool plain_dtw = dtw && !bf16;
+    const bool plain_strips = needs_strips(t, p);
     const std::vector<int64_t> tiles = pooled ? tile_prefix(t, p) : std::vector<int64_t>();
-    const PlainPlan strips = plain_dtw ? plain_plan(t, plain_dmat_cells()) : PlainPlan();
+    const PlainPlan strips = plain_strips ? plain_plan(t, plain_dmat_cells()) : PlainPlan();
     tr.mark("plans");
 
     // ---- device tables (items / groups / cells are fixed for the task): one copy
@@ -717,6 +728,9 @@ std::shared_ptr<ResultImpl> launch_score(const std::shared_ptr<TaskImpl> &tp, co
         res->fused = fcfg;
         st.fused_cols = fcfg.cols;
         st.fused_blocks_per_cu = fcfg.blocks_per_cu;
+    } else if (dtw && !plain_strips) {
+        fcfg = Tuner::default_config();
+        cplan = &col_plan(t, fcfg.cols);
     }
     if (!dv.uploaded) {
         // one DMA for the task's tables (and the column plan this score uses)
@@ -752,7 +766,7 @@ std::shared_ptr<ResultImpl> launch_score(const std::shared_ptr<TaskImpl> &tp, co
     DevPtrs d;
     static const std::vector<int64_t> no_slots;
     const std::vector<int64_t> &long_slots = dtw && bf16 ? t.long_slots : no_slots;
-    if (pooled || plain_dtw || !long_slots.empty()) {
+    if (pooled || plain_strips || !long_slots.empty()) {
         Packer pp;
         const PlanLayout pl = add_plan(pp, tiles, strips, long_slots);
         pp.upload(plan_d, ds.ctx->staging, ds.ctx->copy_stream, stream);
@@ -898,6 +912,9 @@ void score_in_scratch(TaskImpl &t, const ScoreParams &p, char *base, size_t cap,
         cplan = &col_plan(t, fcfg.cols);
         st.fused_cols = fcfg.cols;
         st.fused_blocks_per_cu = fcfg.blocks_per_cu;
+    } else if (dtw && !needs_strips(t, p)) {
+        fcfg = Tuner::default_config();
+        cplan = &col_plan(t, fcfg.cols);
     }
     const std::vector<int64_t> tiles = dtw ? std::vector<int64_t>() : tile_prefix(t, p);
     const bool stream_k = cplan && fcfg.cols >= kStreamMinCols;
@@ -917,7 +934,7 @@ void score_in_scratch(TaskImpl &t, const ScoreParams &p, char *base, size_t cap,
     PlanLayout pl;
     std::array<std::vector<int64_t>, 5> gcols;
     PlainPlan strips;
-    if (dtw && !bf16) {
+    if (needs_strips(t, p)) {
         strips = plain_plan(t, plain_dmat_cells());
         Packer probe;
         std::array<std::vector<int64_t>, 5> gc2;

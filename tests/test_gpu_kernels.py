@@ -117,3 +117,54 @@ def test_sorted_rows(nb, na, repeat, margin):
             s += int((2 * len(b) - np.searchsorted(b, a, "left") - np.searchsorted(b, a, "right")).sum())
         want.append(s)
     assert res.half_units.tolist() == want
+
+
+# The plain FP32 form's fused kernel against its strip form (which a task takes
+# once any item has more than 64 frames): every pair value bit for bit.  Lengths
+# to the row block's 64 frames, groups over several column blocks, dims off and on
+# the staging chunk, frames of two codes (ties between paths of different length),
+# infinities and NaN in the features (Euclidean: the order of comparisons shows).
+@pytest.mark.parametrize("norm", ["path", "none"])
+@pytest.mark.parametrize("case,distance", [("ragged", "angular"), ("ragged", "euclidean"), ("one-frame", "angular"),
+                                           ("codes", "angular"), ("codes", "euclidean"), ("odd", "euclidean"),
+                                           ("units", "units")])
+def test_plain_fused_equals_strips(case, distance, norm):
+    import paper_2505_02692_amd as fx
+    from test_gpu_parity import ctx
+    len_hi = {"one-frame": 1, "units": 40}.get(case, 64)
+    w = workloads.batched_c4(n_groups=9, size_lo=15, size_hi=40, len_lo=1, len_hi=len_hi, dim=70 if case == "ragged" else 8,
+                             centroid_std=0.3, dtype=torch.float32, seed=17)
+    rng = np.random.default_rng(3)
+    feats = w.features.clone()
+    if case == "codes":
+        feats = torch.nn.functional.one_hot(torch.from_numpy(rng.integers(0, 2, w.n_frames)), 8).float()
+    if case == "odd":
+        for v in (np.nan, np.inf, -np.inf, 3e38):
+            for f in rng.integers(0, w.n_frames, 12):
+                feats[f, int(rng.integers(0, 8))] = v
+    if case == "units":
+        feats = torch.from_numpy(rng.integers(0, 3, w.n_frames).astype(np.int32))
+    # the same items and a group of their own for two long ones
+    extra = torch.ones((66 + 3, 8 if case != "ragged" else 70)) if case != "units" else torch.ones(69, dtype=torch.int32)
+    attrs = np.concatenate([w.attrs, [[0, 9999], [0, 9999], [1, 9999]]]).astype(np.int32)
+    off = np.concatenate([w.offsets, w.offsets[-1] + np.array([1, 67, 69])]).astype(np.int64)
+    kw = dict(precision="fp32", distance=distance, norm=norm, keep_pairs=True)
+    print(f"[case] plain fused {case} {distance} {norm}", flush=True)
+    short = fx.Task(fx.Dataset(ctx(), feats.cuda().contiguous(), w.offsets, w.attrs), 0, [1]).score(**kw)
+    both = fx.Task(fx.Dataset(ctx(), torch.cat([feats, extra.to(feats.dtype)]).cuda().contiguous(), off, attrs), 0,
+                   [1]).score(**kw)
+    xs, ys = [], []
+    for g in np.unique(w.attrs[:, 1]):
+        items = np.flatnonzero(w.attrs[:, 1] == g)
+        if len(np.unique(w.attrs[items, 0])) == 2 and len(items) > 2:
+            i, j = np.meshgrid(items, items, indexing="ij")
+            xs.append(i.ravel())
+            ys.append(j.ravel())
+    xs, ys = np.concatenate(xs), np.concatenate(ys)
+    a, b = short.pairs(xs, ys)[0], both.pairs(xs, ys)[0]
+    assert len(xs) > 1000
+    assert np.array_equal(a, b, equal_nan=True)
+    if case == "odd":
+        assert np.isnan(a).any() and np.isinf(a).any()
+    else:
+        assert np.isfinite(a).all()

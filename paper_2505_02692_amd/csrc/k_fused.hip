@@ -21,6 +21,10 @@
 //     Every step all lanes do useful work except the fill and drain of the
 //     longest row item.
 //
+// What bounds it: the vector ALUs (65% busy; matrix cores under 10%) and the
+// latency of the DTW's dependent chain.  Four blocks per CU hide it better than two
+// of 256 columns do.
+//
 // Path length (FABX_NORM_PATH): with BF16 distances the predecessor chosen in
 // FP32 can differ from the FP64 one when their cumulative costs are within
 // the error bound, and then the length (the divisor) changes.  Each cell
@@ -31,6 +35,7 @@
 // in the interval; a pair whose interval is not a single value is flagged
 // non-robust (flag bit 0) and recomputed in FP64.
 #include "device_common.h"
+#include "fused_unit.h"
 #include "kernels.h"
 
 namespace fabx {
@@ -65,11 +70,12 @@ struct Tile {
     static constexpr int kCT = kWaveCols / 32;
     static constexpr int kDStride = kC + 2;  // LDS distance tile stride (floats)
     static constexpr int kStageBytes = (kRows + kC) * kLdsRow * 2;
-    // distance tile + a tail guard: the DTW loop reads up to 67 columns past a
-    // row's end (64 of drain, 3 of read-ahead)
+    // distance tile + a tail guard: the DTW loop reads up to 69 columns past a
+    // row's last (63 of drain, 6 of rounding up and read-ahead), two of them inside
+    // the row's padding
     static constexpr int kTileBytes = (kRows * kDStride + kWave + 4) * 4;
-    // column flags: a zero guard of one wave before the span and one wave + 4 after
-    static constexpr int kFlagLen = kWave + kC + kWave + 4;
+    // column flags: a zero guard of one wave before the span and one wave + 8 after
+    static constexpr int kFlagLen = kWave + kC + kWave + 8;
     static constexpr int kSmemBytes = kStageBytes > kTileBytes ? kStageBytes : kTileBytes;
 };
 
@@ -225,7 +231,7 @@ __device__ __forceinline__ int acc_row(int i, int lane) { return 8 * (i / 4) + 4
 // set (the DTW of a careful unit takes its magnitude and notes it), and delta
 // is in units of the largest frame length (*scale, FP32 bits).
 template <int kC, bool kPath, bool kEuclid>
-__global__ __launch_bounds__(256, 4) void k_fused(const uint16_t *__restrict__ xn,
+__global__ __launch_bounds__(256, kC == 128 ? 4 : 2) void k_fused(const uint16_t *__restrict__ xn,
                                                   const float *__restrict__ rinv, int dim_pad,
                                                   const int64_t *__restrict__ g_item0,
                                                   const int64_t *__restrict__ g_n,
@@ -253,6 +259,7 @@ __global__ __launch_bounds__(256, 4) void k_fused(const uint16_t *__restrict__ x
     __shared__ __attribute__((aligned(16))) float len_s[kEuclid ? kRows + kC : 1];  // and lengths
     if constexpr (kEuclid) delta *= __uint_as_float(*scale);
     __shared__ int near_s;  // the unit holds a near-parallel frame pair
+    __shared__ unit::Items<kC> items_s;  // where the unit's items begin and end
     // XCD-aware order: the 8 XCDs take blocks round-robin, so XCD x works
     // through the contiguous unit range [x * grid_q, (x+1) * grid_q) (units of
     // one group share its frames in that XCD's L2).  gridDim.x is a multiple
@@ -275,23 +282,24 @@ __global__ __launch_bounds__(256, 4) void k_fused(const uint16_t *__restrict__ x
     };
     const int lane = threadIdx.x % kWave;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    colflag[w][lane] = 0;  // the guard before every span
     // the band of the block's previous unit and its unit range: a persistent
     // block's next unit usually lies in it, which spares the band search
     int64_t band_c = -1, band_lo = 0, band_hi = 0;
     for (int64_t j = take ? next(0) : int64_t(blockIdx.x / 8); j < grid_q; j = next(j)) {
-    const int64_t unit = xcd * grid_q + j;
-    if (unit >= n_units) break;  // uniform across the block; later units are larger
+    const int64_t u = xcd * grid_q + j;
+    if (u >= n_units) break;  // uniform across the block; later units are larger
 
     // the unit's band, row block, group and column block: within a band,
     // column blocks from the band's first kept one on, row blocks fastest
-    if (band_c < 0 || unit < band_lo || unit >= band_hi) {  // uniform
-        band_c = dev::find_segment_wave(unit_prefix, n_bands, unit);
+    if (band_c < 0 || u < band_lo || u >= band_hi) {  // uniform
+        band_c = dev::find_segment_wave(unit_prefix, n_bands, u);
         band_lo = unit_prefix[band_c];
         band_hi = unit_prefix[band_c + 1];
     }
     const int64_t bi = band_c;
     const int rb0 = band_rb[bi], band_rows = band_rb[bi + 1] - rb0;
-    const int64_t local = unit - band_lo;
+    const int64_t local = u - band_lo;
     // 32-bit division whenever the offset fits (a band holds fewer than 2^32
     // units unless a group has hundreds of millions of column blocks)
     int64_t rbi;
@@ -310,6 +318,7 @@ __global__ __launch_bounds__(256, 4) void k_fused(const uint16_t *__restrict__ x
     const int r_item0 = rb[4 * rbi + 1], r_nitems = rb[4 * rbi + 2], r_frames = rb[4 * rbi + 3];
     const int c_item0 = cb[4 * cbi + 1], c_nitems = cb[4 * cbi + 2], c_frames = cb[4 * cbi + 3];
     const int64_t r_frame0 = item_dst[r_item0], c_frame0 = item_dst[c_item0];
+    const int64_t pbase = g_pair_base[g], gn = g_n[g], gitem0 = g_item0[g];  // (used last, loaded with the others)
 
     if (threadIdx.x == 0) near_s = 0;  // read after the barriers of the Gram tile and the epilogue
     // 1. Gram tile
@@ -318,10 +327,9 @@ __global__ __launch_bounds__(256, 4) void k_fused(const uint16_t *__restrict__ x
     if constexpr (kEuclid) ls.load(flen, r_frame0, r_frames, c_frame0, c_frames);
     // column items before the row block's first item pair only with rows after
     // them, which other units write: their columns (the first c_skip of the
-    // block) are not needed
-    const int k_first = max(0, r_item0 - c_item0);
-    int c_skip = 0;
-    for (int k = 0; k < min(k_first, c_nitems); ++k) c_skip += item_len[c_item0 + k];
+    // block; the group's packed frames lie in item order) are not needed
+    const int c_skip = int(min(max(r_frame0 - c_frame0, int64_t(0)), int64_t(c_frames)));
+    unit::find_items<kC>(items_s, item_len, r_item0, r_nitems, c_item0, c_nitems);
     f32x16 acc[2][T::kCT];
     gram_tile<kC>(reinterpret_cast<uint16_t *>(smem_raw), xn, dim_pad, r_frame0, r_frames, c_frame0,
                   c_frames, c_skip, acc, [&] {
@@ -411,68 +419,30 @@ __global__ __launch_bounds__(256, 4) void k_fused(const uint16_t *__restrict__ x
 
     // 3. DTW.  Column items of this block split over the 4 waves by start frame.
     // Lane constants: the row item of lane `lane`.
-    int ir = 0, nx = 0, x_task = -1;
-    {
-        int start = 0;
-        for (int k = 0; k < r_nitems; ++k) {
-            const int L = item_len[r_item0 + k];
-            if (lane >= start && lane < start + L) { ir = lane - start; nx = L; x_task = r_item0 + k; }
-            start += L;
-        }
-    }
-    int max_n = 0;
-    for (int k = 0; k < r_nitems; ++k) max_n = max(max_n, item_len[r_item0 + k]);
-    // this wave's column items: those whose first frame falls in its quarter of
-    // the needed columns (from item k_first on).  A lane reads distances at most
-    // 63 columns left of its span's start only in steps whose cells are never
-    // used (an item's first column resets the left and diagonal neighbours);
-    // those columns may hold stale values when their tiles were skipped.
-    int y_begin = 0, y_end = 0, s_begin = 0, s_end = 0;
-    {
-        const int skip = c_skip;
-        const int kept = max(c_frames - skip, 1);
-        // item k belongs to wave floor(4 (start - skip) / kept), tested as
-        // w kept <= 4 (start - skip) < (w + 1) kept without a division
-        const int own_lo = w * kept, own_hi = own_lo + kept;
-        int start = skip;
-        bool seen = false;
-        for (int k = k_first; k < c_nitems; ++k) {
-            const int L = item_len[c_item0 + k];
-            const int a4 = 4 * (start - skip);
-            if (a4 >= own_lo && a4 < own_hi) {
-                if (!seen) { y_begin = k; s_begin = start; seen = true; }
-                y_end = k + 1;
-                s_end = start + L;
-            }
-            start += L;
-        }
-        // column c of this wave's span is entry kWave + c: byte 0 = 1 at the
-        // first column of an item (tested with one byte-select compare), bits
-        // 8..21 = the item's index in the column block, bit 31 =
-        // last column.  The guards read as 0 (no item start, no output).
-        // Same-wave LDS stores land in issue order.
-        for (int j = lane; j < kFlagLen; j += kWave) colflag[w][j] = 0;
-        if (seen) {
-            int start2 = s_begin;
-            for (int k = y_begin; k < y_end; ++k) {
-                const int L = item_len[c_item0 + k];
-                for (int j = lane; j < L; j += kWave)
-                    colflag[w][kWave + start2 - s_begin + j] =
-                        uint32_t((j == 0 ? 1u : 0u) | (uint32_t(k) << 8) | (j == L - 1 ? 0x80000000u : 0u));
-                start2 += L;
-            }
-        }
+    const unit::Row row = unit::row_of(items_s, lane, r_frames);
+    const int ir = row.ir;
+    const int max_n = __builtin_amdgcn_readfirstlane(int(items_s.longest));
+    // this wave's columns.  A lane reads distances at most 63 columns left of its
+    // span's start only in steps whose cells are never used (an item's first column
+    // resets the left and diagonal neighbours); those columns may hold stale values
+    // when their tiles were skipped.
+    const unit::Cols<kC> cols(items_s);
+    const unit::Span span = unit::span_of<kC>(cols, w, c_skip, c_frames);
+    const int s_begin = span.begin, s_end = span.end;
+    // column c of the span is entry kWave + c of colflag; the guards on either side
+    // read as 0 (no item start, no output).  The one before is written once.
+    // Same-wave LDS stores land in issue order.
+    if (s_end > s_begin) {
+        const int n = s_end - s_begin;
+        for (int j = lane; j < n; j += kWave) colflag[w][kWave + j] = cols.flag(s_begin + j, c_frames);
+        for (int j = n + lane; j < n + kWave + 8; j += kWave) colflag[w][kWave + j] = 0;
     }
     __syncthreads();
     const int S = s_end - s_begin;
     if (S > 0) {  // this wave has column items
 
-    const int64_t pbase = g_pair_base[g];
-    const int64_t gn = g_n[g];
-    const int64_t gitem0 = g_item0[g];
-    const bool row_valid = x_task >= 0;
     const bool top = ir == 0;
-    const bool last_row = row_valid && ir == nx - 1;
+    const bool last_row = row.last;
     // The first row of an item has no row above: it adds +inf to whatever the
     // lane above sends (the last row of another item, or a row past the
     // block's frames; lane 0 reads 0).  That lane may be on columns outside its
@@ -484,17 +454,21 @@ __global__ __launch_bounds__(256, 4) void k_fused(const uint16_t *__restrict__ x
     const float top_pen = top ? kInf : 0.0f;
     const float diag_first = top ? 0.0f : kInf;       // virtual c[-1][-1] = 0 at an item start
     const uint32_t pd_first = top ? 0x0000FFFFu : 0u;  // its length interval: Lmin = Lmax = 0
-    const int64_t px = row_valid ? int64_t(x_task) - gitem0 : 0;  // row item's position in the group
     // at step t the lane is on column t - ir of the wave's span: distance
     // dcol[t], flags fcol[t], read four steps ahead.  ir <= lane, so dcol[0] is
-    // inside the tile; the last read-ahead is at most max_n + 2 <= 66 columns
-    // past the span: row 63 then ends 3 floats short of the tile's tail guard,
-    // and the flags' zero guard covers it.
+    // inside the tile; the last read-ahead (step steps + 6) is max_n + 6 - ir columns
+    // past the span's last.  In row 63 that is at most 69, as ir = 63 when max_n = 64:
+    // inside the tile's tail guard, as it is inside the flags' zero guard.
     const float *dcol = dt + lane * kDStride + s_begin - ir;
     const uint32_t *fcol = &colflag[w][kWave - ir];
-    // a cell is output on the item's last row and last column: flags >=
-    // 0x80000000 (flags never reach 0xFFFFFFFF)
+    // a pair ends on its items' last row and last column: flags >= 0x80000000
+    // (flags never reach 0xFFFFFFFF).  Its cost then replaces the distance there in
+    // the tile, and its length interval the distance above it, both already read
+    // (in an item of one row it would be another item's; there the only path has the
+    // column item's length, and the cost overwrites the interval).
     const uint32_t out_min = last_row ? 0x80000000u : 0xFFFFFFFFu;
+    float *cost_at = dt + lane * kDStride + s_begin - ir;
+    uint32_t *len_at = reinterpret_cast<uint32_t *>(cost_at - (top ? 0 : kDStride));
 
     // Cells outside a lane's column range are computed too (on guard columns)
     // but never read: the first column of every item resets left and diagonal.
@@ -538,38 +512,9 @@ __global__ __launch_bounds__(256, 4) void k_fused(const uint16_t *__restrict__ x
         c = dvc + m;
         up_prev = up;
         Pup_prev = Pup;
-        // Pair (x, y) of the group, x the row item: kept when x comes before y
-        // (or is y) and written at (x, y) and (y, x), the distance being
-        // symmetric (a pair whose path length is ambiguous is flagged in both
-        // slots and recomputed in FP64 in each orientation).  Each slot has one
-        // writer: the pairs with x after y are written by the unit holding
-        // (y, x).
-        if (cf >= out_min) {
-            const int64_t py = int64_t(c_item0) + ((cf >> 8) & 0x3FFF) - gitem0;
-            if (px <= py) {
-                const int64_t slot = pbase + px * gn + py, mirror = pbase + py * gn + px;
-                float v;
-                uint8_t fl = 0;
-                if (kPath) {
-                    const uint32_t lmax = P >> 16, lmin = 0xFFFFu - (P & 0xFFFFu);
-                    v = c * __builtin_amdgcn_rcpf(float(lmin));
-                    fl = lmin == lmax ? 0 : 1;
-                } else {
-                    v = c;
-                }
-                if (careful && nz && px != py) fl = 1;  // (x, x) is never compared
-                if (fl) atomicAdd(nonrobust_n, px < py ? 2u : 1u);
-                p32[slot] = v;
-                flags[slot] = fl;
-                if (px < py) {
-                    p32[mirror] = v;
-                    flags[mirror] = fl;
-                }
-            }
-        }
     };
     // four steps at a time from one of two register buffers while the other
-    // takes the next four (read ahead up to step steps + 3); the buffers
+    // takes the next four (read ahead up to step steps + 6); the buffers
     // alternate, so no values are copied between them
     auto load4 = [&](uint32_t (&f)[4], float (&d)[4], int t0) {
 #pragma unroll
@@ -578,41 +523,91 @@ __global__ __launch_bounds__(256, 4) void k_fused(const uint16_t *__restrict__ x
             d[k] = dcol[t0 + k];
         }
     };
-    auto run4 = [&](const uint32_t (&f)[4], const float (&d)[4]) {
+    // four steps without a branch, keeping each one's cost and length, then one test
+    // whether any lane ends a pair in them: with a test per step every step was a
+    // block of its own, whose DPP wait states and dependent chain nothing filled
+    // (1200 groups of 11-2000 items of 1-60 frames, 512 features: 392 -> 375 ms).
+    // The sign of a cost carries the pair's near bit.
+    auto run_n = [&](const uint32_t (&f)[4], const float (&d)[4], int t0, auto n_tag) {
+        constexpr int N = decltype(n_tag)::value;
+        float cs[N];
+        uint32_t ps[N], top_f = f[0];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) step(f[k], d[k]);
-    };
-    auto tail = [&](const uint32_t (&f)[4], const float (&d)[4], int n) {
+        for (int k = 0; k < N; ++k) {
+            top_f = max(top_f, f[k]);
+            step(f[k], d[k]);
+            cs[k] = careful && nz ? -c : c;
+            ps[k] = P;
+        }
+        if (top_f >= out_min) {
 #pragma unroll
-        for (int k = 0; k < 3; ++k)
-            if (k < n) step(f[k], d[k]);
+            for (int k = 0; k < N; ++k)
+                if (f[k] >= out_min) {
+                    if (kPath) len_at[t0 + k] = ps[k];
+                    cost_at[t0 + k] = cs[k];
+                }
+        }
     };
     uint32_t fa[4], fb[4];
     float da[4], db[4];
     load4(fa, da, 0);
-    for (int t = 0;;) {
-        if (t + 4 > steps) {
-            tail(fa, da, steps - t);
-            break;
-        }
+    auto rest = [&](const uint32_t (&f)[4], const float (&d)[4], int t0, int n) {  // uniform n
+        if (n >= 4) run_n(f, d, t0, std::integral_constant<int, 4>{});
+        else if (n == 3) run_n(f, d, t0, std::integral_constant<int, 3>{});
+        else if (n == 2) run_n(f, d, t0, std::integral_constant<int, 2>{});
+        else run_n(f, d, t0, std::integral_constant<int, 1>{});
+    };
+    int t = 0;
+    for (; t + 8 <= steps; t += 8) {
         load4(fb, db, t + 4);
-        run4(fa, da);
-        t += 4;
-        if (t + 4 > steps) {
-            tail(fb, db, steps - t);
-            break;
-        }
-        load4(fa, da, t + 4);
-        run4(fb, db);
-        t += 4;
+        run_n(fa, da, t, std::integral_constant<int, 4>{});
+        load4(fa, da, t + 8);
+        run_n(fb, db, t + 4, std::integral_constant<int, 4>{});
+    }
+    if (t < steps) {
+        load4(fb, db, t + 4);
+        rest(fa, da, t, steps - t);
+        if (t + 4 < steps) rest(fb, db, t + 4, steps - t - 4);
     }
     };
     if (near_s != 0)  // uniform: written before the barrier above
         run(std::true_type{});
     else
         run(std::false_type{});
+    // 4. The pairs of the wave's columns.  Pair (x, y) of the group, x the row item,
+    // is kept when x comes before y (or is y) and written at (x, y) and (y, x), the
+    // distance being symmetric (a pair whose path length is ambiguous is flagged in
+    // both slots and recomputed in FP64 in each orientation).  Each slot has one
+    // writer: the pairs with x after y are written by the unit holding (y, x).  A lane
+    // per pair, after the sweep: written by the lane that ended it, at its step, a
+    // pair cost a few dozen instructions with most of the wave idle.
+    __builtin_amdgcn_wave_barrier();
+    unit::for_pairs<kC>(cols, span, r_nitems, r_item0 - gitem0, c_item0 - gitem0,
+                        [&](int i, int j, int64_t px, int64_t py) {
+        const int r = items_s.row_last[i], col = items_s.col_last[j];
+        const float stored = dt[r * kDStride + col];
+        float v = fabsf(stored);
+        uint8_t fl = 0;
+        if (kPath) {
+            const int r0 = i > 0 ? items_s.row_last[i - 1] + 1 : 0, c0 = j > 0 ? items_s.col_last[j - 1] + 1 : 0;
+            const uint32_t P = __float_as_uint(dt[max(r - 1, 0) * kDStride + col]);
+            const uint32_t lmax = r == r0 ? uint32_t(col - c0 + 1) : P >> 16;
+            const uint32_t lmin = r == r0 ? lmax : 0xFFFFu - (P & 0xFFFFu);
+            v *= __builtin_amdgcn_rcpf(float(lmin));
+            fl = lmin == lmax ? 0 : 1;
+        }
+        if (near_s != 0 && signbit(stored) && px != py) fl = 1;  // a near pair; (x, x) is never compared
+        const int64_t slot = pbase + px * gn + py, mirror = pbase + py * gn + px;
+        if (fl) atomicAdd(nonrobust_n, px < py ? 2u : 1u);
+        p32[slot] = v;
+        flags[slot] = fl;
+        if (px < py) {
+            p32[mirror] = v;
+            flags[mirror] = fl;
+        }
+    });
     }  // S > 0
-    __syncthreads();  // the next unit overwrites the LDS tile and column flags
+    __syncthreads();  // the next unit overwrites the LDS tile, the items and the column flags
     }
 }
 

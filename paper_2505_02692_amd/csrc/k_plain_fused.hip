@@ -21,6 +21,7 @@
 // most 128, lane = frame row, each of four waves streaming its share of the
 // column items past all rows.
 #include "device_common.h"
+#include "fused_unit.h"
 #include "kernels.h"
 
 namespace fabx {
@@ -37,7 +38,7 @@ constexpr int kRows = 64, kCols = kFusedColFrames;
 constexpr int kAngular = 0, kEuclid = 1, kUnits = 2;
 constexpr int kDStride = kCols + 2;                           // LDS distance tile stride
 constexpr int kTileFloats = kRows * kDStride + kWave + 4;     // with the sweep's tail guard
-constexpr int kFlagLen = kWave + kCols + kWave + 4;           // column flags between zero guards
+constexpr int kFlagLen = kWave + kCols + kWave + 8;           // column flags between zero guards
 // angular staging: K chunks of 32 features; each 8 of a row lie as k 0 2 4 6, 1 3 5 7,
 // so that a lane (half-wave h takes features of parity h) reads four steps' operands
 // at once; rows of 36 floats keep those reads off each other's banks
@@ -53,9 +54,9 @@ __device__ __forceinline__ uint32_t shr1(uint32_t v) {
 }
 
 // 64 x 128 frame distances (theta / pi) of packed unit rows r0.. and c0.. into
-// dt; odd collects the largest bit pattern.  Rows past nr and nc repeat the last.
+// dt.  Rows past nr and nc repeat the last.
 __device__ __forceinline__ void angular_tile(float *smem, const float *__restrict__ xn, int dim_pad, int64_t r0,
-                                             int nr, int64_t c0, int nc, int c_lo, float *dt, uint32_t &odd) {
+                                             int nr, int64_t c0, int nc, int c_lo, float *dt) {
     const int lane = threadIdx.x % kWave, w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     constexpr int kPer = (kRows + kCols) * (kKc / 8) / 256;  // 8-feature pieces per thread
     f32x4 lo[kPer], hi[kPer];
@@ -111,16 +112,15 @@ __device__ __forceinline__ void angular_tile(float *smem, const float *__restric
             for (int i = 4 * g4; i < 4 * g4 + 4; ++i) {
                 const int r = 32 * h + 8 * g4 + 4 * half + i % 4;
                 const float cs = fminf(fmaxf(acc[h][i], -1.0f), 1.0f);
-                // (the clamp drops a NaN sum where the strip form's does too)
-                const float d = acosf(cs) * dev::kInvPi;
-                odd = max(odd, __float_as_uint(d) & 0x7FFFFFFFu);
-                dt[r * kDStride + col0 + lane % 32] = d;
+                // (the clamp drops a NaN sum, as the strip form's does: always finite)
+                dt[r * kDStride + col0 + lane % 32] = acosf(cs) * dev::kInvPi;
             }
         }
     }
 }
 
-// The same of raw rows' Euclidean distances: 4 x 8 elements a thread.
+// The same of raw rows' Euclidean distances: 4 x 8 elements a thread; odd collects
+// the largest bit pattern.
 __device__ __forceinline__ void euclid_tile(float *smem, const float *__restrict__ xn, int dim_pad, int64_t r0,
                                             int nr, int64_t c0, int nc, float *dt, uint32_t &odd) {
     const int ty = threadIdx.x / 16, tx = threadIdx.x % 16;
@@ -188,16 +188,18 @@ __global__ __launch_bounds__(256, 4) void k_plain_fused(const void *__restrict__
     __shared__ __attribute__((aligned(16))) float smem[kStage > kTileFloats ? kStage : kTileFloats];
     __shared__ uint32_t colflag[4][kFlagLen];
     __shared__ uint32_t odd_s;
+    __shared__ unit::Items<kCols> items_s;  // where the unit's items begin and end
     float *dt = smem;
     const int lane = threadIdx.x % kWave, w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    colflag[w][lane] = 0;  // the guard before every span
     // XCD x takes the contiguous unit range [x * grid_q, (x + 1) * grid_q), as the BF16 kernel
     const int64_t xcd = blockIdx.x % 8, n_m = gridDim.x / 8;
     for (int64_t j = blockIdx.x / 8; j < grid_q; j += n_m) {
-        const int64_t unit = xcd * grid_q + j;
-        if (unit >= plan.n_units) break;  // uniform; later units are larger
-        const int64_t bi = dev::find_segment_wave(plan.unit_prefix, plan.n_bands, unit);
+        const int64_t u = xcd * grid_q + j;
+        if (u >= plan.n_units) break;  // uniform; later units are larger
+        const int64_t bi = dev::find_segment_wave(plan.unit_prefix, plan.n_bands, u);
         const int rb0 = plan.band_rb[bi], band_rows = plan.band_rb[bi + 1] - rb0;
-        const int64_t local = unit - plan.unit_prefix[bi];
+        const int64_t local = u - plan.unit_prefix[bi];
         const int64_t rbi = rb0 + local % band_rows;
         const int c_local = plan.rb_cstart[rb0] + int(local / band_rows);
         if (c_local < plan.rb_cstart[rbi]) continue;  // uniform: wholly below the group's diagonal
@@ -206,16 +208,16 @@ __global__ __launch_bounds__(256, 4) void k_plain_fused(const void *__restrict__
         const int r_item0 = plan.rb[4 * rbi + 1], r_nitems = plan.rb[4 * rbi + 2], r_frames = plan.rb[4 * rbi + 3];
         const int c_item0 = plan.cb[4 * cbi + 1], c_nitems = plan.cb[4 * cbi + 2], c_frames = plan.cb[4 * cbi + 3];
         const int64_t r0 = item_dst[r_item0], c0 = item_dst[c_item0];
-        // column items before the row block's first item belong to other units
-        const int k_first = max(0, r_item0 - c_item0);
-        int c_skip = 0;
-        for (int k = 0; k < min(k_first, c_nitems); ++k) c_skip += item_len[c_item0 + k];
+        const int64_t pbase = g_pair_base[g], gn = g_n[g], gitem0 = g_item0[g];
+        // columns before the row block's first item belong to other units
+        const int c_skip = int(min(max(r0 - c0, int64_t(0)), int64_t(c_frames)));
+        unit::find_items<kCols>(items_s, item_len, r_item0, r_nitems, c_item0, c_nitems);
         if (threadIdx.x == 0) odd_s = 0;
 
-        uint32_t odd = 0;
+        [[maybe_unused]] uint32_t odd = 0;  // the largest distance's bits
         if constexpr (kKind == kAngular) {
-            angular_tile(smem, static_cast<const float *>(packed), dim_pad, r0, r_frames, c0, c_frames, c_skip, dt,
-                         odd);
+            angular_tile(smem, static_cast<const float *>(packed), dim_pad, r0, r_frames, c0, c_frames, c_skip,
+                         dt);
         } else if constexpr (kKind == kEuclid) {
             euclid_tile(smem, static_cast<const float *>(packed), dim_pad, r0, r_frames, c0, c_frames, dt, odd);
         } else {
@@ -230,145 +232,162 @@ __global__ __launch_bounds__(256, 4) void k_plain_fused(const void *__restrict__
 #pragma unroll
                 for (int c = 0; c < 2; ++c) dt[(w + 4 * i) * kDStride + lane + 64 * c] = rc[i] != cc[c] ? 1.0f : 0.0f;
         }
-        if (kKind != kUnits && __ballot(odd >= 0x7F800000u) != 0 && lane == 0) atomicOr(&odd_s, 1u);
+        if (kKind == kEuclid && __ballot(odd >= 0x7F800000u) != 0 && lane == 0) atomicOr(&odd_s, 1u);
 
-        // lane constants: the row item of lane `lane`
-        int ir = 0, nx = 0, x_task = -1, max_n = 0;
-        {
-            int start = 0;
-            for (int k = 0; k < r_nitems; ++k) {
-                const int L = item_len[r_item0 + k];
-                if (lane >= start && lane < start + L) { ir = lane - start; nx = L; x_task = r_item0 + k; }
-                start += L;
-                max_n = max(max_n, L);
-            }
-        }
-        // this wave's column items: those whose first frame falls in its quarter of
-        // the needed columns; and their flags (byte 0: first column, bits 8..21: item,
-        // bit 31: last column) between zero guards
-        int y_begin = 0, y_end = 0, s_begin = 0, s_end = 0;
-        {
-            const int kept = max(c_frames - c_skip, 1), own_lo = w * kept, own_hi = own_lo + kept;
-            int start = c_skip;
-            bool seen = false;
-            for (int k = k_first; k < c_nitems; ++k) {
-                const int L = item_len[c_item0 + k], a4 = 4 * (start - c_skip);
-                if (a4 >= own_lo && a4 < own_hi) {
-                    if (!seen) { y_begin = k; s_begin = start; seen = true; }
-                    y_end = k + 1;
-                    s_end = start + L;
-                }
-                start += L;
-            }
-            for (int c = lane; c < kFlagLen; c += kWave) colflag[w][c] = 0;
-            int at = s_begin;
-            for (int k = y_begin; k < y_end; ++k) {
-                const int L = item_len[c_item0 + k];
-                for (int c = lane; c < L; c += kWave)
-                    colflag[w][kWave + at - s_begin + c] =
-                        uint32_t((c == 0 ? 1u : 0u) | (uint32_t(k) << 8) | (c == L - 1 ? 0x80000000u : 0u));
-                at += L;
-            }
+        if constexpr (kKind == kUnits) __syncthreads();  // the masks (the other forms' tiles have barriers)
+        // the row item of lane `lane`, this wave's columns and their flags between
+        // zero guards
+        const unit::Row row = unit::row_of(items_s, lane, r_frames);
+        const int ir = row.ir;
+        const int max_n = __builtin_amdgcn_readfirstlane(int(items_s.longest));
+        const unit::Cols<kCols> cols(items_s);
+        const unit::Span span = unit::span_of<kCols>(cols, w, c_skip, c_frames);
+        const int s_begin = span.begin, s_end = span.end;
+        if (s_end > s_begin) {
+            const int n = s_end - s_begin;
+            for (int c = lane; c < n; c += kWave) colflag[w][kWave + c] = cols.flag(s_begin + c, c_frames);
+            for (int c = n + lane; c < n + kWave + 8; c += kWave) colflag[w][kWave + c] = 0;
         }
         __syncthreads();
         const int S = s_end - s_begin;
-        if (S > 0) {
-            const int64_t pbase = g_pair_base[g], gn = g_n[g], gitem0 = g_item0[g];
-            const bool top = ir == 0, last_row = x_task >= 0 && ir == nx - 1;
+        // kBoth: one sweep for both orientations; kXY, kYX: one orientation with the
+        // strip form's comparisons
+        constexpr int kBoth = 0, kXY = 1, kYX = 2;
+        const bool odd_unit = kKind == kEuclid && odd_s != 0;  // uniform
+        // A pair's end: its cost replaces the distance there in the tile, its path
+        // lengths the distance above (both already read; in an item of one row the only
+        // path has the column item's length, and the cost overwrites the lengths).
+        auto sweep = [&](auto mode_tag) {
+            constexpr int mode = decltype(mode_tag)::value;
+            const bool top = ir == 0;
             const float diag_first = top ? 0.0f : kInf;  // virtual cell (-1, -1)
-            const int64_t px = x_task >= 0 ? int64_t(x_task) - gitem0 : 0;
-            const float *dcol = dt + lane * kDStride + s_begin - ir;
+            float *cost_at = dt + lane * kDStride + s_begin - ir;
+            uint32_t *len_at = reinterpret_cast<uint32_t *>(cost_at - (top ? 0 : kDStride));
+            const float *dcol = cost_at;
             const uint32_t *fcol = &colflag[w][kWave - ir];
-            const uint32_t out_min = last_row ? 0x80000000u : 0xFFFFFFFFu;
+            const uint32_t out_min = row.last ? 0x80000000u : 0xFFFFFFFFu;
             const int steps = S + max_n - 1;
-            // kBoth: one sweep for both orientations; kXY, kYX: one orientation with the
-            // strip form's comparisons
-            constexpr int kBoth = 0, kXY = 1, kYX = 2;
-            auto run = [&](auto mode_tag) {
-                constexpr int mode = decltype(mode_tag)::value;
-                float c = kInf, up_prev = kInf;
-                uint32_t L = 0, lup_prev = 0;
-                auto quotient = [&](uint32_t len) {
-                    if (!kPath) return c;
-                    // integer costs: the double quotient rounded once (equal fractions give
-                    // equal values)
-                    if (kKind == kUnits) return float(double(c) / double(len));
-                    return c / float(len);
-                };
-                auto step = [&](const uint32_t cf, const float dv) {
-                    const bool first = uint8_t(cf) != 0;
-                    const float above = shr1(c);
-                    const float up = top ? kInf : above;
-                    const float diag = first ? diag_first : up_prev, left = first ? kInf : c;
-                    const bool from_diag = diag <= left && diag <= up;
-                    const bool le = left <= up, ge = up <= left;
-                    up_prev = up;
-                    if (kPath) {
-                        const uint32_t labove = shr1(L);
-                        const uint32_t lup = top ? 0u : labove;
-                        uint32_t sel;
-                        if (mode == kBoth) {
-                            const uint32_t lo = le ? L : lup, hi = ge ? lup : L;
-                            sel = (hi & 0xFFFF0000u) | (lo & 0xFFFFu);
-                        } else {
-                            sel = (mode == kXY ? le : !ge) ? L : lup;
-                        }
-                        L = (from_diag ? lup_prev : sel) + 0x00010001u;
-                        lup_prev = lup;
+            float c = kInf, up_prev = kInf;
+            uint32_t L = 0, lup_prev = 0;
+            auto step = [&](const uint32_t cf, const float dv) {
+                const bool first = uint8_t(cf) != 0;
+                const float above = shr1(c);
+                const float up = top ? kInf : above;
+                const float diag = first ? diag_first : up_prev, left = first ? kInf : c;
+                const bool from_diag = diag <= left && diag <= up;
+                const bool le = left <= up, ge = up <= left;
+                up_prev = up;
+                if (kPath) {
+                    const uint32_t labove = shr1(L);
+                    const uint32_t lup = top ? 0u : labove;
+                    uint32_t sel;
+                    if (mode == kBoth) {
+                        const uint32_t lo = le ? L : lup, hi = ge ? lup : L;
+                        sel = (hi & 0xFFFF0000u) | (lo & 0xFFFFu);
+                    } else {
+                        sel = (mode == kXY ? le : !ge) ? L : lup;
                     }
-                    float best;
-                    if (mode == kBoth) best = fminf(fminf(diag, left), up);
-                    else best = from_diag ? diag : (mode == kXY ? le : !ge) ? left : up;
-                    c = dv + best;
-                    if (cf >= out_min) {
-                        const int64_t py = int64_t(c_item0) + ((cf >> 8) & 0x3FFF) - gitem0;
-                        if (px <= py) {
-                            if (mode != kYX) p32[pbase + px * gn + py] = quotient(L & 0xFFFFu);
-                            if (mode != kXY && px < py) p32[pbase + py * gn + px] = quotient(L >> 16);
-                        }
-                    }
-                };
-                // four steps at a time from one of two register buffers while the other
-                // takes the next four
-                auto load4 = [&](uint32_t (&f)[4], float (&d)[4], int t0) {
+                    L = (from_diag ? lup_prev : sel) + 0x00010001u;
+                    lup_prev = lup;
+                }
+                float best;
+                if (mode == kBoth) best = fminf(fminf(diag, left), up);
+                else best = from_diag ? diag : (mode == kXY ? le : !ge) ? left : up;
+                c = dv + best;
+            };
+            // four steps at a time from one of two register buffers while the other
+            // takes the next four
+            auto load4 = [&](uint32_t (&f)[4], float (&d)[4], int t0) {
 #pragma unroll
-                    for (int k = 0; k < 4; ++k) {
-                        f[k] = fcol[t0 + k];
-                        d[k] = dcol[t0 + k];
-                    }
-                };
-                uint32_t fa[4], fb[4];
-                float da[4], db[4];
-                load4(fa, da, 0);
-                for (int t = 0;;) {
-                    if (t + 4 > steps) {
-#pragma unroll
-                        for (int k = 0; k < 3; ++k)
-                            if (k < steps - t) step(fa[k], da[k]);
-                        break;
-                    }
-                    load4(fb, db, t + 4);
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) step(fa[k], da[k]);
-                    t += 4;
-                    if (t + 4 > steps) {
-#pragma unroll
-                        for (int k = 0; k < 3; ++k)
-                            if (k < steps - t) step(fb[k], db[k]);
-                        break;
-                    }
-                    load4(fa, da, t + 4);
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) step(fb[k], db[k]);
-                    t += 4;
+                for (int k = 0; k < 4; ++k) {
+                    f[k] = fcol[t0 + k];
+                    d[k] = dcol[t0 + k];
                 }
             };
-            if (kKind != kUnits && odd_s != 0) {  // uniform
-                run(std::integral_constant<int, kXY>{});
-                run(std::integral_constant<int, kYX>{});
-            } else {
-                run(std::integral_constant<int, kBoth>{});
+            auto run_n = [&](const uint32_t (&f)[4], const float (&d)[4], int t0, auto n_tag) {
+                constexpr int N = decltype(n_tag)::value;
+                float cs[N];
+                uint32_t ls[N], top_f = f[0];
+#pragma unroll
+                for (int k = 0; k < N; ++k) {
+                    top_f = max(top_f, f[k]);
+                    step(f[k], d[k]);
+                    cs[k] = c;
+                    ls[k] = L;
+                }
+                if (top_f >= out_min) {
+#pragma unroll
+                    for (int k = 0; k < N; ++k)
+                        if (f[k] >= out_min) {
+                            if (kPath) len_at[t0 + k] = ls[k];
+                            cost_at[t0 + k] = cs[k];
+                        }
+                }
+            };
+            uint32_t fa[4], fb[4];
+            float da[4], db[4];
+            load4(fa, da, 0);
+            auto rest = [&](const uint32_t (&f)[4], const float (&d)[4], int t0, int n) {  // uniform n
+                if (n >= 4) run_n(f, d, t0, std::integral_constant<int, 4>{});
+                else if (n == 3) run_n(f, d, t0, std::integral_constant<int, 3>{});
+                else if (n == 2) run_n(f, d, t0, std::integral_constant<int, 2>{});
+                else run_n(f, d, t0, std::integral_constant<int, 1>{});
+            };
+            int t = 0;
+            for (; t + 8 <= steps; t += 8) {
+                load4(fb, db, t + 4);
+                run_n(fa, da, t, std::integral_constant<int, 4>{});
+                load4(fa, da, t + 8);
+                run_n(fb, db, t + 4, std::integral_constant<int, 4>{});
             }
+            if (t < steps) {
+                load4(fb, db, t + 4);
+                rest(fa, da, t, steps - t);
+                if (t + 4 < steps) rest(fb, db, t + 4, steps - t - 4);
+            }
+        };
+        // the pairs of the wave's columns, a lane each: mode kBoth both slots, kXY / kYX
+        // its own
+        auto write = [&](auto mode_tag) {
+            constexpr int mode = decltype(mode_tag)::value;
+            __builtin_amdgcn_wave_barrier();
+            unit::for_pairs<kCols>(cols, span, r_nitems, r_item0 - gitem0, c_item0 - gitem0,
+                                   [&](int i, int j, int64_t px, int64_t py) {
+                const int r = items_s.row_last[i], col = items_s.col_last[j];
+                const float cost = dt[r * kDStride + col];
+                uint32_t len = 0;
+                if (kPath) {
+                    const int first_r = i > 0 ? items_s.row_last[i - 1] + 1 : 0;
+                    const int first_c = j > 0 ? items_s.col_last[j - 1] + 1 : 0;
+                    len = r == first_r ? uint32_t(col - first_c + 1) * 0x00010001u
+                                       : __float_as_uint(dt[(r - 1) * kDStride + col]);
+                }
+                auto quotient = [&](uint32_t n) {
+                    if (!kPath) return cost;
+                    // integer costs: the double quotient rounded once (equal fractions give
+                    // equal values)
+                    if (kKind == kUnits) return float(double(cost) / double(n));
+                    return cost / float(n);
+                };
+                if (mode != kYX) p32[pbase + px * gn + py] = quotient(len & 0xFFFFu);
+                if (mode != kXY && px < py) p32[pbase + py * gn + px] = quotient(len >> 16);
+            });
+        };
+        auto sweep_and_write = [&](auto mode_tag) {
+            if (S <= 0) return;
+            sweep(mode_tag);
+            write(mode_tag);
+        };
+        if (!odd_unit) {
+            sweep_and_write(std::integral_constant<int, kBoth>{});
+        } else if constexpr (kKind == kEuclid) {
+            // each orientation by itself; the tile again for the second, since the ends of
+            // pairs overwrote distances
+            sweep_and_write(std::integral_constant<int, kXY>{});
+            __syncthreads();
+            euclid_tile(smem, static_cast<const float *>(packed), dim_pad, r0, r_frames, c0, c_frames, dt, odd);
+            __syncthreads();
+            sweep_and_write(std::integral_constant<int, kYX>{});
         }
         __syncthreads();  // the next unit overwrites the tile and the flags
     }

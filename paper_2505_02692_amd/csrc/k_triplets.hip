@@ -189,7 +189,7 @@ __global__ __launch_bounds__(256) void k_triplets(const CellDev *__restrict__ ce
         }
         // (a unit has at most 8192 comparisons or one x)
         if (int64_t(na) * nb <= (int64_t(1) << 24)) {
-            const unsigned int total = dev::wave_sum_u32(unsigned(acc));
+            const unsigned int total = dev::wave_scan_u32(unsigned(acc));
             if (lane == kWave - 1 && total) atomicAdd(&W[cell], (unsigned long long)total);
         } else {
             const unsigned long long total = dev::wave_sum_u64(acc);

@@ -168,3 +168,38 @@ def test_plain_fused_equals_strips(case, distance, norm):
         assert np.isnan(a).any() and np.isinf(a).any()
     else:
         assert np.isfinite(a).all()
+
+
+# The BF16 form's work units where their edges meet: blocks of one-frame items
+# (64 and 128 items), items that fill a row block, items that leave a block's last
+# frame over, pairs that end in the first or last of four steps.  Frames of 70
+# normal features: the BF16 cosine is off by at most 2^-8, an angle by that over
+# its sine (> 0.8), so a distance by less than 0.002 and a path's cost by that a
+# step; and a value depends on neither the column block's width nor the grid.
+@pytest.mark.parametrize("norm", ["path", "none"])
+@pytest.mark.parametrize("lens", [[1], [64], [63, 1], [1, 62, 2, 3], [31, 33, 32], [5, 6, 7, 8, 9]],
+                         ids=lambda v: "-".join(map(str, v)))
+def test_fused_unit_edges(lens, norm):
+    import paper_2505_02692_amd as fx
+    from test_gpu_parity import ctx
+    rng = np.random.default_rng(11)
+    n_of = [3, 65, 150] if lens == [1] else [3, 29, 41]
+    length = np.concatenate([np.resize(lens, n) for n in n_of])
+    off = np.concatenate([[0], np.cumsum(length)]).astype(np.int64)
+    attrs = np.concatenate([np.stack([rng.permutation(np.arange(n) % 2), np.full(n, g)], 1)
+                            for g, n in enumerate(n_of)]).astype(np.int32)
+    feats = torch.from_numpy(rng.standard_normal((int(off[-1]), 70), dtype=np.float32))
+    print(f"[case] unit edges {lens} {norm}", flush=True)
+    ds = fx.Dataset(ctx(), feats.cuda().contiguous(), off, attrs)
+    res = [fx.Task(ds, 0, [1]).score(norm=norm, keep_pairs=True, fused_cols=c, fused_blocks_per_cu=b)
+           for c, b in ((128, 4), (256, 2), (128, 1))]
+    orc = oracle.score(feats.numpy(), off, attrs, 0, [1], [], "dtw", norm)
+    xs, ys, want = all_oracle_pairs(orc)
+    got = [r.pairs(xs, ys) for r in res]
+    for r, (a, fl, _) in zip(res, got):
+        assert np.array_equal(r.half_units, orc.half_units)
+        assert np.array_equal(a, got[0][0]) and np.array_equal(fl & 1, got[0][1] & 1)
+    sure = (got[0][1] & 1) == 0
+    steps = length[xs] + length[ys] - 1
+    tol = 0.002 * (steps if norm == "none" else 1)
+    assert (np.abs(got[0][0] - want) <= tol)[sure].all()

@@ -142,18 +142,21 @@ __device__ __forceinline__ Span span_of(const Cols<kC> &cols, int w, int skip, i
 }
 
 // The pairs (row item i, column item j) of the wave's span that the unit writes,
-// in turn over its lanes: fn(i, j, x, y) with the items' places x <= y in their
-// group; place_r, place_c: those of the blocks' first items.
+// in turn over its lanes: those whose row item comes no later in the packing order.
+// fn(i, j, x, y, same) with the items' places x, y in their group, whose first
+// task item is item0; r_item0, c_item0: the blocks' first positions; order: the
+// task item at each position (null: the position).
 template <int kC, typename Fn>
-__device__ __forceinline__ void for_pairs(const Cols<kC> &cols, const Span &span, int r_nitems, int64_t place_r,
-                                          int64_t place_c, Fn &&fn) {
+__device__ __forceinline__ void for_pairs(const Cols<kC> &cols, const Span &span, int r_nitems, int r_item0,
+                                          int c_item0, int64_t item0, const int32_t *__restrict__ order, Fn &&fn) {
     const int j0 = cols.items_before(span.begin), nj = cols.items_before(span.end) - j0;
     // (exact: at most 64 x 256 pairs, and the half keeps the quotient 1 / 512 away
     // from a whole number)
     const float inv = __builtin_amdgcn_rcpf(float(nj));
     for (int k = threadIdx.x % kWave; k < r_nitems * nj; k += kWave) {
         const int i = int((float(k) + 0.5f) * inv), j = j0 + k - i * nj;
-        if (place_r + i <= place_c + j) fn(i, j, place_r + i, place_c + j);
+        const int pr = r_item0 + i, pc = c_item0 + j;
+        if (pr <= pc) fn(i, j, (order ? order[pr] : pr) - item0, (order ? order[pc] : pc) - item0, pr == pc);
     }
 }
 

@@ -219,8 +219,9 @@ static_assert(sizeof(CellDev) == 32, "CellDev layout");
 struct TableLayout {
     size_t item_src = 0, item_len = 0, item_dst = 0, item_group = 0;
     std::array<size_t, 5> g{};  // item0, n_items (+ sentinel), frame0, n_frames, pair_base (+ total)
-    size_t cells = 0, units = 0, rb = 0, g_rb0 = 0;
-    std::array<size_t, 5> plan{};  // cb, unit_prefix, g_cb0, rb_cstart, band_rb of `plan_cols`
+    size_t cells = 0, units = 0, rb = 0;
+    std::array<size_t, 3> pack{};  // pack_item, pack_len, pack_dst (if the task has a packing order)
+    std::array<size_t, 6> plan{};  // cb, unit_prefix, g_cb0, rb_cstart, band_rb, rb of `plan_cols`
     int plan_cols = 0;             // 0: no column plan in the buffer
 };
 
@@ -228,10 +229,12 @@ struct TaskDevice {
     DevBuf blob;
     const int64_t *item_src = nullptr, *item_dst = nullptr;
     const int32_t *item_len = nullptr, *item_group = nullptr;
+    const int32_t *pack_item = nullptr, *pack_len = nullptr;
+    const int64_t *pack_dst = nullptr;
     const int64_t *g_item0 = nullptr, *g_n = nullptr, *g_frame0 = nullptr, *g_nframes = nullptr,
                   *g_pair_base = nullptr;
     const CellDev *cells = nullptr;
-    const int32_t *units = nullptr, *rb = nullptr, *g_rb0 = nullptr;
+    const int32_t *units = nullptr, *rb = nullptr;
     bool uploaded = false;
 };
 
@@ -263,7 +266,8 @@ struct ResultImpl;
 //    block) and cells are used.
 struct ColPlan {
     int cols = 0;
-    hvec<int32_t> cb;                    // [n_cb][4] = group, first item (task), n items, n frames
+    hvec<int32_t> cb;                    // [n_cb][4] = group, first item (packing order), n items, n frames
+    hvec<int32_t> rb;                    // stream kernel of a task with a packing order: row blocks in task order
     std::vector<int32_t> g_cb0, g_ncb;   // per group: first column block, count
     // Work units: the (row block, column block) pairs of a group whose column
     // block ends after the row block's first item.  A group's pair matrix is
@@ -285,7 +289,7 @@ struct ColPlan {
     int64_t cells = 0;                   // frame pairs the kept units cover (stream kernel: lanes x
                                          // stream columns, 64 per column)
     DevBuf dev;                          // device copy of the above, made on first use
-    const int32_t *d_cb = nullptr, *d_g_cb0 = nullptr, *d_rb_cstart = nullptr, *d_band_rb = nullptr;
+    const int32_t *d_cb = nullptr, *d_g_cb0 = nullptr, *d_rb_cstart = nullptr, *d_band_rb = nullptr, *d_rb = nullptr;
     const int64_t *d_unit_prefix = nullptr;
 };
 
@@ -304,6 +308,12 @@ struct TaskImpl {
     hvec<int32_t> item_group;
     hvec<int64_t> item_pos_of;  // original id -> task position, -1 if absent
 
+    // Order in which the fused DTW kernels take the items of each group (empty:
+    // task order): the task item at each position, its frames and first packed frame.
+    // Chosen so that row blocks are nearly full (plan_order, task.cpp).
+    hvec<int32_t> pack_item, pack_len;
+    hvec<int64_t> pack_dst;
+
     hvec<Group> groups;
     hvec<CellDev> cells;
     hvec<int64_t> n_triplets;
@@ -319,7 +329,7 @@ struct TaskImpl {
                              // (one x each, large cells) from sorted rows
     int64_t n_units_small = 0;
     int64_t sum_nx = 0;             // sum over cells of |X|
-    hvec<int32_t> rb;               // fused kernel row blocks [n][4] (<= 64 frames)
+    hvec<int32_t> rb;               // fused kernel row blocks [n][4] (<= 64 frames, in packing order)
     std::vector<int64_t> long_slots;  // unordered pairs x | y << 32 with an item of more than 64 frames (FP64 kernel)
     std::vector<int32_t> g_rb0, g_nrb;
     std::vector<std::unique_ptr<ColPlan>> col_plans;  // by column block width, made on demand

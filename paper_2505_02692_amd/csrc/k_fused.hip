@@ -238,6 +238,7 @@ __global__ __launch_bounds__(256, kC == 128 ? 4 : 2) void k_fused(const uint16_t
                                                   const int64_t *__restrict__ g_pair_base,
                                                   const int32_t *__restrict__ item_len,
                                                   const int64_t *__restrict__ item_dst,
+                                                  const int32_t *__restrict__ order,
                                                   const int32_t *__restrict__ rb,
                                                   const int32_t *__restrict__ cb,
                                                   const int64_t *__restrict__ unit_prefix,
@@ -575,15 +576,15 @@ __global__ __launch_bounds__(256, kC == 128 ? 4 : 2) void k_fused(const uint16_t
     else
         run(std::false_type{});
     // 4. The pairs of the wave's columns.  Pair (x, y) of the group, x the row item,
-    // is kept when x comes before y (or is y) and written at (x, y) and (y, x), the
+    // is kept when x is packed before y (or is y) and written at (x, y) and (y, x), the
     // distance being symmetric (a pair whose path length is ambiguous is flagged in
     // both slots and recomputed in FP64 in each orientation).  Each slot has one
     // writer: the pairs with x after y are written by the unit holding (y, x).  A lane
     // per pair, after the sweep: written by the lane that ended it, at its step, a
     // pair cost a few dozen instructions with most of the wave idle.
     __builtin_amdgcn_wave_barrier();
-    unit::for_pairs<kC>(cols, span, r_nitems, r_item0 - gitem0, c_item0 - gitem0,
-                        [&](int i, int j, int64_t px, int64_t py) {
+    unit::for_pairs<kC>(cols, span, r_nitems, r_item0, c_item0, gitem0, order,
+                        [&](int i, int j, int64_t px, int64_t py, bool same) {
         const int r = items_s.row_last[i], col = items_s.col_last[j];
         const float stored = dt[r * kDStride + col];
         float v = fabsf(stored);
@@ -596,12 +597,12 @@ __global__ __launch_bounds__(256, kC == 128 ? 4 : 2) void k_fused(const uint16_t
             v *= __builtin_amdgcn_rcpf(float(lmin));
             fl = lmin == lmax ? 0 : 1;
         }
-        if (near_s != 0 && signbit(stored) && px != py) fl = 1;  // a near pair; (x, x) is never compared
+        if (near_s != 0 && signbit(stored) && !same) fl = 1;  // a near pair; (x, x) is never compared
         const int64_t slot = pbase + px * gn + py, mirror = pbase + py * gn + px;
-        if (fl) atomicAdd(nonrobust_n, px < py ? 2u : 1u);
+        if (fl) atomicAdd(nonrobust_n, same ? 1u : 2u);
         p32[slot] = v;
         flags[slot] = fl;
-        if (px < py) {
+        if (!same) {
             p32[mirror] = v;
             flags[mirror] = fl;
         }
@@ -693,7 +694,7 @@ void launch_fused(hipStream_t s, const uint16_t *xn, const float *rinv, int dim_
     const dim3 grid(unsigned(8 * per_xcd)), block(256);
     auto go = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, grid, block, 0, s, xn, rinv, dim_pad, g.item0, g.n_items, g.pair_base, it.len,
-                           it.dst, plan.rb, plan.cb, plan.unit_prefix, plan.band_rb, plan.g_cb0, plan.rb_cstart,
+                           it.dst, it.order, plan.rb, plan.cb, plan.unit_prefix, plan.band_rb, plan.g_cb0, plan.rb_cstart,
                            plan.n_bands, plan.n_units, q, delta, p32, flags, nonrobust_n, unit_ctr, flen, scale);
     };
     const bool path = norm == FABX_NORM_PATH;

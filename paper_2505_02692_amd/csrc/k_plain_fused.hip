@@ -180,7 +180,8 @@ __global__ __launch_bounds__(256, 4) void k_plain_fused(const void *__restrict__
                                                         const int64_t *__restrict__ g_n,
                                                         const int64_t *__restrict__ g_pair_base,
                                                         const int32_t *__restrict__ item_len,
-                                                        const int64_t *__restrict__ item_dst, FusedPlan plan,
+                                                        const int64_t *__restrict__ item_dst,
+                                                        const int32_t *__restrict__ order, FusedPlan plan,
                                                         int64_t grid_q, float *__restrict__ p32) {
     constexpr int kStage = kKind == kAngular ? (kRows + kCols) * kStageLd
                            : kKind == kEuclid ? kKe * (kRowLd + kColLd)
@@ -351,8 +352,8 @@ __global__ __launch_bounds__(256, 4) void k_plain_fused(const void *__restrict__
         auto write = [&](auto mode_tag) {
             constexpr int mode = decltype(mode_tag)::value;
             __builtin_amdgcn_wave_barrier();
-            unit::for_pairs<kCols>(cols, span, r_nitems, r_item0 - gitem0, c_item0 - gitem0,
-                                   [&](int i, int j, int64_t px, int64_t py) {
+            unit::for_pairs<kCols>(cols, span, r_nitems, r_item0, c_item0, gitem0, order,
+                                   [&](int i, int j, int64_t px, int64_t py, bool same) {
                 const int r = items_s.row_last[i], col = items_s.col_last[j];
                 const float cost = dt[r * kDStride + col];
                 uint32_t len = 0;
@@ -370,7 +371,7 @@ __global__ __launch_bounds__(256, 4) void k_plain_fused(const void *__restrict__
                     return cost / float(n);
                 };
                 if (mode != kYX) p32[pbase + px * gn + py] = quotient(len & 0xFFFFu);
-                if (mode != kXY && px < py) p32[pbase + py * gn + px] = quotient(len >> 16);
+                if (mode != kXY && !same) p32[pbase + py * gn + px] = quotient(len >> 16);
             });
         };
         auto sweep_and_write = [&](auto mode_tag) {
@@ -404,7 +405,7 @@ void plain_fused(hipStream_t s, const void *packed, int dim_pad, const GroupTabl
     const dim3 grid(unsigned(8 * std::min<int64_t>(q, dev::kMaxBlocks / 8))), block(256);
     auto go = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, grid, block, 0, s, packed, dim_pad, g.item0, g.n_items, g.pair_base, it.len, it.dst,
-                           plan, q, p32);
+                           it.order, plan, q, p32);
     };
     const bool path = norm == FABX_NORM_PATH;
     if (distance == FABX_DISTANCE_UNITS)

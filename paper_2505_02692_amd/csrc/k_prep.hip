@@ -1,7 +1,8 @@
 // Frame normalisation and time pooling.
 //
 // The angular distance only depends on directions, so every frame is scaled
-// to unit length once and packed in task order (frames of a BY group are
+// to unit length once and packed in task order or, for the fused DTW kernels, in
+// the task's packing order (either way the frames of a BY group are
 // contiguous, row stride padded to a multiple of 64 with zeros) so that a
 // group's frame-distance matrix is one dense Gram product.  For the Euclidean
 // distance the frames (or means) are packed the same way, unscaled.
@@ -113,14 +114,16 @@ __global__ __launch_bounds__(256) void k_normalize(const Tin *__restrict__ src, 
                                                    const int64_t *__restrict__ item_src,
                                                    const int32_t *__restrict__ item_len,
                                                    const int64_t *__restrict__ item_dst,
+                                                   const int32_t *__restrict__ order,
                                                    void *out, int out_form, float *rinv, int *err,
                                                    int64_t n_items, unsigned long long *err_item,
                                                    float *len_out, unsigned int *scale) {
     const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
     float lmax = 0.0f;  // kUnitBF16Len: the largest row length this thread saw
-    for (int64_t item = blockIdx.x; item < n_items; item += gridDim.x) {
-    const int L = item_len[item];
-    const int64_t s0 = item_src[item], d0 = item_dst[item];
+    for (int64_t q = blockIdx.x; q < n_items; q += gridDim.x) {
+    const int64_t item = order ? int64_t(order[q]) : q;
+    const int L = item_len[q];
+    const int64_t s0 = item_src[item], d0 = item_dst[q];
     // two frames per wave in flight (t and t + 4) to keep more loads outstanding
     for (int t = wave; t < L; t += 8) {
         const bool two = t + 4 < L;
@@ -224,11 +227,12 @@ __global__ __launch_bounds__(256) void k_pool_normalize(const Tin *__restrict__ 
 __global__ __launch_bounds__(256) void k_pack_units(const int32_t *__restrict__ src,
                                                     const int64_t *__restrict__ item_src,
                                                     const int32_t *__restrict__ item_len,
-                                                    const int64_t *__restrict__ item_dst, int64_t n_items,
+                                                    const int64_t *__restrict__ item_dst,
+                                                    const int32_t *__restrict__ order, int64_t n_items,
                                                     int32_t *__restrict__ out) {
-    for (int64_t item = blockIdx.x; item < n_items; item += gridDim.x) {
-        const int L = item_len[item];
-        const int64_t s0 = item_src[item], d0 = item_dst[item];
+    for (int64_t q = blockIdx.x; q < n_items; q += gridDim.x) {
+        const int L = item_len[q];
+        const int64_t s0 = item_src[order ? order[q] : q], d0 = item_dst[q];
         for (int f = threadIdx.x; f < L; f += blockDim.x) out[d0 + f] = src[s0 + f];
     }
 }
@@ -295,11 +299,12 @@ void launch_norm(hipStream_t s, const void *features, int dtype, int dim, int di
         if (dtype == FABX_DTYPE_F32)
             hipLaunchKernelGGL((k_normalize<float, kChunks>), grid, dim3(256), 0, s,
                                static_cast<const float *>(features), dim, dim_pad, it.src, it.len,
-                               it.dst, out, out_form, rinv, err, it.n_items, err_item, len_out, scale);
+                               it.dst, it.order, out, out_form, rinv, err, it.n_items, err_item, len_out, scale);
         else
             hipLaunchKernelGGL((k_normalize<uint16_t, kChunks>), grid, dim3(256), 0, s,
                                static_cast<const uint16_t *>(features), dim, dim_pad, it.src,
-                               it.len, it.dst, out, out_form, rinv, err, it.n_items, err_item, len_out, scale);
+                               it.len, it.dst, it.order, out, out_form, rinv, err, it.n_items, err_item, len_out,
+                               scale);
     }
     FABX_HIP(hipGetLastError());
 }
@@ -351,7 +356,7 @@ void probe_stream(hipStream_t s, const float *src, int dim, int64_t n_rows, uint
 void pack_units(hipStream_t s, const int32_t *codes, const ItemTables &it, int32_t *out) {
     if (it.n_items <= 0) return;
     hipLaunchKernelGGL(k_pack_units, dim3(grid_for(it.n_items, 1)), dim3(256), 0, s, codes, it.src, it.len,
-                       it.dst, it.n_items, out);
+                       it.dst, it.order, it.n_items, out);
     FABX_HIP(hipGetLastError());
 }
 

@@ -20,12 +20,14 @@ inline unsigned grid_for(int64_t work, int64_t per_block, int64_t cap = int64_t(
     return unsigned(b);
 }
 
-// Per-item task tables on the device.
+// Per-item task tables on the device, in task order or in the fused kernels'
+// packing order.
 struct ItemTables {
     const int64_t *src;    // first source frame of each task item
-    const int32_t *len;    // frames per item
-    const int64_t *dst;    // first packed frame
+    const int32_t *len;    // frames of the item at each position
+    const int64_t *dst;    // its first packed frame
     int64_t n_items;
+    const int32_t *order;  // the task item at each position; null: the position itself
 };
 
 // Per-group tables on the device (n_groups entries; *_prefix arrays have n_groups + 1).
@@ -104,7 +106,7 @@ void unit_mismatch(hipStream_t s, const int32_t *codes, const GramSegments &seg,
 
 // --- k_fused.hip (BF16 form)
 struct FusedPlan {
-    const int32_t *rb;        // row blocks: [n_rb][4] = group, first item (task), n items, n frames
+    const int32_t *rb;        // row blocks: [n_rb][4] = group, first item (position), n items, n frames
     const int32_t *cb;        // col blocks: same layout
     const int64_t *unit_prefix; // per band: prefix of its work units, n_bands + 1
     const int32_t *band_rb;     // band b = row blocks [band_rb[b], band_rb[b + 1]) of one group

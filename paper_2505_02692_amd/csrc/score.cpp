@@ -79,9 +79,19 @@ struct Packer {
     }
 };
 
-// Host side of the task tables: adds them (and `plan`, if any) to `pk`; the
-// group columns are built in `gcols`, which must live until the copy is made.
-TableLayout add_task_tables(const TaskImpl &t, const ColPlan *plan, Packer &pk,
+std::array<size_t, 3> add_order(const TaskImpl &t, Packer &pk) {
+    return {pk.add(t.pack_item), pk.add(t.pack_len), pk.add(t.pack_dst)};
+}
+
+std::array<size_t, 6> add_col_plan(const ColPlan &cp, Packer &pk) {
+    return {pk.add(cp.cb),        pk.add(cp.unit_prefix), pk.add(cp.g_cb0),
+            pk.add(cp.rb_cstart), pk.add(cp.band_rb),     cp.rb.empty() ? 0 : pk.add(cp.rb)};
+}
+
+// Host side of the task tables: adds them (and the packing order and `plan`, if
+// any) to `pk`; the group columns are built in `gcols`, which must live until the
+// copy is made.
+TableLayout add_task_tables(const TaskImpl &t, const ColPlan *plan, bool with_order, Packer &pk,
                             std::array<std::vector<int64_t>, 5> &gcols) {
     const size_t G = t.groups.size();
     for (auto &v : gcols) v.resize(G);
@@ -106,21 +116,21 @@ TableLayout add_task_tables(const TaskImpl &t, const ColPlan *plan, Packer &pk,
     L.cells = pk.add(t.cells);
     L.units = pk.add(t.units);
     L.rb = pk.add(t.rb);
-    L.g_rb0 = pk.add(t.g_rb0);
+    if (with_order) L.pack = add_order(t, pk);
     if (plan) {
-        L.plan = {pk.add(plan->cb), pk.add(plan->unit_prefix), pk.add(plan->g_cb0), pk.add(plan->rb_cstart),
-                  pk.add(plan->band_rb)};
+        L.plan = add_col_plan(*plan, pk);
         L.plan_cols = plan->cols;
     }
     return L;
 }
 
-void set_col_plan(ColPlan &cp, const DevBuf &buf, const std::array<size_t, 5> &o) {
+void set_col_plan(ColPlan &cp, const DevBuf &buf, const std::array<size_t, 6> &o) {
     cp.d_cb = Packer::at<int32_t>(buf, o[0]);
     cp.d_unit_prefix = Packer::at<int64_t>(buf, o[1]);
     cp.d_g_cb0 = Packer::at<int32_t>(buf, o[2]);
     cp.d_rb_cstart = Packer::at<int32_t>(buf, o[3]);
     cp.d_band_rb = Packer::at<int32_t>(buf, o[4]);
+    if (!cp.rb.empty()) cp.d_rb = Packer::at<int32_t>(buf, o[5]);
 }
 
 // Device pointers of the task tables in dv.blob (and of the column plan packed
@@ -139,7 +149,11 @@ void set_task_tables(TaskImpl &t, const TableLayout &L) {
     dv.cells = Packer::at<CellDev>(dv.blob, L.cells);
     dv.units = Packer::at<int32_t>(dv.blob, L.units);
     dv.rb = Packer::at<int32_t>(dv.blob, L.rb);
-    dv.g_rb0 = Packer::at<int32_t>(dv.blob, L.g_rb0);
+    if (!t.pack_item.empty()) {
+        dv.pack_item = Packer::at<int32_t>(dv.blob, L.pack[0]);
+        dv.pack_len = Packer::at<int32_t>(dv.blob, L.pack[1]);
+        dv.pack_dst = Packer::at<int64_t>(dv.blob, L.pack[2]);
+    }
     if (L.plan_cols)
         for (auto &cp : t.col_plans)
             if (cp->cols == L.plan_cols && !cp->d_cb) set_col_plan(*cp, dv.blob, L.plan);
@@ -380,7 +394,7 @@ void prepack_tables(TaskImpl &t) {
     Packer pk;
     std::array<std::vector<int64_t>, 5> gcols;
     const ColPlan *plan = t.col_plans.empty() ? nullptr : t.col_plans.front().get();
-    const TableLayout L = add_task_tables(t, plan, pk, gcols);
+    const TableLayout L = add_task_tables(t, plan, !t.pack_item.empty(), pk, gcols);
     if (pk.total > kPrepackMaxBytes || ctx->pinned.packed_bytes.load() + pk.total > kPrepackBudget) return;
     FABX_HIP(hipSetDevice(ctx->device));
     std::unique_ptr<PinnedBlock> blk;
@@ -405,6 +419,7 @@ namespace {
 // the fused kernel, the plan of the pooled / plain kernels, and the workspace.
 struct DevPtrs {
     kern::ItemTables it{};
+    kern::ItemTables pack{};                    // in the packing order (the same as `it` when there is none)
     kern::GroupTables gt{};
     const CellDev *cells = nullptr;
     const int32_t *units = nullptr, *rb = nullptr, *item_group = nullptr;
@@ -504,7 +519,7 @@ void enqueue_score(const TaskImpl &t, const ScoreParams &p, const FusedConfig &f
     const DatasetImpl &ds = *t.ds;
     const bool bf16 = p.precision == FABX_PREC_BF16_RECHECK;
     const bool dtw = p.mode == FABX_MODE_DTW;
-    const bool plain_strips = needs_strips(t, p);
+    const bool plain_strips = !strips.group.empty();
     const int dim = ds.dim;
     const int dim_pad = int(round_up(dim, 64));
     const int64_t n_cells = int64_t(t.cells.size());
@@ -512,6 +527,10 @@ void enqueue_score(const TaskImpl &t, const ScoreParams &p, const FusedConfig &f
     const int64_t G = int64_t(t.groups.size());
     const kern::ItemTables &it = d.it;
     const kern::GroupTables &gt = d.gt;
+    // frames are packed as the DTW kernel takes the items: task order for the strips
+    // and the stream kernel, else the packing order
+    const bool stream_k = dtw && bf16 && fcfg.cols >= kStreamMinCols;
+    const kern::ItemTables &packed = plain_strips || stream_k ? d.it : d.pack;
     char *counters = reinterpret_cast<char *>(d.half_units) + size_t(n_cells) * 8;
     int *err = reinterpret_cast<int *>(counters);
     unsigned long long *err_item = reinterpret_cast<unsigned long long *>(counters + 8);
@@ -533,9 +552,9 @@ void enqueue_score(const TaskImpl &t, const ScoreParams &p, const FusedConfig &f
     const int out_form = bf16 ? (euclid ? 3 : 1) : euclid ? 2 : 0;
     const bool units = p.distance == FABX_DISTANCE_UNITS;
     if (units)
-        kern::pack_units(stream, static_cast<const int32_t *>(ds.features), it, static_cast<int32_t *>(d.xn));
+        kern::pack_units(stream, static_cast<const int32_t *>(ds.features), packed, static_cast<int32_t *>(d.xn));
     else if (dtw)
-        kern::normalize(stream, ds.features, ds.dtype, dim, dim_pad, it, d.xn, out_form, d.rinv, err, err_item,
+        kern::normalize(stream, ds.features, ds.dtype, dim, dim_pad, packed, d.xn, out_form, d.rinv, err, err_item,
                         flen, scale);
     else
         kern::pool_normalize(stream, ds.features, ds.dtype, dim, dim_pad, it, d.xn, out_form, d.rinv, err,
@@ -548,7 +567,7 @@ void enqueue_score(const TaskImpl &t, const ScoreParams &p, const FusedConfig &f
                                fcfg.blocks_per_cu, ds.ctx->n_cu};
     };
     if (dtw && !bf16 && !plain_strips) {
-        kern::plain_fused(stream, d.xn, dim_pad, gt, it, fused_plan(), p.distance, p.dtw_norm, d.p32);
+        kern::plain_fused(stream, d.xn, dim_pad, gt, packed, fused_plan(), p.distance, p.dtw_norm, d.p32);
         st.computed_dtw_cells = cplan->cells;
     } else if (plain_strips) {
         // one batch of strips at a time through the distance buffer (stream order
@@ -568,16 +587,16 @@ void enqueue_score(const TaskImpl &t, const ScoreParams &p, const FusedConfig &f
             kern::dtw_plain(stream, d.dmat, ps, gt, it, p.dtw_norm, t.max_len > kFusedRowFrames, units, d.p32);
         }
         st.computed_dtw_cells = t.n_dmat;
-    } else if (dtw && fcfg.cols >= kStreamMinCols) {
+    } else if (stream_k) {
         kern::frame_info(stream, it, d.item_group, gt.item0, d.finfo);
-        const kern::StreamPlan sp{d.rb, d.unit_prefix, int64_t(t.rb.size() / 4), cplan->unit_prefix.back(),
+        const kern::StreamPlan sp{d.rb, d.unit_prefix, int64_t(cplan->unit_prefix.size()) - 1, cplan->unit_prefix.back(),
                                   fcfg.cols, fcfg.blocks_per_cu, ds.ctx->n_cu};
         const uint32_t delta_q = uint32_t(std::ceil(p.delta * 65535.0));
         kern::stream_bf16(stream, static_cast<const uint16_t *>(d.xn), d.rinv, dim_pad, d.finfo, gt, it, sp,
                           p.dtw_norm, delta_q, d.p32, d.flags, nonrobust_n, unit_ctr);
         st.computed_dtw_cells = cplan->cells;
     } else if (dtw) {
-        kern::fused_bf16(stream, static_cast<const uint16_t *>(d.xn), d.rinv, dim_pad, gt, it, fused_plan(),
+        kern::fused_bf16(stream, static_cast<const uint16_t *>(d.xn), d.rinv, dim_pad, gt, packed, fused_plan(),
                          p.dtw_norm, float(p.delta), d.p32, d.flags, nonrobust_n, unit_ctr, flen, scale);
         // pairs with an item over 64 frames: FP64 from the raw features
         kern::long_dtw(stream, ds.features, ds.dtype, dim, gt, it, d.item_group, d.long_slots,
@@ -746,7 +765,8 @@ std::shared_ptr<ResultImpl> launch_score(const std::shared_ptr<TaskImpl> &tp, co
         } else {
             Packer pk;
             std::array<std::vector<int64_t>, 5> gcols;
-            const TableLayout L = add_task_tables(t, cplan && !cplan->d_cb ? cplan : nullptr, pk, gcols);
+            const TableLayout L = add_task_tables(t, cplan && !cplan->d_cb ? cplan : nullptr,
+                                                  !t.pack_item.empty(), pk, gcols);
             pk.upload(dv.blob, ds.ctx->staging, ds.ctx->copy_stream, stream);
             set_task_tables(t, L);
         }
@@ -754,8 +774,7 @@ std::shared_ptr<ResultImpl> launch_score(const std::shared_ptr<TaskImpl> &tp, co
     }
     if (cplan && !cplan->d_cb) {  // another column width for an already uploaded task
         Packer pc;
-        const std::array<size_t, 5> o{pc.add(cplan->cb), pc.add(cplan->unit_prefix), pc.add(cplan->g_cb0),
-                                      pc.add(cplan->rb_cstart), pc.add(cplan->band_rb)};
+        const std::array<size_t, 6> o = add_col_plan(*cplan, pc);
         cplan->dev.pool = pool;
         pc.upload(cplan->dev, ds.ctx->staging, ds.ctx->copy_stream, stream);
         set_col_plan(*cplan, cplan->dev, o);
@@ -790,7 +809,9 @@ std::shared_ptr<ResultImpl> launch_score(const std::shared_ptr<TaskImpl> &tp, co
     pend->host_bytes = size_t(n_cells) * 8 + kern::kCounterBytes;
     pend->host = ds.ctx->pinned.get(pend->host_bytes, &pend->host_bytes);
 
-    d.it = kern::ItemTables{dv.item_src, dv.item_len, dv.item_dst, n_items};
+    d.it = kern::ItemTables{dv.item_src, dv.item_len, dv.item_dst, n_items, nullptr};
+    d.pack = t.pack_item.empty() ? d.it
+                                 : kern::ItemTables{dv.item_src, dv.pack_len, dv.pack_dst, n_items, dv.pack_item};
     d.gt = kern::GroupTables{dv.g_item0, dv.g_n, dv.g_frame0, dv.g_nframes, dv.g_pair_base, G, t.n_pair_slots};
     d.cells = dv.cells;
     d.units = dv.units;
@@ -802,6 +823,7 @@ std::shared_ptr<ResultImpl> launch_score(const std::shared_ptr<TaskImpl> &tp, co
         d.rb_cstart = cplan->d_rb_cstart;
         d.unit_prefix = cplan->d_unit_prefix;
         d.band_rb = cplan->d_band_rb;
+        if (!cplan->rb.empty()) d.rb = cplan->d_rb;
     }
     d.xn = ws.xn.ptr;
     d.rinv = ws.rinv.as<float>();
@@ -916,14 +938,21 @@ void score_in_scratch(TaskImpl &t, const ScoreParams &p, char *base, size_t cap,
         fcfg = Tuner::default_config();
         cplan = &col_plan(t, fcfg.cols);
     }
+    bool use_strips = needs_strips(t, p);
     const std::vector<int64_t> tiles = dtw ? std::vector<int64_t>() : tile_prefix(t, p);
     const bool stream_k = cplan && fcfg.cols >= kStreamMinCols;
     // Layout in the scratch buffer: tables (task, column plan, plan), then the
     // workspace.  The plain DTW form's distance buffer takes what is left, at
     // most its usual size; its strips are planned for that size.
+    // The packing order is only read until the distances are there: it lies in the
+    // memory of the recheck list, which is written after them, if there is one.
+    const bool order = cplan && !stream_k && !t.pack_item.empty();
+    Packer pk_order;
+    const std::array<size_t, 3> order_at = order ? add_order(t, pk_order) : std::array<size_t, 3>{};
+    const bool order_in_list = order && bf16 && pk_order.total <= size_t(t.n_pair_slots) * 8;
     auto layout = [&](const PlainPlan &strips, Packer &pk, TableLayout &tl, PlanLayout &pl,
                       std::array<std::vector<int64_t>, 5> &gcols) {
-        tl = add_task_tables(t, cplan, pk, gcols);
+        tl = add_task_tables(t, cplan, order && !use_strips && !order_in_list, pk, gcols);
         static const std::vector<int64_t> no_slots;  // the packer keeps pointers: no temporaries
         pl = add_plan(pk, tiles, strips, dtw && bf16 ? t.long_slots : no_slots);
         const size_t tables = (pk.total + 255) & ~size_t(255);
@@ -934,7 +963,17 @@ void score_in_scratch(TaskImpl &t, const ScoreParams &p, char *base, size_t cap,
     PlanLayout pl;
     std::array<std::vector<int64_t>, 5> gcols;
     PlainPlan strips;
-    if (needs_strips(t, p)) {
+    if (dtw && !bf16 && !use_strips) {
+        // the plain form's fused kernel has larger tables than a distance buffer of the
+        // least size: a task of very many small items that fills the scratch takes strips
+        Packer probe;
+        std::array<std::vector<int64_t>, 5> gc2;
+        if (layout(strips, probe, tl, pl, gc2) > cap) {
+            use_strips = true;
+            cplan = nullptr;
+        }
+    }
+    if (use_strips) {
         strips = plain_plan(t, plain_dmat_cells());
         Packer probe;
         std::array<std::vector<int64_t>, 5> gc2;
@@ -959,7 +998,7 @@ void score_in_scratch(TaskImpl &t, const ScoreParams &p, char *base, size_t cap,
     auto at = [&](size_t off) { return base + off; };
     d.it = kern::ItemTables{reinterpret_cast<const int64_t *>(at(tl.item_src)),
                             reinterpret_cast<const int32_t *>(at(tl.item_len)),
-                            reinterpret_cast<const int64_t *>(at(tl.item_dst)), int64_t(t.items.size())};
+                            reinterpret_cast<const int64_t *>(at(tl.item_dst)), int64_t(t.items.size()), nullptr};
     d.gt = kern::GroupTables{reinterpret_cast<const int64_t *>(at(tl.g[0])),
                              reinterpret_cast<const int64_t *>(at(tl.g[1])),
                              reinterpret_cast<const int64_t *>(at(tl.g[2])),
@@ -976,6 +1015,7 @@ void score_in_scratch(TaskImpl &t, const ScoreParams &p, char *base, size_t cap,
         d.g_cb0 = reinterpret_cast<const int32_t *>(at(tl.plan[2]));
         d.rb_cstart = reinterpret_cast<const int32_t *>(at(tl.plan[3]));
         d.band_rb = reinterpret_cast<const int32_t *>(at(tl.plan[4]));
+        if (!cplan->rb.empty()) d.rb = reinterpret_cast<const int32_t *>(at(tl.plan[5]));
     }
     set_plan(d, base, pl);
     const WorkspaceSizes wz = workspace_sizes(t, p, strips, stream_k);
@@ -997,6 +1037,19 @@ void score_in_scratch(TaskImpl &t, const ScoreParams &p, char *base, size_t cap,
     d.half_units = reinterpret_cast<unsigned long long *>(take(wz.half_units));
     d.finfo = reinterpret_cast<uint32_t *>(take(wz.finfo));
     d.flen = reinterpret_cast<float *>(take(wz.flen));
+    d.pack = d.it;
+    std::vector<char> h_order(order_in_list ? pk_order.total : 0);
+    if (order && !use_strips) {
+        const char *b = order_in_list ? reinterpret_cast<const char *>(d.recheck_list) : base;
+        const std::array<size_t, 3> &o = order_in_list ? order_at : tl.pack;
+        d.pack = kern::ItemTables{d.it.src, reinterpret_cast<const int32_t *>(b + o[1]),
+                                  reinterpret_cast<const int64_t *>(b + o[2]), d.it.n_items,
+                                  reinterpret_cast<const int32_t *>(b + o[0])};
+        if (order_in_list) {
+            pk_order.copy_to(h_order.data());
+            FABX_HIP(hipMemcpyAsync(d.recheck_list, h_order.data(), pk_order.total, hipMemcpyHostToDevice, stream));
+        }
+    }
     st.workspace_bytes = int64_t(wz.total_aligned());
     std::vector<char> host(size_t(n_cells) * 8 + kern::kCounterBytes);
     try {
@@ -1031,6 +1084,7 @@ void release_device(TaskImpl &t) {
         cp->d_rb_cstart = nullptr;
         cp->d_unit_prefix = nullptr;
         cp->d_band_rb = nullptr;
+        cp->d_rb = nullptr;
     }
     t.packed.reset();
 }

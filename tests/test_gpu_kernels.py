@@ -203,3 +203,58 @@ def test_fused_unit_edges(lens, norm):
     steps = length[xs] + length[ys] - 1
     tol = 0.002 * (steps if norm == "none" else 1)
     assert (np.abs(got[0][0] - want) <= tol)[sure].all()
+
+
+# Tasks whose items are taken in the packing order (an item meets 12,000 frames or
+# more of its group; group sizes from one row block to several column blocks, one
+# group of two items) against the same scores in task order: the streaming kernel
+# for the BF16 form, FP64 oracle for the counts, and the score from the scratch
+# memory, where the order lies in the recheck list.  Pair values: as above.
+@pytest.mark.parametrize("kind", ["bf16", "euclidean", "fp32", "units"])
+@pytest.mark.parametrize("norm", ["path", "none"])
+def test_packing_order(kind, norm):
+    import paper_2505_02692_amd as fx
+    from test_gpu_parity import ctx
+    rng = np.random.default_rng(23)
+    n_of = [2, 9, 40, 77, 150]
+    length = rng.integers(1, 65, sum(n_of))
+    off = np.concatenate([[0], np.cumsum(length)]).astype(np.int64)
+    attrs = np.concatenate([np.stack([rng.permutation(np.arange(n) % 3), np.full(n, g)], 1)
+                            for g, n in enumerate(n_of)]).astype(np.int32)
+    meet = sum(length[attrs[:, 1] == g].sum() ** 2 for g in range(1, len(n_of))) / sum(n_of[1:])
+    assert meet > 12000
+    if kind == "units":
+        feats = torch.from_numpy(rng.integers(0, 5, int(off[-1])).astype(np.int32))
+        ref = torch.nn.functional.one_hot(feats.long(), 5).numpy().astype(np.float32)
+    else:
+        feats = torch.from_numpy(rng.standard_normal((int(off[-1]), 40), dtype=np.float32))
+        ref = feats.numpy()
+    opts = dict(norm=norm, precision="fp32" if kind == "fp32" else "bf16",
+                distance={"bf16": "angular", "fp32": "angular"}.get(kind, kind))
+    print(f"[case] packing order {kind} {norm}", flush=True)
+    ds = fx.Dataset(ctx(), feats.cuda().contiguous(), off, attrs)
+    t = fx.Task(ds, 0, [1])
+    res = t.score(keep_pairs=True, **opts)
+    scratch, _ = fx.fabx_score_noalloc(t.h, fx.make_opts(**opts), len(t))
+    assert np.array_equal(scratch, res.half_units)
+    if kind == "bf16":
+        assert np.array_equal(t.score(fused_cols=512, **opts).half_units, res.half_units)
+        assert np.array_equal(t.score(fused_cols=256, **opts).half_units, res.half_units)
+    if kind in ("bf16", "euclidean"):
+        orc = oracle.score(ref, off, attrs, 0, [1], [], "dtw", norm, distance=opts["distance"])
+        assert np.array_equal(res.half_units, orc.half_units)
+        if kind == "bf16":
+            xs, ys, want = all_oracle_pairs(orc)
+            got, fl, _ = res.pairs(xs, ys)
+            tol = 0.002 * (length[xs] + length[ys] - 1 if norm == "none" else 1)
+            assert (np.abs(got - want) <= tol)[(fl & 1) == 0].all()
+    else:
+        # a long item in a group of its own turns the task to the strip form in task order
+        extra = torch.ones((66 + 3,) + feats.shape[1:], dtype=feats.dtype)
+        off2 = np.concatenate([off, off[-1] + np.array([1, 67, 69])]).astype(np.int64)
+        attrs2 = np.concatenate([attrs, [[0, 9999], [0, 9999], [1, 9999]]]).astype(np.int32)
+        t2 = fx.Task(fx.Dataset(ctx(), torch.cat([feats, extra]).cuda().contiguous(), off2, attrs2), 0, [1])
+        strips = t2.score(keep_pairs=True, **opts)
+        xs, ys = np.nonzero((attrs[:, None, 1] == attrs[None, :, 1]) & (attrs[:, None, 1] > 0))
+        assert np.array_equal(res.pairs(xs, ys)[0], strips.pairs(xs, ys)[0])
+        assert np.array_equal(res.half_units, strips.half_units[:len(res.half_units)])

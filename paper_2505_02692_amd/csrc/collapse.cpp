@@ -8,8 +8,8 @@
 // one key.  Rows with equal keys are averaged (unweighted, summed in row
 // order): when the key space is small, through a direct table indexed by the
 // mixed-radix key (no sort; parts of the table's key range run in parallel),
-// otherwise after a stable radix sort of the bit-packed key.  The averaged
-// rows, in key order and with the ranks of the columns they keep, carry on to
+// otherwise after a stable radix sort of the bit-packed key, by buckets of its
+// top bits for many rows.  The averaged rows, in key order and with the ranks of the columns they keep, carry on to
 // the next level; the last rows are averaged flat.
 #include <algorithm>
 #include <numeric>
@@ -202,6 +202,73 @@ double collapse(const ResultImpl &res, const int32_t *level_attr, const int32_t 
                         carry(o, tab[k].first);
                         ++o;
                     }
+            });
+        } else if (total_bits <= 64 && m >= (size_t(1) << 15)) {
+            // Rows into buckets by the key's top bits, stably, then every bucket by
+            // itself: sorted stably by the other bits in cache, its runs of equal keys
+            // averaged in row order.  Buckets ascend with the key, so the rows come out
+            // as from one sort.  (1.77M cells: three passes of one sort over 21 MB and
+            // the averaging took 33 ms on one thread, this 8 ms on sixteen.)
+            const int top_bits = std::min(total_bits, 10), rest = total_bits - top_bits;
+            const size_t n_b = size_t(1) << top_bits, kRowChunk = size_t(1) << 14;
+            const size_t n_rc = (m + kRowChunk - 1) / kRowChunk;
+            hvec<uint64_t> key(m), key2(m);
+            hvec<uint32_t> row(m), row2(m);
+            std::vector<uint32_t> cnt(n_rc * n_b, 0);
+            hp.parallel_for(int(n_rc), [&](int c) {
+                uint32_t *h = cnt.data() + size_t(c) * n_b;
+                for (size_t i = size_t(c) * kRowChunk; i < std::min(m, size_t(c + 1) * kRowChunk); ++i) {
+                    uint64_t k = 0;
+                    for (size_t j = 0; j < nw; ++j) {
+                        const int b = t.key_bits[cols[kept_pos[j]]];
+                        if (b) k = (k << b) | C[i * w + kept_pos[j]];
+                    }
+                    key2[i] = k;
+                    ++h[k >> rest];
+                }
+            });
+            std::vector<size_t> bucket(n_b + 1);
+            size_t run = 0;
+            for (size_t b = 0; b < n_b; ++b) {
+                bucket[b] = run;
+                for (size_t c = 0; c < n_rc; ++c) {
+                    const uint32_t v = cnt[c * n_b + b];
+                    cnt[c * n_b + b] = uint32_t(run);
+                    run += v;
+                }
+            }
+            bucket[n_b] = run;
+            hp.parallel_for(int(n_rc), [&](int c) {
+                uint32_t *o = cnt.data() + size_t(c) * n_b;
+                for (size_t i = size_t(c) * kRowChunk; i < std::min(m, size_t(c + 1) * kRowChunk); ++i) {
+                    const uint32_t at = o[key2[i] >> rest]++;
+                    key[at] = key2[i];
+                    row[at] = uint32_t(i);
+                }
+            });
+            tr.mark("level.buckets");
+            std::vector<size_t> out(n_b + 1, 0);  // averaged rows per bucket, then their prefix
+            hp.parallel_for(int(n_b), [&](int b) {
+                const size_t i0 = bucket[size_t(b)], i1 = bucket[size_t(b) + 1];
+                sort_range(key.data() + i0, row.data() + i0, key2.data() + i0, row2.data() + i0, i1 - i0, rest);
+                size_t runs = 0;
+                for (size_t i = i0; i < i1; ++i) runs += i == i0 || key[i] != key[i - 1];
+                out[size_t(b) + 1] = runs;
+            });
+            tr.mark("level.sort");
+            for (size_t b = 0; b < n_b; ++b) out[b + 1] += out[b];
+            nscore.resize(out[n_b]);
+            ncur.resize(out[n_b] * nw);
+            hp.parallel_for(int(n_b), [&](int b) {
+                size_t o = out[size_t(b)];
+                for (size_t i = bucket[size_t(b)]; i < bucket[size_t(b) + 1];) {
+                    size_t j = i;
+                    double sacc = 0.0;
+                    while (j < bucket[size_t(b) + 1] && key[j] == key[i]) sacc += score[row[j++]];
+                    nscore[o] = sacc / double(j - i);
+                    carry(o++, row[i]);
+                    i = j;
+                }
             });
         } else {
             hvec<uint32_t> order(m);

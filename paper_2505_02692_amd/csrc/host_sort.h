@@ -32,6 +32,47 @@ void radix_sort_pairs(KeyVec &key, IdxVec &idx, int key_bits) {
     }
 }
 
+// Stable sort of n (key, idx) pairs by the keys' low `key_bits` bits, for ranges that
+// fit the caches: by insertion up to 32 pairs, else LSD radix with 8-bit digits
+// through the equally large k2, i2.  Allocates nothing.
+inline void sort_range(uint64_t *key, uint32_t *idx, uint64_t *k2, uint32_t *i2, size_t n, int key_bits) {
+    if (key_bits <= 0 || n < 2) return;
+    if (n <= 32) {
+        const uint64_t mask = ~uint64_t(0) >> (64 - key_bits);
+        for (size_t i = 1; i < n; ++i) {
+            const uint64_t k = key[i];
+            const uint32_t v = idx[i];
+            size_t j = i;
+            for (; j > 0 && (key[j - 1] & mask) > (k & mask); --j) {
+                key[j] = key[j - 1];
+                idx[j] = idx[j - 1];
+            }
+            key[j] = k;
+            idx[j] = v;
+        }
+        return;
+    }
+    uint64_t *const key0 = key;
+    uint32_t *const idx0 = idx;
+    for (int shift = 0; shift < key_bits; shift += 8) {
+        const uint64_t digit = (uint64_t(1) << std::min(8, key_bits - shift)) - 1;
+        size_t count[257] = {};
+        for (size_t i = 0; i < n; ++i) ++count[((key[i] >> shift) & digit) + 1];
+        for (size_t b = 0; b < 256; ++b) count[b + 1] += count[b];
+        for (size_t i = 0; i < n; ++i) {
+            const size_t d = count[(key[i] >> shift) & digit]++;
+            k2[d] = key[i];
+            i2[d] = idx[i];
+        }
+        std::swap(key, k2);
+        std::swap(idx, i2);
+    }
+    if (key != key0) {
+        std::copy(key, key + n, key0);
+        std::copy(idx, idx + n, idx0);
+    }
+}
+
 // Dense ranks (0 .. u-1, in value order) of an int32 column; returns the bits
 // needed to hold a rank.  A direct table is used when the value range is small.
 inline int dense_ranks(const int32_t *vals, size_t n, size_t stride, std::vector<uint32_t> &rank) {

@@ -258,3 +258,34 @@ def test_packing_order(kind, norm):
         xs, ys = np.nonzero((attrs[:, None, 1] == attrs[None, :, 1]) & (attrs[:, None, 1] > 0))
         assert np.array_equal(res.pairs(xs, ys)[0], strips.pairs(xs, ys)[0])
         assert np.array_equal(res.half_units, strips.half_units[:len(res.half_units)])
+
+
+# Collapse of many cells with a sparse key space (buckets of the key's top bits)
+# and of few (one sort), bit for bit the level-by-level definition: rows of equal
+# kept keys averaged, summed in row order, in key order.
+@pytest.mark.parametrize("labels,sorted_by", [(100, "buckets"), (12, "one sort")])
+def test_collapse_sparse_keys(labels, sorted_by):
+    import paper_2505_02692_amd as fx
+    from test_gpu_parity import ctx
+    rng = np.random.default_rng(31)
+    attrs = np.array([(lab, c, sp) for lab in range(labels) for c in range(3)
+                      for sp in rng.choice(60, 6, replace=False)], np.int32)
+    n = len(attrs)
+    feats = torch.from_numpy(rng.standard_normal((n, 8), dtype=np.float32)).cuda()
+    print(f"[case] collapse sparse {sorted_by} items={n}", flush=True)
+    t = fx.Task(fx.Dataset(ctx(), feats, np.arange(n + 1), attrs), 0, [1], [2])
+    res = t.score(mode="pooled")
+    keys, attr_of = t.keys, np.array([0, 0, 1, 2, 2])
+    score = res.half_units / (2.0 * res.n_triplets)
+    assert (len(score) >= 1 << 15) == (sorted_by == "buckets")
+    for levels in ([[1], [2]], [[1]], [[1, 2]]):
+        rows, cols = score, keys
+        attr = attr_of
+        for lv in levels:
+            keep = ~np.isin(attr, lv)
+            cols, attr = cols[:, keep], attr[keep]
+            uniq, first, inv = np.unique(cols, axis=0, return_index=True, return_inverse=True)
+            total = np.zeros(len(uniq))
+            np.add.at(total, inv.ravel(), rows)  # one by one, in row order
+            rows, cols = total / np.bincount(inv.ravel()), uniq
+        assert res.collapse(levels) == 1.0 - np.cumsum(rows)[-1] / len(rows)

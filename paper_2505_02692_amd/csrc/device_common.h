@@ -123,6 +123,12 @@ __device__ __forceinline__ float acos_over_pi(float x) {
     return x < 0.0f ? 1.0f - r : r;
 }
 
+// A value equal in all lanes, for scalar registers.
+__device__ __forceinline__ int64_t uniform64(int64_t v) {
+    return int64_t(uint64_t(uint32_t(__builtin_amdgcn_readfirstlane(int(v)))) |
+                   (uint64_t(uint32_t(__builtin_amdgcn_readfirstlane(int(v >> 32)))) << 32));
+}
+
 // acos_over_pi from ax = |x| (at most 1) and the sign of x, taken from s,
 // with the reflection folded into the last steps: r = acos(ax) / pi as above
 // lies in [0, 1/2], so h = r - 1/2 <= 0 and acos(x) / pi = 1/2 - copysign(h, s)

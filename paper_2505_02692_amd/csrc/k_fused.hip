@@ -99,50 +99,61 @@ __device__ __forceinline__ uint32_t pk_step(uint32_t a) {
     return __builtin_bit_cast(uint32_t, x + inc);
 }
 
-// A K chunk of the tile's rows, held in registers between its global load
-// and its store to LDS: each thread owns kN * kKc / 8 / 256 pieces of 16 bytes.
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+// Rows of a K chunk: kN rows from packed row `row0`, of which `nr` exist, as a buffer
+// in scalar registers and one 32-bit offset per piece of 16 bytes (each thread owns
+// kN * kKc / 8 / 256 of them), so that the chunks' addresses cost no vector work
+// and six registers rather than twelve.  Rows beyond nr (>= 1) repeat row nr - 1:
+// finite values whose products only reach accumulator rows or columns that are never
+// used, or that are scaled by a zero inverse norm (no zero fill, no masked loads).
 template <int kN>
-struct Chunk {
+struct Rows {
     static constexpr int kPer = kN * (kKc / 8) / 256;
-    // one vector value, not an array, so it stays in registers
-    typedef uint32_t Vec __attribute__((ext_vector_type(4 * kPer)));
-    Vec v;
-    // rows beyond nr (>= 1) repeat row nr - 1: finite values whose products
-    // only reach accumulator rows or columns that are never used, or that are
-    // scaled by a zero inverse norm (no zero fill, no masked loads)
-    __device__ __forceinline__ void load(const uint16_t *__restrict__ xn, int dim_pad, int64_t row0, int nr,
-                                         int k0) {
+    __amdgpu_buffer_rsrc_t buf;
+    uint32_t at[kPer];
+    __device__ __forceinline__ Rows(const uint16_t *__restrict__ xn, int dim_pad, int64_t row0, int nr) {
+        buf = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(xn + row0 * dim_pad), 0,
+                                                nr * dim_pad * 2, 0x00027000);
 #pragma unroll
         for (int i = 0; i < kPer; ++i) {
             const int p = threadIdx.x + 256 * i;
-            const int r = min(p / (kKc / 8), nr - 1), q = p % (kKc / 8);
-            const uint4 t = *reinterpret_cast<const uint4 *>(xn + (row0 + r) * dim_pad + k0 + q * 8);
-            v[4 * i] = t.x;
-            v[4 * i + 1] = t.y;
-            v[4 * i + 2] = t.z;
-            v[4 * i + 3] = t.w;
+            at[i] = uint32_t(min(p / (kKc / 8), nr - 1) * dim_pad * 2 + p % (kKc / 8) * 16);
         }
+    }
+};
+
+// A K chunk of the tile's rows, held in registers between its global load
+// and its store to LDS.
+template <int kN>
+struct Chunk {
+    static constexpr int kPer = Rows<kN>::kPer;
+    u32x4 v[kPer];
+    __device__ __forceinline__ void load(const Rows<kN> &rows, int k0) {
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) v[i] = __builtin_amdgcn_raw_buffer_load_b128(rows.buf, rows.at[i], 2 * k0, 0);
     }
     __device__ __forceinline__ void store(uint16_t *lds) const {
 #pragma unroll
         for (int i = 0; i < kPer; ++i) {
             const int p = threadIdx.x + 256 * i;
-            const int r = p / (kKc / 8), q = p % (kKc / 8);
-            *reinterpret_cast<uint4 *>(lds + r * kLdsRow + q * 8) =
-                make_uint4(v[4 * i], v[4 * i + 1], v[4 * i + 2], v[4 * i + 3]);
+            *reinterpret_cast<u32x4 *>(lds + p / (kKc / 8) * kLdsRow + p % (kKc / 8) * 8) = v[i];
         }
     }
 };
 
 // acc[h][ct] = rows [32h, 32h + 32) against columns kWaveCols * w + 32 ct + [0, 32).
 // Software-pipelined: the next K chunk is loaded from memory into registers
-// while the MFMAs consume the current one from LDS.  Column tiles that lie
-// past nc skip their MFMAs, and so does the second row half when nr <= 32
-// (those accumulators are never read).  Every product accumulates its K
-// range in the same order whatever the tile width, so results do not depend
-// on it.  Column tiles wholly below c_lo (columns nobody reads) skip their
-// MFMAs too.  `stash` runs once, after the first chunk is stored and before the
-// barrier that publishes it, so LDS it writes is visible to the epilogue.
+// while the MFMAs consume the current one from LDS (two chunks ahead spills and is
+// slower: 263 against 257 ms).  Column tiles that lie past nc, or wholly below c_lo
+// (columns nobody reads), skip their MFMAs.  The second row half does not when nr <=
+// 32, though nobody reads it then: a branch per product put every read from LDS and
+// its wait right before its MFMA.  With the buffer loads (see Rows) that was 268 ->
+// 256 ms for 1200 groups of 11-2000 items of 1-60 frames, 512 features, and 3.05 ->
+// 2.73 ms for 40 groups of 1000 items, 1024 features.  Every product accumulates its
+// K range in the same order whatever the tile width, so results do not depend on it.
+// `stash` runs once, after the first chunk is stored and before the barrier that
+// publishes it, so LDS it writes is visible to the epilogue.
 template <int kC, typename Stash>
 __device__ __forceinline__ void gram_tile(uint16_t *smem, const uint16_t *__restrict__ xn, int dim_pad,
                                           int64_t r0, int nr, int64_t c0, int nc, int c_lo,
@@ -150,44 +161,46 @@ __device__ __forceinline__ void gram_tile(uint16_t *smem, const uint16_t *__rest
     using T = Tile<kC>;
     const int lane = threadIdx.x % kWave;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const bool do1 = nr > 32;
     uint16_t *As = smem;
     uint16_t *Bs = smem + kRows * kLdsRow;
 #pragma unroll
     for (int ct = 0; ct < T::kCT; ++ct)
         for (int i = 0; i < 16; ++i) { acc[0][ct][i] = 0.0f; acc[1][ct][i] = 0.0f; }
+    const Rows<kRows> ra(xn, dim_pad, r0, nr);
+    const Rows<kC> rc(xn, dim_pad, c0, nc);
     Chunk<kRows> ca;
     Chunk<kC> cb;
-    ca.load(xn, dim_pad, r0, nr, 0);
-    cb.load(xn, dim_pad, c0, nc, 0);
-    for (int k0 = 0; k0 < dim_pad; k0 += kKc) {
-        ca.store(As);
-        cb.store(Bs);
-        if (k0 == 0) stash();
+    ca.load(ra, 0);
+    cb.load(rc, 0);
+    ca.store(As);
+    cb.store(Bs);
+    stash();
+    const uint16_t *a_at = As + (lane % 32) * kLdsRow + lane / 32 * 8;
+    const uint16_t *b_at = Bs + (T::kWaveCols * w + lane % 32) * kLdsRow + lane / 32 * 8;
+    auto frag = [](const uint16_t *p) { return *reinterpret_cast<const bf16x8 *>(p); };
+    for (int k0 = kKc;; k0 += kKc) {
         __syncthreads();
-        if (k0 + kKc < dim_pad) {
-            ca.load(xn, dim_pad, r0, nr, k0 + kKc);
-            cb.load(xn, dim_pad, c0, nc, k0 + kKc);
+        if (k0 < dim_pad) {
+            ca.load(ra, k0);
+            cb.load(rc, k0);
         }
 #pragma unroll
         for (int ct = 0; ct < T::kCT; ++ct) {
             const int col0 = T::kWaveCols * w + 32 * ct;
-            if (col0 < nc && col0 + 32 > c_lo) {
+            if (col0 >= nc || col0 + 32 <= c_lo) continue;
+            const uint16_t *bt = b_at + 32 * ct * kLdsRow;
 #pragma unroll
-                for (int ks = 0; ks < kKc / 16; ++ks) {
-                    const int kk = ks * 16 + (lane / 32) * 8;
-                    const bf16x8 a0 = *reinterpret_cast<const bf16x8 *>(As + (lane % 32) * kLdsRow + kk);
-                    const bf16x8 b = *reinterpret_cast<const bf16x8 *>(Bs + (col0 + lane % 32) * kLdsRow + kk);
-                    acc[0][ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, b, acc[0][ct], 0, 0, 0);
-                    if (do1) {
-                        const bf16x8 a1 =
-                            *reinterpret_cast<const bf16x8 *>(As + (32 + lane % 32) * kLdsRow + kk);
-                        acc[1][ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, b, acc[1][ct], 0, 0, 0);
-                    }
-                }
+            for (int ks = 0; ks < kKc / 16; ++ks) {
+                const bf16x8 b = frag(bt + 16 * ks);
+                acc[0][ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(a_at + 16 * ks), b, acc[0][ct], 0, 0, 0);
+                acc[1][ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(a_at + 32 * kLdsRow + 16 * ks), b,
+                                                                     acc[1][ct], 0, 0, 0);
             }
         }
         __syncthreads();
+        if (k0 >= dim_pad) break;
+        ca.store(As);
+        cb.store(Bs);
     }
 }
 
@@ -277,7 +290,7 @@ __global__ __launch_bounds__(256, kC == 128 ? 4 : 2) void k_fused(const uint16_t
         if (!take) return j + n_m;
         if (threadIdx.x == 0) taken_s = int64_t(atomicAdd(unit_ctr + xcd, 1u));
         __syncthreads();
-        const int64_t v = taken_s;
+        const int64_t v = dev::uniform64(taken_s);
         __syncthreads();
         return v;
     };

@@ -30,7 +30,8 @@
 // the error bound, and then the length (the divisor) changes.  Each cell
 // therefore carries the interval [Lmin, Lmax] of lengths over all
 // predecessors within `delta` of the minimum (packed as two u16 halves,
-// high = Lmax, low = 0xFFFF - Lmin, so one packed max merges both ends).
+// high = Lmax, low = -Lmin mod 2^16, so one packed max merges both ends; 0 is both
+// "no predecessor" and the empty path's interval, which is only ever taken alone).
 // If delta is at least twice the cumulative-cost error, the FP64 length lies
 // in the interval; a pair whose interval is not a single value is flagged
 // non-robust (flag bit 0) and recomputed in FP64.
@@ -93,7 +94,7 @@ __device__ __forceinline__ uint32_t pk_max(uint32_t a, uint32_t b) {
     return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(x, y));
 }
 __device__ __forceinline__ uint32_t pk_step(uint32_t a) {
-    // Lmax + 1 (high half), (0xFFFF - Lmin) - 1 (low half), each half wrapping
+    // Lmax + 1 (high half), -Lmin - 1 (low half), each half wrapping
     u16x2 x = __builtin_bit_cast(u16x2, a);
     u16x2 inc = {(unsigned short)0xFFFF, (unsigned short)1};
     return __builtin_bit_cast(uint32_t, x + inc);
@@ -150,7 +151,8 @@ struct Chunk {
 // 32, though nobody reads it then: a branch per product put every read from LDS and
 // its wait right before its MFMA.  With the buffer loads (see Rows) that was 268 ->
 // 256 ms for 1200 groups of 11-2000 items of 1-60 frames, 512 features, and 3.05 ->
-// 2.73 ms for 40 groups of 1000 items, 1024 features.  Every product accumulates its
+// 2.73 ms for 40 groups of 1000 items, 1024 features.  The first product of the first
+// chunk starts from the constant 0, so that no accumulator is cleared.  Every product accumulates its
 // K range in the same order whatever the tile width, so results do not depend on it.
 // `stash` runs once, after the first chunk is stored and before the barrier that
 // publishes it, so LDS it writes is visible to the epilogue.
@@ -163,9 +165,6 @@ __device__ __forceinline__ void gram_tile(uint16_t *smem, const uint16_t *__rest
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     uint16_t *As = smem;
     uint16_t *Bs = smem + kRows * kLdsRow;
-#pragma unroll
-    for (int ct = 0; ct < T::kCT; ++ct)
-        for (int i = 0; i < 16; ++i) { acc[0][ct][i] = 0.0f; acc[1][ct][i] = 0.0f; }
     const Rows<kRows> ra(xn, dim_pad, r0, nr);
     const Rows<kC> rc(xn, dim_pad, c0, nc);
     Chunk<kRows> ca;
@@ -178,12 +177,8 @@ __device__ __forceinline__ void gram_tile(uint16_t *smem, const uint16_t *__rest
     const uint16_t *a_at = As + (lane % 32) * kLdsRow + lane / 32 * 8;
     const uint16_t *b_at = Bs + (T::kWaveCols * w + lane % 32) * kLdsRow + lane / 32 * 8;
     auto frag = [](const uint16_t *p) { return *reinterpret_cast<const bf16x8 *>(p); };
-    for (int k0 = kKc;; k0 += kKc) {
-        __syncthreads();
-        if (k0 < dim_pad) {
-            ca.load(ra, k0);
-            cb.load(rc, k0);
-        }
+    auto products = [&](auto first_tag) {
+        constexpr bool first = decltype(first_tag)::value;
 #pragma unroll
         for (int ct = 0; ct < T::kCT; ++ct) {
             const int col0 = T::kWaveCols * w + 32 * ct;
@@ -192,15 +187,27 @@ __device__ __forceinline__ void gram_tile(uint16_t *smem, const uint16_t *__rest
 #pragma unroll
             for (int ks = 0; ks < kKc / 16; ++ks) {
                 const bf16x8 b = frag(bt + 16 * ks);
-                acc[0][ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(a_at + 16 * ks), b, acc[0][ct], 0, 0, 0);
-                acc[1][ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(a_at + 32 * kLdsRow + 16 * ks), b,
-                                                                     acc[1][ct], 0, 0, 0);
+                const f32x16 c0 = first && ks == 0 ? f32x16{} : acc[0][ct], c1 = first && ks == 0 ? f32x16{} : acc[1][ct];
+                acc[0][ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(a_at + 16 * ks), b, c0, 0, 0, 0);
+                acc[1][ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(a_at + 32 * kLdsRow + 16 * ks), b, c1, 0,
+                                                                     0, 0);
             }
         }
+    };
+    auto chunk = [&](auto first_tag, int k0) {
         __syncthreads();
-        if (k0 >= dim_pad) break;
+        if (k0 + kKc < dim_pad) {
+            ca.load(ra, k0 + kKc);
+            cb.load(rc, k0 + kKc);
+        }
+        products(first_tag);
+        __syncthreads();
+    };
+    chunk(std::true_type{}, 0);
+    for (int k0 = kKc; k0 < dim_pad; k0 += kKc) {
         ca.store(As);
         cb.store(Bs);
+        chunk(std::false_type{}, k0);
     }
 }
 
@@ -467,7 +474,11 @@ __global__ __launch_bounds__(256, kC == 128 ? 4 : 2) void k_fused(const uint16_t
     // it sends, is always finite on its columns.
     const float top_pen = top ? kInf : 0.0f;
     const float diag_first = top ? 0.0f : kInf;       // virtual c[-1][-1] = 0 at an item start
-    const uint32_t pd_first = top ? 0x0000FFFFu : 0u;  // its length interval: Lmin = Lmax = 0
+    // 0 in a first row: taken with the lane shift in one instruction, where a selection
+    // (which the compiler makes of a mask it sees through) costs one more per step.
+    // With the accumulators no longer cleared 261.4 -> 257.7 ms (as at gram_tile)
+    uint32_t not_top = top ? 0u : ~0u;
+    asm("" : "+v"(not_top));
     // at step t the lane is on column t - ir of the wave's span: distance
     // dcol[t], flags fcol[t], read four steps ahead.  ir <= lane, so dcol[0] is
     // inside the tile; the last read-ahead (step steps + 6) is max_n + 6 - ir columns
@@ -498,15 +509,16 @@ __global__ __launch_bounds__(256, kC == 128 ? 4 : 2) void k_fused(const uint16_t
     auto step = [&](const uint32_t cf, const float dv) {
         const bool first = uint8_t(cf) != 0;
         up = shr1z(c) + top_pen;
-        // (lane 0 reads 0: a first row, whose up interval is never taken)
-        if (kPath) Pup = shr1uz(P);
+        // (0 in a first row: its up neighbour is never taken, its diagonal one only as
+        // the virtual cell.  Elsewhere an item's first column has a diagonal cost of
+        // +inf, which is not taken either, so the interval needs no selection there.)
+        if (kPath) Pup = shr1uz(P) & not_top;
         const float diag = first ? diag_first : up_prev;
         const float left = first ? kInf : c;
         const float m = fminf(fminf(diag, left), up);
         if (kPath) {
-            const uint32_t Pd = first ? pd_first : Pup_prev;
             const float thr = m + delta;
-            const uint32_t sd = diag <= thr ? Pd : 0u;
+            const uint32_t sd = diag <= thr ? Pup_prev : 0u;
             const uint32_t sl = left <= thr ? P : 0u;
             const uint32_t su = up <= thr ? Pup : 0u;
             P = pk_step(pk_max(pk_max(sd, sl), su));
@@ -606,7 +618,7 @@ __global__ __launch_bounds__(256, kC == 128 ? 4 : 2) void k_fused(const uint16_t
             const int r0 = i > 0 ? items_s.row_last[i - 1] + 1 : 0, c0 = j > 0 ? items_s.col_last[j - 1] + 1 : 0;
             const uint32_t P = __float_as_uint(dt[max(r - 1, 0) * kDStride + col]);
             const uint32_t lmax = r == r0 ? uint32_t(col - c0 + 1) : P >> 16;
-            const uint32_t lmin = r == r0 ? lmax : 0xFFFFu - (P & 0xFFFFu);
+            const uint32_t lmin = r == r0 ? lmax : -P & 0xFFFFu;
             v *= __builtin_amdgcn_rcpf(float(lmin));
             fl = lmin == lmax ? 0 : 1;
         }

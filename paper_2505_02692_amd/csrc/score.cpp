@@ -90,8 +90,8 @@ std::array<size_t, 6> add_col_plan(const ColPlan &cp, Packer &pk) {
 
 // Host side of the task tables: adds them (and the packing order and `plan`, if
 // any) to `pk`; the group columns are built in `gcols`, which must live until the
-// copy is made.
-TableLayout add_task_tables(const TaskImpl &t, const ColPlan *plan, bool with_order, Packer &pk,
+// copy is made.  with_rows: the row blocks too (a plan with its own needs none).
+TableLayout add_task_tables(const TaskImpl &t, const ColPlan *plan, bool with_order, bool with_rows, Packer &pk,
                             std::array<std::vector<int64_t>, 5> &gcols) {
     const size_t G = t.groups.size();
     for (auto &v : gcols) v.resize(G);
@@ -115,7 +115,7 @@ TableLayout add_task_tables(const TaskImpl &t, const ColPlan *plan, bool with_or
     for (size_t k = 0; k < 5; ++k) L.g[k] = pk.add(gcols[k]);
     L.cells = pk.add(t.cells);
     L.units = pk.add(t.units);
-    L.rb = pk.add(t.rb);
+    if (with_rows) L.rb = pk.add(t.rb);
     if (with_order) L.pack = add_order(t, pk);
     if (plan) {
         L.plan = add_col_plan(*plan, pk);
@@ -394,7 +394,7 @@ void prepack_tables(TaskImpl &t) {
     Packer pk;
     std::array<std::vector<int64_t>, 5> gcols;
     const ColPlan *plan = t.col_plans.empty() ? nullptr : t.col_plans.front().get();
-    const TableLayout L = add_task_tables(t, plan, !t.pack_item.empty(), pk, gcols);
+    const TableLayout L = add_task_tables(t, plan, !t.pack_item.empty(), true, pk, gcols);
     if (pk.total > kPrepackMaxBytes || ctx->pinned.packed_bytes.load() + pk.total > kPrepackBudget) return;
     FABX_HIP(hipSetDevice(ctx->device));
     std::unique_ptr<PinnedBlock> blk;
@@ -766,7 +766,7 @@ std::shared_ptr<ResultImpl> launch_score(const std::shared_ptr<TaskImpl> &tp, co
             Packer pk;
             std::array<std::vector<int64_t>, 5> gcols;
             const TableLayout L = add_task_tables(t, cplan && !cplan->d_cb ? cplan : nullptr,
-                                                  !t.pack_item.empty(), pk, gcols);
+                                                  !t.pack_item.empty(), true, pk, gcols);
             pk.upload(dv.blob, ds.ctx->staging, ds.ctx->copy_stream, stream);
             set_task_tables(t, L);
         }
@@ -952,7 +952,7 @@ void score_in_scratch(TaskImpl &t, const ScoreParams &p, char *base, size_t cap,
     const bool order_in_list = order && bf16 && pk_order.total <= size_t(t.n_pair_slots) * 8;
     auto layout = [&](const PlainPlan &strips, Packer &pk, TableLayout &tl, PlanLayout &pl,
                       std::array<std::vector<int64_t>, 5> &gcols) {
-        tl = add_task_tables(t, cplan, order && !use_strips && !order_in_list, pk, gcols);
+        tl = add_task_tables(t, cplan, order && !use_strips && !order_in_list, !cplan || cplan->rb.empty(), pk, gcols);
         static const std::vector<int64_t> no_slots;  // the packer keeps pointers: no temporaries
         pl = add_plan(pk, tiles, strips, dtw && bf16 ? t.long_slots : no_slots);
         const size_t tables = (pk.total + 255) & ~size_t(255);

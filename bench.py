@@ -379,7 +379,8 @@ def cpu_baseline(oracle, fx, w, target_seconds=15.0, seed=0):
                       f"workload would take about {whole_s:.0f} s by the rescaled estimate"}
 
 
-FUSED_SOURCES = ("paper_2505_02692_amd/csrc/k_fused.hip", "paper_2505_02692_amd/csrc/device_common.h")
+FUSED_SOURCES = ("paper_2505_02692_amd/csrc/k_fused.hip", "paper_2505_02692_amd/csrc/fused_unit.h",
+                 "paper_2505_02692_amd/csrc/device_common.h")
 
 
 def fused_source_hash():

@@ -21,9 +21,9 @@
 //     Every step all lanes do useful work except the fill and drain of the
 //     longest row item.
 //
-// What bounds it: the vector ALUs (65% busy; matrix cores under 10%) and the
-// latency of the DTW's dependent chain.  Four blocks per CU hide it better than two
-// of 256 columns do.
+// What bounds it: the vector ALUs (78% busy on 5000 groups of 2-2000 items of 1-60
+// frames, 512 features; matrix cores 18%) and the latency of a unit's phases behind
+// them.  Four blocks per CU hide it better than two of 256 columns do.
 //
 // Path length (FABX_NORM_PATH): with BF16 distances the predecessor chosen in
 // FP32 can differ from the FP64 one when their cumulative costs are within

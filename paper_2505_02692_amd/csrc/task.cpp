@@ -462,47 +462,49 @@ void walk_groups(const WalkCtx &w, int64_t s_begin, int64_t s_end, Sink &out) {
 // the first example below); the last bin, which may have room left that the next
 // one's first item would fit, stays last.  Linear: items lie in lists by length, a
 // bit mask names the lengths left.
-void order_group(TaskImpl &t, int64_t gi) {
+// next, binned: one entry an item of the task, bin: one more a group (no memory is
+// taken here, on the pool's threads).
+void order_group(TaskImpl &t, int64_t gi, int32_t *next, int32_t *binned, int32_t *bin) {
     const Group &g = t.groups[size_t(gi)];
     const int32_t n = int32_t(g.n_items);
+    next += g.item0;
+    binned += g.item0;    // items (of the group) by bin
+    bin += g.item0 + gi;  // the first place of each bin, then their end
     std::array<int32_t, kFusedRowFrames + 1> head;
     head.fill(-1);
-    std::vector<int32_t> next(static_cast<size_t>(n));
     uint64_t left = 0;  // bit l - 1: items of l frames are left
     for (int32_t k = n - 1; k >= 0; --k) {
         const int32_t l = t.item_len[size_t(g.item0 + k)];
-        next[size_t(k)] = head[size_t(l)];
+        next[k] = head[size_t(l)];
         head[size_t(l)] = k;
         left |= uint64_t(1) << (l - 1);
     }
-    // task item (in the group) by bin, the first place of each bin
-    std::vector<int32_t> binned, bin{0};
-    binned.reserve(size_t(n));
+    int32_t n_bins = 0, placed = 0;
     while (left) {
+        bin[n_bins++] = placed;
         int room = kFusedRowFrames;
         for (uint64_t fit = left; fit; fit = room > 0 ? left & (~uint64_t(0) >> (64 - room)) : 0) {
             const int l = 64 - __builtin_clzll(fit);
             const int32_t k = head[size_t(l)];
-            head[size_t(l)] = next[size_t(k)];
+            head[size_t(l)] = next[k];
             if (head[size_t(l)] < 0) left &= ~(uint64_t(1) << (l - 1));
-            binned.push_back(k);
+            binned[placed++] = k;
             room -= l;
         }
-        bin.push_back(int32_t(binned.size()));
     }
+    bin[n_bins] = placed;
     int64_t q = g.item0, frame = g.frame0;
-    auto emit = [&](size_t b) {
+    auto emit = [&](int32_t b) {
         for (int32_t i = bin[b]; i < bin[b + 1]; ++i, ++q) {
-            const int64_t item = g.item0 + binned[size_t(i)];
+            const int64_t item = g.item0 + binned[i];
             t.pack_item[size_t(q)] = int32_t(item);
             t.pack_len[size_t(q)] = t.item_len[size_t(item)];
             t.pack_dst[size_t(q)] = frame;
             frame += t.item_len[size_t(item)];
         }
     };
-    const size_t n_bins = bin.size() - 1;
-    for (size_t b = n_bins - 1; b-- > 0;) emit(b);
-    emit(n_bins - 1);
+    for (int32_t b = n_bins - 1; b-- > 0;) emit(b);
+    if (n_bins > 0) emit(n_bins - 1);
 }
 
 // Makes the packing order where it pays: the distance stage falls by 28% for 1200
@@ -522,9 +524,11 @@ void plan_order(TaskImpl &t) {
     t.pack_item.resize(size_t(n));
     t.pack_len.resize(size_t(n));
     t.pack_dst.resize(size_t(n));
+    hvec<int32_t> next(static_cast<size_t>(n)), binned(static_cast<size_t>(n)), bin(static_cast<size_t>(n + G));
     const int64_t kGroups = group_chunk(G);
     parallel_for(int((G + kGroups - 1) / kGroups), [&](int c) {
-        for (int64_t gi = c * kGroups; gi < std::min<int64_t>(G, (c + 1) * kGroups); ++gi) order_group(t, gi);
+        for (int64_t gi = c * kGroups; gi < std::min<int64_t>(G, (c + 1) * kGroups); ++gi)
+            order_group(t, gi, next.data(), binned.data(), bin.data());
     });
 }
 

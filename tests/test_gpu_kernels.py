@@ -242,6 +242,8 @@ def test_packing_order(kind, norm):
         assert np.array_equal(fx.fabx_score_noalloc(t.h, fx.make_opts(fused_cols=512, **opts), len(t))[0],
                               res.half_units)
         assert np.array_equal(t.score(fused_cols=256, **opts).half_units, res.half_units)
+        sub = fx.Task(ds, 0, [1], [], fx.Subsampler(seed=3, max_a=30, max_b=30, max_x=30))
+        assert np.array_equal(sub.score(fused_cols=512, **opts).half_units, sub.score(**opts).half_units)
     if kind in ("bf16", "euclidean"):
         orc = oracle.score(ref, off, attrs, 0, [1], [], "dtw", norm, distance=opts["distance"])
         assert np.array_equal(res.half_units, orc.half_units)

@@ -293,3 +293,24 @@ def test_collapse_sparse_keys(labels, sorted_by):
             np.add.at(total, inv.ravel(), rows)  # one by one, in row order
             rows, cols = total / np.bincount(inv.ravel()), uniq
         assert res.collapse(levels) == 1.0 - np.cumsum(rows)[-1] / len(rows)
+
+
+# Rows of large cells with more infinities than a bucket takes (frames whose FP32
+# length overflows, in the Euclidean BF16 form): the sort's padding must not come
+# before the row's own infinities, whose places it would stand for.
+@pytest.mark.parametrize("na,nb", [(40, 300), (12, 1025)])
+def test_sorted_rows_with_infinities(na, nb):
+    rng = np.random.default_rng(na)
+    n = na + nb
+    x = rng.standard_normal((n, 8)).astype(np.float32)
+    x[::2] *= 1e25
+    attrs = np.stack([np.r_[np.zeros(na, np.int32), np.ones(nb, np.int32)], np.zeros(n, np.int32)], 1)
+    w = workloads.Workload("infinities", torch.from_numpy(x), np.arange(n + 1, dtype=np.int64), attrs, ["l", "g"], 0,
+                           [1], [])
+    print(f"[case] sorted rows with infinities na={na} nb={nb}", flush=True)
+    t, res = gpu_score(w, mode="pooled", distance="euclidean", keep_pairs=True)
+    orc = oracle.score(x, w.offsets, attrs, 0, [1], [], "pooled", "path", distance="euclidean")
+    xs, ys, _ = all_oracle_pairs(orc)
+    f32, fl, _ = res.pairs(xs, ys)
+    assert np.isinf(f32).sum() > 1000 and ((fl & 2) != 0).all()  # the margin is infinite too
+    assert np.array_equal(res.half_units, orc.half_units)

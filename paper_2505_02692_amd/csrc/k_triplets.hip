@@ -339,19 +339,28 @@ __device__ __forceinline__ uint32_t block_prefix(uint32_t v, uint32_t *scratch, 
     return before + incl - v;
 }
 
+// Whether value v at place i comes after value u at place j in a sorted row: NaN
+// after every number, equal values (and NaN) by place.
+__device__ __forceinline__ bool comes_after(float v, int i, float u, int j) {
+    return v > u || (v == u ? i > j : v != v && (u == u || i > j));
+}
+
 // The n <= kCap values src[0..n) sorted into sv, with their positions in si, by
-// a 256-thread block.  The values go to kCap buckets of equal width between the
-// least and the largest (their bucket grows with the value), each bucket's few
-// values are then sorted by insertion.  Values that crowd a bucket (many exact
-// ties, an infinity, a NaN) take the bitonic sort instead, padded to a power of two
-// with infinities that come after the row's own (equal values lie by place).  Bound by LDS
+// a 256-thread block; returns how many are numbers (any NaN lie last: a comparison
+// with one is never true, so the counts leave them out).  The values go to kCap
+// buckets of equal width between the least and the largest (their bucket grows with
+// the value, NaN in the last), each bucket's few values are then sorted by
+// insertion.  Values that crowd a bucket (many exact ties or NaN, an infinity, which
+// leaves the others in one bucket) take the bitonic sort instead, padded to a power
+// of two with NaN of later places.  Bound by LDS
 // latency: 9 barriers where the bitonic sort of 1024 values has 55 (the sorted
 // counting of 7.3e10 triples, |B| up to 1000: 5.8 -> 3.0 ms).
 template <int kCap>
-__device__ __forceinline__ void sort_row(const float *__restrict__ src, int n, float *sv, uint16_t *si,
-                                         uint32_t *bucket, uint32_t *scratch) {
+__device__ __forceinline__ int sort_row(const float *__restrict__ src, int n, float *sv, uint16_t *si,
+                                        uint32_t *bucket, uint32_t *scratch) {
     constexpr int kPer = kCap / 256, kCrowd = 24;
     const int tid = threadIdx.x, lane = tid % kWave, w = tid / kWave;
+    auto numbers = [&] { return sv[n - 1] == sv[n - 1] ? n : count_below(sv, n, __builtin_inff(), true); };
     float v[kPer], lo = __builtin_inff(), hi = -__builtin_inff();
 #pragma unroll
     for (int m = 0; m < kPer; ++m) {
@@ -384,7 +393,7 @@ __device__ __forceinline__ void sort_row(const float *__restrict__ src, int n, f
 #pragma unroll
     for (int m = 0; m < kPer; ++m)
         if (tid + 256 * m < n) {
-            at[m] = min(max(int((v[m] - lo) * scale), 0), kCap - 1);
+            at[m] = v[m] == v[m] ? int(fminf(fmaxf((v[m] - lo) * scale, 0.0f), float(kCap - 1))) : kCap - 1;
             pos[m] = atomicAdd(&bucket[at[m]], 1u);
         }
     __syncthreads();
@@ -419,7 +428,7 @@ __device__ __forceinline__ void sort_row(const float *__restrict__ src, int n, f
                 const float x = sv[k];
                 const uint16_t xi = si[k];
                 uint32_t p = k;
-                for (; p > first && sv[p - 1] > x; --p) {
+                for (; p > first && comes_after(sv[p - 1], si[p - 1], x, xi); --p) {
                     sv[p] = sv[p - 1];
                     si[p] = si[p - 1];
                 }
@@ -429,12 +438,12 @@ __device__ __forceinline__ void sort_row(const float *__restrict__ src, int n, f
             first += cnt[m];
         }
         __syncthreads();
-        return;
+        return numbers();
     }
     int n2 = 2;
     while (n2 < n) n2 <<= 1;
     for (int j = tid; j < n2; j += 256) {
-        sv[j] = j < n ? src[j] : __builtin_inff();
+        sv[j] = j < n ? src[j] : __builtin_nanf("");
         si[j] = uint16_t(j);
     }
     __syncthreads();
@@ -446,7 +455,7 @@ __device__ __forceinline__ void sort_row(const float *__restrict__ src, int n, f
                     const bool up = (i & k) == 0;
                     const float vi = sv[i], vl = sv[l];
                     const uint16_t pi = si[i], pl = si[l];
-                    if ((vi > vl || (vi == vl && pi > pl)) == up) {
+                    if (comes_after(vi, pi, vl, pl) == up) {
                         sv[i] = vl;
                         sv[l] = vi;
                         si[i] = pl;
@@ -456,6 +465,7 @@ __device__ __forceinline__ void sort_row(const float *__restrict__ src, int n, f
             }
             __syncthreads();
         }
+    return numbers();
 }
 
 // Large cells, one block per unit (cell, one x): the row's distances to B are
@@ -494,7 +504,7 @@ __global__ __launch_bounds__(256) void k_triplets_sorted(const CellDev *__restri
         const int xl = c.x0 + xi;
         const float *row = p32 + base + int64_t(xl) * n;
         uint8_t *frow = flags ? flags + base + int64_t(xl) * n : nullptr;
-        sort_row<kCap>(row + c.b0, nb, sv, si, bucket, scratch);
+        const int nv = sort_row<kCap>(row + c.b0, nb, sv, si, bucket, scratch);
         // count, near ties, non-robust pairs
         unsigned long long cnt = 0;
         int dirty = 0, all_b = 0, all_a = 0;
@@ -502,16 +512,16 @@ __global__ __launch_bounds__(256) void k_triplets_sorted(const CellDev *__restri
             const int al = c.a0 + a;
             if (c.exclude_self && al == xl) continue;
             const float da = row[al];
-            const int lb = count_below(sv, nb, da, false), ub = count_below(sv, nb, da, true);
-            cnt += unsigned(2 * nb - lb - ub);
+            const int lb = count_below(sv, nv, da, false), ub = count_below(sv, nv, da, true);
+            if (da == da) cnt += unsigned(2 * nv - lb - ub);
             if (frow) {
                 const uint8_t fa = frow[al];
                 if (fa & kNonRobust) {
                     dirty = all_b = 1;
                     frow[al] = fa | kMarked;
                 }
-                const int lo = count_below(sv, nb, da - margin, false);
-                const int hi = count_below(sv, nb, da + margin, true);
+                const int lo = count_below(sv, nv, da - margin, false);
+                const int hi = count_below(sv, nv, da + margin, true);
                 if (lo < hi) {
                     dirty = 1;
                     frow[al] = frow[al] | kMarked;
@@ -742,7 +752,7 @@ __global__ __launch_bounds__(256) void k_recount_sorted(const CellDev *__restric
     constexpr int kPer = kCap / 256;
     __shared__ float sv[kCap];
     __shared__ uint16_t si[kCap];
-    __shared__ uint32_t marked[kCap + 1], scratch[8];  // marked[k]: recomputed b among the first k in order
+    __shared__ uint32_t marked[kCap + 1], scratch[8];  // marked[k]: recomputed b among the row's first k numbers
     __shared__ double sd[kCap];
     const int tid = threadIdx.x, lane = tid % kWave;
     const int64_t total = min(int64_t(*n_rows), max_rows);
@@ -755,23 +765,29 @@ __global__ __launch_bounds__(256) void k_recount_sorted(const CellDev *__restric
         const float *row = p32 + roff;
         const double *row64 = p64 + roff;
         const uint8_t *frow = flags + roff;
-        sort_row<kCap>(row + c.b0, nb, sv, si, marked, scratch);
-        uint32_t bits = 0, n_m;
+        const int nv = sort_row<kCap>(row + c.b0, nb, sv, si, marked, scratch);
+        uint32_t bits = 0, bits64 = 0, n_both;  // bits64: those whose FP64 distance is a number
+        double v64[kPer];
 #pragma unroll
         for (int m = 0; m < kPer; ++m) {
             const int k = kPer * tid + m;
-            if (k < nb && (frow[c.b0 + si[k]] & kMarked)) bits |= 1u << m;
+            if (k < nb && (frow[c.b0 + si[k]] & kMarked)) {
+                if (k < nv) bits |= 1u << m;
+                v64[m] = row64[c.b0 + si[k]];
+                if (v64[m] == v64[m]) bits64 |= 1u << m;
+            }
         }
-        uint32_t at = block_prefix(uint32_t(__popc(bits)), scratch, n_m);
+        const uint32_t before = block_prefix(uint32_t(__popc(bits)) | (uint32_t(__popc(bits64)) << 16), scratch, n_both);
+        uint32_t at = before & 0xFFFFu, at64 = before >> 16;
 #pragma unroll
         for (int m = 0; m < kPer; ++m) {
-            const int k = kPer * tid + m;
-            marked[k] = at;
-            if ((bits >> m) & 1u) sd[at++] = row64[c.b0 + si[k]];
+            marked[kPer * tid + m] = at;
+            at += (bits >> m) & 1u;
+            if ((bits64 >> m) & 1u) sd[at64++] = v64[m];
         }
-        if (tid == 255) marked[kCap] = n_m;
+        const int nm32 = int(n_both & 0xFFFFu), nm = int(n_both >> 16);
+        if (tid == 255) marked[kCap] = uint32_t(nm32);
         __syncthreads();
-        const int nm = int(n_m);
         for (int moved = 1; moved;) {
             int swapped = 0;
             for (int odd = 0; odd < 2; ++odd) {
@@ -792,12 +808,13 @@ __global__ __launch_bounds__(256) void k_recount_sorted(const CellDev *__restric
             const int al = c.a0 + a;
             if (c.exclude_self && al == xl) continue;
             const float da = row[al];
-            const int lb = count_below(sv, nb, da, false), ub = count_below(sv, nb, da, true);
-            int half = 2 * nb - lb - ub;
+            const int lb = count_below(sv, nv, da, false), ub = count_below(sv, nv, da, true);
+            int half = da == da ? 2 * nv - lb - ub : 0;
             if (frow[al] & kMarked) {
                 const double da64 = row64[al];
-                half -= 2 * nm - int(marked[lb]) - int(marked[ub]);
-                half += 2 * nm - count_below(sd, nm, da64, false) - count_below(sd, nm, da64, true);
+                if (da == da) half -= 2 * nm32 - int(marked[lb]) - int(marked[ub]);
+                if (da64 == da64)
+                    half += 2 * nm - count_below(sd, nm, da64, false) - count_below(sd, nm, da64, true);
             }
             cnt += unsigned(half);
         }

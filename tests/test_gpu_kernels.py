@@ -314,3 +314,37 @@ def test_sorted_rows_with_infinities(na, nb):
     f32, fl, _ = res.pairs(xs, ys)
     assert np.isinf(f32).sum() > 1000 and ((fl & 2) != 0).all()  # the margin is infinite too
     assert np.array_equal(res.half_units, orc.half_units)
+
+
+# Rows of large cells with NaN distances (features with NaN or infinities): a
+# comparison with a NaN is neither less nor equal, so it adds nothing, whatever its
+# place in the sorted row.  One NaN (the insertion sort of a bucket) and more than a
+# bucket takes, in the plain form's values and in the FP64 ones of the recheck.
+@pytest.mark.parametrize("n_odd", [1, 60])
+@pytest.mark.parametrize("precision,distance,value", [("fp32", "euclidean", np.nan), ("bf16", "angular", np.inf),
+                                                      ("bf16", "euclidean", np.nan)])
+@pytest.mark.parametrize("na,nb", [(40, 300), (12, 1025)])
+def test_sorted_rows_with_nan(na, nb, precision, distance, value, n_odd):
+    rng = np.random.default_rng(nb)
+    n = na + nb
+    x = rng.standard_normal((n, 8)).astype(np.float32)
+    x[rng.choice(np.arange(na, n), n_odd, replace=False), 3] = value
+    x[rng.choice(na, 3, replace=False), 5] = value
+    attrs = np.stack([np.r_[np.zeros(na, np.int32), np.ones(nb, np.int32)], np.zeros(n, np.int32)], 1)
+    w = workloads.Workload("nan", torch.from_numpy(x), np.arange(n + 1, dtype=np.int64), attrs, ["l", "g"], 0, [1], [])
+    print(f"[case] sorted rows with NaN na={na} nb={nb} {precision} {distance} n_odd={n_odd}", flush=True)
+    t, res = gpu_score(w, mode="pooled", precision=precision, distance=distance, margin=1e4, keep_pairs=True)
+    xs, ys = (v.ravel() for v in np.meshgrid(np.arange(n), np.arange(n), indexing="ij"))
+    f32, fl, f64 = res.pairs(xs, ys)
+    if precision == "bf16":
+        assert ((fl & 2) != 0)[xs != ys].all()
+    d = (f32 if precision == "fp32" else f64).reshape(n, n)
+    assert np.isnan(d[:na, na:]).any()
+    want = []
+    for A, B in ((np.arange(na), np.arange(na, n)), (np.arange(na, n), np.arange(na))):
+        s = 0
+        for i in A:
+            a, b = d[i, A[A != i]][:, None], d[i, B][None]
+            s += 2 * int((a < b).sum()) + int((a == b).sum())
+        want.append(s)
+    assert res.half_units.tolist() == want

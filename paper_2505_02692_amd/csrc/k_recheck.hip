@@ -16,7 +16,11 @@
 // through the same steps whatever the frames' places in the tiles and
 // whichever item comes first (a fused multiply-add chain over the features in
 // one fixed order), so equal inputs still give equal distances, and the two
-// orientations of a pair share one evaluation.
+// orientations of a pair share one evaluation.  Only where Euclidean distances of
+// frames with infinities are NaN does the order of comparisons show in the costs:
+// such a pair's transposed problem is swept by itself, with its own comparisons.
+// (An angular frame with an infinity is at NaN from every frame, and every path
+// then meets that row or column, in either orientation.)
 #include "device_common.h"
 #include "kernels.h"
 
@@ -113,7 +117,9 @@ __device__ __forceinline__ double shr1_cost(double v, Row16 r) {
 // half: the transposed problem, whose left is this one's up).  The costs are
 // the same in both.  Steps off a row's columns compute values that nothing
 // reads: the first column of a row takes +inf to its left, and a row's last
-// cell is read at its own step.
+// cell is read at its own step.  kFlip: the transposed problem alone, in the high
+// half, with the costs its own comparisons choose (they differ where NaN occur).
+template <bool kFlip>
 struct Sweep {
     double c = 0.0, up_prev = 0.0;
     uint32_t len = 0, lup_prev = 0;
@@ -124,8 +130,8 @@ struct Sweep {
         const double left = first ? inf : c;
         const bool from_diag = diag <= left && diag <= up;
         const bool from_left = row0 || left <= up;  // before up, rows as given
-        const bool from_up = up <= left;            // before left, transposed
-        const double best = from_diag ? diag : from_left ? left : up;
+        const bool from_up = (kFlip && first) || up <= left;  // before left, transposed
+        const double best = from_diag ? diag : (kFlip ? !from_up : from_left) ? left : up;
         const uint32_t lo = from_diag ? lup_prev : from_left ? len : lup;
         const uint32_t hi = from_diag ? lup_prev : from_up ? lup : len;
         up_prev = up;
@@ -140,10 +146,10 @@ struct Sweep {
 // fin = the step of the lane's result.  Distances are read four steps ahead;
 // the reads may run 8 past the last column and i before the first (the rows
 // lie one after another, so both stay in the tile or its pad of 8).
-template <typename Row16>
+template <typename Row16, bool kFlip = false>
 __device__ __forceinline__ void sweep_rows(const double *row, int i, int steps, int fin, double &cost,
                                            uint32_t &len) {
-    Sweep w;
+    Sweep<kFlip> w;
     const double *at = row - i;
     double da[4], db[4];
 #pragma unroll
@@ -231,14 +237,14 @@ __device__ __forceinline__ double ror1(double v) {
 //  Euclidean: the differences cannot go through a product without cancelling,
 //    so each lane keeps its row frame against all 16 column frames, which it
 //    gets by rotating them through the 16 lanes (DPP), and sums the squares of
-//    its quarter of the features.
+//    its quarter of the features.  Returns whether this lane met a NaN distance.
 //    (only where want(u, i, j))
 struct All {
     __device__ bool operator()(int, int, int) const { return true; }
 };
 template <typename T, bool kEuclid, int kT, int kStages = sizeof(T) == 4 ? 3 : 4, typename Ptr, typename At,
           typename Want = All>
-__device__ __forceinline__ void tile_distances(int n_tiles, Ptr &&ptr, int dim, At &&at, Want &&want = All{}) {
+__device__ __forceinline__ bool tile_distances(int n_tiles, Ptr &&ptr, int dim, At &&at, Want &&want = All{}) {
     const int lane = threadIdx.x % dev::kWave, i16 = lane % 16, q = lane / 16;
     const T *pa[kT], *pb[kT];
     int nr[kT], nc[kT];
@@ -253,6 +259,7 @@ __device__ __forceinline__ void tile_distances(int n_tiles, Ptr &&ptr, int dim, 
             pb[u] = b0 + int64_t(min(i16, nc[u] - 1)) * dim;
         }
     }
+    bool odd = false;
     if constexpr (kEuclid) {
         for (int u = 0; u < n_tiles; ++u) {
             const T *a_row = pa[0], *b_row = pb[0];
@@ -282,6 +289,7 @@ __device__ __forceinline__ void tile_distances(int n_tiles, Ptr &&ptr, int dim, 
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 const double s = sum_quarters(acc[r]);
+                odd = odd || s != s;
                 if (q == r / 4) *at(u, i16, j) = sqrt(s);
                 j = __builtin_amdgcn_update_dpp(0, j, 0x121, 0xf, 0xf, true);
             }
@@ -374,6 +382,7 @@ __device__ __forceinline__ void tile_distances(int n_tiles, Ptr &&ptr, int dim, 
                 }
             }
     }
+    return odd;
 }
 
 // A listed pair: task items x (low word) and y (high word) of one group.
@@ -394,30 +403,54 @@ __device__ __forceinline__ PairSlots slots_of(const Pair &pr, const int32_t *__r
     return {base + (pr.x - i0) * n + (pr.y - i0), base + (pr.y - i0) * n + (pr.x - i0)};
 }
 
-// The value of both orientations, from the cost and the packed path lengths.
-__device__ __forceinline__ void store_pair(const Pair &pr, double cost, uint32_t len, int norm,
+// Costs of both orientations and their packed path lengths, and the pair's values.
+struct Costs {
+    double xy, yx;
+    uint32_t len;
+    __device__ __forceinline__ double value_xy(int norm) const {
+        return norm == FABX_NORM_PATH ? xy / double(len & 0xFFFFu) : xy;
+    }
+    __device__ __forceinline__ double value_yx(int norm) const {
+        return norm == FABX_NORM_PATH ? yx / double(len >> 16) : yx;
+    }
+};
+__device__ __forceinline__ void store_pair(const Pair &pr, const Costs &c, int norm,
                                            const int32_t *__restrict__ item_group,
                                            const int64_t *__restrict__ g_item0, const int64_t *__restrict__ g_n,
                                            const int64_t *__restrict__ g_pair_base, double *__restrict__ p64) {
     const PairSlots s = slots_of(pr, item_group, g_item0, g_n, g_pair_base);
-    const bool path = norm == FABX_NORM_PATH;
-    p64[s.xy] = path ? cost / double(len & 0xFFFFu) : cost;
-    p64[s.yx] = path ? cost / double(len >> 16) : cost;
+    p64[s.xy] = c.value_xy(norm);
+    p64[s.yx] = c.value_yx(norm);
+}
+
+// Costs of a pair by sweep_rows; odd: its tile holds a NaN (uniform over the wave).
+template <typename Row16>
+__device__ __forceinline__ Costs sweep_pair(const double *row, int i, int steps, int fin, bool odd) {
+    Costs c{0.0, 0.0, 0};
+    sweep_rows<Row16>(row, i, steps, fin, c.xy, c.len);
+    c.yx = c.xy;
+    if (odd) {
+        uint32_t len = 0;
+        sweep_rows<Row16, true>(row, i, steps, fin, c.yx, len);
+        c.len = (c.len & 0xFFFFu) | (len & 0xFFFF0000u);
+    }
+    return c;
 }
 
 // Tiles t0, t0 + step, ... (row-major) of a pair's frame distances into dm, two
-// at a time.
+// at a time; whether this lane met a NaN.
 template <typename T, bool kEuclid>
-__device__ __forceinline__ void pair_tiles(const T *__restrict__ feat, int dim, const Pair &pr, int N, int M,
+__device__ __forceinline__ bool pair_tiles(const T *__restrict__ feat, int dim, const Pair &pr, int N, int M,
                                            const int64_t *__restrict__ item_src, int t0, int step, double *dm,
                                            int ld_dm) {
     const T *fx = feat + item_src[pr.x] * int64_t(dim);
     const T *fy = feat + item_src[pr.y] * int64_t(dim);
     const int tm = (M + 15) / 16, n_tiles = (N + 15) / 16 * tm;
+    bool odd = false;
 #pragma unroll 1
     for (int t = t0; t < n_tiles; t += 2 * step) {
         const int ti[2] = {t / tm, (t + step) / tm}, tj[2] = {t % tm, (t + step) % tm};
-        tile_distances<T, kEuclid, 2>(
+        odd |= tile_distances<T, kEuclid, 2>(
             t + step < n_tiles ? 2 : 1,
             [&](int u, const T *&a, int &nr, const T *&b, int &nc) {
                 a = fx + int64_t(16 * ti[u]) * dim;
@@ -427,6 +460,7 @@ __device__ __forceinline__ void pair_tiles(const T *__restrict__ feat, int dim, 
             },
             dim, [&](int u, int r, int c) { return dm + (16 * ti[u] + r) * ld_dm + 16 * tj[u] + c; });
     }
+    return odd;
 }
 
 // Pairs of items of at most 16 frames: one tile each.  A wave takes kP pairs
@@ -453,9 +487,10 @@ __device__ __forceinline__ void small_pairs(const T *__restrict__ feat, int dim,
     const int lane = threadIdx.x % dev::kWave, i = lane % 16, q = lane / 16;
     const int n_pairs = int(min<int64_t>(kP, total - e0));
     // (the previous DTW's reads of dm are over: same wave, LDS in order)
+    bool odd = false;
 #pragma unroll 1
     for (int h = 0; h < n_pairs; h += 2)
-        tile_distances<T, kEuclid, kP < 2 ? 1 : 2>(
+        odd |= tile_distances<T, kEuclid, kP < 2 ? 1 : 2>(
             min(2, n_pairs - h),
             [&](int u, const T *&a, int &nr, const T *&b, int &nc) {
                 const Pair pr = pair_of(list[e0 + h + u]);
@@ -472,11 +507,9 @@ __device__ __forceinline__ void small_pairs(const T *__restrict__ feat, int dim,
     int steps = N + M - 1;
 #pragma unroll
     for (int o = 32; o >= 16; o >>= 1) steps = max(steps, __shfl_xor(steps, o, dev::kWave));
-    double cost = 0.0;
-    uint32_t len = 0;
-    sweep_rows<std::true_type>(dm + (qp * 16 + i) * kTileLd, i,
-                               __builtin_amdgcn_readfirstlane(steps), N + M - 2, cost, len);
-    if (q == qp && i == N - 1) store_pair(pr, cost, len, norm, item_group, g_item0, g_n, g_pair_base, p64);
+    const Costs c = sweep_pair<std::true_type>(dm + (qp * 16 + i) * kTileLd, i, __builtin_amdgcn_readfirstlane(steps),
+                                               N + M - 2, kEuclid && __any(odd));
+    if (q == qp && i == N - 1) store_pair(pr, c, norm, item_group, g_item0, g_n, g_pair_base, p64);
     __builtin_amdgcn_wave_barrier();
 }
 
@@ -541,12 +574,11 @@ __global__ __launch_bounds__(256, 3) void k_recheck_mid(const T *__restrict__ fe
     for (int64_t e = lo + int64_t(blockIdx.x / 8) * 4 + w; e < hi; e += int64_t(gridDim.x / 8) * 4) {
         const Pair pr = pair_of(list[e]);
         const int N = item_len[pr.x], M = item_len[pr.y];
-        pair_tiles<T, kEuclid>(feat, dim, pr, N, M, item_src, 0, 1, dm, kLd);
+        const bool odd = pair_tiles<T, kEuclid>(feat, dim, pr, N, M, item_src, 0, 1, dm, kLd);
         __builtin_amdgcn_wave_barrier();
-        double cost = 0.0;
-        uint32_t len = 0;
-        sweep_rows<std::false_type>(dm + min(lane, kMidL - 1) * kLd, lane, N + M - 1, N + M - 2, cost, len);
-        if (lane == N - 1) store_pair(pr, cost, len, norm, item_group, g_item0, g_n, g_pair_base, p64);
+        const Costs c = sweep_pair<std::false_type>(dm + min(lane, kMidL - 1) * kLd, lane, N + M - 1, N + M - 2,
+                                                    kEuclid && __any(odd));
+        if (lane == N - 1) store_pair(pr, c, norm, item_group, g_item0, g_n, g_pair_base, p64);
         __builtin_amdgcn_wave_barrier();
     }
 }
@@ -566,6 +598,11 @@ __global__ __launch_bounds__(256, 3) void k_recheck_tiled(const T *__restrict__ 
                                                           PairLists lists, int norm, double *__restrict__ p64) {
     constexpr int kLd = kMaxL + 1;
     __shared__ double dm[kMaxL * kLd + 8 + kMaxL];
+    __shared__ int odd_s;  // the pair has a NaN distance
+    if constexpr (kEuclid) {
+        if (threadIdx.x == 0) odd_s = 0;
+        __syncthreads();
+    }
     const int lane = threadIdx.x % dev::kWave;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / dev::kWave);
     const int64_t n_mid = *lists.n_mid < kMidMin ? int64_t(*lists.n_mid) : 0;
@@ -575,13 +612,13 @@ __global__ __launch_bounds__(256, 3) void k_recheck_tiled(const T *__restrict__ 
         // the large class fills its list from the end
         const Pair pr = pair_of(e < n_mid ? lists.mid[e] : lists.small_large[lists.cap - 1 - (e - n_mid)]);
         const int N = item_len[pr.x], M = item_len[pr.y];
-        pair_tiles<T, kEuclid>(feat, dim, pr, N, M, item_src, w, 4, dm, kLd);
+        if (pair_tiles<T, kEuclid>(feat, dim, pr, N, M, item_src, w, 4, dm, kLd) && kEuclid) odd_s = 1;
         __syncthreads();
         if (w == 0) {
-            double cost = 0.0;
-            uint32_t len = 0;
-            sweep_rows<std::false_type>(dm + lane * kLd, lane, N + M - 1, N + M - 2, cost, len);
-            if (lane == N - 1) store_pair(pr, cost, len, norm, item_group, g_item0, g_n, g_pair_base, p64);
+            const bool odd = kEuclid && __builtin_amdgcn_readfirstlane(odd_s) != 0;
+            const Costs c = sweep_pair<std::false_type>(dm + lane * kLd, lane, N + M - 1, N + M - 2, odd);
+            if (lane == N - 1) store_pair(pr, c, norm, item_group, g_item0, g_n, g_pair_base, p64);
+            if (odd && lane == 0) odd_s = 0;
         }
         __syncthreads();
     }
@@ -616,6 +653,11 @@ __global__ __launch_bounds__(320, 3) void k_long_dtw(const T *__restrict__ feat,
     __shared__ double dm[dev::kWave * kLd];        // [row of chunk][ring column]
     __shared__ double rowc[kLongMax];              // previous chunk's last row: costs
     __shared__ uint32_t rowl[kLongMax];            // and path lengths
+    __shared__ int odd_s;                          // the pair has a NaN distance
+    if constexpr (kEuclid) {
+        if (threadIdx.x == 0) odd_s = 0;
+        __syncthreads();
+    }
     const int lane = threadIdx.x % dev::kWave;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / dev::kWave);
     for (int64_t e = blockIdx.x; e < n_list; e += gridDim.x) {
@@ -631,81 +673,95 @@ __global__ __launch_bounds__(320, 3) void k_long_dtw(const T *__restrict__ feat,
         const T *fx = feat + item_src[pr.x] * int64_t(dim);
         const T *fy = feat + item_src[pr.y] * int64_t(dim);
         const int n_tiles = (M + kTc - 1) / kTc;
-        Sweep s;
-        for (int r0 = 0; r0 < N; r0 += dev::kWave) {
-            const int nr = min(dev::kWave, N - r0);
-            s = Sweep{};
-            int t = 0;
-            const int steps = M + nr - 1;
-            // tile k is made in phase k and swept in phase k + 1
-            for (int k = 0; k <= n_tiles; ++k) {
-                if (w < 4) {
-                    const int r = 16 * w, c0 = k * kTc;
-                    if (k < n_tiles && r < nr) {
-                        const int nc = min(kTc, M - c0);
-                        double *out = dm + r * kLd + (k % kRing) * kTc;
-                        tile_distances<T, kEuclid, 2, 2>(
-                            nc > 16 ? 2 : 1,
-                            [&](int u, const T *&a, int &na, const T *&b, int &nb) {
-                                a = fx + int64_t(r0 + r) * dim;
-                                b = fy + int64_t(c0 + 16 * u) * dim;
-                                na = min(16, nr - r);
-                                nb = min(16, nc - 16 * u);
-                            },
-                            dim,
-                            [&](int u, int i, int j) { return out + i * kLd + 16 * u + j; });
-                    }
-                } else if (k > 0) {
-                    const int i = lane, t_end = k == n_tiles ? steps : k * kTc;
-                    // four steps' distances (and the row above the chunk, lane 0's) at a time
-                    auto four = [&](const double (&d)[4], const double (&ru)[4], const uint32_t (&rl)[4], int n) {
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            if (q >= n) break;
-                            const int j = t - i;
-                            double up = shr1_cost(s.c, std::false_type{});  // lane i - 1's cost, step t - 1
-                            uint32_t lup = uint32_t(shr1(0, int(s.len), std::false_type{}));
-                            if (r0 > 0 && i == 0) {
-                                up = ru[q];
-                                lup = rl[q];
-                            }
-                            s.step(j == 0, r0 == 0 && i == 0, d[q], up, lup);
-                            if (i == nr - 1 && j >= 0 && j < M) {  // this chunk's last row, for the next chunk
-                                rowc[j] = s.c;
-                                rowl[j] = s.len;
-                            }
-                            ++t;
+        auto sweep = [&](auto &s) {
+            for (int r0 = 0; r0 < N; r0 += dev::kWave) {
+                const int nr = min(dev::kWave, N - r0);
+                s = {};
+                int t = 0;
+                const int steps = M + nr - 1;
+                // tile k is made in phase k and swept in phase k + 1
+                for (int k = 0; k <= n_tiles; ++k) {
+                    if (w < 4) {
+                        const int r = 16 * w, c0 = k * kTc;
+                        if (k < n_tiles && r < nr) {
+                            const int nc = min(kTc, M - c0);
+                            double *out = dm + r * kLd + (k % kRing) * kTc;
+                            const bool odd = tile_distances<T, kEuclid, 2, 2>(
+                                nc > 16 ? 2 : 1,
+                                [&](int u, const T *&a, int &na, const T *&b, int &nb) {
+                                    a = fx + int64_t(r0 + r) * dim;
+                                    b = fy + int64_t(c0 + 16 * u) * dim;
+                                    na = min(16, nr - r);
+                                    nb = min(16, nc - 16 * u);
+                                },
+                                dim,
+                                [&](int u, int i, int j) { return out + i * kLd + 16 * u + j; });
+                            if (kEuclid && odd) odd_s = 1;
                         }
-                    };
-                    auto fetch = [&](double (&d)[4], double (&ru)[4], uint32_t (&rl)[4], int t0) {
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            d[q] = dm[i * kLd + ((t0 + q - i) & (kRing * kTc - 1))];
-                            const int j = min(t0 + q, kLongMax - 1);
-                            ru[q] = r0 > 0 ? rowc[j] : 0.0;
-                            rl[q] = r0 > 0 ? rowl[j] : 0;
+                    } else if (k > 0) {
+                        const int i = lane, t_end = k == n_tiles ? steps : k * kTc;
+                        // four steps' distances (and the row above the chunk, lane 0's) at a time
+                        auto four = [&](const double (&d)[4], const double (&ru)[4], const uint32_t (&rl)[4], int n) {
+    #pragma unroll
+                            for (int q = 0; q < 4; ++q) {
+                                if (q >= n) break;
+                                const int j = t - i;
+                                double up = shr1_cost(s.c, std::false_type{});  // lane i - 1's cost, step t - 1
+                                uint32_t lup = uint32_t(shr1(0, int(s.len), std::false_type{}));
+                                if (r0 > 0 && i == 0) {
+                                    up = ru[q];
+                                    lup = rl[q];
+                                }
+                                s.step(j == 0, r0 == 0 && i == 0, d[q], up, lup);
+                                if (i == nr - 1 && j >= 0 && j < M) {  // this chunk's last row, for the next chunk
+                                    rowc[j] = s.c;
+                                    rowl[j] = s.len;
+                                }
+                                ++t;
+                            }
+                        };
+                        auto fetch = [&](double (&d)[4], double (&ru)[4], uint32_t (&rl)[4], int t0) {
+    #pragma unroll
+                            for (int q = 0; q < 4; ++q) {
+                                d[q] = dm[i * kLd + ((t0 + q - i) & (kRing * kTc - 1))];
+                                const int j = min(t0 + q, kLongMax - 1);
+                                ru[q] = r0 > 0 ? rowc[j] : 0.0;
+                                rl[q] = r0 > 0 ? rowl[j] : 0;
+                            }
+                        };
+                        double d0[4], d1[4], u0[4], u1[4];
+                        uint32_t l0[4], l1[4];
+                        fetch(d0, u0, l0, t);
+                        while (t < t_end) {
+                            fetch(d1, u1, l1, t + 4);
+                            four(d0, u0, l0, t_end - t);
+                            if (t >= t_end) break;
+                            fetch(d0, u0, l0, t + 4);
+                            four(d1, u1, l1, t_end - t);
                         }
-                    };
-                    double d0[4], d1[4], u0[4], u1[4];
-                    uint32_t l0[4], l1[4];
-                    fetch(d0, u0, l0, t);
-                    while (t < t_end) {
-                        fetch(d1, u1, l1, t + 4);
-                        four(d0, u0, l0, t_end - t);
-                        if (t >= t_end) break;
-                        fetch(d0, u0, l0, t + 4);
-                        four(d1, u1, l1, t_end - t);
                     }
+                    __syncthreads();
                 }
+            }
+        };
+        // lane (N - 1) % 64 of wave 4 ends on cell (N - 1, M - 1)
+        Sweep<false> s;
+        sweep(s);
+        Costs c{s.c, s.c, s.len};
+        if constexpr (kEuclid) {
+            const bool odd = odd_s != 0;  // uniform: written before the sweep's last barrier
+            __syncthreads();              // and not again before every wave has read it
+            if (odd) {
+                Sweep<true> t;
+                sweep(t);
+                c = {s.c, t.c, (s.len & 0xFFFFu) | (t.len & 0xFFFF0000u)};
+                if (threadIdx.x == 0) odd_s = 0;
                 __syncthreads();
             }
         }
-        // lane (N - 1) % 64 of wave 4 ended on cell (N - 1, M - 1)
         if (w == 4 && lane == (N - 1) % dev::kWave) {
             const PairSlots sl = slots_of(pr, item_group, g_item0, g_n, g_pair_base);
-            const bool path = norm == FABX_NORM_PATH;
-            const double vxy = path ? s.c / double(s.len & 0xFFFFu) : s.c;
-            const double vyx = path ? s.c / double(s.len >> 16) : s.c;
+            const double vxy = c.value_xy(norm), vyx = c.value_yx(norm);
             p64[sl.xy] = vxy;
             p64[sl.yx] = vyx;
             p32[sl.xy] = float(vxy);

@@ -348,3 +348,45 @@ def test_sorted_rows_with_nan(na, nb, precision, distance, value, n_odd):
             s += 2 * int((a < b).sum()) + int((a == b).sum())
         want.append(s)
     assert res.half_units.tolist() == want
+
+
+# The FP64 recheck of features with infinities or NaN.  Euclidean distances of frames
+# with equal infinities are NaN among infinite ones: there the order of comparisons
+# shows in the costs, and each orientation has its own.
+@pytest.mark.parametrize("norm", ["path", "none"])
+@pytest.mark.parametrize("distance,value", [("angular", np.inf), ("euclidean", np.nan), ("euclidean", np.inf)])
+@pytest.mark.parametrize("case", list(RECHECK))
+def test_fp64_recheck_nan(case, distance, value, norm):
+    w = workloads.batched_c4(centroid_std=0.1, seed=82, **dict(RECHECK[case], dtype=torch.float32))
+    rng = np.random.default_rng(7)
+    for k in range(0, w.n_items, 2):
+        lo, hi = int(w.offsets[k]), int(w.offsets[k + 1])
+        for f in rng.integers(lo, hi, 3):
+            w.features[int(f), int(rng.integers(0, 2))] = value if k % 3 else -value
+    print(f"[case] recheck with NaN {case} {distance} {value} {norm} items={w.n_items}", flush=True)
+    t, res = gpu_score(w, norm=norm, distance=distance, margin=1e4, keep_pairs=True)
+    orc = oracle.score(w.features_f32_host(), w.offsets, w.attrs, w.on, w.by, w.across, "dtw", norm, distance=distance)
+    xs, ys, want = [], [], []
+    for items, m in orc.groups.values():
+        i, j = np.nonzero(~np.eye(len(items), dtype=bool))
+        xs.append(items[i])
+        ys.append(items[j])
+        want.append(m[i, j])
+    xs, ys, want = (np.concatenate(v) for v in (xs, ys, want))
+    _, fl, f64 = res.pairs(xs, ys)
+    # pairs with an item of more than 64 frames are in FP64 from the start, marked or not
+    # (an unmarked one's value is returned rounded to FP32)
+    length, marked = np.diff(w.offsets), (fl & 2) != 0
+    known = marked | (np.maximum(length[xs], length[ys]) > 64)
+    assert np.isnan(want[known]).any()
+    if np.isinf(value) and distance == "euclidean":
+        swapped = {(int(x), int(y)): v for x, y, v in zip(xs, ys, want)}
+        assert any(np.isnan(v) != np.isnan(swapped[int(y), int(x)]) for x, y, v in zip(xs, ys, want))
+        assert known.mean() > 0.9  # infinite values tie, and are not compared in FP64 for that alone
+    else:
+        assert known.all()
+        assert np.array_equal(res.half_units, orc.half_units)
+    assert np.array_equal(np.isnan(f64[known]), np.isnan(want[known]))
+    assert np.array_equal(np.isinf(f64[known]), np.isinf(want[known]))
+    ok = marked & np.isfinite(want)
+    assert (np.abs(f64[ok] - want[ok]) <= 1e-12 * np.maximum(want[ok], 1.0)).all()

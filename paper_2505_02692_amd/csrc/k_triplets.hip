@@ -339,133 +339,127 @@ __device__ __forceinline__ uint32_t block_prefix(uint32_t v, uint32_t *scratch, 
     return before + incl - v;
 }
 
-// Whether value v at place i comes after value u at place j in a sorted row: NaN
-// after every number, equal values (and NaN) by place.
-__device__ __forceinline__ bool comes_after(float v, int i, float u, int j) {
-    return v > u || (v == u ? i > j : v != v && (u == u || i > j));
+// v of lane ^ kD.
+template <int kD>
+__device__ __forceinline__ uint32_t xor_lane(uint32_t v) {
+    const int i = int(v);
+    if constexpr (kD == 1) return uint32_t(__builtin_amdgcn_update_dpp(0, i, 0xB1, 0xf, 0xf, true));  // quad 1 0 3 2
+    if constexpr (kD == 2) return uint32_t(__builtin_amdgcn_update_dpp(0, i, 0x4E, 0xf, 0xf, true));  // quad 2 3 0 1
+    if constexpr (kD == 4) {  // half rows mirrored, then the quads
+        const int m = __builtin_amdgcn_update_dpp(0, i, 0x141, 0xf, 0xf, true);
+        return uint32_t(__builtin_amdgcn_update_dpp(0, m, 0x1B, 0xf, 0xf, true));
+    }
+    if constexpr (kD == 8) return uint32_t(__builtin_amdgcn_update_dpp(0, i, 0x128, 0xf, 0xf, true));  // row_ror:8
+    if constexpr (kD == 16) {
+        const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+        return threadIdx.x & 16 ? r[0] : r[1];
+    }
+    const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    return threadIdx.x & 32 ? r[0] : r[1];
 }
 
-// The n <= kCap values src[0..n) sorted into sv, with their positions in si, by
+// The n <= 256 kPer values src[0..n) sorted into sv, with their positions in si, by
 // a 256-thread block; returns how many are numbers (any NaN lie last: a comparison
-// with one is never true, so the counts leave them out).  The values go to kCap
-// buckets of equal width between the least and the largest (their bucket grows with
-// the value, NaN in the last), each bucket's few values are then sorted by
-// insertion.  Values that crowd a bucket (many exact ties or NaN, an infinity, which
-// leaves the others in one bucket) take the bitonic sort instead, padded to a power
-// of two with NaN of later places.  Bound by LDS
-// latency: 9 barriers where the bitonic sort of 1024 values has 55 (the sorted
-// counting of 7.3e10 triples, |B| up to 1000: 5.8 -> 3.0 ms).
-template <int kCap>
-__device__ __forceinline__ int sort_row(const float *__restrict__ src, int n, float *sv, uint16_t *si,
-                                        uint32_t *bucket, uint32_t *scratch) {
-    constexpr int kPer = kCap / 256, kCrowd = 24;
-    const int tid = threadIdx.x, lane = tid % kWave, w = tid / kWave;
-    auto numbers = [&] { return sv[n - 1] == sv[n - 1] ? n : count_below(sv, n, __builtin_inff(), true); };
-    float v[kPer], lo = __builtin_inff(), hi = -__builtin_inff();
+// with one is never true, so the counts leave them out).  A bitonic sort of kPer
+// consecutive places a thread, in registers: an exchange of places lies within a
+// thread, a wave (lane exchanges), or, three times in all, between waves through sv
+// and si.  Keys are the values' bits in an unsigned order, NaN above the numbers and
+// the padding above both.  Where a merge descends the keys are inverted, so that the
+// lower place always takes the lower key.  Its time does not depend on the values
+// (buckets of equal width left rows of tied or far-flung values to a sort through
+// LDS, and cost such tasks 30%).  Bound by the vector ALUs.  The sorted counting of
+// 16,000 rows of 2000 values: 1.37 ms with a bitonic sort through LDS, 0.59 here;
+// 40,000 rows of 500: 0.71 and 0.36.
+template <int kPer>
+__device__ __forceinline__ int sort_places(const float *__restrict__ src, int n, float *sv, uint16_t *si) {
+    constexpr int kLogPer = kPer == 1 ? 0 : kPer == 2 ? 1 : kPer == 4 ? 2 : kPer == 8 ? 3 : 4;
+    // merges needed (with one place a thread the values start in the first n places)
+    const int merges = kPer > 1 || n < 2 ? kLogPer + 8 : 32 - __builtin_clz(unsigned(n - 1));
+    const int tid = threadIdx.x;
+    uint32_t key[kPer], id[kPer];
 #pragma unroll
     for (int m = 0; m < kPer; ++m) {
-        const int e = tid + 256 * m;
-        bucket[e] = 0;
-        if (e < n) {
-            v[m] = src[e];
-            lo = fminf(lo, v[m]);
-            hi = fmaxf(hi, v[m]);
+        id[m] = uint32_t(tid + 256 * m);
+        key[m] = ~0u;
+        if (int(id[m]) < n) {
+            const float v = src[id[m]];
+            const uint32_t b = __float_as_uint(v);
+            key[m] = v == v ? b ^ (uint32_t(int(b) >> 31) | 0x80000000u) : ~1u;
         }
     }
+    // the lower of this place's and the other's key, or the higher where `upper`
+    auto keep = [](uint32_t &k, uint32_t &i, uint32_t ok, uint32_t oi, bool upper) {
+        const bool take = upper ? k < ok : ok < k;
+        k = take ? ok : k;
+        i = take ? oi : i;
+    };
+    auto lanes = [&](auto d_tag) {
+        constexpr int d = decltype(d_tag)::value;
+        const bool upper = (tid & d) != 0;
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        lo = fminf(lo, __shfl_xor(lo, o, kWave));
-        hi = fmaxf(hi, __shfl_xor(hi, o, kWave));
-    }
-    if (lane == 0) {
-        scratch[w] = __float_as_uint(lo);
-        scratch[4 + w] = __float_as_uint(hi);
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        lo = fminf(lo, __uint_as_float(scratch[k]));
-        hi = fmaxf(hi, __uint_as_float(scratch[4 + k]));
-    }
-    const float scale = hi > lo ? float(kCap - 1) / (hi - lo) : 0.0f;
-    int at[kPer];
-    uint32_t pos[kPer];
-#pragma unroll
-    for (int m = 0; m < kPer; ++m)
-        if (tid + 256 * m < n) {
-            at[m] = v[m] == v[m] ? int(fminf(fmaxf((v[m] - lo) * scale, 0.0f), float(kCap - 1))) : kCap - 1;
-            pos[m] = atomicAdd(&bucket[at[m]], 1u);
-        }
-    __syncthreads();
-    // bucket counts -> first places; each thread has kPer consecutive buckets
-    uint32_t cnt[kPer], sum = 0, crowd = 0, total;
-#pragma unroll
-    for (int m = 0; m < kPer; ++m) {
-        cnt[m] = bucket[kPer * tid + m];
-        sum += cnt[m];
-        crowd |= cnt[m] > kCrowd ? 1u : 0u;
-    }
-    const uint32_t base = block_prefix(sum, scratch, total);
-    uint32_t run = base;
-#pragma unroll
-    for (int m = 0; m < kPer; ++m) {
-        bucket[kPer * tid + m] = run;
-        run += cnt[m];
-    }
-    if (__syncthreads_or(int(crowd)) == 0) {
-#pragma unroll
-        for (int m = 0; m < kPer; ++m)
-            if (tid + 256 * m < n) {
-                const uint32_t k = bucket[at[m]] + pos[m];
-                sv[k] = v[m];
-                si[k] = uint16_t(tid + 256 * m);
-            }
-        __syncthreads();
-        uint32_t first = base;
+        for (int m = 0; m < kPer; ++m) keep(key[m], id[m], xor_lane<d>(key[m]), xor_lane<d>(id[m]), upper);
+    };
+    uint32_t *xk = reinterpret_cast<uint32_t *>(sv);
+    auto waves = [&](int d) {
 #pragma unroll
         for (int m = 0; m < kPer; ++m) {
-            for (uint32_t k = first + 1; k < first + cnt[m]; ++k) {
-                const float x = sv[k];
-                const uint16_t xi = si[k];
-                uint32_t p = k;
-                for (; p > first && comes_after(sv[p - 1], si[p - 1], x, xi); --p) {
-                    sv[p] = sv[p - 1];
-                    si[p] = si[p - 1];
-                }
-                sv[p] = x;
-                si[p] = xi;
-            }
-            first += cnt[m];
+            xk[256 * m + tid] = key[m];
+            si[256 * m + tid] = uint16_t(id[m]);
         }
         __syncthreads();
-        return numbers();
+#pragma unroll
+        for (int m = 0; m < kPer; ++m)
+            keep(key[m], id[m], xk[256 * m + (tid ^ d)], si[256 * m + (tid ^ d)], (tid & d) != 0);
+        __syncthreads();
+    };
+    // merges of 2^p places
+#pragma unroll 1
+    for (int p = 1; p <= merges; ++p) {
+#pragma unroll
+        for (int m = 0; m < kPer; ++m) {  // (the last merge ascends where the values are)
+            const uint32_t at = uint32_t(tid * kPer + m);
+            key[m] ^= 0u - (((at >> p) ^ (p > 1 ? at >> (p - 1) : 0u)) & 1u);
+        }
+        if (p > kLogPer + 7) waves(128);
+        if (p > kLogPer + 6) waves(64);
+        if (p > kLogPer + 5) lanes(std::integral_constant<int, 32>{});
+        if (p > kLogPer + 4) lanes(std::integral_constant<int, 16>{});
+        if (p > kLogPer + 3) lanes(std::integral_constant<int, 8>{});
+        if (p > kLogPer + 2) lanes(std::integral_constant<int, 4>{});
+        if (p > kLogPer + 1) lanes(std::integral_constant<int, 2>{});
+        if (p > kLogPer) lanes(std::integral_constant<int, 1>{});
+#pragma unroll
+        for (int d = kPer / 2; d > 0; d /= 2)
+            if ((1 << p) > d)
+#pragma unroll
+                for (int m = 0; m < kPer; ++m)
+                    if ((m & d) == 0 && key[m + d] < key[m]) {
+                        const uint32_t k = key[m], i = id[m];
+                        key[m] = key[m + d];
+                        id[m] = id[m + d];
+                        key[m + d] = k;
+                        id[m + d] = i;
+                    }
     }
-    int n2 = 2;
-    while (n2 < n) n2 <<= 1;
-    for (int j = tid; j < n2; j += 256) {
-        sv[j] = j < n ? src[j] : __builtin_nanf("");
-        si[j] = uint16_t(j);
+#pragma unroll
+    for (int m = 0; m < kPer; ++m) {
+        const uint32_t b = key[m] ^ (uint32_t(~int(key[m]) >> 31) | 0x80000000u);
+        sv[tid * kPer + m] = key[m] >= ~1u ? __builtin_nanf("") : __uint_as_float(b);
+        si[tid * kPer + m] = uint16_t(id[m]);
     }
     __syncthreads();
-    for (int k = 2; k <= n2; k <<= 1)
-        for (int jj = k >> 1; jj > 0; jj >>= 1) {
-            for (int i = tid; i < n2; i += 256) {
-                const int l = i ^ jj;
-                if (l > i) {
-                    const bool up = (i & k) == 0;
-                    const float vi = sv[i], vl = sv[l];
-                    const uint16_t pi = si[i], pl = si[l];
-                    if (comes_after(vi, pi, vl, pl) == up) {
-                        sv[i] = vl;
-                        sv[l] = vi;
-                        si[i] = pl;
-                        si[l] = pi;
-                    }
-                }
-            }
-            __syncthreads();
-        }
-    return numbers();
+    return sv[n - 1] == sv[n - 1] ? n : count_below(sv, n, __builtin_inff(), true);
+}
+// As few places a thread as hold the row (n <= kCap).
+template <int kCap>
+__device__ __forceinline__ int sort_row(const float *__restrict__ src, int n, float *sv, uint16_t *si) {
+    if (n <= 256) return sort_places<1>(src, n, sv, si);
+    if (n <= 512) return sort_places<2>(src, n, sv, si);
+    if (kCap <= 1024 || n <= 1024) return sort_places<4>(src, n, sv, si);
+    if constexpr (kCap > 1024) {
+        if (n <= 2048) return sort_places<8>(src, n, sv, si);
+        return sort_places<16>(src, n, sv, si);
+    }
 }
 
 // Large cells, one block per unit (cell, one x): the row's distances to B are
@@ -490,7 +484,6 @@ __global__ __launch_bounds__(256) void k_triplets_sorted(const CellDev *__restri
     if (scale) margin *= __uint_as_float(*scale);  // margin in units of the largest frame length
     __shared__ float sv[kCap];
     __shared__ uint16_t si[kCap];
-    __shared__ uint32_t bucket[kCap], scratch[8];
     __shared__ unsigned long long red[4];
     __shared__ int bad[4];
     const int tid = threadIdx.x, lane = tid % kWave, w = tid / kWave;
@@ -504,7 +497,7 @@ __global__ __launch_bounds__(256) void k_triplets_sorted(const CellDev *__restri
         const int xl = c.x0 + xi;
         const float *row = p32 + base + int64_t(xl) * n;
         uint8_t *frow = flags ? flags + base + int64_t(xl) * n : nullptr;
-        const int nv = sort_row<kCap>(row + c.b0, nb, sv, si, bucket, scratch);
+        const int nv = sort_row<kCap>(row + c.b0, nb, sv, si);
         // count, near ties, non-robust pairs
         unsigned long long cnt = 0;
         int dirty = 0, all_b = 0, all_a = 0;
@@ -752,7 +745,7 @@ __global__ __launch_bounds__(256) void k_recount_sorted(const CellDev *__restric
     constexpr int kPer = kCap / 256;
     __shared__ float sv[kCap];
     __shared__ uint16_t si[kCap];
-    __shared__ uint32_t marked[kCap + 1], scratch[8];  // marked[k]: recomputed b among the row's first k numbers
+    __shared__ uint32_t marked[kCap + 1], scratch[4];  // marked[k]: recomputed b among the row's first k numbers
     __shared__ double sd[kCap];
     const int tid = threadIdx.x, lane = tid % kWave;
     const int64_t total = min(int64_t(*n_rows), max_rows);
@@ -765,7 +758,7 @@ __global__ __launch_bounds__(256) void k_recount_sorted(const CellDev *__restric
         const float *row = p32 + roff;
         const double *row64 = p64 + roff;
         const uint8_t *frow = flags + roff;
-        const int nv = sort_row<kCap>(row + c.b0, nb, sv, si, marked, scratch);
+        const int nv = sort_row<kCap>(row + c.b0, nb, sv, si);
         uint32_t bits = 0, bits64 = 0, n_both;  // bits64: those whose FP64 distance is a number
         double v64[kPer];
 #pragma unroll

@@ -390,3 +390,35 @@ def test_fp64_recheck_nan(case, distance, value, norm):
     assert np.array_equal(np.isinf(f64[known]), np.isinf(want[known]))
     ok = marked & np.isfinite(want)
     assert (np.abs(f64[ok] - want[ok]) <= 1e-12 * np.maximum(want[ok], 1.0)).all()
+
+
+# Rows of large cells at the edges of the sort's sizes (64 places a wave, 256 to 4096
+# a block), with many equal values and one far away: counts by the definition from
+# the pair values they compare, and every near tie marked.
+@pytest.mark.parametrize("precision", ["fp32", "bf16"])
+@pytest.mark.parametrize("nb", [2, 64, 65, 128, 129, 256, 257, 512, 513, 1024, 2048, 2049])
+def test_sorted_row_sizes(nb, precision):
+    rng = np.random.default_rng(nb)
+    na = max(2, -(-8192 // nb))
+    n = na + nb
+    x = rng.integers(1, 9, (n, 3)).astype(np.float32)
+    x[n - 1] = (-50, -49, -51)
+    attrs = np.stack([np.r_[np.zeros(na, np.int32), np.ones(nb, np.int32)], np.zeros(n, np.int32)], 1)
+    w = workloads.Workload("sizes", torch.from_numpy(x), np.arange(n + 1, dtype=np.int64), attrs, ["l", "g"], 0, [1], [])
+    print(f"[case] sorted row sizes nb={nb} na={na} {precision}", flush=True)
+    t, res = gpu_score(w, mode="pooled", precision=precision, keep_pairs=True, **({"margin": 1e-3} if precision == "bf16" else {}))
+    xs, ys = (v.ravel() for v in np.meshgrid(np.arange(n), np.arange(n), indexing="ij"))
+    f32, fl, f64 = (v.reshape(n, n) for v in res.pairs(xs, ys))
+    marked = (fl & 2) != 0
+    want = []
+    for A, B in ((np.arange(na), np.arange(na, n)), (np.arange(na, n), np.arange(na))):
+        s = 0
+        for i in A:
+            a, b = A[A != i][:, None], B[None]
+            both = marked[i, a] & marked[i, b]
+            s += 2 * int(np.where(both, f64[i, a] < f64[i, b], f32[i, a] < f32[i, b]).sum())
+            s += int(np.where(both, f64[i, a] == f64[i, b], f32[i, a] == f32[i, b]).sum())
+            if precision == "bf16":
+                assert both[np.abs(f32[i, a] - f32[i, b]) <= 0.99e-3].all()
+        want.append(s)
+    assert res.half_units.tolist() == want

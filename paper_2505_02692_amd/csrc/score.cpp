@@ -338,7 +338,7 @@ int64_t footprint_bytes(const TaskImpl &t, const ScoreParams &p) {
     const int64_t rows = p.mode == FABX_MODE_DTW ? t.n_frames : int64_t(t.items.size());
     int64_t b = p.distance == FABX_DISTANCE_UNITS ? rows * 4 : rows * dim_pad * (bf16 ? 2 : 4) + rows * 4;
     if (bf16 && p.distance == FABX_DISTANCE_EUCLIDEAN) b += rows * 4;  // frame lengths
-    if (p.mode == FABX_MODE_DTW && !bf16) b += std::min(t.n_dmat, plain_dmat_cells()) * 4;
+    if (needs_strips(t, p)) b += std::min(t.n_dmat, plain_dmat_cells()) * 4;
     b += t.n_pair_slots * 4;
     if (bf16) b += t.n_pair_slots * (1 + 8 + 8) + int64_t(t.long_slots.size()) * 8;
     b += int64_t(t.cells.size()) * (8 + 32) + int64_t(t.units.size()) * 4 + t.sum_nx * 8 +

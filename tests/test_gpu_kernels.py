@@ -422,3 +422,30 @@ def test_sorted_row_sizes(nb, precision):
                 assert both[np.abs(f32[i, a] - f32[i, b]) <= 0.99e-3].all()
         want.append(s)
     assert res.half_units.tolist() == want
+
+
+# The memory a server counts for a job: plain and unit scores of items of at most 64
+# frames take no distance matrix, so they are admitted next to one another in a
+# budget far below their squared frame count.
+@pytest.mark.parametrize("kind", ["fp32", "units"])
+def test_server_admits_plain_jobs_without_a_distance_buffer(kind):
+    import paper_2505_02692_amd as fx
+    from test_gpu_parity import ctx
+    rng = np.random.default_rng(2)
+    n, budget = 600, 64 << 20
+    length = rng.integers(10, 31, n)
+    off = np.concatenate([[0], np.cumsum(length)]).astype(np.int64)
+    assert int(off[-1]) ** 2 * 4 > 8 * budget
+    attrs = np.stack([np.arange(n) % 3, np.zeros(n)], 1).astype(np.int32)
+    feats = (torch.from_numpy(rng.integers(0, 9, int(off[-1])).astype(np.int32)) if kind == "units" else
+             torch.from_numpy(rng.standard_normal((int(off[-1]), 16), dtype=np.float32)))
+    opts = dict(distance="units") if kind == "units" else dict(precision="fp32")
+    print(f"[case] server budget {kind}", flush=True)
+    ds = fx.Dataset(ctx(), feats.cuda().contiguous(), off, attrs)
+    want = fx.Task(ds, 0, [1]).score(**opts).half_units
+    srv = fx.Server(ctx(), hbm_budget_bytes=budget, n_streams=2)
+    ids = [srv.submit(ds, 0, [1], **opts) for _ in range(3)]
+    got = [srv.wait(i)[1] for i in ids]
+    high = srv.stats["hbm_high_water"]
+    srv.close()
+    assert all(np.array_equal(g, want) for g in got) and 0 < high <= budget

@@ -342,7 +342,7 @@ int64_t footprint_bytes(const TaskImpl &t, const ScoreParams &p) {
     b += t.n_pair_slots * 4;
     if (bf16) b += t.n_pair_slots * (1 + 8 + 8) + int64_t(t.long_slots.size()) * 8;
     b += int64_t(t.cells.size()) * (8 + 32) + int64_t(t.units.size()) * 4 + t.sum_nx * 8 +
-         int64_t(t.items.size()) * 24;
+         int64_t(t.items.size()) * 24 + int64_t(t.pack_item.size()) * 16;
     return b + (1 << 20);
 }
 

@@ -449,3 +449,26 @@ def test_server_admits_plain_jobs_without_a_distance_buffer(kind):
     high = srv.stats["hbm_high_water"]
     srv.close()
     assert all(np.array_equal(g, want) for g in got) and 0 < high <= budget
+
+
+# The packing order of a task's items (16 bytes each on the device) counts in a job's
+# footprint: the same items in task order, which one group with an item of more than
+# 64 frames makes them keep, count that much less but for the group itself.
+def test_server_footprint_counts_the_packing_order():
+    import re
+    import paper_2505_02692_amd as fx
+    from test_gpu_parity import ctx
+    n = 10000
+    off = np.arange(0, 6 * n + 1, 6, dtype=np.int64)
+    attrs = np.stack([np.arange(n) % 2, np.arange(n) // 500], 1).astype(np.int32)
+    off2 = np.concatenate([off, off[-1] + np.array([1, 2, 67])]).astype(np.int64)
+    attrs2 = np.concatenate([attrs, [[0, 99], [1, 99], [0, 99]]]).astype(np.int32)
+    srv = fx.Server(ctx(), hbm_budget_bytes=1, n_streams=1)
+    footprint = []
+    for o, a in ((off, attrs), (off2, attrs2)):
+        ds = fx.Dataset(ctx(), torch.ones((int(o[-1]), 4), device="cuda"), o, a)
+        with pytest.raises(fx.FabxError) as e:
+            srv.submit(ds, 0, [1])
+        footprint.append(int(re.search(r"footprint (\d+) bytes", str(e.value)).group(1)))
+    srv.close()
+    assert footprint[0] - footprint[1] >= 16 * n - 32768

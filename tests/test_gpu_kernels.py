@@ -472,3 +472,28 @@ def test_server_footprint_counts_the_packing_order():
         footprint.append(int(re.search(r"footprint (\d+) bytes", str(e.value)).group(1)))
     srv.close()
     assert footprint[0] - footprint[1] >= 16 * n - 32768
+
+
+# The rounding of the FP64 distances over many features: an angle or a length takes
+# about ten roundings after its sums, whose own error, added up in blocks, is no
+# more than theirs: 1.5 half units in the last place as a root mean square (one chain
+# over 1024 features: 2.7 and more).
+@pytest.mark.parametrize("distance", ["angular", "euclidean"])
+@pytest.mark.parametrize("mode", ["dtw", "pooled"])
+@pytest.mark.parametrize("dim", [64, 1024])
+def test_fp64_recheck_rounding(dim, mode, distance):
+    n, m = dim + 6 if mode == "pooled" else 60, 60
+    w = workloads.batched_c4(n_groups=1, size_lo=n, size_hi=n, len_lo=1, len_hi=1, dim=dim, dtype=torch.float32,
+                             centroid_std=0.1, seed=n)
+    print(f"[case] rounding {mode} {distance} dim={dim}", flush=True)
+    t, res = gpu_score(w, mode=mode, distance=distance, margin=1e4, keep_pairs=True)
+    xs, ys = np.triu_indices(m, 1)
+    _, fl, f64 = res.pairs(xs, ys)
+    assert ((fl & 2) != 0).all()
+    f = w.features[:m].numpy().astype(np.longdouble)
+    if distance == "angular":
+        u = f / np.sqrt((f * f).sum(1, keepdims=True))
+        want = np.arccos((u[xs] * u[ys]).sum(1)) / (4 * np.arctan(np.longdouble(1)))
+    else:
+        want = np.sqrt(((f[xs] - f[ys]) ** 2).sum(1))
+    assert np.sqrt((((f64 - want) / want) ** 2).mean()) <= 1.5 * 2.0 ** -53

@@ -241,10 +241,11 @@ __device__ __forceinline__ double ror1(double v) {
 //    its quarter of the features.  Returns whether this lane met a NaN distance.
 //    (only where want(u, i, j))
 // The sums are made in blocks of features that are then added up (the products in
-// the elements' own places in LDS), about as many blocks as a block has terms, which
-// keeps their rounding to that of a sum split over 64 lanes: at 1024 features one
-// chain is off by 3.1e-16 (relative, root mean square over frame pairs), the blocks
-// by 0.9e-16, for 3% of the time of 365,261 pairs of 5-25 frames, 768 features.
+// the elements' own places in LDS, once in a turn of the load pipeline: a test per 16
+// features for a block by width cost long items 5%), which keeps their rounding to
+// that of a sum split over 64 lanes: at 1024 features one chain is off by 3.1e-16
+// (relative, root mean square over frame pairs), the blocks by 0.9e-16, for 3% of a
+// pass over 365,261 pairs of 5-25 frames, 768 features.
 struct All {
     __device__ bool operator()(int, int, int) const { return true; }
 };
@@ -252,7 +253,6 @@ template <typename T, bool kEuclid, int kT, int kStages = sizeof(T) == 4 ? 3 : 4
           typename Want = All>
 __device__ __forceinline__ bool tile_distances(int n_tiles, Ptr &&ptr, int dim, At &&at, Want &&want = All{}) {
     const int lane = threadIdx.x % dev::kWave, i16 = lane % 16, q = lane / 16;
-    const int block = dim <= 64 ? 16 : dim <= 256 ? 32 : 64;
     const T *pa[kT], *pb[kT];
     int nr[kT], nc[kT];
 #pragma unroll
@@ -277,7 +277,7 @@ __device__ __forceinline__ bool tile_distances(int n_tiles, Ptr &&ptr, int dim, 
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[r] = sum[r] = 0.0;
             for (int k0 = 0; k0 < dim; k0 += 16) {
-                if (k0 > 0 && (k0 & (block - 1)) == 0)
+                if (k0 > 0 && k0 % 32 == 0)
 #pragma unroll
                     for (int r = 0; r < 16; ++r) {
                         sum[r] += acc[r];
@@ -308,6 +308,7 @@ __device__ __forceinline__ bool tile_distances(int n_tiles, Ptr &&ptr, int dim, 
             }
         }
     } else {
+        constexpr int kBlock = kStages > 2 ? 16 * kStages : 64;
         f64x4 acc[kT];
         double sa[kT], sb[kT], na[kT], nb[kT];  // a block's norm sums, and those of the blocks before
 #pragma unroll
@@ -361,18 +362,17 @@ __device__ __forceinline__ bool tile_distances(int n_tiles, Ptr &&ptr, int dim, 
         for (int st = 0; st < kStages - 1; ++st)
             if (16 * st < full) load(st, 16 * st);
         for (int k0 = 0; k0 < full; k0 += 16 * kStages) {
+            if (k0 > 0 && k0 % kBlock == 0) flush(k0 == kBlock);
 #pragma unroll
             for (int st = 0; st < kStages; ++st) {
                 const int k = k0 + 16 * st;
                 if (k >= full) break;
-                if (k > 0 && (k & (block - 1)) == 0) flush(k == block);
                 const int ahead = k + 16 * (kStages - 1);
                 if (ahead < full) load((st + kStages - 1) % kStages, ahead);
                 products(st);
             }
         }
         if (full < dim) {
-            if (full > 0 && (full & (block - 1)) == 0) flush(full == block);
 #pragma unroll
             for (int u = 0; u < kT; ++u)
                 if (u < n_tiles) {
@@ -385,14 +385,18 @@ __device__ __forceinline__ bool tile_distances(int n_tiles, Ptr &&ptr, int dim, 
 #pragma unroll
         for (int u = 0; u < kT; ++u) {
             if (u >= n_tiles) continue;
-            const double su = 1.0 / sqrt(sum_quarters(na[u] + sa[u])), sv = 1.0 / sqrt(sum_quarters(nb[u] + sb[u]));
+            const double ssa = sum_quarters(na[u] + sa[u]), ssb = sum_quarters(nb[u] + sb[u]);
+            const double su = 1.0 / sqrt(ssa), sv = 1.0 / sqrt(ssb);
             // (not unrolled: one copy of acos keeps the registers few)
 #pragma unroll 1
             for (int r = 0; r < 4; ++r) {
                 const int i = q + 4 * r;
                 double dot = r == 0 ? acc[u][0] : r == 1 ? acc[u][1] : r == 2 ? acc[u][2] : acc[u][3];
-                if (dim > block) dot += *at(u, i, i16);
-                const double c = dot * (__shfl(su, i, dev::kWave) * sv);
+                if (full > kBlock) dot += *at(u, i, i16);
+                // 1 / (||u|| ||v||), with one step towards the square root's reciprocal, which
+                // takes away most of the norms' own roundings
+                const double s0 = __shfl(su, i, dev::kWave) * sv, pp = __shfl(ssa, i, dev::kWave) * ssb;
+                const double c = dot * __builtin_fma(0.5 * s0, __builtin_fma(-(pp * s0), s0, 1.0), s0);
                 const bool is_near = !(fabs(c) < 1.0 - 0x1p-20);
                 near = near || (is_near && want(u, i, i16));
                 *at(u, i, i16) = is_near ? -1.0 : acos(c) / kPi;

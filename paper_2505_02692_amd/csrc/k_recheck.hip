@@ -241,15 +241,16 @@ __device__ __forceinline__ double ror1(double v) {
 //    its quarter of the features.  Returns whether this lane met a NaN distance.
 //    (only where want(u, i, j))
 // The sums are made in blocks of features that are then added up (the products in
-// the elements' own places in LDS, once in a turn of the load pipeline: a test per 16
+// the elements' own places in LDS, at a turn of the load pipeline: a test per 16
 // features for a block by width cost long items 5%), which keeps their rounding to
 // that of a sum split over 64 lanes: at 1024 features one chain is off by 3.1e-16
 // (relative, root mean square over frame pairs), the blocks by 0.9e-16, for 3% of a
-// pass over 365,261 pairs of 5-25 frames, 768 features.
+// pass over 365,261 pairs of 5-25 frames, 768 features.  Blocks are the same in every
+// kernel, and with them the distance of two frames.
 struct All {
     __device__ bool operator()(int, int, int) const { return true; }
 };
-template <typename T, bool kEuclid, int kT, int kStages = sizeof(T) == 4 ? 3 : 4, typename Ptr, typename At,
+template <typename T, bool kEuclid, int kT, int kStages = sizeof(T) == 4 ? 2 : 4, typename Ptr, typename At,
           typename Want = All>
 __device__ __forceinline__ bool tile_distances(int n_tiles, Ptr &&ptr, int dim, At &&at, Want &&want = All{}) {
     const int lane = threadIdx.x % dev::kWave, i16 = lane % 16, q = lane / 16;
@@ -308,7 +309,7 @@ __device__ __forceinline__ bool tile_distances(int n_tiles, Ptr &&ptr, int dim, 
             }
         }
     } else {
-        constexpr int kBlock = kStages > 2 ? 16 * kStages : 64;
+        constexpr int kBlock = 64;  // a multiple of every kernel's turn
         f64x4 acc[kT];
         double sa[kT], sb[kT], na[kT], nb[kT];  // a block's norm sums, and those of the blocks before
 #pragma unroll
@@ -334,8 +335,8 @@ __device__ __forceinline__ bool tile_distances(int n_tiles, Ptr &&ptr, int dim, 
                 }
         };
         // kStages register buffers of 16 features each, kStages - 1 of them in
-        // flight while the products take one (a listed pair's frames are usually
-        // not in L2: one buffer ahead left the wave waiting on memory)
+        // flight while the products take one.  BF16 frames hold four in few registers;
+        // for FP32 two are as fast as three, which no longer fit beside the sums.
         typename Four<T>::V a[kStages][kT], b[kStages][kT];
         auto load = [&](int st, int k0) {
 #pragma unroll

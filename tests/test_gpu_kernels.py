@@ -497,3 +497,30 @@ def test_fp64_recheck_rounding(dim, mode, distance):
     else:
         want = np.sqrt(((f[xs] - f[ys]) ** 2).sum(1))
     assert np.sqrt((((f64 - want) / want) ** 2).mean()) <= 1.5 * 2.0 ** -53
+
+
+# The FP64 distance of two frames is the same in the kernels of all length classes: one
+# frame against k copies of another costs k times their distance, added one by one.
+@pytest.mark.parametrize("distance", ["angular", "euclidean"])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("dim", [47, 200, 1000])
+def test_fp64_recheck_same_sums_in_all_classes(dim, dtype, distance):
+    rng = np.random.default_rng(dim)
+    copies, n = [1, 7, 20, 40, 64, 65, 130], 6
+    f = torch.from_numpy(rng.standard_normal((2 * n, dim)).astype(np.float32)).to(dtype)
+    feats, length, attrs = [], [], []
+    for i in range(n):  # group i: the frame, the other's copies, and a second of the frame's label
+        for label, frame, k in [(0, 2 * i, 1)] + [(1, 2 * i + 1, k) for k in copies] + [(0, 2 * i + 1, 2)]:
+            feats.append(f[frame].repeat(k, 1))
+            length.append(k)
+            attrs.append((label, i))
+    w = workloads.Workload("copies", torch.cat(feats), np.concatenate([[0], np.cumsum(length)]).astype(np.int64),
+                           np.array(attrs, np.int32), ["l", "g"], 0, [1], [])
+    print(f"[case] copies dim={dim} {dtype} {distance}", flush=True)
+    t, res = gpu_score(w, norm="none", distance=distance, margin=1e4, keep_pairs=True)
+    per = len(copies) + 2
+    for i in range(n):
+        ys = np.arange(i * per + 1, i * per + 1 + len(copies))
+        _, fl, f64 = res.pairs(np.full(len(ys), i * per), ys)
+        assert ((fl & 2) != 0).all()
+        assert np.array_equal(f64, [np.cumsum(np.full(k, f64[0]))[-1] for k in copies])

@@ -19,33 +19,39 @@ using dev::kWave;
 constexpr uint8_t kNonRobust = 1;
 constexpr uint8_t kMarked = 2;
 
-// A unit by a wave: the larger of A and B lies in the lanes (as many rows x side
-// by side as fit), and the other one's values pass by, one per step, so a row's
-// values and flags are read once and a step is a lane shuffle and three
+// A unit by a wave.  |A| x |B| of at most a wave's lanes: as many whole rows x as
+// fit, a lane each comparison.  Otherwise the larger of A and B lies in the lanes (as
+// many rows side by side as fit), and the other one's values pass by, one per step,
+// so a row's values and flags are read once and a step is a lane shuffle and three
 // comparisons; a row whose grid was walked in passes of 64 read four values per
-// comparison and waited for them.
-//  kMany = false: a wave takes one unit at a time; with few units each is split
-//    by x into `parts`.
+// comparison and waited for them.  (Passing values for small rows too made 131,671
+// cells of well separated labels take 113 us instead of 86; with the grid 88.)
+//  kMany = false: a wave takes one unit at a time; few units are split by x into
+//    1 << log_parts.  At most 12,288 blocks: a block costs its tables' latency and an
+//    atomic for its recount rows (131,671 cells 96, 87 and 88 us with 8192, 12,288 and
+//    16,384 blocks; 60,000 cells of 2 x 2 items 25, 28 and 30; 40,000 such cells with
+//    18,475 recount rows 93, 106 and 106).  Split four ways below 512 units: 4 cells
+//    of 20 items 10 -> 8 us, 12 cells of 60 17 -> 15, but 760 cells 11 -> 14.
 //  kMany = true, from kManyUnits units on (tasks across speakers have millions of
 //    cells of a few triples, and a wave per unit spent its time on the unit's tables
 //    and its reduction): a wave takes `chunk` consecutive units, one per lane; those
 //    of at most kLaneWork comparisons are done by their lane alone, the others by
-//    the wave one after another.  (100,000 items, 131,671 cells: 184 us with 4 units
-//    a wave, 590 with 16, whose larger units queue in a few waves.)
+//    the wave one after another.  (1.77e6 cells across speakers 0.52 -> 0.15 ms, 863,150
+//    such cells 0.25 -> 0.07; but 960,000 cells of 27 comparisons, just past kLaneWork,
+//    0.32 -> 0.35, and 131,671 cells of uneven sizes 0.09 -> 0.18 with 4 units a wave,
+//    0.59 with 16, whose larger units queue in a few waves.)
 // Rows for the recount are collected in LDS and leave 128 at a time, or with one
 // atomic of the block at its end: one atomic per row on the common counter was
 // most of the time where many rows go there.
 // Bound by the latency of the chain unit, cell, row values.  100,000 items with
-// 149,174 rows for the recount: 1.41 -> 0.14 ms (0.089 -> 0.116 without such rows);
-// 1.77e6 cells across speakers: 0.76 -> 0.23 ms; 668,000 triples in 957 cells:
-// 53 -> 14 us.
+// 126,303 rows for the recount: 1.27 -> 0.13 ms (0.086 -> 0.088 without such rows).
 constexpr int kLaneWork = 24, kRowBuf = 128;
 constexpr int64_t kManyUnits = 16 * 32768;
 
 template <bool kMany>
 __global__ __launch_bounds__(256) void k_triplets(const CellDev *__restrict__ cells,
                                                   const int32_t *__restrict__ units, int64_t n_units, int chunk,
-                                                  int parts, const int64_t *__restrict__ g_pair_base,
+                                                  int log_parts, const int64_t *__restrict__ g_pair_base,
                                                   const int64_t *__restrict__ g_n,
                                                   const float *__restrict__ p32,
                                                   unsigned long long *__restrict__ W,
@@ -99,6 +105,44 @@ __global__ __launch_bounds__(256) void k_triplets(const CellDev *__restrict__ ce
         if (p) rowbuf[n_rows + __popcll(m & ((1ull << lane) - 1ull))] = make_int2(cell, xi);
         __builtin_amdgcn_wave_barrier();
         n_rows += c;
+    };
+    // a unit of few comparisons a row: as many whole rows as fit, a lane each comparison
+    auto unit_by_grid = [&](const int cell, const int xb, const int xe, const int a0, const int na, const int b0,
+                            const int nb, const int x0, const int excl, const int64_t base, const int64_t n) {
+        const int per = na * nb;
+        const float inv = __builtin_amdgcn_rcpf(float(per));  // (exact as below)
+        const int rows = int((kWave + 0.5f) * inv), r = int((float(lane) + 0.5f) * inv), k = lane - r * per;
+        const int a = int((float(k) + 0.5f) * __builtin_amdgcn_rcpf(float(nb))), al = a0 + a, bl = b0 + k - a * nb;
+        unsigned int acc = 0;
+        for (int xs = xb; xs < xe; xs += rows) {
+            const int xi = xs + r, xl = x0 + xi;
+            const bool on = r < rows && xi < xe;
+            const int64_t row = base + int64_t(xl) * n;
+            unsigned int add = 0;
+            bool near = false;
+            if (on && !(excl && al == xl)) {
+                const float da = p32[row + al], db = p32[row + bl];
+                add = (da < db ? 1u : 0u) + (da <= db ? 1u : 0u);
+                if (flags) {
+                    const uint8_t fa = flags[row + al], fb = flags[row + bl];
+                    near = fabsf(da - db) <= margin || ((fa | fb) & kNonRobust) != 0;
+                    if (near) {
+                        if (!(fa & kMarked)) flags[row + al] = fa | kMarked;
+                        if (!(fb & kMarked)) flags[row + bl] = fb | kMarked;
+                    }
+                }
+            }
+            const unsigned long long dirty = __ballot(near);
+            if (dirty) {  // uniform
+                const unsigned long long seg = per == kWave ? ~0ull : ((1ull << per) - 1ull) << (r * per);
+                const bool row_dirty = r < rows && (dirty & seg) != 0;
+                push(on && row_dirty && k == 0, cell, xi);
+                if (row_dirty) add = 0;
+            }
+            acc += add;
+        }
+        const unsigned int total = dev::wave_scan_u32(acc);
+        if (lane == kWave - 1 && total) atomicAdd(&W[cell], (unsigned long long)total);
     };
     auto unit_by_wave = [&](const int cell, const int xb, const int xe, const int a0, const int na, const int b0,
                             const int nb, const int x0, const int excl, const int64_t base, const int64_t n) {
@@ -196,7 +240,7 @@ __global__ __launch_bounds__(256) void k_triplets(const CellDev *__restrict__ ce
             if (lane == 0 && total) atomicAdd(&W[cell], total);
         }
     };
-    const int64_t n_work = n_units * parts;
+    const int64_t n_work = n_units << log_parts;
     const int64_t wave = int64_t(blockIdx.x) * 4 + wv, waves = int64_t(gridDim.x) * 4;
     if constexpr (!kMany) {
         // the tables of the next units are read ahead, one level (unit, cell, group)
@@ -206,10 +250,9 @@ __global__ __launch_bounds__(256) void k_triplets(const CellDev *__restrict__ ce
         };
         auto unit_at = [&](int64_t u) {
             u = min(u, n_work - 1);
-            const int64_t unit = u / parts;
-            const int32_t *un = units + 3 * unit;
-            const int per = (un[2] - un[1] + parts - 1) / parts;
-            const int xb = un[1] + int(u - unit * parts) * per;
+            const int32_t *un = units + 3 * (u >> log_parts);
+            const int per = (un[2] - un[1] + (1 << log_parts) - 1) >> log_parts;
+            const int xb = un[1] + int(u & ((1 << log_parts) - 1)) * per;
             return Unit{un[0], xb, min(xb + per, un[2])};
         };
         Unit u1 = unit_at(wave), u2 = unit_at(wave + waves), u3;
@@ -220,8 +263,12 @@ __global__ __launch_bounds__(256) void k_triplets(const CellDev *__restrict__ ce
             base2 = g_pair_base[c2.group];
             n2 = g_n[c2.group];
             u3 = unit_at(u + 2 * waves);
-            if (c1.na > 0 && c1.nb > 0 && u1.xb < u1.xe)  // uniform
-                unit_by_wave(u1.cell, u1.xb, u1.xe, c1.a0, c1.na, c1.b0, c1.nb, c1.x0, c1.exclude_self, base1, n1);
+            if (c1.na > 0 && c1.nb > 0 && u1.xb < u1.xe) {  // uniform
+                if (int64_t(c1.na) * c1.nb <= kWave)
+                    unit_by_grid(u1.cell, u1.xb, u1.xe, c1.a0, c1.na, c1.b0, c1.nb, c1.x0, c1.exclude_self, base1, n1);
+                else
+                    unit_by_wave(u1.cell, u1.xb, u1.xe, c1.a0, c1.na, c1.b0, c1.nb, c1.x0, c1.exclude_self, base1, n1);
+            }
             u1 = u2;
             c1 = c2;
             base1 = base2;
@@ -827,13 +874,13 @@ void triplets(hipStream_t s, const CellDev *cells, const int32_t *units, int64_t
     if (n_units >= kManyUnits) {
         const int chunk = int(std::min<int64_t>(kWave, n_units / 32768));
         hipLaunchKernelGGL(k_triplets<true>, dim3(grid_for(n_units, 4 * chunk)), dim3(256), 0, s, cells, units, n_units,
-                           chunk, 1, g.pair_base, g.n_items, p32, W, flags, margin, recount, recount_n, recount_cap,
+                           chunk, 0, g.pair_base, g.n_items, p32, W, flags, margin, recount, recount_n, recount_cap,
                            scale);
     } else {
         // a wave's units lie far apart, so that neighbouring large ones spread out
-        const int parts = n_units >= 8192 ? 1 : n_units >= 2048 ? 4 : 8;
-        hipLaunchKernelGGL(k_triplets<false>, dim3(grid_for(n_units * parts, 4, 8192)), dim3(256), 0, s, cells, units,
-                           n_units, 1, parts, g.pair_base, g.n_items, p32, W, flags, margin, recount, recount_n,
+        const int log_parts = n_units >= 512 ? 0 : 2;
+        hipLaunchKernelGGL(k_triplets<false>, dim3(grid_for(n_units << log_parts, 4, 12288)), dim3(256), 0, s, cells, units,
+                           n_units, 1, log_parts, g.pair_base, g.n_items, p32, W, flags, margin, recount, recount_n,
                            recount_cap, scale);
     }
     FABX_HIP(hipGetLastError());

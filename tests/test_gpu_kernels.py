@@ -524,3 +524,43 @@ def test_fp64_recheck_same_sums_in_all_classes(dim, dtype, distance):
         _, fl, f64 = res.pairs(np.full(len(ys), i * per), ys)
         assert ((fl & 2) != 0).all()
         assert np.array_equal(f64, [np.cumsum(np.full(k, f64[0]))[-1] for k in copies])
+
+
+# Cells whose |A| x |B| fits a wave's lanes, and those just past it: few units (split
+# by x) and many, X = A without x itself and X of another speaker.  Points of a coarse
+# lattice, so that many comparisons tie or are left to the recount.
+@pytest.mark.parametrize("groups", [3, 300])
+@pytest.mark.parametrize("across", [False, True])
+@pytest.mark.parametrize("na,nb", [(2, 1), (2, 2), (9, 7), (8, 8), (13, 5), (64, 1), (65, 1), (3, 21), (3, 22)])
+def test_triplet_units_by_grid(na, nb, across, groups):
+    rng = np.random.default_rng(na * 100 + nb)
+    label = np.tile(np.r_[np.zeros(na, np.int32), np.ones(nb, np.int32)], (1 + across) * groups)
+    speaker = np.tile(np.repeat(np.arange(1 + across), na + nb), groups)
+    group = np.repeat(np.arange(groups), (1 + across) * (na + nb))
+    n = len(label)
+    x = rng.integers(1, 7, (n, 3)).astype(np.float32)
+    attrs = np.stack([label, group, speaker], 1).astype(np.int32)
+    w = workloads.Workload("grid", torch.from_numpy(x), np.arange(n + 1, dtype=np.int64), attrs, ["l", "g", "s"], 0, [1],
+                           [2] if across else [])
+    print(f"[case] units by grid na={na} nb={nb} across={across} groups={groups}", flush=True)
+    t, res = gpu_score(w, mode="pooled", margin=1e-3, keep_pairs=True)
+    # the definition, from the pair values that the counts compare
+    per = n // groups
+    xs, ys = (v.ravel() for v in np.meshgrid(np.arange(n), np.arange(per), indexing="ij"))
+    f32, fl, f64 = (v.reshape(groups, per, per) for v in res.pairs(xs, xs // per * per + ys))
+    marked = (fl & 2) != 0
+    want, n_near = [], 0
+    for c in oracle.cells(attrs, 0, [1], w.across):
+        g, s = c.A[0] // per, 0
+        for i in c.X % per:
+            a, b = (c.A[c.A != c.X[0] // per * per + i] if c.exclude_self else c.A)[:, None] % per, c.B[None] % per
+            both = marked[g, i, a] & marked[g, i, b]
+            near = np.abs(f32[g, i, a] - f32[g, i, b]) <= 0.99e-3
+            assert both[near].all()
+            n_near += int(near.sum())
+            s += 2 * int(np.where(both, f64[g, i, a] < f64[g, i, b], f32[g, i, a] < f32[g, i, b]).sum())
+            s += int(np.where(both, f64[g, i, a] == f64[g, i, b], f32[g, i, a] == f32[g, i, b]).sum())
+        want.append(s)
+    assert n_near > 0 or groups * na * nb < 20
+    wrong = np.flatnonzero(res.half_units != want)
+    assert len(wrong) == 0, f"{len(wrong)} of {len(want)} cells"

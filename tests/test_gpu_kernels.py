@@ -564,3 +564,62 @@ def test_triplet_units_by_grid(na, nb, across, groups):
     assert n_near > 0 or groups * na * nb < 20
     wrong = np.flatnonzero(res.half_units != want)
     assert len(wrong) == 0, f"{len(wrong)} of {len(want)} cells"
+
+
+# More units than kManyUnits (524,288), which a wave takes many at a time: cells on
+# both sides of the 24 comparisons that one lane does alone, X = A without x itself and
+# X of another speaker, rows left to the recount.
+@pytest.mark.parametrize("precision", ["fp32", "bf16"])
+@pytest.mark.parametrize("across", [False, True])
+def test_triplets_of_many_units(across, precision):
+    rng = np.random.default_rng(9)
+    # (items of label 0, of label 1, groups); comparisons a cell: 8, 24, 24, 27, 48, 288, 729 (or without x itself)
+    shapes = [(2, 2, 200000), (2, 6, 20000), (6, 2, 20000), (3, 3, 30000), (2, 12, 3000), (12, 2, 3000), (9, 9, 1000)]
+    if across:
+        shapes = [(a, b, g // 2) for a, b, g in shapes]
+    spk = 1 + across
+    label = np.concatenate([np.tile(np.r_[np.zeros(a, np.int32), np.ones(b, np.int32)], spk * g) for a, b, g in shapes])
+    speaker = np.concatenate([np.tile(np.repeat(np.arange(spk), a + b), g) for a, b, g in shapes])
+    size = np.concatenate([np.full(g, spk * (a + b)) for a, b, g in shapes])
+    n = len(label)
+    attrs = np.stack([label, np.repeat(np.arange(len(size)), size), speaker], 1).astype(np.int32)
+    x = rng.integers(1, 9, (n, 3)).astype(np.float32)
+    w = workloads.Workload("many", torch.from_numpy(x), np.arange(n + 1, dtype=np.int64), attrs, ["l", "g", "s"], 0, [1],
+                           [2] if across else [])
+    print(f"[case] many units across={across} {precision} items={n}", flush=True)
+    t, res = gpu_score(w, mode="pooled", precision=precision, keep_pairs=True,
+                       **({"margin": 1e-3} if precision == "bf16" else {}))
+    assert len(t) >= 16 * 32768
+    keys, hu = t.keys, res.half_units
+    first_item = first_cell = 0
+    for a, b, g in shapes:
+        per = a + b
+        # a group's cells in key order: labels (0, 1) then (1, 0), then speakers
+        local = []
+        for on, A0, B0 in ((0, np.arange(a), a + np.arange(b)), (1, a + np.arange(b), np.arange(a))):
+            for s in range(spk):
+                local.append((on, s, A0 + s * per, B0 + s * per, A0 + (spk - 1 - s) * per))
+        m = spk * per
+        i, j = (v.ravel() for v in np.meshgrid(np.arange(m), np.arange(m), indexing="ij"))
+        at = first_item + m * np.arange(g)[:, None]
+        f32, fl, f64 = (v.reshape(g, m, m) for v in res.pairs((at + i).ravel(), (at + j).ravel()))
+        marked = (fl & 2) != 0
+        got, k = (v[first_cell:first_cell + g * len(local)].reshape(g, len(local), -1) for v in (hu, keys))
+        for c, (on, s, A, B, X) in enumerate(local):
+            assert (k[:, c, 0] == on).all() and (k[:, c, 1] == 1 - on).all()
+            assert not across or (k[:, c, 3] == s).all()
+            want = np.zeros(g, np.int64)
+            for xx in X:
+                for aa in A:
+                    if aa == xx:
+                        continue
+                    for bb in B:
+                        both = marked[:, xx, aa] & marked[:, xx, bb]
+                        da, db = (np.where(both, f64[:, xx, v], f32[:, xx, v].astype(np.float64)) for v in (aa, bb))
+                        want += 2 * (da < db) + (da == db)
+                        if precision == "bf16":
+                            assert both[np.abs(f32[:, xx, aa] - f32[:, xx, bb]) <= 0.99e-3].all()
+            assert np.array_equal(got[:, c, 0], want)
+        first_item += g * m
+        first_cell += g * len(local)
+    assert precision == "fp32" or res.stats["n_recount_rows"] > 10000

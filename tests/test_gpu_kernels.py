@@ -623,3 +623,41 @@ def test_triplets_of_many_units(across, precision):
         first_item += g * m
         first_cell += g * len(local)
     assert precision == "fp32" or res.stats["n_recount_rows"] > 10000
+
+
+# The plain form's strips, which a task with an item of more than 64 frames takes: many
+# batches through a small buffer, one item a strip (items of up to 90 frames in groups of
+# about 700), equal the one batch of the full buffer bit for bit, and the oracle.
+@pytest.mark.parametrize("norm", ["path", "none"])
+@pytest.mark.parametrize("distance", ["angular", "euclidean", "units"])
+def test_plain_strips_in_batches(monkeypatch, distance, norm):
+    import paper_2505_02692_amd as fx
+    from test_gpu_parity import ctx
+    w = workloads.batched_c4(n_groups=6, size_lo=14, size_hi=16, len_lo=3, len_hi=90, dim=20, dtype=torch.float32,
+                             centroid_std=0.3, seed=23)
+    if distance == "units":
+        w.features = torch.from_numpy(np.random.default_rng(4).integers(0, 4, w.n_frames).astype(np.int32))
+    length = np.diff(w.offsets)
+    assert length.max() > 64
+    opts = dict(precision="fp32", distance=distance, norm=norm, keep_pairs=True)
+    ds = fx.Dataset(ctx(), w.features.cuda().contiguous(), w.offsets, w.attrs)
+    res = {}
+    for cells in ("4096", "40000", None):
+        print(f"[case] strips in batches {distance} {norm} cells={cells}", flush=True)
+        monkeypatch.delenv("FABX_PLAIN_DMAT_CELLS", raising=False)
+        if cells:
+            monkeypatch.setenv("FABX_PLAIN_DMAT_CELLS", cells)
+        res[cells] = fx.Task(ds, w.on, w.by).score(**opts)
+    feats = w.features.reshape(-1, 1).float().numpy() if distance == "units" else w.features_f32_host()
+    orc = oracle.score(feats, w.offsets, w.attrs, w.on, w.by, [], "dtw", norm, distance=distance)
+    xs, ys, want = all_oracle_pairs(orc)
+    whole = res[None]
+    f32 = whole.pairs(xs, ys)[0]
+    for cells in ("4096", "40000"):
+        assert np.array_equal(res[cells].half_units, whole.half_units)
+        assert np.array_equal(res[cells].pairs(xs, ys)[0], f32)
+    # FP32 sums: 2e-6 a step of the path, as for the whole form
+    steps = length[xs] + length[ys] - 1 if norm == "none" else 1
+    assert (np.abs(f32 - want) <= 2e-6 * steps * np.maximum(1, w.features.abs().max().item())).all()
+    if distance == "units":
+        assert np.array_equal(whole.half_units, orc.half_units)

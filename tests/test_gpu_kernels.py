@@ -661,3 +661,41 @@ def test_plain_strips_in_batches(monkeypatch, distance, norm):
     assert (np.abs(f32 - want) <= 2e-6 * steps * np.maximum(1, w.features.abs().max().item())).all()
     if distance == "units":
         assert np.array_equal(whole.half_units, orc.half_units)
+
+
+# The no-allocation score of discrete units where the fused kernel's tables (with the
+# packing order's) no longer fit the scratch beside the task, but strips through a small
+# distance buffer do: a number of groups between those and the first that is refused.
+def test_noalloc_units_fall_back_to_strips():
+    import paper_2505_02692_amd as fx
+    from test_gpu_parity import ctx
+    rng = np.random.default_rng(8)
+    per, L, most = 4, 60, 220000
+    codes = torch.from_numpy(rng.integers(0, 5, most * per * L).astype(np.int32)).cuda()
+    off = np.arange(0, most * per * L + 1, L, dtype=np.int64)
+    attrs = np.stack([np.arange(most * per) % 2, np.arange(most * per) // per], 1).astype(np.int32)
+    opts = fx.make_opts(distance="units")
+
+    def attempt(groups):
+        n = groups * per
+        t = fx.Task(fx.Dataset(ctx(), codes[:n * L], off[:n + 1], attrs[:n]), 0, [1])
+        print(f"[case] noalloc units, {groups} groups", flush=True)
+        try:
+            return t, fx.fabx_score_noalloc(t.h, opts, len(t))
+        except fx.FabxError as e:
+            assert e.code == -2
+            return None
+
+    lo, hi = 120000, most   # taken, refused
+    t, (got, st) = attempt(lo)
+    assert st["computed_dtw_cells"] != lo * (per * L) ** 2  # the fused kernel
+    assert attempt(hi) is None
+    while hi - lo > 1 and st["computed_dtw_cells"] != lo * (per * L) ** 2:
+        mid = (lo + hi) // 2
+        res = attempt(mid)
+        if res is None:
+            hi = mid
+        else:
+            lo, (t, (got, st)) = mid, res
+    assert st["computed_dtw_cells"] == lo * (per * L) ** 2  # strips
+    assert np.array_equal(got, t.score(distance="units").half_units)

@@ -219,8 +219,9 @@ static_assert(sizeof(CellDev) == 32, "CellDev layout");
 struct TableLayout {
     size_t item_src = 0, item_len = 0, item_dst = 0, item_group = 0;
     std::array<size_t, 5> g{};  // item0, n_items (+ sentinel), frame0, n_frames, pair_base (+ total)
-    size_t cells = 0, units = 0, rb = 0;
-    std::array<size_t, 3> pack{};  // pack_item, pack_len, pack_dst (if the task has a packing order)
+    size_t cells = 0, units = 0;
+    std::array<size_t, 4> rows{};  // rb, pack_item, pack_len, pack_dst (the last three if the task has a packing order)
+    bool has_rows = false;         // those are in the buffer
     std::array<size_t, 6> plan{};  // cb, unit_prefix, g_cb0, rb_cstart, band_rb, rb of `plan_cols`
     int plan_cols = 0;             // 0: no column plan in the buffer
 };
@@ -235,7 +236,7 @@ struct TaskDevice {
                   *g_pair_base = nullptr;
     const CellDev *cells = nullptr;
     const int32_t *units = nullptr, *rb = nullptr;
-    bool uploaded = false;
+    bool uploaded = false, rows_uploaded = false;
 };
 
 // Device workspace kept by a task between scores.
@@ -310,7 +311,9 @@ struct TaskImpl {
 
     // Order in which the fused DTW kernels take the items of each group (empty:
     // task order): the task item at each position, its frames and first packed frame.
-    // Chosen so that row blocks are nearly full (plan_order, task.cpp).
+    // Chosen so that row blocks are nearly full (plan_order, task.cpp).  A task for
+    // which order_pays() holds gets it, its row blocks and plans from its first score
+    // that reads them (col_plan), the others at the end of the build.
     hvec<int32_t> pack_item, pack_len;
     hvec<int64_t> pack_dst;
 
@@ -332,8 +335,8 @@ struct TaskImpl {
     hvec<int32_t> rb;               // fused kernel row blocks [n][4] (<= 64 frames, in packing order)
     std::vector<int64_t> long_slots;  // unordered pairs x | y << 32 with an item of more than 64 frames (FP64 kernel)
     std::vector<int32_t> g_rb0, g_nrb;
+    bool rows_planned = false;      // rb and the packing order are made
     std::vector<std::unique_ptr<ColPlan>> col_plans;  // by column block width, made on demand
-    int64_t fused_cells = 0;        // frame pairs the fused kernel covers
 
     int64_t n_frames = 0;
     int64_t n_pair_slots = 0;       // sum over groups of n_items^2
@@ -379,9 +382,12 @@ struct ResultImpl {
 // task.cpp
 // Cell keys (attribute values) of cells [0, n) into out [n * key_width].
 void cell_keys(const TaskImpl &t, int32_t *out);
-// The task's column plan for `cols` (128 or 256), built on first use; the caller
-// holds the task's mutex.
+// The task's column plan for `cols` (128 or 256), built on first use (with the row
+// blocks and the packing order, if they are not there); the caller holds the task's
+// mutex.
 ColPlan &col_plan(TaskImpl &t, int cols);
+// Whether the fused DTW kernels take the task's items in a packing order.
+bool order_pays(const TaskImpl &t);
 // score.cpp: packs the task's device tables (and its default column plan) into
 // a pinned block of the context, for a task on a device context.
 void prepack_tables(TaskImpl &t);

@@ -83,6 +83,15 @@ std::array<size_t, 3> add_order(const TaskImpl &t, Packer &pk) {
     return {pk.add(t.pack_item), pk.add(t.pack_len), pk.add(t.pack_dst)};
 }
 
+std::array<size_t, 4> add_rows(const TaskImpl &t, bool with_order, Packer &pk) {
+    std::array<size_t, 4> o{pk.add(t.rb), 0, 0, 0};
+    if (with_order) {
+        const std::array<size_t, 3> p = add_order(t, pk);
+        std::copy(p.begin(), p.end(), o.begin() + 1);
+    }
+    return o;
+}
+
 std::array<size_t, 6> add_col_plan(const ColPlan &cp, Packer &pk) {
     return {pk.add(cp.cb),        pk.add(cp.unit_prefix), pk.add(cp.g_cb0),
             pk.add(cp.rb_cstart), pk.add(cp.band_rb),     cp.rb.empty() ? 0 : pk.add(cp.rb)};
@@ -90,7 +99,8 @@ std::array<size_t, 6> add_col_plan(const ColPlan &cp, Packer &pk) {
 
 // Host side of the task tables: adds them (and the packing order and `plan`, if
 // any) to `pk`; the group columns are built in `gcols`, which must live until the
-// copy is made.  with_rows: the row blocks too (a plan with its own needs none).
+// copy is made.  with_rows: the row blocks too (a plan with its own needs none), with
+// the packing order if with_order.
 TableLayout add_task_tables(const TaskImpl &t, const ColPlan *plan, bool with_order, bool with_rows, Packer &pk,
                             std::array<std::vector<int64_t>, 5> &gcols) {
     const size_t G = t.groups.size();
@@ -115,8 +125,8 @@ TableLayout add_task_tables(const TaskImpl &t, const ColPlan *plan, bool with_or
     for (size_t k = 0; k < 5; ++k) L.g[k] = pk.add(gcols[k]);
     L.cells = pk.add(t.cells);
     L.units = pk.add(t.units);
-    if (with_rows) L.rb = pk.add(t.rb);
-    if (with_order) L.pack = add_order(t, pk);
+    if (with_rows) L.rows = add_rows(t, with_order, pk);
+    L.has_rows = with_rows;
     if (plan) {
         L.plan = add_col_plan(*plan, pk);
         L.plan_cols = plan->cols;
@@ -131,6 +141,18 @@ void set_col_plan(ColPlan &cp, const DevBuf &buf, const std::array<size_t, 6> &o
     cp.d_rb_cstart = Packer::at<int32_t>(buf, o[3]);
     cp.d_band_rb = Packer::at<int32_t>(buf, o[4]);
     if (!cp.rb.empty()) cp.d_rb = Packer::at<int32_t>(buf, o[5]);
+}
+
+// Device pointers of the row blocks and the packing order in `buf`.
+void set_rows(TaskImpl &t, const DevBuf &buf, const std::array<size_t, 4> &o) {
+    TaskDevice &dv = t.dev;
+    dv.rb = Packer::at<int32_t>(buf, o[0]);
+    if (!t.pack_item.empty()) {
+        dv.pack_item = Packer::at<int32_t>(buf, o[1]);
+        dv.pack_len = Packer::at<int32_t>(buf, o[2]);
+        dv.pack_dst = Packer::at<int64_t>(buf, o[3]);
+    }
+    dv.rows_uploaded = true;
 }
 
 // Device pointers of the task tables in dv.blob (and of the column plan packed
@@ -148,12 +170,7 @@ void set_task_tables(TaskImpl &t, const TableLayout &L) {
     dv.g_pair_base = Packer::at<int64_t>(dv.blob, L.g[4]);
     dv.cells = Packer::at<CellDev>(dv.blob, L.cells);
     dv.units = Packer::at<int32_t>(dv.blob, L.units);
-    dv.rb = Packer::at<int32_t>(dv.blob, L.rb);
-    if (!t.pack_item.empty()) {
-        dv.pack_item = Packer::at<int32_t>(dv.blob, L.pack[0]);
-        dv.pack_len = Packer::at<int32_t>(dv.blob, L.pack[1]);
-        dv.pack_dst = Packer::at<int64_t>(dv.blob, L.pack[2]);
-    }
+    if (L.has_rows) set_rows(t, dv.blob, L.rows);
     if (L.plan_cols)
         for (auto &cp : t.col_plans)
             if (cp->cols == L.plan_cols && !cp->d_cb) set_col_plan(*cp, dv.blob, L.plan);
@@ -342,7 +359,8 @@ int64_t footprint_bytes(const TaskImpl &t, const ScoreParams &p) {
     b += t.n_pair_slots * 4;
     if (bf16) b += t.n_pair_slots * (1 + 8 + 8) + int64_t(t.long_slots.size()) * 8;
     b += int64_t(t.cells.size()) * (8 + 32) + int64_t(t.units.size()) * 4 + t.sum_nx * 8 +
-         int64_t(t.items.size()) * 24 + int64_t(t.pack_item.size()) * 16;
+         int64_t(t.items.size()) * 24;
+    if (p.mode == FABX_MODE_DTW && order_pays(t)) b += int64_t(t.items.size()) * 16;
     return b + (1 << 20);
 }
 
@@ -394,7 +412,7 @@ void prepack_tables(TaskImpl &t) {
     Packer pk;
     std::array<std::vector<int64_t>, 5> gcols;
     const ColPlan *plan = t.col_plans.empty() ? nullptr : t.col_plans.front().get();
-    const TableLayout L = add_task_tables(t, plan, !t.pack_item.empty(), true, pk, gcols);
+    const TableLayout L = add_task_tables(t, plan, !t.pack_item.empty(), t.rows_planned, pk, gcols);
     if (pk.total > kPrepackMaxBytes || ctx->pinned.packed_bytes.load() + pk.total > kPrepackBudget) return;
     FABX_HIP(hipSetDevice(ctx->device));
     std::unique_ptr<PinnedBlock> blk;
@@ -766,18 +784,21 @@ std::shared_ptr<ResultImpl> launch_score(const std::shared_ptr<TaskImpl> &tp, co
             Packer pk;
             std::array<std::vector<int64_t>, 5> gcols;
             const TableLayout L = add_task_tables(t, cplan && !cplan->d_cb ? cplan : nullptr,
-                                                  !t.pack_item.empty(), true, pk, gcols);
+                                                  !t.pack_item.empty(), t.rows_planned, pk, gcols);
             pk.upload(dv.blob, ds.ctx->staging, ds.ctx->copy_stream, stream);
             set_task_tables(t, L);
         }
         dv.uploaded = true;
     }
-    if (cplan && !cplan->d_cb) {  // another column width for an already uploaded task
+    if (cplan && !cplan->d_cb) {  // another column width for an already uploaded task, or its first
+        const bool rows = cplan->rb.empty() && !dv.rows_uploaded;
         Packer pc;
         const std::array<size_t, 6> o = add_col_plan(*cplan, pc);
+        const std::array<size_t, 4> r = rows ? add_rows(t, !t.pack_item.empty(), pc) : std::array<size_t, 4>{};
         cplan->dev.pool = pool;
         pc.upload(cplan->dev, ds.ctx->staging, ds.ctx->copy_stream, stream);
         set_col_plan(*cplan, cplan->dev, o);
+        if (rows) set_rows(t, cplan->dev, r);  // (all device copies of a task go together)
     }
     // Gram tile prefix of this score (pooled mode), or the strips of the plain DTW form
     DevBuf &plan_d = pend->plan_d;
@@ -810,8 +831,9 @@ std::shared_ptr<ResultImpl> launch_score(const std::shared_ptr<TaskImpl> &tp, co
     pend->host = ds.ctx->pinned.get(pend->host_bytes, &pend->host_bytes);
 
     d.it = kern::ItemTables{dv.item_src, dv.item_len, dv.item_dst, n_items, nullptr};
-    d.pack = t.pack_item.empty() ? d.it
-                                 : kern::ItemTables{dv.item_src, dv.pack_len, dv.pack_dst, n_items, dv.pack_item};
+    d.pack = !dv.rows_uploaded || t.pack_item.empty()
+                 ? d.it
+                 : kern::ItemTables{dv.item_src, dv.pack_len, dv.pack_dst, n_items, dv.pack_item};
     d.gt = kern::GroupTables{dv.g_item0, dv.g_n, dv.g_frame0, dv.g_nframes, dv.g_pair_base, G, t.n_pair_slots};
     d.cells = dv.cells;
     d.units = dv.units;
@@ -1007,7 +1029,7 @@ void score_in_scratch(TaskImpl &t, const ScoreParams &p, char *base, size_t cap,
                              t.n_pair_slots};
     d.cells = reinterpret_cast<const CellDev *>(at(tl.cells));
     d.units = reinterpret_cast<const int32_t *>(at(tl.units));
-    d.rb = reinterpret_cast<const int32_t *>(at(tl.rb));
+    d.rb = reinterpret_cast<const int32_t *>(at(tl.rows[0]));
     d.item_group = reinterpret_cast<const int32_t *>(at(tl.item_group));
     if (cplan) {
         d.cb = reinterpret_cast<const int32_t *>(at(tl.plan[0]));
@@ -1041,7 +1063,7 @@ void score_in_scratch(TaskImpl &t, const ScoreParams &p, char *base, size_t cap,
     std::vector<char> h_order(order_in_list ? pk_order.total : 0);
     if (order && !use_strips) {
         const char *b = order_in_list ? reinterpret_cast<const char *>(d.recheck_list) : base;
-        const std::array<size_t, 3> &o = order_in_list ? order_at : tl.pack;
+        const std::array<size_t, 3> o = order_in_list ? order_at : std::array<size_t, 3>{tl.rows[1], tl.rows[2], tl.rows[3]};
         d.pack = kern::ItemTables{d.it.src, reinterpret_cast<const int32_t *>(b + o[1]),
                                   reinterpret_cast<const int64_t *>(b + o[2]), d.it.n_items,
                                   reinterpret_cast<const int32_t *>(b + o[0])};
@@ -1076,7 +1098,7 @@ void release_device(TaskImpl &t) {
     t.ws.release();
     TaskDevice &dv = t.dev;
     dv.blob.release();
-    dv.uploaded = false;
+    dv.uploaded = dv.rows_uploaded = false;
     for (auto &cp : t.col_plans) {
         cp->dev.release();
         cp->d_cb = nullptr;

@@ -507,20 +507,19 @@ void order_group(TaskImpl &t, int64_t gi, int32_t *next, int32_t *binned, int32_
     if (n_bins > 0) emit(n_bins - 1);
 }
 
-// Makes the packing order where it pays: the distance stage falls by 28% for 1200
+// Makes the packing order, where it pays (order_pays): the distance stage falls by 28% for 1200
 // groups of up to 2000 items of 1-60 frames (383 -> 268 ms), by 14% for 40 groups of
 // 1000 items of 3-40 frames (3.7 -> 3.2 ms) and by 8% for 1600 groups of 60 items of
 // 9 frames (0.66 -> 0.61 ms), while the order costs the host and the upload about
 // 0.6 ns an item, the whole gain of that last task (an item meets 5,800 frames in
 // it).  From 12,000 frames an item on the gain is at least twice the cost.  Tasks
 // with items over kFusedRowFrames frames keep the task order: those end a block.
+// Pooled scores and the stream kernel never read it, so such a task's order and row
+// blocks are made by its first score that does (with the task they cost a pooled
+// score of 100,000 items 3-6%).
 constexpr int64_t kPackMinMeet = 12000;
 void plan_order(TaskImpl &t) {
     const int64_t n = int64_t(t.items.size()), G = int64_t(t.groups.size());
-    t.pack_item.clear();
-    t.pack_len.clear();
-    t.pack_dst.clear();
-    if (t.max_len > kFusedRowFrames || n == 0 || t.n_dmat / n < kPackMinMeet) return;
     t.pack_item.resize(size_t(n));
     t.pack_len.resize(size_t(n));
     t.pack_dst.resize(size_t(n));
@@ -596,7 +595,20 @@ void plan_rows(const TaskImpl &t, const hvec<int32_t> &len, hvec<int32_t> &rb, s
     });
 }
 
+// The task's packing order and row blocks, made on first use.
+void ensure_rows(TaskImpl &t) {
+    if (t.rows_planned) return;
+    if (order_pays(t)) plan_order(t);
+    plan_rows(t, packed_len(t), t.rb, t.g_rb0, t.g_nrb);
+    t.rows_planned = true;
+}
+
 }  // namespace
+
+bool order_pays(const TaskImpl &t) {
+    const int64_t n = int64_t(t.items.size());
+    return t.max_len <= kFusedRowFrames && n > 0 && t.n_dmat / n >= kPackMinMeet;
+}
 
 void cell_keys(const TaskImpl &t, int32_t *out) {
     const size_t K = size_t(t.key_width), n = t.cells.size();
@@ -672,7 +684,7 @@ void plan_stream(const TaskImpl &t, ColPlan &cp) {
     // its row blocks are in task order: the task's own, or made here when those
     // follow a packing order
     std::vector<int32_t> own_rb0, own_nrb;
-    if (!t.pack_item.empty()) plan_rows(t, t.item_len, cp.rb, own_rb0, own_nrb);
+    if (order_pays(t)) plan_rows(t, t.item_len, cp.rb, own_rb0, own_nrb);
     const hvec<int32_t> &rb = own_rb0.empty() ? t.rb : cp.rb;
     const std::vector<int32_t> &g_rb0 = own_rb0.empty() ? t.g_rb0 : own_rb0, &g_nrb = own_rb0.empty() ? t.g_nrb : own_nrb;
     const size_t n_rb = rb.size() / 4;
@@ -705,6 +717,7 @@ ColPlan &col_plan(TaskImpl &t, int cols) {
         if (p->cols == cols) return *p;
     auto cp = std::make_unique<ColPlan>();
     cp->cols = cols;
+    if (cols < kStreamMinCols || !order_pays(t)) ensure_rows(t);
     if (cols >= kStreamMinCols) {
         plan_stream(t, *cp);
         t.col_plans.push_back(std::move(cp));
@@ -735,11 +748,10 @@ ColPlan &col_plan(TaskImpl &t, int cols) {
 }
 
 void plan_blocks(TaskImpl &t) {
-    plan_order(t);
-    // DTW row blocks, then the default work plan (other launch choices are planned
-    // by col_plan on demand)
-    plan_rows(t, packed_len(t), t.rb, t.g_rb0, t.g_nrb);
-    t.fused_cells = col_plan(t, Tuner::default_config().cols).cells;
+    // DTW row blocks and the default work plan (other launch choices are planned by
+    // col_plan on demand); with a packing order both are left to the first score that
+    // reads them
+    if (!order_pays(t)) col_plan(t, Tuner::default_config().cols);
     // unordered pairs with an item of more than kFusedRowFrames frames, (x, x)
     // left out: the FP64 long-item kernel's list (task items, x | y << 32)
     t.long_slots.clear();

@@ -699,3 +699,27 @@ def test_noalloc_units_fall_back_to_strips():
             lo, (t, (got, st)) = mid, res
     assert st["computed_dtw_cells"] == lo * (per * L) ** 2  # strips
     assert np.array_equal(got, t.score(distance="units").half_units)
+
+
+# A task that would have a packing order makes it, its row blocks and plans at the first
+# score that reads them: every order of first uses gives the scores of a fresh task.
+@pytest.mark.parametrize("sequence", ["pdsw", "sdpw", "ndps", "wdnp", "fpds", "psnfwd"])
+def test_packing_order_made_on_first_use(sequence):
+    import paper_2505_02692_amd as fx
+    from test_gpu_parity import ctx
+    rng = np.random.default_rng(5)
+    n, per = 400, 100
+    length = rng.integers(10, 17, n)
+    off = np.concatenate([[0], np.cumsum(length)]).astype(np.int64)
+    assert sum(int(off[k + per] - off[k]) ** 2 for k in range(0, n, per)) // n >= 12000
+    attrs = np.stack([np.arange(n) % 3, np.arange(n) // per], 1).astype(np.int32)
+    feats = torch.from_numpy(rng.standard_normal((int(off[-1]), 24), dtype=np.float32)).cuda()
+    kinds = dict(p=dict(mode="pooled"), d=dict(), s=dict(fused_cols=512), w=dict(fused_cols=256),
+                 f=dict(precision="fp32"), n=dict())
+    ds = fx.Dataset(ctx(), feats, off, attrs)
+    want = {k: fx.Task(ds, 0, [1]).score(**o).half_units for k, o in kinds.items()}
+    t = fx.Task(ds, 0, [1])
+    for k in sequence + sequence[::-1]:
+        print(f"[case] order on first use {sequence} {k}", flush=True)
+        got = (fx.fabx_score_noalloc(t.h, fx.make_opts(), len(t))[0] if k == "n" else t.score(**kinds[k]).half_units)
+        assert np.array_equal(got, want[k])

@@ -245,6 +245,9 @@ int fabx_server_submit(fabx_server *srv, fabx_dataset *ds, int32_t on, const int
         if (job.footprint > s.budget)
             fail(FABX_ENOMEM, "job footprint " + std::to_string(job.footprint) +
                                   " bytes exceeds the server budget");
+        // with the order and plans its score will read, so that the worker finds them packed
+        if (job.params.mode == FABX_MODE_DTW && job.params.fused.cols < kStreamMinCols && order_pays(*job.task))
+            col_plan(*job.task, Tuner::default_config().cols);  // (no other thread has the task yet)
         prepack_tables(*job.task);
         FABX_HIP(hipSetDevice(s.ctx->device));
         job.ready = s.ctx->events.get();

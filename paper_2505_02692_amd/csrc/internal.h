@@ -108,6 +108,17 @@ constexpr int kSortedMaxB = 4096;      // largest |B| counted from sorted rows (
 constexpr int64_t kSortedMinPerX = 8192;  // comparisons per x from which on rows are sorted
 // Cells counted from sorted rows rather than by brute force.
 constexpr bool sorted_cell(int64_t na, int64_t nb) { return na * nb >= kSortedMinPerX && nb <= kSortedMaxB; }
+// Rows x of a triplet work unit of a cell with per_x comparisons a row, counted by
+// brute force: at most kUnitBudget comparisons and kUnitPasses passes of a wave (which
+// takes as many whole rows at once as its lanes hold), since every pass waits for
+// memory: with the comparisons alone a cell of 90 x against 1 was a unit of 180 waits
+// (21,018 uneven cells 113 -> 56 us; 8 passes 54, but 27,000 cells of 10 x 10 x 10
+// items 35 -> 54).
+constexpr int64_t kUnitBudget = 8192, kUnitPasses = 16;
+constexpr int64_t unit_rows(int64_t per_x) {
+    const int64_t a = kUnitBudget / per_x, b = kUnitPasses * (per_x < 64 ? 64 / per_x : 1);
+    return a < 1 ? 1 : a < b ? a : b;
+}
 constexpr int kFusedColFrames = 128;  // default: tile kernel, 128-frame column blocks (the other is 256)
 constexpr int kStreamMinCols = 512;   // cols at or above this select the stream kernel
 // Units of a group with at least kBandMinCols column blocks go in bands of

@@ -25,13 +25,14 @@ constexpr uint8_t kMarked = 2;
 // so a row's values and flags are read once and a step is a lane shuffle and three
 // comparisons; a row whose grid was walked in passes of 64 read four values per
 // comparison and waited for them.  (Passing values for small rows too made 131,671
-// cells of well separated labels take 113 us instead of 86; with the grid 88.)
-//  kMany = false: a wave takes one unit at a time; few units are split by x into
-//    1 << log_parts.  At most 12,288 blocks: a block costs its tables' latency and an
-//    atomic for its recount rows (131,671 cells 96, 87 and 88 us with 8192, 12,288 and
-//    16,384 blocks; 60,000 cells of 2 x 2 items 25, 28 and 30; 40,000 such cells with
-//    18,475 recount rows 93, 106 and 106).  Split four ways below 512 units: 4 cells
-//    of 20 items 10 -> 8 us, 12 cells of 60 17 -> 15, but 760 cells 11 -> 14.
+// cells of well separated labels take 113 us instead of 86; with the grid 82.)
+//  kMany = false: a wave takes one unit at a time (at most 16 passes over rows, see
+//    unit_rows()); below 4096 units each is split by x into four, where a few large
+//    ones would otherwise end last (957 uneven cells 26 -> 13 us, 3635 31 -> 15; 760
+//    even ones 12 -> 14, 4000 even ones 11 -> 18).  At most 12,288 blocks: a block
+//    costs its tables' latency and an atomic for its recount rows (131,671 cells 96, 87
+//    and 88 us with 8192, 12,288 and 16,384 blocks; 60,000 cells of 2 x 2 items 25, 28
+//    and 30; 40,000 such cells with 18,475 recount rows 93, 106 and 106).
 //  kMany = true, from kManyUnits units on (tasks across speakers have millions of
 //    cells of a few triples, and a wave per unit spent its time on the unit's tables
 //    and its reduction): a wave takes `chunk` consecutive units, one per lane; those
@@ -44,7 +45,7 @@ constexpr uint8_t kMarked = 2;
 // atomic of the block at its end: one atomic per row on the common counter was
 // most of the time where many rows go there.
 // Bound by the latency of the chain unit, cell, row values.  100,000 items with
-// 126,303 rows for the recount: 1.27 -> 0.13 ms (0.086 -> 0.088 without such rows).
+// 126,303 rows for the recount: 1.27 -> 0.14 ms (0.086 -> 0.082 without such rows).
 constexpr int kLaneWork = 24, kRowBuf = 128;
 constexpr int64_t kManyUnits = 16 * 32768;
 
@@ -878,7 +879,7 @@ void triplets(hipStream_t s, const CellDev *cells, const int32_t *units, int64_t
                            scale);
     } else {
         // a wave's units lie far apart, so that neighbouring large ones spread out
-        const int log_parts = n_units >= 512 ? 0 : 2;
+        const int log_parts = n_units < 4096 ? 2 : 0;
         hipLaunchKernelGGL(k_triplets<false>, dim3(grid_for(n_units << log_parts, 4, 12288)), dim3(256), 0, s, cells, units,
                            n_units, 1, log_parts, g.pair_base, g.n_items, p32, W, flags, margin, recount, recount_n,
                            recount_cap, scale);

@@ -63,7 +63,6 @@ std::vector<int32_t> pick(const Philox &ph, int64_t cell, int which, int32_t n, 
     return pos;
 }
 
-constexpr int64_t kUnitBudget = 8192;     // as the task build: comparisons per triplet work unit
 
 }  // namespace
 
@@ -179,14 +178,14 @@ std::shared_ptr<TaskImpl> subsample_task(const TaskImpl &t, const fabx_subsample
         std::memcpy(&u.rkeys[k * K], &t.rkeys[size_t(s.cell) * K], K * 4);
     }
     // triplet work units, as the task build makes them: small cells first (one
-    // unit per run of x with at most kUnitBudget comparisons), then one unit per
+    // unit per run of unit_rows() x), then one unit per
     // x of the cells counted from sorted rows
     std::vector<int32_t> small_u, big_u;
     for (size_t k = 0; k < cells.size(); ++k) {
         const CellDev &nc = u.cells[k];
         const int64_t per_x = std::max<int64_t>(1, int64_t(nc.na) * nc.nb);
         const bool big = sorted_cell(nc.na, nc.nb);
-        const int64_t chunk = big ? 1 : std::max<int64_t>(1, kUnitBudget / per_x);
+        const int64_t chunk = big ? 1 : unit_rows(per_x);
         auto &dst = big ? big_u : small_u;
         for (int64_t x = 0; x < nc.nx; x += chunk) {
             dst.push_back(int32_t(k));

@@ -223,9 +223,6 @@ struct Sink {
     int64_t slot_base = 0;
 };
 
-constexpr int64_t kUnitBudget = 8192;  // comparisons per triplet work unit (at least one x)
-// (cells counted from sorted rows, sorted_cell(): one unit per x, after the others)
-
 struct WalkCtx {
     const DatasetImpl *ds;
     const TaskImpl *t;
@@ -299,14 +296,14 @@ void walk_groups(const WalkCtx &w, int64_t s_begin, int64_t s_end, Sink &out) {
             const int64_t na = cls[ia].count, nb = cls[ib].count, nx = cls[ix].count;
             const int64_t nt = excl ? na * (na - 1) * nb : na * nb * nx;
             const size_t cid = out.cell_base + out.n_cells;
-            // triplet work units: split X so one unit does <= kUnitBudget comparisons;
-            // large cells get one unit per x, in the sorted-row region
+            // triplet work units: runs of unit_rows() x; large cells get one unit per x, in
+            // the sorted-row region
             const int64_t per_x = std::max<int64_t>(1, na * nb);
             const bool big = sorted_cell(na, nb);
-            // nx * per_x <= budget (the usual case): one unit for the whole cell,
-            // which is what the division below gives, without dividing
-            const bool one = !big && nx >= 1 && nx * per_x <= kUnitBudget;
-            const int64_t chunk = one ? nx : big ? 1 : std::max<int64_t>(1, kUnitBudget / per_x);
+            // few x and comparisons (the usual case): one unit for the whole cell, which
+            // is what the divisions below give, without dividing
+            const bool one = !big && nx >= 1 && nx <= kUnitPasses && nx * per_x <= kUnitBudget;
+            const int64_t chunk = one ? nx : big ? 1 : unit_rows(per_x);
             const int64_t n_units_cell = one ? 1 : (nx + chunk - 1) / chunk;
             if (kWrite) {
                 // The task's per-cell arrays are far larger than the caches and

@@ -526,12 +526,13 @@ def test_fp64_recheck_same_sums_in_all_classes(dim, dtype, distance):
         assert np.array_equal(f64, [np.cumsum(np.full(k, f64[0]))[-1] for k in copies])
 
 
-# Cells whose |A| x |B| fits a wave's lanes, and those just past it: few units (split
-# by x) and many, X = A without x itself and X of another speaker.  Points of a coarse
+# Cells whose |A| x |B| fits a wave's lanes, those just past it, and cells of more rows
+# x than a unit takes: few units (split by x once more) and many, X = A without x itself and X of another speaker.  Points of a coarse
 # lattice, so that many comparisons tie or are left to the recount.
 @pytest.mark.parametrize("groups", [3, 300])
 @pytest.mark.parametrize("across", [False, True])
-@pytest.mark.parametrize("na,nb", [(2, 1), (2, 2), (9, 7), (8, 8), (13, 5), (64, 1), (65, 1), (3, 21), (3, 22)])
+@pytest.mark.parametrize("na,nb", [(2, 1), (2, 2), (9, 7), (8, 8), (13, 5), (64, 1), (65, 1), (3, 21), (3, 22),
+                                   (90, 1), (17, 40), (40, 17), (33, 2), (128, 3)])
 def test_triplet_units_by_grid(na, nb, across, groups):
     rng = np.random.default_rng(na * 100 + nb)
     label = np.tile(np.r_[np.zeros(na, np.int32), np.ones(nb, np.int32)], (1 + across) * groups)

@@ -65,10 +65,10 @@ __device__ __forceinline__ void find_items(Items<kC> &m, const int32_t *__restri
     }
 }
 
-// Frame r of the row block (lane r): its index in its item, its item's place in
-// the block, whether it is the item's last.
+// Frame r of the row block (lane r): its index in its item, whether it is the
+// item's last.
 struct Row {
-    int ir, item;
+    int ir;
     bool last;
 };
 template <int kC>
@@ -77,9 +77,8 @@ __device__ __forceinline__ Row row_of(const Items<kC> &m, int r, int frames) {
     const uint64_t upto = first & (~0ull >> (63 - r));  // bit 0 is always set
     Row o;
     o.ir = r - (63 - __builtin_clzll(upto));
-    o.item = __popcll(upto) - 1;
     o.last = r == frames - 1 || (r < 63 && ((first >> (r + 1)) & 1u));
-    if (r >= frames) o = Row{0, -1, false};
+    if (r >= frames) o = Row{0, false};
     return o;
 }
 

@@ -510,7 +510,7 @@ __device__ __forceinline__ bool pair_tiles(const T *__restrict__ feat, int dim, 
 // ends sooner.  The XCDs take contiguous parts of the list (its pairs are
 // grouped by row item, so a part's frames stay in that XCD's L2).  365,261
 // marked pairs of the 100,000-item task at dim 768 (lengths 5-25): 22.1 ms with
-// a block per pair and a wave per frame pair, 2.6 ms here.
+// a block per pair and a wave per frame pair, 2.7 ms here.
 constexpr int kTileLd = 17;
 template <typename T, bool kEuclid, int kP>
 __device__ __forceinline__ void small_pairs(const T *__restrict__ feat, int dim, int64_t e0, int64_t total,
@@ -588,7 +588,7 @@ __global__ __launch_bounds__(256, 3) void k_recheck_small(const T *__restrict__ 
 // left to k_recheck_tiled, whose four waves a pair end sooner (2,664 marked pairs
 // of the same task: 68 us with a wave a pair, 32 us with a block).  The 17-25
 // frame pairs of that task's 365,261: 4.6 ms from LDS-staged register tiles,
-// 2.2 ms with a block per pair, 1.35 ms here.
+// 2.2 ms with a block per pair, 1.4 ms here.
 constexpr int kMidL = 32, kMidMin = 2048;
 template <typename T, bool kEuclid>
 __global__ __launch_bounds__(256, 3) void k_recheck_mid(const T *__restrict__ feat, int dim,
@@ -673,7 +673,7 @@ __global__ __launch_bounds__(256, 3) void k_recheck_tiled(const T *__restrict__ 
 // tile k - 3 was.  Rows are the item that needs fewer chunk steps.  Bound by the
 // sweep's chain of dependent FP64 steps (two blocks fit a CU by their LDS).
 // 682 items of 10-200 frames in 60 groups, dim 256, 9.3e7 frame pairs: 92 ms
-// (each orientation by itself, a wave per frame pair), 4.1 ms here.
+// (each orientation by itself, a wave per frame pair), 4.2 ms here.
 // The value of pair (x, y) goes to p64, p32 and flags (0: robust, unmarked) of
 // both its slots.
 template <typename T, bool kEuclid>

@@ -778,7 +778,7 @@ __global__ __launch_bounds__(256) void k_recount(const CellDev *__restrict__ cel
 // counted again from their sorted FP64 values.  Those start in FP32 order, which
 // is theirs but for neighbours within the FP32 error, so odd-even exchanges until
 // nothing moves sort them in a few rounds.  63,037 rows of up to 1000 x 1000
-// comparisons: 42.9 ms with a wave a row over all of them, 2.1 ms here; 550 such
+// comparisons: 42.9 ms with a wave a row over all of them, 1.4 ms here; 550 such
 // rows (one wave each left most of the chip idle): 4.4 ms, 0.03 here.
 template <int kCap>
 __global__ __launch_bounds__(256) void k_recount_sorted(const CellDev *__restrict__ cells,

@@ -214,7 +214,7 @@ void recount(hipStream_t s, const CellDev *cells, const int32_t *rows, const uns
 
 // --- k_recheck.hip
 // FP64 distances from the raw features (cosine of the frames from their FP64
-// product, acos or the half-chord atan2 form near |cos| = 1, DTW with
+// product, acos or an arcsine series of the half chord near |cos| = 1, DTW with
 // diagonal > left > up); euclid: the Euclidean distance.  Each evaluation gives
 // both orientations of a pair.
 // DTW mode, the pairs listed by collect_pairs; max_len: the task's longest

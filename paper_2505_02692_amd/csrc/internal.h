@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <array>
 #include <atomic>
 #include <cstdint>
@@ -114,10 +115,16 @@ constexpr bool sorted_cell(int64_t na, int64_t nb) { return na * nb >= kSortedMi
 // memory: with the comparisons alone a cell of 90 x against 1 was a unit of 180 waits
 // (21,018 uneven cells 113 -> 56 us; 8 passes 54, but 27,000 cells of 10 x 10 x 10
 // items 35 -> 54).
+// (Without a division but for the largest rows: a build asks for millions of cells.)
 constexpr int64_t kUnitBudget = 8192, kUnitPasses = 16;
-constexpr int64_t unit_rows(int64_t per_x) {
-    const int64_t a = kUnitBudget / per_x, b = kUnitPasses * (per_x < 64 ? 64 / per_x : 1);
-    return a < 1 ? 1 : a < b ? a : b;
+constexpr std::array<uint8_t, 65> kRowsPerPass = [] {
+    std::array<uint8_t, 65> a{};
+    for (int k = 1; k <= 64; ++k) a[size_t(k)] = uint8_t(64 / k);
+    return a;
+}();
+inline int64_t unit_rows(int64_t per_x) {
+    if (per_x <= 64) return kUnitPasses * kRowsPerPass[size_t(per_x)];
+    return per_x * kUnitPasses <= kUnitBudget ? kUnitPasses : std::max<int64_t>(1, kUnitBudget / per_x);
 }
 constexpr int kFusedColFrames = 128;  // default: tile kernel, 128-frame column blocks (the other is 256)
 constexpr int kStreamMinCols = 512;   // cols at or above this select the stream kernel

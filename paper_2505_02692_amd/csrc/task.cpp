@@ -300,10 +300,10 @@ void walk_groups(const WalkCtx &w, int64_t s_begin, int64_t s_end, Sink &out) {
             // the sorted-row region
             const int64_t per_x = std::max<int64_t>(1, na * nb);
             const bool big = sorted_cell(na, nb);
-            // few x and comparisons (the usual case): one unit for the whole cell, which
-            // is what the divisions below give, without dividing
-            const bool one = !big && nx >= 1 && nx <= kUnitPasses && nx * per_x <= kUnitBudget;
-            const int64_t chunk = one ? nx : big ? 1 : unit_rows(per_x);
+            // (one unit for the whole cell is the usual case, without dividing)
+            const int64_t rows = big ? 1 : unit_rows(per_x);
+            const bool one = nx >= 1 && nx <= rows;
+            const int64_t chunk = one ? nx : rows;
             const int64_t n_units_cell = one ? 1 : (nx + chunk - 1) / chunk;
             if (kWrite) {
                 // The task's per-cell arrays are far larger than the caches and

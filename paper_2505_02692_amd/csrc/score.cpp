@@ -924,6 +924,40 @@ void finish_score(ResultImpl &res) {
     }
 }
 
+namespace {
+
+// The task's triplet units with the bound on comparisons alone, in the place of its own
+// until the end of the scope (the caller holds the task's mutex).
+struct FewestUnits {
+    TaskImpl &t;
+    hvec<int32_t> own;
+    int64_t own_small = 0;
+    bool taken = false;
+    void take() {
+        own.swap(t.units);
+        own_small = t.n_units_small;
+        taken = true;
+        const size_t small = 3 * size_t(own_small);
+        for (size_t u = 0; u < small;) {
+            const int32_t cell = own[u];
+            const CellDev &c = t.cells[size_t(cell)];
+            const int64_t rows = std::max<int64_t>(1, kUnitBudget / std::max<int64_t>(1, int64_t(c.na) * c.nb));
+            for (int64_t x = 0; x < c.nx; x += rows)
+                t.units.insert(t.units.end(), {cell, int32_t(x), int32_t(std::min<int64_t>(c.nx, x + rows))});
+            while (u < small && own[u] == cell) u += 3;
+        }
+        t.n_units_small = int64_t(t.units.size() / 3);
+        t.units.insert(t.units.end(), own.begin() + std::ptrdiff_t(small), own.end());
+    }
+    ~FewestUnits() {
+        if (!taken) return;
+        t.units.swap(own);
+        t.n_units_small = own_small;
+    }
+};
+
+}  // namespace
+
 void score_in_scratch(TaskImpl &t, const ScoreParams &p, char *base, size_t cap, hipStream_t stream,
                       int64_t *half_units, fabx_stats *stats) {
     std::lock_guard<std::mutex> lock(t.mu);
@@ -985,30 +1019,46 @@ void score_in_scratch(TaskImpl &t, const ScoreParams &p, char *base, size_t cap,
     PlanLayout pl;
     std::array<std::vector<int64_t>, 5> gcols;
     PlainPlan strips;
-    if (dtw && !bf16 && !use_strips) {
-        // the plain form's fused kernel has larger tables than a distance buffer of the
-        // least size: a task of very many small items that fills the scratch takes strips
-        Packer probe;
-        std::array<std::vector<int64_t>, 5> gc2;
-        if (layout(strips, probe, tl, pl, gc2) > cap) {
-            use_strips = true;
-            cplan = nullptr;
+    ColPlan *const fused = cplan;
+    // Plans the layout; the bytes it needs.
+    auto plan_layout = [&]() -> size_t {
+        use_strips = needs_strips(t, p);
+        cplan = fused;
+        strips = PlainPlan();
+        if (dtw && !bf16 && !use_strips) {
+            // the plain form's fused kernel has larger tables than a distance buffer of the
+            // least size: a task of very many small items that fills the scratch takes strips
+            Packer probe;
+            std::array<std::vector<int64_t>, 5> gc2;
+            if (layout(strips, probe, tl, pl, gc2) > cap) {
+                use_strips = true;
+                cplan = nullptr;
+            }
         }
-    }
-    if (use_strips) {
-        strips = plain_plan(t, plain_dmat_cells());
-        Packer probe;
-        std::array<std::vector<int64_t>, 5> gc2;
-        const size_t need = layout(strips, probe, tl, pl, gc2);
-        if (need > cap) {
-            // the distance buffer gets what the rest leaves (1 MiB kept for the longer strip tables)
-            const size_t rest = need - ((size_t(std::max<int64_t>(strips.max_cells, 1)) * 4 + 255) & ~size_t(255));
-            const int64_t cells = rest + (size_t(1) << 20) < cap ? int64_t((cap - rest - (size_t(1) << 20)) / 4) : 0;
-            if (cells < 4096) fail(FABX_ENOMEM, "task needs more scratch than the no-allocation limit");
-            strips = plain_plan(t, cells);
+        if (use_strips) {
+            strips = plain_plan(t, plain_dmat_cells());
+            Packer probe;
+            std::array<std::vector<int64_t>, 5> gc2;
+            const size_t need = layout(strips, probe, tl, pl, gc2);
+            if (need > cap) {
+                // the distance buffer gets what the rest leaves (1 MiB kept for the longer strip tables)
+                const size_t rest = need - ((size_t(std::max<int64_t>(strips.max_cells, 1)) * 4 + 255) & ~size_t(255));
+                const int64_t cells = rest + (size_t(1) << 20) < cap ? int64_t((cap - rest - (size_t(1) << 20)) / 4) : 0;
+                if (cells < 4096) return need;
+                strips = plain_plan(t, cells);
+            }
         }
+        pk = Packer();
+        return layout(strips, pk, tl, pl, gcols);
+    };
+    size_t need = plan_layout();
+    // A task that does not fit takes the fewest triplet units, of kUnitBudget comparisons
+    // whatever their passes, for this call.
+    FewestUnits fewest{t};
+    if (need > cap) {
+        fewest.take();
+        need = plan_layout();
     }
-    const size_t need = layout(strips, pk, tl, pl, gcols);
     if (need > cap)
         fail(FABX_ENOMEM, "task needs " + std::to_string(need) + " bytes of scratch; the no-allocation limit is " +
                               std::to_string(cap));

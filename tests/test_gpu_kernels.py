@@ -724,3 +724,46 @@ def test_packing_order_made_on_first_use(sequence):
         print(f"[case] order on first use {sequence} {k}", flush=True)
         got = (fx.fabx_score_noalloc(t.h, fx.make_opts(), len(t))[0] if k == "n" else t.score(**kinds[k]).half_units)
         assert np.array_equal(got, want[k])
+
+
+# The no-allocation score takes the fewest triplet units where the task's own would not
+# fit (three a cell here, 12 bytes each, against one): the largest task it takes is within
+# a group of what the fewest need.
+def test_noalloc_takes_the_fewest_units_at_its_limit():
+    import re
+    import paper_2505_02692_amd as fx
+    from test_gpu_parity import ctx
+    rng = np.random.default_rng(8)
+    per, most = 36, 22000
+    feats = torch.from_numpy(rng.standard_normal((most * per, 4), dtype=np.float32)).cuda()
+    off = np.arange(most * per + 1, dtype=np.int64)
+    attrs = np.stack([np.tile(np.r_[np.zeros(34, np.int32), 1, 1], most), np.arange(most * per) // per], 1).astype(np.int32)
+    opts = fx.make_opts(mode="pooled", precision="fp32")
+
+    def attempt(groups):
+        n = groups * per
+        t = fx.Task(fx.Dataset(ctx(), feats[:n], off[:n + 1], attrs[:n]), 0, [1])
+        print(f"[case] noalloc fewest units, {groups} groups", flush=True)
+        try:
+            return t, fx.fabx_score_noalloc(t.h, opts, len(t))[0]
+        except fx.FabxError as e:
+            assert e.code == -2
+            return int(re.search(r"needs (\d+) bytes", str(e)).group(1))
+
+    lo, hi = 1000, most   # taken, refused
+    small, _ = attempt(lo)
+    need = attempt(hi)
+    per_group = need / hi
+    while hi - lo > 1:
+        mid = (lo + hi) // 2
+        res = attempt(mid)
+        if isinstance(res, int):
+            hi, need = mid, res
+        else:
+            lo, (t, got) = mid, res
+    # refused by less than a group, of the bytes it takes with two units: frames, pair
+    # matrix, items, cells, units, group tables, counts, tile prefix, row block
+    assert abs(per_group - (36 * 64 * 4 + 36 * 36 * 4 + 36 * 24 + 2 * 32 + 2 * 12 + 5 * 8 + 2 * 8 + 8 + 16)) < 2
+    assert need - (256 << 20) <= per_group + 4096
+    assert np.array_equal(got, t.score(mode="pooled", precision="fp32").half_units)
+    assert len(small) == 2000
